@@ -889,6 +889,9 @@ ff_status core_backward_run(const ff_core_desc& d, const void* q, const void* k,
     a.biasK = (float*)p; p += bbytes;
     a.row_chunks = bias ? dbias_chunks(d) : 1;
     a.rows_per_chunk = (d.rows + a.row_chunks - 1) / a.row_chunks;
+    // (rounding the share up can leave the last chunks without rows, and nobody writes their partial sums: 81 rows in
+    // ten shares of 9 are nine chunks)
+    a.row_chunks = (d.rows + a.rows_per_chunk - 1) / a.rows_per_chunk;
     a.dbias_part = a.row_chunks > 1 ? (float*)p : nullptr;
     a.qscale2 = kLog2e / sqrtf((float)d.head_dim);
     a.scale = 1.f / sqrtf((float)d.head_dim);

@@ -87,6 +87,16 @@ def test_fully_masked_rows_have_zero_gradients():
     check_all(case, got, oracle(case), "dead row")
 
 
+def test_workspace_content_does_not_reach_the_bias_gradient():
+    """81 rows: the rounded-up share of nine rows leaves one of the ten row chunks without rows.  Its partial sums are
+    never written, so they must not be added; the workspace holds NaN patterns here."""
+    case = I.make_core_case(I.CoreSpec("t_core_chunks", 81, 1, 32, 8, True, "random:0.8"))
+    desc, t, mask = P.core_to_device(case, DEV)
+    ws = torch.full((P.ff_attention_core_backward_workspace_bytes(desc),), 0xFF, dtype=torch.uint8, device=DEV)
+    got = P.ff_attention_core_backward(desc, t["q"], t["k"], t["v"], t["g"], t["bias"], mask, t["do"], ws=ws)
+    check_all(case, got, oracle(case), "dirty workspace")
+
+
 @pytest.mark.parametrize("name", ["core_row_256", "core_tri_256"])
 def test_paper_shapes(name):
     """The attention cores of the initial-training shapes: MSA row attention (128 x 8 x 256 x 32 with pair bias)
