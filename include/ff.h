@@ -289,8 +289,8 @@ ff_status ff_gated_attention_static(const ff_attn_desc* desc, const ff_attn_weig
 /* Size in bytes of the library's own device array used by ff_gated_attention_static. */
 size_t ff_static_scratch_bytes(void);
 
-/* Name of the kernel family the SHAPE allows: "mfma_bf16" (matrix-core path) or "generic"
- * (float32 vector path).  NULL if desc is invalid.  A call takes the matrix-core family only
+/* Name of the kernel family the SHAPE allows: "mfma_bf16" (bfloat16 matrix-core path) or
+ * "generic" (float32 path).  NULL if desc is invalid.  A call takes the matrix-core family only
  * if, in addition, x, z, out and every weight pointer are 16-byte aligned and the chunk has
  * fewer than 2^22 attention work items; ff_attention_last_path tells what a call really took. */
 const char* ff_attention_path(const ff_attn_desc* desc);

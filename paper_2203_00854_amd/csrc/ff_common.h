@@ -86,15 +86,12 @@ ff_status fail(ff_status st, const char* fmt, ...);
 ff_status check_launch(const char* what);
 
 // ---- kernel families (each returns after enqueueing on `stream`) ---------------------
-// generic float32 vector path (ff_generic.hip); T selected by p.dtype
+// generic float32 path (ff_generic.hip); T selected by p.dtype
 size_t generic_workspace(const Problem& p, int chunk, Workspace* ws, void* base);
 // once per call, before the chunks: the pair-bias tensor (and, for the matrix-core family, the
-// prepared weights)
+// prepared weights; for the generic one the token statistics of the first chunk)
 ff_status generic_prepare(const Problem& p, const ff_attn_weights& w, const void* x, const void* z,
                           const Workspace& ws, hipStream_t stream);
-// the generic bias kernel writing into a [H][Lq][Lp] tensor (both families use it)
-ff_status generic_bias_into(const Problem& p, const ff_attn_weights& w, const void* x, const void* z, float* bias,
-                            int Lq, int Lp, hipStream_t stream);
 // res: NULL, or a tensor laid out like out that is added to the module's output (may be out itself)
 ff_status generic_chunk(const Problem& p, const ff_attn_weights& w, const void* x, const float* mask,
                         const void* res, void* out, const Workspace& ws, int r0, int rows, hipStream_t stream);
