@@ -1,0 +1,499 @@
+// Attention of the bf16 matrix-core family at head dimension 32 (FastFold Section 5.2's fused scale + mask + bias
+// softmax between the two contractions), for the sequences that k_proj_attn does not take.
+//
+// A wavefront owns 32 queries of NR batch rows and walks over the keys in steps of 32: NR tiles of 32 x 32 scores
+// per step, S^T = K Q^T with the pair-bias tile as accumulator input, exponentials, O^T += V^T P^T.  The bias tile
+// does not depend on the batch row, so it is loaded once per step, in accumulator register order (bias_index), straight
+// into the registers that the first matrix instruction of all NR rows reads.  k and v^T of the NR rows are
+// the same for all NW wavefronts of a block (they hold other queries): they pass through a ring of four steps
+// in LDS, filled by loads that write LDS directly, three steps ahead, with one barrier per step.
+//
+// The vector unit and the matrix cores bound it together: per tile 16 exponentials (8 cycles each) and 8 packs (4)
+// against four 32 x 32 x 16 matrix instructions (32 each) and four 4 x 4 x 4 ones for the denominator, so nothing else is
+// left in the loop:
+//  - no reference is subtracted from the scores.  float32 and bfloat16 keep their relative precision over the whole
+//    exponent range, so exp2(s) / sum exp2(s) needs none while the sum stays in range; a row of a
+//    wavefront whose sum does not is done again with a running maximum (end of the kernel).
+//  - the denominator is summed from the rounded weights by 4 x 4 x 4 matrix instructions: eight v_dot2 per tile do not overlap
+//    with matrix instructions (bare loops of the tile's mix, two wavefronts per SIMD: 123 ns with dots, 104 so, 93
+//    without any denominator).
+//  - masked keys cost one more matrix instruction, in steps that hold any; steps before the first masked key skip the test.
+//  - matrix instructions of the next and the previous tile alternate with the exponentials of this one.
+// Measured, 64 rows x 4 heads x 2048^2 with bias: 249 us for the kernel before (a wavefront per batch row with 64 queries,
+// bias through LDS, five matrix instructions per tile), 190 now; 333 rows x 4 x 333^2: 81 -> 58.  Without its loads the
+// kernel takes 164, without the LDS reads as well 135; the shader clock is 2.0 - 2.1 GHz under this load (2.37 without).
+#include "ff_attn_rows.h"
+
+namespace ff {
+
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+typedef __attribute__((__vector_size__(4 * sizeof(short)))) short i16x4;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef void __attribute__((address_space(3)))* lptr_t;
+
+namespace {
+
+union Frag {
+    bf16x8 v;
+    uint4 u;
+    uint32_t w[4];
+};
+
+__device__ __forceinline__ uint32_t pack2(float a, float b) {   // a -> low half (first element)
+    bf16x2 t;
+    t[0] = (__bf16)a;
+    t[1] = (__bf16)b;
+    return __builtin_bit_cast(uint32_t, t);
+}
+__device__ __forceinline__ float lo_f32(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float hi_f32(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+// Sum of the lane's own four bf16 values (w0, w1), added to every element of acc: a 4 x 4 x 4 matrix instruction (sixteen
+// independent blocks of four lanes) against ones.
+__device__ __forceinline__ f32x4 add_four(uint32_t w0, uint32_t w1, f32x4 acc) {
+    const i16x4 ones = __builtin_bit_cast(i16x4, make_uint2(0x3f803f80u, 0x3f803f80u));
+    return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_bit_cast(i16x4, make_uint2(w0, w1)), acc, 0, 0, 0);
+}
+// sum of the two bf16 halves of w, added to acc
+__device__ __forceinline__ float add_pair(uint32_t w, float acc) {
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), __builtin_bit_cast(bf16x2, 0x3f803f80u), acc,
+                                           false);
+}
+// value of the other half-wave's lane (l ^ 32)
+__device__ __forceinline__ float other_half(float v) {
+    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return (threadIdx.x & 32) ? __uint_as_float(r[0]) : __uint_as_float(r[1]);
+}
+// (see ff_mfma.hip) two 4-element groups that are adjacent in memory end up in one lane
+__device__ __forceinline__ void merge_halves(uint32_t& a, uint32_t& b) {
+    auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+__device__ __forceinline__ uint4 ldg16(const void* base, uint32_t lane_bytes) {
+    return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(base) + lane_bytes);
+}
+// 16 bytes per lane from base + lane_bytes straight into LDS at lds_base + 16 * lane (base and lds_base uniform).
+// Assembly, because the compiler would make every later LDS read wait for a load it knows to write LDS; whoever
+// reads the data waits (vmcnt) and passes a barrier first.
+__device__ __forceinline__ void load16_to_lds(const void* base, uint32_t lane_bytes, unsigned lds_base) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :
+                 : "v"(lane_bytes), "s"(base), "s"(lds_base)
+                 : "memory", "m0");
+}
+constexpr int kWaitVmcnt0 = 0x0F70;      // s_waitcnt vmcnt(0), the other counters untouched
+
+constexpr int kRing = 4;                 // steps in the LDS ring
+constexpr int kTileBytes = 2048;         // a tile of 32 keys x 32 elements (k) or 32 elements x 32 keys (v^T)
+
+__device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+}  // namespace
+
+template <int NR, int NW, bool HAS_BIAS>
+__global__ __launch_bounds__(NW * 64, 2) void k_attn_rows(AttnRowsArgs a) {
+    static_assert(NR == 2 || NR == 4, "rows per wavefront");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int STEP = NR * 2 * kTileBytes;                                        // bytes of a ring slot: [row][k | v^T]
+    uint32_t* s_live = reinterpret_cast<uint32_t*>(smem + kRing * STEP);             // [key tile][NR]: bit = key is attended to
+
+    const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, hf = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    // ---- which rows, head and queries.  Work-groups go to the 8 XCDs round-robin and every XCD has its own L2:
+    // an XCD takes a contiguous range of the order (head, group of 8 row blocks, query block, row block inside the
+    // group), so that the blocks it runs at about the same time share k and v^T (same rows) eight ways and the
+    // bias (same queries) eight ways.
+    int lg;
+    {
+        const int per_xcd = (a.n_items + 7) >> 3;
+        const int slot = blockIdx.x >> 3;
+        lg = (blockIdx.x & 7) * per_xcd + slot;
+        if (slot >= per_xcd || lg >= a.n_items) return;      // (whole block)
+    }
+    const int h = lg / (a.n_rb * a.n_qb);
+    int rem = lg - h * a.n_rb * a.n_qb;
+    const int grp = rem / (8 * a.n_qb);
+    rem -= grp * 8 * a.n_qb;
+    const int gsz = a.n_rb - 8 * grp < 8 ? a.n_rb - 8 * grp : 8;
+    const int qb = rem / gsz;
+    const int rb = 8 * grp + rem - qb * gsz;
+    const int nt = (a.L + 31) >> 5;                           // key tiles; also query tiles
+    const int qt = qb * NW + wave;
+    const bool active = qt < nt;                              // (wave-uniform)
+    int row[NR];
+#pragma unroll
+    for (int j = 0; j < NR; ++j) row[j] = rb * NR + j < a.rows ? rb * NR + j : a.rows - 1;
+
+    // ---- k and v^T on their way into the ring.  Chunk c of a step is KiB c % 4 of row c / 4 (two of k, two of v^T);
+    // lane i of a load fills 16-byte slot i, and the piece it fetches is chosen so that the operand reads below
+    // spread over the banks (sixteen lanes at a time read one 16-byte piece each, four rows make a line of 64 banks):
+    // piece p of key (element) r sits at slot 4 r + (p ^ (r / 4) % 4).
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lptr_t)smem);
+    const uint32_t st_lane = (uint32_t)((lane >> 2) * 64 + (((lane & 3) ^ ((lane >> 4) & 3)) * 16));
+    const size_t head_elems = (size_t)a.Lp * 32;
+    constexpr int CPW = 4 * NR / NW;                          // chunks of a step per wavefront
+    const char* st_src[CPW];                                  // (scalar) the chunk in key tile 0
+#pragma unroll
+    for (int i = 0; i < CPW; ++i) {
+        const int c = i * NW + wave, part = c & 3;
+        int r = rb * NR + (c >> 2);
+        if (r > a.rows - 1) r = a.rows - 1;
+        st_src[i] = reinterpret_cast<const char*>((part < 2 ? a.k : a.vt) + ((size_t)r * a.H + h) * head_elems + (part & 1) * 512);
+    }
+    auto stage = [&](int kt) __attribute__((always_inline)) {
+        const uint32_t off = st_lane + (uint32_t)kt * kTileBytes;
+        const unsigned dst = lds0 + (unsigned)(kt & (kRing - 1)) * STEP + wave * 1024;
+#pragma unroll
+        for (int i = 0; i < CPW; ++i) load16_to_lds(st_src[i], off, dst + i * NW * 1024);
+    };
+    // ---- mask entries of 64 keys per load, eight loads in flight (the ballots follow below)
+    const int n_pairs = (nt + 1) >> 1;
+    float mv[8];
+    auto load_mask = [&](int i0) __attribute__((always_inline)) {
+        if (a.mask == nullptr) return;
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            const int i = i0 + m * NW;
+            int r = rb * NR + i % NR, l = 64 * (i / NR) + lane;
+            if (r > a.rows - 1) r = a.rows - 1;
+            if (l > a.L - 1) l = a.L - 1;
+            mv[m] = a.mask[(int64_t)(a.r0 + r) * a.sr + (int64_t)l * a.sl];
+        }
+    };
+#pragma unroll
+    for (int m = 0; m < 8; ++m) mv[m] = 1.f;
+    load_mask(wave);
+    stage(0);
+    if (nt > 1) stage(1);
+    if (nt > 2) stage(2);
+
+    // ---- q: B operand of S^T (lane = query, 8 consecutive elements)
+    Frag qf[NR][2];
+    const int qtc = active ? qt : nt - 1;
+    const uint32_t q_lane = (uint32_t)(col * 32 + 8 * hf) * 2;
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+        const bf16_t* qp = a.q + ((size_t)row[j] * a.H + h) * head_elems + (size_t)qtc * 1024;
+        qf[j][0].u = ldg16(qp, q_lane);
+        qf[j][1].u = ldg16(qp + 16, q_lane);
+    }
+    // ---- bias tiles of the wavefront's queries, one after the other
+    const float* bias_q = HAS_BIAS ? a.bias + ((size_t)h * (a.Lq >> 5) + qtc) * (a.Lp >> 5) * 1024 : nullptr;
+    const uint32_t b_lane = (uint32_t)lane * 16;
+    auto load_bias = [&](int kt, f32x16& b) __attribute__((always_inline)) {
+        if constexpr (HAS_BIAS) {
+            if (kt > nt - 1) kt = nt - 1;
+            const char* bp = reinterpret_cast<const char*>(bias_q + (size_t)kt * 1024);
+            uint32_t off = b_lane;
+            asm volatile("" : "+v"(off));
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float4 x4 = *reinterpret_cast<const float4*>(bp + g * 1024 + off);
+                b[4 * g] = x4.x; b[4 * g + 1] = x4.y; b[4 * g + 2] = x4.z; b[4 * g + 3] = x4.w;
+            }
+        } else {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) b[v] = 0.f;
+        }
+    };
+    f32x16 bias_a, bias_b;
+    load_bias(0, bias_a);
+    load_bias(1, bias_b);
+
+    // ---- which keys are attended to, one bit per key
+    for (int i0 = wave; i0 < NR * n_pairs; i0 += 8 * NW) {
+        if (i0 != wave) load_mask(i0);
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            const int i = i0 + m * NW, j = i % NR, pair = i / NR;
+            const uint64_t bits = __ballot(mv[m] != 0.f && 64 * pair + lane < a.L);
+            if (lane == 0 && pair < n_pairs) {
+                s_live[(2 * pair) * NR + j] = (uint32_t)bits;
+                s_live[(2 * pair + 1) * NR + j] = (uint32_t)(bits >> 32);
+            }
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    __syncthreads();
+
+    // permuted key of S^T row m = col: the lane's registers 8c .. 8c+7 then hold the keys 16c + 8hf .. + 7
+    const int kperm = 16 * (col >> 4) + 8 * ((col >> 2) & 1) + 4 * ((col >> 3) & 1) + (col & 3);
+    const uint32_t rd_k = (uint32_t)(kperm * 64 + ((hf ^ ((kperm >> 2) & 3)) * 16));
+    const uint32_t rd_v = (uint32_t)(kTileBytes + col * 64 + ((hf ^ ((col >> 2) & 3)) * 16));
+    auto lds16 = [&](uint32_t off) __attribute__((always_inline)) { return *reinterpret_cast<const uint4*>(smem + off); };
+
+    // publishes what set out a step ago and sends the next step on its way (the ring slot it fills was last read before
+    // the barrier)
+    auto turn = [&](int kt) __attribute__((always_inline)) {
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (kt + 3 < nt) stage(kt + 3);
+    };
+    if (!active) {                                            // (no queries: only the share of the loads)
+        for (int kt = 0; kt < nt; ++kt) turn(kt);
+        return;
+    }
+
+    f32x16 o_acc[NR], s_acc[2];
+    float l_run[NR];
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+        l_run[j] = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o_acc[j][v] = 0.f;
+    }
+    Frag kf[2][2], vf[2][2], pf[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) pf[c].u = vf[1][c].u = make_uint4(0, 0, 0, 0);
+    // (query side of the mask step: a one against the key side's 0 or -inf)
+    const bf16x4 q_one = __builtin_bit_cast(bf16x4, make_uint2(hf == 0 ? 0x00003f80u : 0u, 0u));
+    auto mask_step = [&](uint32_t live, f32x16 s) __attribute__((always_inline)) {
+        const uint32_t term = (live >> kperm) & 1u ? 0u : 0x0000ff80u;
+        const bf16x4 k_mask = __builtin_bit_cast(bf16x4, make_uint2(hf == 0 ? term : 0u, 0u));
+        return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(i16x4, k_mask), __builtin_bit_cast(i16x4, q_one), s, 0, 0, 0);
+    };
+    // One tile (row j of the step) of the software pipeline: the exponentials of tile t run while the matrix core forms
+    // the scores of tile t + 1 (bias bn, query operand qn, keys kn) and the context of tile t - 1 (weights pp, values vp),
+    // and the operands k of tile t + 2 and v^T of tile t come from LDS.
+    auto tile = [&](auto plain_c, uint32_t live, f32x16& sc, f32x16& sn, const f32x16& bn, Frag (&kn)[2], Frag (&kl)[2], Frag (&vp)[2], Frag (&vl)[2], Frag (&qn)[2], uint32_t kl_off, uint32_t vl_off,
+                    f32x16& op, float& lp) __attribute__((always_inline)) {
+        Frag pc[2];
+        f32x4 lt = {0.f, 0.f, 0.f, 0.f};
+        float e0 = __builtin_amdgcn_exp2f(sc[0]), e1 = __builtin_amdgcn_exp2f(sc[1]);
+#pragma unroll
+        for (int g = 0; g < 8; ++g) {
+            if (!decltype(plain_c)::value && g == 4 && live != 0xffffffffu) sn = mask_step(live, sn);
+            if (g == 1) lt = add_four(pf[0].w[0], pf[0].w[1], lt);
+            if (g == 3) lt = add_four(pf[0].w[2], pf[0].w[3], lt);
+            if (g == 5) lt = add_four(pf[1].w[0], pf[1].w[1], lt);
+            if (g == 7) lt = add_four(pf[1].w[2], pf[1].w[3], lt);
+            if (g == 0) sn = mfma(kn[0].v, qn[0].v, bn);
+            if (g == 2) sn = mfma(kn[1].v, qn[1].v, sn);
+            if (g == 4) op = mfma(vp[0].v, pf[0].v, op);
+            if (g == 6) op = mfma(vp[1].v, pf[1].v, op);
+            if (g == 1) {
+                vl[0].u = lds16(vl_off + rd_v);
+                vl[1].u = lds16(vl_off + (rd_v ^ 32u));
+            }
+            if (g == 0) {
+                kl[0].u = lds16(kl_off + rd_k);
+                kl[1].u = lds16(kl_off + (rd_k ^ 32u));
+            }
+            float n0 = 0.f, n1 = 0.f;
+            if (g < 7) {
+                n0 = __builtin_amdgcn_exp2f(sc[2 * g + 2]);
+                n1 = __builtin_amdgcn_exp2f(sc[2 * g + 3]);
+                asm volatile("" : "+v"(n0), "+v"(n1));
+            }
+            uint32_t& w = pc[g >> 2].w[g & 3];
+            w = pack2(e0, e1);
+            asm volatile("" : "+v"(w));
+            __builtin_amdgcn_sched_barrier(0);
+            e0 = n0;
+            e1 = n1;
+        }
+        lp += lt[0];
+        pf[0] = pc[0];
+        pf[1] = pc[1];
+    };
+    // A step: NR tiles.  bc: bias of this step, bn: of the next one (its registers receive the one after next).
+    uint32_t live_c[NR], live_n[NR];           // keys of this step (scalar) and the next
+    auto fetch_live = [&](int kt, uint32_t (&lv)[NR]) __attribute__((always_inline)) {
+        if (kt > nt - 1) kt = nt - 1;
+#pragma unroll
+        for (int j = 0; j < NR; ++j) lv[j] = s_live[kt * NR + j];
+    };
+    auto step = [&](auto plain_c, int kt, f32x16& bc, f32x16& bn) __attribute__((always_inline)) {
+        const uint32_t cur = (uint32_t)(kt & (kRing - 1)) * STEP, nxt = (uint32_t)((kt + 1) & (kRing - 1)) * STEP;
+        constexpr bool PLAIN = decltype(plain_c)::value;
+        if constexpr (!PLAIN) fetch_live(kt + 1, live_n);
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+            constexpr int LAST = NR - 1;
+            if (j == LAST) {
+                turn(kt);
+                if constexpr (!PLAIN)
+#pragma unroll
+                for (int i = 0; i < NR; ++i) live_n[i] = __builtin_amdgcn_readfirstlane(live_n[i]);
+            }
+            const uint32_t kl_off = j + 2 < NR ? cur + (uint32_t)(j + 2) * 2 * kTileBytes : nxt + (uint32_t)(j + 2 - NR) * 2 * kTileBytes;
+            const uint32_t vl_off = cur + (uint32_t)j * 2 * kTileBytes;
+            Frag(&qn)[2] = qf[j == LAST ? 0 : j + 1];
+            f32x16& op = o_acc[j == 0 ? LAST : j - 1];
+            const f32x16& bt = j == LAST ? bn : bc;
+            tile(plain_c, j == LAST ? live_n[0] : live_c[j == LAST ? 0 : j + 1], s_acc[j & 1], s_acc[(j + 1) & 1], bt, kf[(j + 1) & 1], kf[j & 1], vf[(j + 1) & 1], vf[j & 1], qn, kl_off, vl_off, op, l_run[j == 0 ? LAST : j - 1]);
+            if (j == LAST) load_bias(kt + 2, bc);
+        }
+        if constexpr (!PLAIN) {
+#pragma unroll
+            for (int j = 0; j < NR; ++j) live_c[j] = live_n[j];
+        }
+    };
+
+    // ---- the scores of the first tile
+    fetch_live(0, live_c);
+#pragma unroll
+    for (int j = 0; j < NR; ++j) live_c[j] = __builtin_amdgcn_readfirstlane(live_c[j]);
+    kf[0][0].u = lds16(rd_k);
+    kf[0][1].u = lds16(rd_k ^ 32u);
+    s_acc[0] = mfma(kf[0][0].v, qf[0][0].v, bias_a);
+    s_acc[0] = mfma(kf[0][1].v, qf[0][1].v, s_acc[0]);
+    s_acc[0] = mask_step(live_c[0], s_acc[0]);
+    kf[1][0].u = lds16(2 * kTileBytes + rd_k);
+    kf[1][1].u = lds16(2 * kTileBytes + (rd_k ^ 32u));
+    // Steps before the first one that holds a masked (or missing) key have a loop of their own without the mask tests.
+    int n_plain = nt;
+    for (int i = 0; i < nt * NR && n_plain == nt; i += 64) {
+        const uint64_t part = __ballot(i + lane < nt * NR && s_live[i + lane] != 0xffffffffu);
+        if (part) n_plain = (i + (int)__builtin_ctzll(part)) / NR;
+    }
+    int kt = 0;
+    using std::integral_constant;
+    for (; kt + 2 < n_plain; kt += 2) {                       // (a step also forms the first scores of the next one)
+        step(integral_constant<bool, true>{}, kt, bias_a, bias_b);
+        step(integral_constant<bool, true>{}, kt + 1, bias_b, bias_a);
+    }
+    fetch_live(kt, live_c);
+#pragma unroll
+    for (int j = 0; j < NR; ++j) live_c[j] = __builtin_amdgcn_readfirstlane(live_c[j]);
+    for (; kt + 1 < nt; kt += 2) {
+        step(integral_constant<bool, false>{}, kt, bias_a, bias_b);
+        step(integral_constant<bool, false>{}, kt + 1, bias_b, bias_a);
+    }
+    if (kt < nt) step(integral_constant<bool, false>{}, kt, bias_a, bias_b);
+    o_acc[NR - 1] = mfma(vf[1][0].v, pf[0].v, o_acc[NR - 1]);
+    {
+        f32x4 lt = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) lt = add_four(pf[c >> 1].w[2 * (c & 1)], pf[c >> 1].w[2 * (c & 1) + 1], lt);
+        l_run[NR - 1] += lt[0];
+    }
+    o_acc[NR - 1] = mfma(vf[1][1].v, pf[1].v, o_acc[NR - 1]);
+
+    // ---- normalise, gate, store.  Lane = query, register v = element 8*(v/4) + 4*hf + v%4
+    const int qi = 32 * qt + col;
+    auto load_gate = [&](int r, uint2 (&gr)[4]) __attribute__((always_inline)) {
+        const bf16_t* gp = a.g + ((size_t)r * a.H + h) * head_elems + (size_t)qt * 1024;
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            gr[g] = *reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(gp + 8 * g) + (uint32_t)(col * 32 + 4 * hf) * 2);
+    };
+    auto finish = [&](const f32x16& o, float l_tot, int r, const uint2 (&gate)[4]) __attribute__((always_inline)) {
+        const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+        const size_t off = ((size_t)r * a.H + h) * head_elems + (size_t)qt * 1024;
+        uint32_t pk[8];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const uint2 gr = gate[g];
+            pk[2 * g] = pack2(o[4 * g] * inv * lo_f32(gr.x), o[4 * g + 1] * inv * hi_f32(gr.x));
+            pk[2 * g + 1] = pack2(o[4 * g + 2] * inv * lo_f32(gr.y), o[4 * g + 3] * inv * hi_f32(gr.y));
+        }
+        merge_halves(pk[0], pk[2]);      // lower half-wave: e 0..7, upper: e 8..15
+        merge_halves(pk[1], pk[3]);
+        merge_halves(pk[4], pk[6]);      // lower: e 16..23, upper: e 24..31
+        merge_halves(pk[5], pk[7]);
+        if (qi < a.L) {
+            char* op = reinterpret_cast<char*>(a.o + off) + q_lane;
+            *reinterpret_cast<uint4*>(op) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+            *reinterpret_cast<uint4*>(op + 32) = make_uint4(pk[4], pk[5], pk[6], pk[7]);
+        }
+    };
+    // A denominator outside [2^-60, 2^96] (some weights overflowed, or all of them are tiny, or NaN): the row is done
+    // again below with a running maximum.  0 is right where no key is attended to: redone as well, it costs nothing.
+    int again = 0;
+    uint2 gate[NR][4];
+#pragma unroll
+    for (int j = 0; j < NR; ++j) load_gate(row[j], gate[j]);
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+        const float l_tot = l_run[j] + other_half(l_run[j]);
+        const bool fine = l_tot >= 0x1p-60f && l_tot <= 0x1p96f;
+        if (rb * NR + j >= a.rows) continue;
+        if (__any(!fine && qi < a.L)) again |= 1 << j;
+        else finish(o_acc[j], l_tot, row[j], gate[j]);
+    }
+    // ---- the general softmax, one row after the other, operands straight from memory
+    while (again != 0) {
+        const int j = __builtin_ctz(again);
+        again &= again - 1;
+        const int r = rb * NR + j;
+        const size_t off = ((size_t)r * a.H + h) * head_elems;
+        Frag q0, q1;
+        q0.u = ldg16(a.q + off + (size_t)qt * 1024, q_lane);
+        q1.u = ldg16(a.q + off + (size_t)qt * 1024 + 16, q_lane);
+        f32x16 o;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[v] = 0.f;
+        float m = -INFINITY, l = 0.f;
+        for (int kt = 0; kt < nt; ++kt) {
+            const uint32_t live = __builtin_amdgcn_readfirstlane(s_live[kt * NR + j]);
+            if (live == 0) continue;
+            f32x16 s;
+            load_bias(kt, s);
+            Frag k0, k1, v0, v1;
+            const uint32_t kv = (uint32_t)(kperm * 32 + 8 * hf) * 2;
+            k0.u = ldg16(a.k + off + (size_t)kt * 1024, kv);
+            k1.u = ldg16(a.k + off + (size_t)kt * 1024 + 16, kv);
+            v0.u = ldg16(a.vt + off + (size_t)kt * 1024, q_lane);
+            v1.u = ldg16(a.vt + off + (size_t)kt * 1024 + 16, q_lane);
+            s = mfma(k0.v, q0.v, s);
+            s = mfma(k1.v, q1.v, s);
+            s = mask_step(live, s);
+            float mx = s[0];
+#pragma unroll
+            for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
+            const float m_new = fmaxf(m, fmaxf(mx, other_half(mx)));       // (finite: the tile holds a live key)
+            const float sc = __builtin_amdgcn_exp2f(m - m_new);
+            m = m_new;
+            l *= sc;
+            Frag p[2];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) o[v] *= sc;
+#pragma unroll
+            for (int g = 0; g < 8; ++g) {
+                p[g >> 2].w[g & 3] = pack2(__builtin_amdgcn_exp2f(s[2 * g] - m), __builtin_amdgcn_exp2f(s[2 * g + 1] - m));
+                l = add_pair(p[g >> 2].w[g & 3], l);
+            }
+            o = mfma(v0.v, p[0].v, o);
+            o = mfma(v1.v, p[1].v, o);
+        }
+        uint2 gr[4];
+        load_gate(r, gr);
+        finish(o, l + other_half(l), r, gr);
+    }
+}
+
+bool attn_rows_ok(int d, int L) { return d == 32 && L <= 16384; }
+
+template <int NR, int NW, bool HAS_BIAS>
+static ff_status launch(AttnRowsArgs a, hipStream_t st) {
+    const int nt = (a.L + 31) / 32;
+    const size_t smem = (size_t)kRing * NR * 2 * kTileBytes + (size_t)((nt + 1) & ~1) * NR * 4;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_rows<NR, NW, HAS_BIAS>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+    if (attr != hipSuccess) return fail(FF_EHIP, "k_attn_rows: dynamic LDS limit: %s", hipGetErrorString(attr));
+    a.n_qb = (nt + NW - 1) / NW;
+    a.n_rb = (a.rows + NR - 1) / NR;
+    a.n_items = a.n_qb * a.n_rb * a.H;
+    hipLaunchKernelGGL((k_attn_rows<NR, NW, HAS_BIAS>), dim3((a.n_items + 7) / 8 * 8), dim3(NW * 64), smem, st, a);
+    return FF_OK;
+}
+
+ff_status attn_rows_launch(const AttnRowsArgs& a, hipStream_t st) {
+    // Four rows per wavefront share a bias tile four ways.  Two rows where four would leave compute units with fewer than two
+    // blocks (128 x 128 triangle attention, the whole call: 32.5 us with four, 29.5 with two; 8 x 300 row attention: 43.8, 40.9).
+    const int nt = (a.L + 31) / 32;
+    const int64_t blocks4 = (int64_t)((nt + 3) / 4) * ((a.rows + 3) / 4) * a.H;
+    if (blocks4 < 2 * compute_units()) return a.bias ? launch<2, 4, true>(a, st) : launch<2, 4, false>(a, st);
+    return a.bias ? launch<4, 4, true>(a, st) : launch<4, 4, false>(a, st);
+}
+
+}  // namespace ff

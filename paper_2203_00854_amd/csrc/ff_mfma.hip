@@ -10,7 +10,7 @@
 //               step (operands split into bf16 hi + lo pairs) and the epilogue is a multiplication
 //               by rstd: q scaled, gate = sigmoid(. + b_g), q,k,gate head-major, v transposed,
 //               pair-bias columns as float32 [H][Lq][Lp]
-//   k_attn      flash-style attention: S^T = K Q^T on the matrix cores with the bias tile as
+//   k_attn      flash-style attention at head dims 8 and 16 (32: k_attn_rows, ff_attn_rows.hip): S^T = K Q^T on the matrix cores with the bias tile as
 //               accumulator input; the key mask and the running reference maximum ride in
 //               two spare slots of the contraction, so the matrix core already returns
 //               s - m (+ -inf for masked keys) and the vector unit only exponentiates
@@ -31,10 +31,11 @@
 // fetched, so nothing moves between the two contractions.
 //
 // Workspace layout of this family (Lp = Lq = L rounded up to 64, token p = rl*Lp + l):
-//   bias [H][Lq][Lp] float32 (times log2 e); for k_proj_attn the same elements in 32 x 32 tiles (bias_index)
+//   bias [H][Lq][Lp] float32 (times log2 e); for k_proj_attn and k_attn_rows the same elements in 32 x 32 tiles (bias_index)
 //   q, k, g, o [rows][H][Lp][D] bf16;  vt [rows][H][Lp/32][D][32] bf16
 //   prepared weights [(4*Hd + 32)][c] (+ [32][c_z] in row mode) bf16, their sums and offsets
 // Pad tokens (l in [L, Lp)) hold finite values everywhere; they are masked as keys.
+#include "ff_attn_rows.h"
 #include "ff_common.h"
 
 #include <type_traits>
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(256) void k_prep(PrepArgs a) {
 // the first chunk) and the weight preparation in ONE launch (they do not depend on each other).  Blocks below bias_blocks take
 // 256 pairs each (one 32-pair tile per wavefront, the folded 32 x K weight tile built by the block
 // itself in LDS, same algebra as k_gemm's pair-bias tile); the blocks above them run prep_row.
-// Element (h, q, k) of the pair bias.  Plain: [H][Lq][Lp].  Tiled (for k_proj_attn): 32 x 32 tiles in
+// Element (h, q, k) of the pair bias.  Plain: [H][Lq][Lp].  Tiled (for k_proj_attn and k_attn_rows): 32 x 32 tiles in
 // the register order of an S^T accumulator, [H][Lq/32][Lp/32][4][64 lanes][4]: lane = (q % 32) + 32 hf
 // holds the keys 16c + 8hf + 4i + e of the tile in element e of group 2c + i, so that a wavefront
 // fetches a tile with four loads of 1 KiB each.
@@ -466,7 +467,8 @@ struct GemmArgs {
     float invD;            // 1 / D
     int nt_main;           // PROJ: 32-feature tiles of q|k|v|gate; tile nt_main is the pair-bias tile
     bf16_t *q, *k, *g, *vt;  // PROJ outputs
-    float* bias;             // PROJ pair-bias output [H][Lq][Lp]
+    float* bias;             // PROJ pair-bias output [H][Lq][Lp], in the layout that tiled says (bias_index)
+    int tiled;
     bf16_t* out;             // OUT output, token (r,l) at (r*sr + l*sl)*N
     const bf16_t* res;       // OUT with RES: added to the output, laid out like out (may be out itself)
     int N;                   // OUT: features
@@ -704,7 +706,7 @@ __global__ __launch_bounds__(kGemmWaves * 64, 2) void k_gemm(GemmArgs a) {
             hlim = a.H - 4 * hf;
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt)
-                qk_off[tt] = (size_t)(a.r0 + tok_rl[tt]) * a.Lp + tok_l[tt] + (size_t)(4 * hf) * a.Lq * a.Lp;
+                qk_off[tt] = bias_index(a.tiled != 0, 4 * hf, a.r0 + tok_rl[tt], tok_l[tt], a.Lq, a.Lp);
         }
         // value v of the lane: one multiplication by 1/std (the matrix core has already added the
         // LayerNorm mean and offset terms), the sigmoid for the gate, bf16
@@ -954,11 +956,11 @@ constexpr int kBiasPad = 4;      // floats added to an LDS bias row: conflict-fr
 constexpr float kRaise = 10.f;   // log2 units
 constexpr float kOver = 1048576.f;   // 2^20: partial denominator (16 keys) that triggers a raise of the reference
 
-// (bias-free 4-row blocks for head dims below 32 are held to 168 registers, three wavefronts per
-// SIMD: d = 8 fits as it is, d = 16 spills fifteen registers and is still 9 % faster; at d = 32 the
-// same bound costs more in spills than the third wavefront brings)
+// (bias-free 4-row blocks are held to 168 registers, three wavefronts per SIMD: d = 8 fits as it is, d = 16 spills
+// fifteen registers and is still 9 % faster; head dim 32 has k_attn_rows)
 template <int D, bool HAS_BIAS, int RB, int GK, bool PERSIST>
-__global__ __launch_bounds__(RB * 64, (RB == 4 && !HAS_BIAS && D < 32) ? 3 : 2) void k_attn(AttnArgs a) {
+__global__ __launch_bounds__(RB * 64, (RB == 4 && !HAS_BIAS) ? 3 : 2) void k_attn(AttnArgs a) {
+    static_assert(D == 8 || D == 16, "head dim 32 has a kernel of its own");
     constexpr int PCX = D / 8;              // index of the 8-slot piece holding the two extra slots
     constexpr int KS = PCX / 2 + 1;         // 16-wide contraction steps
     constexpr int SX = PCX / 2, HX = PCX % 2;
@@ -1336,10 +1338,8 @@ __global__ __launch_bounds__(RB * 64, (RB == 4 && !HAS_BIAS && D < 32) ? 3 : 2) 
     // barrier of the group) at the end of the even half of the iteration before.
     // (the last pair of tiles has a body of its own: the loop proper then holds no load that
     // depends on a condition, which keeps the compiler's wait counts exact)
-    // Head dims below 32: the next tile's contraction is issued from inside the exponentials (soft_pv,
-    // FUSE).  Measured at 1024 keys, d = 8: 702 -> 671 us.  At d = 32, with three times the matrix
-    // instructions per tile, the same weave is 2 % slower than the contraction issued ahead in one go.
-    constexpr bool WEAVE_QK = D < 32;
+    // The next tile's contraction is issued from inside the exponentials (soft_pv,
+    // FUSE).  Measured at 1024 keys, d = 8: 702 -> 671 us.
     auto tile_pair = [&](int i, auto last_c) __attribute__((always_inline)) {
         constexpr bool LAST = decltype(last_c)::value;
         // ---- even tile i: K(i+2) -> set 0, V(i+1) -> set 1, S^T(i+1) -> s1, exponentials of s0
@@ -1371,13 +1371,8 @@ __global__ __launch_bounds__(RB * 64, (RB == 4 && !HAS_BIAS && D < 32) ? 3 : 2) 
                 fetch_k(kb0, mv0, 0);
             }
         }
-        if constexpr (WEAVE_QK) {
-            if (live0) live1 = soft_pv(s0, vb0, s1, false, integral_constant<bool, true>{}, kb1, mv1, i + 1);
-            else live1 = qk_mma(kb1, mv1, i + 1, s1);
-        } else {
-            live1 = qk_mma(kb1, mv1, i + 1, s1);
-            if (live0) soft_pv(s0, vb0, s1, live1, integral_constant<bool, false>{}, kb1, mv1, 0);
-        }
+        if (live0) live1 = soft_pv(s0, vb0, s1, false, integral_constant<bool, true>{}, kb1, mv1, i + 1);
+        else live1 = qk_mma(kb1, mv1, i + 1, s1);
         if constexpr (HAS_BIAS && !LAST) {
             if ((i + 2) % TPG == 0) {
                 store_bias(((i + 2) / TPG + gbase) & 1);
@@ -1393,13 +1388,8 @@ __global__ __launch_bounds__(RB * 64, (RB == 4 && !HAS_BIAS && D < 32) ? 3 : 2) 
             if constexpr (HAS_BIAS) {
                 if ((i + 4) % TPG == 0 && i + 4 < nt) load_bias((i + 4) / TPG);
             }
-            if constexpr (WEAVE_QK) {
-                if (live1) live0 = soft_pv(s1, vb1, s0, false, integral_constant<bool, true>{}, kb0, mv0, i + 2);
-                else live0 = qk_mma(kb0, mv0, i + 2, s0);
-            } else {
-                live0 = qk_mma(kb0, mv0, i + 2, s0);
-                if (live1) soft_pv(s1, vb1, s0, live0, integral_constant<bool, false>{}, kb0, mv0, 0);
-            }
+            if (live1) live0 = soft_pv(s1, vb1, s0, false, integral_constant<bool, true>{}, kb0, mv0, i + 2);
+            else live0 = qk_mma(kb0, mv0, i + 2, s0);
         } else {
             if constexpr (PERSIST) {
                 fetch_k(kb1, mv1, 1);
@@ -1929,7 +1919,7 @@ static int pick_split(int blocks_m, int tiles_n) {
     return split;
 }
 
-// Batch rows per attention block (one wavefront each).  With a bias, 8 rows halve the bias traffic
+// Batch rows per block of k_attn (one wavefront each).  With a bias, 8 rows halve the bias traffic
 // of 4.  Without one nothing is shared inside a block, and for head dims below 32 the kernel needs
 // at most 168 registers: blocks of 4 wavefronts then fit three to a compute unit (three
 // wavefronts per SIMD) where a block of 8 leaves a third of the register file empty.
@@ -1991,6 +1981,8 @@ static ff_status launch_attn(int n_items, size_t smem, hipStream_t st, const Att
 }
 
 static bool fused_proj_attn(const Problem& p);
+// whether the pair bias is written in the tiles of bias_index: k_proj_attn and k_attn_rows read it so
+static bool tiled_bias(const Problem& p) { return fused_proj_attn(p) || attn_rows_ok(p.d, p.L); }
 
 static GemmArgs proj_args(const Problem& p, const MfmaWs& m, const Workspace& ws) {
     const int Lp = round_up(p.L, 64), Lq = round_up(p.L, 64);
@@ -1998,7 +1990,7 @@ static GemmArgs proj_args(const Problem& p, const MfmaWs& m, const Workspace& ws
     g.sr = p.sr; g.sl = p.sl; g.L = p.L; g.Lp = Lp; g.Lq = Lq; g.K = p.c; g.eps = p.eps;
     g.w = m.wp; g.aug = m.aug; g.Hd = p.Hd; g.H = p.H; g.D = p.d; g.invD = 1.f / (float)p.d; g.dsh = p.d == 8 ? 3 : (p.d == 16 ? 4 : 5);
     g.nt_main = 4 * p.Hd / 32;
-    g.q = m.q; g.k = m.k; g.g = m.g; g.vt = m.vt; g.bias = ws.bias;
+    g.q = m.q; g.k = m.k; g.g = m.g; g.vt = m.vt; g.bias = ws.bias; g.tiled = tiled_bias(p) ? 1 : 0;
     return g;
 }
 
@@ -2029,7 +2021,7 @@ ff_status mfma_prepare(const Problem& p, const ff_attn_weights& w, const void* x
             // triangle attention needs the bias of all rows before the first chunk
             PrepBiasArgs b{};
             b.prep = a;
-            b.tiled = fused_proj_attn(p) ? 1 : 0;
+            b.tiled = tiled_bias(p) ? 1 : 0;
             b.bias_blocks = (p.L * (Lp / 32) + 7) / 8;
             b.w_b = (const bf16_t*)w.w_b;
             if (chunked_tri) {
@@ -2052,7 +2044,7 @@ ff_status mfma_prepare(const Problem& p, const ff_attn_weights& w, const void* x
             hipLaunchKernelGGL(k_prep, dim3((rows + 3) / 4), dim3(256), 0, st, a);
         }
     }
-    if (p.has_bias && Lq > p.L) {
+    if (p.has_bias && Lq > p.L && (fused_proj_attn(p) || !attn_rows_ok(p.d, p.L))) {
         const int n = (Lq - p.L) * Lp * p.H;
         Timed t(KK_PREP, st);
         hipLaunchKernelGGL(k_zero_bias_pad, dim3((n + 255) / 256), dim3(256), 0, st, ws.bias, p.L, Lq, Lp, p.H,
@@ -2125,7 +2117,14 @@ ff_status mfma_chunk(const Problem& p, const ff_attn_weights& w, const void* x, 
     a.q = m.q; a.k = m.k; a.g = m.g; a.vt = m.vt; a.o = m.o; a.bias = ws.bias; a.mask = mask;
     a.sr = p.sr; a.sl = p.sl; a.r0 = r0; a.rows = rows; a.L = p.L; a.Lp = Lp; a.Lq = Lq; a.H = p.H; a.Hd = p.Hd;
     a.inv_nq = 1.f / (float)(Lp / 64); a.inv_nqh = 1.f / (float)((Lp / 64) * p.H);
-    if (!fused) {
+    if (!fused && attn_rows_ok(p.d, p.L)) {
+        AttnRowsArgs r{};
+        r.q = m.q; r.k = m.k; r.g = m.g; r.vt = m.vt; r.o = m.o; r.bias = ws.bias; r.mask = mask;
+        r.sr = p.sr; r.sl = p.sl; r.r0 = r0; r.rows = rows; r.L = p.L; r.Lp = Lp; r.Lq = Lq; r.H = p.H;
+        Timed t(KK_ATTN, st);
+        const ff_status ls = attn_rows_launch(r, st);
+        if (ls != FF_OK) return ls;
+    } else if (!fused) {
         Timed t(KK_ATTN, st);
         ff_status ls = FF_OK;
         const int rb = attn_rows_per_block(p, rows);
@@ -2153,8 +2152,7 @@ ff_status mfma_chunk(const Problem& p, const ff_attn_weights& w, const void* x, 
         else FF_ATTN2(DD, 4);        \
     } while (0)
         if (p.d == 8) FF_ATTN(8);
-        else if (p.d == 16) FF_ATTN(16);
-        else FF_ATTN(32);
+        else FF_ATTN(16);
 #undef FF_ATTN
 #undef FF_ATTN2
 #undef FF_ATTN3

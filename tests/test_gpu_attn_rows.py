@@ -1,0 +1,69 @@
+"""GPU parity of k_attn_rows (attention at head dimension 32 outside the sequences of k_proj_attn) against the float64 oracle.
+
+Sizes at its edges: one key, remainders of 32 keys, of four query tiles per block and of the two / four batch rows of a
+wavefront, more than eight row blocks, a last ring slot of every index; masks that empty whole key tiles or rows; logits
+far outside the range in which a softmax needs no reference.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2203_00854_amd as P
+from oracle import evoformer_attention as O
+from paper_2203_00854_amd import inputs as I
+from helpers import small_spec, f64_inputs, max_abs, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+ROW, COL, TS, TE = I.MODE_ROW, I.MODE_COL, I.MODE_TRI_START, I.MODE_TRI_END
+DEV = "cuda:0"
+
+
+def run(case, chunk=0):
+    desc, w, x, z, mask = P.to_device(case, DEV)
+    ws = torch.full((P.ff_attention_workspace_bytes(desc, chunk),), 0xFF, dtype=torch.uint8, device=DEV)      # (NaN patterns)
+    out = P.ff_attention_chunked(desc, w, x, z, mask, chunk_rows=chunk, ws=ws) if chunk else P.ff_gated_attention(desc, w, x, z, mask, ws=ws)
+    torch.cuda.synchronize()
+    assert P.ff_attention_last_path() == "mfma_bf16"
+    return out.float().cpu().numpy().astype(np.float64)
+
+
+def check(case, got, what):
+    x, z, m, w = f64_inputs(case)
+    ref = O.gated_attention(case.spec.mode, x, z, m, w, case.spec.heads, case.spec.ln_eps)
+    ma, rl = max_abs(got, ref), rel_l2(got, ref)
+    print(f"{what}: max_abs={ma:.3e} rel_l2={rl:.3e}", flush=True)
+    assert np.isfinite(got).all() and ma <= 2e-2 and rl <= 1e-2, (what, ma, rl)
+
+
+@pytest.mark.parametrize("mode,n_a,n_b,c,H,c_z,mask,chunk", [
+    (ROW, 3, 1, 64, 2, 16, "none", 0),
+    (ROW, 5, 31, 32, 1, 16, "tail:3", 0),
+    (ROW, 2, 65, 96, 3, 16, "random:0.7", 0),
+    (ROW, 150, 97, 64, 8, 32, "tail:40", 0),                 # many row blocks; the last key tiles hold no valid key
+    (ROW, 40, 300, 256, 8, 32, "random:0.9", 0),
+    (ROW, 3, 513, 64, 2, 16, "tail:1", 0),
+    (COL, 128, 5, 64, 2, 0, "none", 0),
+    (COL, 290, 45, 256, 8, 0, "tail:30", 0),
+    (TS, 127, 127, 128, 4, 0, "outer:0.9", 50),
+    (TE, 257, 257, 64, 2, 0, "none", 0),
+    (TS, 275, 275, 128, 4, 0, "outer:0.95", 0),
+])
+def test_shapes(mode, n_a, n_b, c, H, c_z, mask, chunk):
+    case = I.make_case(small_spec(mode, n_a, n_b, c, H, 32, c_z=c_z, dtype="bf16", mask=mask))
+    check(case, run(case, chunk), case.spec.name)
+
+
+@pytest.mark.parametrize("n_a,n_b", [(3, 70), (300, 260)])
+def test_logits_far_from_zero(n_a, n_b):
+    """The softmax runs without a reference while the denominator stays inside [2^-60, 2^96].  An offset of the pair bias moves all
+    logits of a head by the same amount (which the softmax removes): heads at about -140, +140, -50 and +50 log2 units, the
+    first two outside that range; one batch row is fully masked."""
+    case = I.make_case(small_spec(ROW, n_a, n_b, 64, 4, 32, c_z=16, dtype="bf16", mask="random:0.8"))
+    case.mask[1, :] = 0.0
+    case.weights["lnz_b"] = I.to_storage(np.full(16, 4.0), "bf16")
+    wb = I.widen(case.weights["w_b"]).astype(np.float64)
+    for h, shift in enumerate((-97.0, 97.0, -35.0, 35.0)):
+        wb[h] += shift / 64.0
+    case.weights["w_b"] = I.to_storage(wb, "bf16")
+    check(case, run(case), f"{n_a} x {n_b}")
