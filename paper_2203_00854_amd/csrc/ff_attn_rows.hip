@@ -1,5 +1,5 @@
-// Attention of the bf16 matrix-core family at head dimension 32 (FastFold Section 5.2's fused scale + mask + bias
-// softmax between the two contractions), for the sequences that k_proj_attn does not take.
+// Attention of the bf16 matrix-core family (FastFold Section 5.2's fused scale + mask + bias softmax between the two
+// contractions) at head dimensions 8, 16 and 32, for the calls that k_proj_attn does not take.
 //
 // A wavefront owns 32 queries of NR batch rows and walks over the keys in steps of 32: NR tiles of 32 x 32 scores
 // per step, S^T = K Q^T with the pair-bias tile as accumulator input, exponentials, O^T += V^T P^T.  The bias tile
@@ -17,11 +17,13 @@
 //  - the denominator is summed from the rounded weights by 4 x 4 x 4 matrix instructions: eight v_dot2 per tile do not overlap
 //    with matrix instructions (bare loops of the tile's mix, two wavefronts per SIMD: 123 ns with dots, 104 so, 93
 //    without any denominator).
+//    Below head dim 32 the context's matrix instructions have rows to spare: a row of ones in v^T sums the denominator.
 //  - masked keys cost one more matrix instruction, in steps that hold any; steps before the first masked key skip the test.
 //  - matrix instructions of the next and the previous tile alternate with the exponentials of this one.
 // Measured, 64 rows x 4 heads x 2048^2 with bias: 249 us for the kernel before (a wavefront per batch row with 64 queries,
 // bias through LDS, five matrix instructions per tile), 190 now; 333 rows x 4 x 333^2: 81 -> 58.  Without its loads the
 // kernel takes 164, without the LDS reads as well 135; the shader clock is 2.0 - 2.1 GHz under this load (2.37 without).
+// 384 columns x 8 heads of 8 x 1024^2: 534 -> 409 us (the exponentials and packs alone: about 250).
 #include "ff_attn_rows.h"
 
 namespace ff {
@@ -87,7 +89,6 @@ __device__ __forceinline__ void load16_to_lds(const void* base, uint32_t lane_by
 constexpr int kWaitVmcnt0 = 0x0F70;      // s_waitcnt vmcnt(0), the other counters untouched
 
 constexpr int kRing = 4;                 // steps in the LDS ring
-constexpr int kTileBytes = 2048;         // a tile of 32 keys x 32 elements (k) or 32 elements x 32 keys (v^T)
 
 __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
@@ -95,12 +96,25 @@ __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
 
 }  // namespace
 
-template <int NR, int NW, bool HAS_BIAS>
-__global__ __launch_bounds__(NW * 64, 2) void k_attn_rows(AttnRowsArgs a) {
-    static_assert(NR == 2 || NR == 4, "rows per wavefront");
+// wavefronts per SIMD the registers of an instantiation are held to.  Without a bias and below head dim 32 two rows fit 128
+// registers: four wavefronts per SIMD, where the exponentials of a wavefront hide another's waits (1024-sequence column
+// attention at d = 8, the whole call: 438 us; three wavefronts 456; four rows and three wavefronts 499, two 469).
+constexpr int attn_rows_waves(int D, bool has_bias) { return D == 32 || has_bias ? 2 : 4; }
+
+template <int D, int NR, int NW, bool HAS_BIAS>
+__global__ __launch_bounds__(NW * 64, attn_rows_waves(D, HAS_BIAS)) void k_attn_rows(AttnRowsArgs a) {
+    static_assert((D == 8 || D == 16 || D == 32) && (NR == 2 || NR == 4), "head dimension, rows per wavefront");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr int STEP = NR * 2 * kTileBytes;                                        // bytes of a ring slot: [row][k | v^T]
-    uint32_t* s_live = reinterpret_cast<uint32_t*>(smem + kRing * STEP);             // [key tile][NR]: bit = key is attended to
+    constexpr int TILE = 64 * D;                    // bytes of a tile of 32 keys: k as [key][D], v^T as [D][key]
+    constexpr int KS = D / 16 > 0 ? D / 16 : 1;     // contraction steps of S^T
+    constexpr int STEP = NR * 2 * TILE;             // bytes of a ring slot; k and v^T of its row j:
+    constexpr auto k_at = [](int j) { return D == 8 ? (j >> 1) * 4 * TILE + (j & 1) * TILE : j * 2 * TILE; };
+    constexpr auto v_at = [](int j) { return D == 8 ? (j >> 1) * 4 * TILE + (j & 1) * TILE + 2 * TILE : j * 2 * TILE + TILE; };
+    // below head dim 32 rows D .. 31 of the v^T operand are free: row D holds ones, so that the context's matrix
+    // instructions sum the denominator; the lanes of rows D .. 31 read it from an area of alternating 64-byte blocks of ones and zeros
+    constexpr bool ONES = D < 32;
+    unsigned char* s_ones = smem + kRing * STEP;                                                   // [STEP]
+    uint32_t* s_live = reinterpret_cast<uint32_t*>(smem + (kRing + (ONES ? 1 : 0)) * STEP);        // [key tile][NR]: bit = key is attended to
 
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, hf = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -130,27 +144,39 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_rows(AttnRowsArgs a) {
 #pragma unroll
     for (int j = 0; j < NR; ++j) row[j] = rb * NR + j < a.rows ? rb * NR + j : a.rows - 1;
 
-    // ---- k and v^T on their way into the ring.  Chunk c of a step is KiB c % 4 of row c / 4 (two of k, two of v^T);
-    // lane i of a load fills 16-byte slot i, and the piece it fetches is chosen so that the operand reads below
-    // spread over the banks (sixteen lanes at a time read one 16-byte piece each, four rows make a line of 64 banks):
-    // piece p of key (element) r sits at slot 4 r + (p ^ (r / 4) % 4).
+    // ---- k and v^T on their way into the ring, a KiB per wavefront and load: lane i fills 16-byte slot i of the chunk, and
+    // the piece it fetches is chosen so that the operand reads below spread over the banks (sixteen lanes at a time
+    // read one 16-byte piece each): piece p of element e of v^T sits at slot 4 e + (p ^ (e / 4) % 4), piece p of key r at slot
+    // 4 r + (p ^ (r / 4) % 4), 2 r + (p ^ (r / 8) % 2) or r for 32, 16 or 8 elements.
     const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lptr_t)smem);
-    const uint32_t st_lane = (uint32_t)((lane >> 2) * 64 + (((lane & 3) ^ ((lane >> 4) & 3)) * 16));
-    const size_t head_elems = (size_t)a.Lp * 32;
-    constexpr int CPW = 4 * NR / NW;                          // chunks of a step per wavefront
+    const size_t head_elems = (size_t)a.Lp * D;
+    constexpr int CHUNKS = STEP / 1024, CPW = (CHUNKS + NW - 1) / NW;      // of a step, and of them per wavefront
     const char* st_src[CPW];                                  // (scalar) the chunk in key tile 0
+    uint32_t st_lane[CPW];
 #pragma unroll
     for (int i = 0; i < CPW; ++i) {
-        const int c = i * NW + wave, part = c & 3;
-        int r = rb * NR + (c >> 2);
-        if (r > a.rows - 1) r = a.rows - 1;
-        st_src[i] = reinterpret_cast<const char*>((part < 2 ? a.k : a.vt) + ((size_t)r * a.H + h) * head_elems + (part & 1) * 512);
+        const int c = i * NW + wave;
+        // chunk c: D = 32: half c % 2 of k (c % 4 < 2) or v^T of row c / 4; D = 16: k or v^T of row c / 2; D = 8: k or v^T of rows c, c + 1 (c even)
+        const int j = D == 32 ? c >> 2 : (D == 16 ? c >> 1 : c & ~1);
+        const bool is_v = D == 32 ? (c & 2) != 0 : (c & 1) != 0;
+        auto clamp_row = [&](int jj) __attribute__((always_inline)) { return rb * NR + jj < a.rows ? rb * NR + jj : a.rows - 1; };
+        const int r0 = clamp_row(j);
+        st_src[i] = reinterpret_cast<const char*>((is_v ? a.vt : a.k) + ((size_t)r0 * a.H + h) * head_elems + (D == 32 ? (c & 1) * 512 : 0));
+        const uint32_t v_piece = (uint32_t)((lane & 3) ^ ((lane >> 4) & 3));           // (element lane / 4 of the chunk)
+        uint32_t off = (uint32_t)(lane >> 2) * 64 + v_piece * 16;
+        if (D == 16 && !is_v) off = (uint32_t)(lane >> 1) * 32 + (uint32_t)((lane & 1) ^ ((lane >> 4) & 1)) * 16;
+        if (D == 8) {
+            const int i5 = lane & 31;
+            off = is_v ? (uint32_t)(i5 >> 2) * 64 + (uint32_t)((i5 & 3) ^ ((i5 >> 4) & 3)) * 16 : (uint32_t)i5 * 16;
+            if (lane >= 32) off += (uint32_t)((size_t)(clamp_row(j + 1) - r0) * a.H * head_elems * 2);
+        }
+        st_lane[i] = off;
     }
     auto stage = [&](int kt) __attribute__((always_inline)) {
-        const uint32_t off = st_lane + (uint32_t)kt * kTileBytes;
         const unsigned dst = lds0 + (unsigned)(kt & (kRing - 1)) * STEP + wave * 1024;
 #pragma unroll
-        for (int i = 0; i < CPW; ++i) load16_to_lds(st_src[i], off, dst + i * NW * 1024);
+        for (int i = 0; i < CPW; ++i)
+            if (CHUNKS % NW == 0 || i * NW + wave < CHUNKS) load16_to_lds(st_src[i], st_lane[i] + (uint32_t)kt * TILE, dst + i * NW * 1024);
     };
     // ---- mask entries of 64 keys per load, eight loads in flight (the ballots follow below)
     const int n_pairs = (nt + 1) >> 1;
@@ -174,14 +200,17 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_rows(AttnRowsArgs a) {
     if (nt > 2) stage(2);
 
     // ---- q: B operand of S^T (lane = query, 8 consecutive elements)
-    Frag qf[NR][2];
+    Frag qf[NR][KS];
     const int qtc = active ? qt : nt - 1;
-    const uint32_t q_lane = (uint32_t)(col * 32 + 8 * hf) * 2;
+    const uint32_t q_lane = (uint32_t)(col * D + (D > 8 ? 8 * hf : 0)) * 2;
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
-        const bf16_t* qp = a.q + ((size_t)row[j] * a.H + h) * head_elems + (size_t)qtc * 1024;
-        qf[j][0].u = ldg16(qp, q_lane);
-        qf[j][1].u = ldg16(qp + 16, q_lane);
+        const bf16_t* qp = a.q + ((size_t)row[j] * a.H + h) * head_elems + (size_t)qtc * (32 * D);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            qf[j][s].u = ldg16(qp + 16 * s, q_lane);
+            if (D == 8 && hf != 0) qf[j][s].u = make_uint4(0, 0, 0, 0);      // (the upper half of the contraction is empty)
+        }
     }
     // ---- bias tiles of the wavefront's queries, one after the other
     const float* bias_q = HAS_BIAS ? a.bias + ((size_t)h * (a.Lq >> 5) + qtc) * (a.Lp >> 5) * 1024 : nullptr;
@@ -219,13 +248,24 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_rows(AttnRowsArgs a) {
             }
         }
     }
+    if constexpr (ONES) {
+        for (int i = tid; i < STEP / 16; i += NW * 64) {
+            const uint32_t v = i & 4 ? 0u : 0x3f803f80u;
+            *reinterpret_cast<uint4*>(s_ones + i * 16) = make_uint4(v, v, v, v);
+        }
+    }
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     __syncthreads();
 
     // permuted key of S^T row m = col: the lane's registers 8c .. 8c+7 then hold the keys 16c + 8hf .. + 7
     const int kperm = 16 * (col >> 4) + 8 * ((col >> 2) & 1) + 4 * ((col >> 3) & 1) + (col & 3);
-    const uint32_t rd_k = (uint32_t)(kperm * 64 + ((hf ^ ((kperm >> 2) & 3)) * 16));
-    const uint32_t rd_v = (uint32_t)(kTileBytes + col * 64 + ((hf ^ ((col >> 2) & 3)) * 16));
+    const uint32_t rd_k = D == 32 ? (uint32_t)(kperm * 64 + ((hf ^ ((kperm >> 2) & 3)) * 16))
+                                  : (D == 16 ? (uint32_t)(kperm * 32 + ((hf ^ ((kperm >> 3) & 1)) * 16)) : (uint32_t)(kperm * 16));
+    // (rows D .. 31 of v^T do not move with the ring slot; their pieces lie in the banks that rows 0 .. 7 leave free)
+    const bool v_row = col < D;
+    const uint32_t rd_v = v_row ? (uint32_t)(col * 64 + ((hf ^ ((col >> 2) & 3)) * 16))
+                                : (uint32_t)(kRing * STEP + (col == D ? 0 : 64) + (hf ^ 2) * 16);
+    const uint32_t v_moves = v_row ? 0xffffffffu : 0u;
     auto lds16 = [&](uint32_t off) __attribute__((always_inline)) { return *reinterpret_cast<const uint4*>(smem + off); };
 
     // publishes what set out a step ago and sends the next step on its way (the ring slot it fills was last read before
@@ -243,14 +283,14 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_rows(AttnRowsArgs a) {
     }
 
     f32x16 o_acc[NR], s_acc[2];
-    float l_run[NR];
+    float l_run[NR];          // denominators (head dim 32; below it they are a row of o_acc)
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
         l_run[j] = 0.f;
 #pragma unroll
         for (int v = 0; v < 16; ++v) o_acc[j][v] = 0.f;
     }
-    Frag kf[2][2], vf[2][2], pf[2];
+    Frag kf[2][KS], vf[2][2], pf[2];
 #pragma unroll
     for (int c = 0; c < 2; ++c) pf[c].u = vf[1][c].u = make_uint4(0, 0, 0, 0);
     // (query side of the mask step: a one against the key side's 0 or -inf)
@@ -263,29 +303,26 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_rows(AttnRowsArgs a) {
     // One tile (row j of the step) of the software pipeline: the exponentials of tile t run while the matrix core forms
     // the scores of tile t + 1 (bias bn, query operand qn, keys kn) and the context of tile t - 1 (weights pp, values vp),
     // and the operands k of tile t + 2 and v^T of tile t come from LDS.
-    auto tile = [&](auto plain_c, uint32_t live, f32x16& sc, f32x16& sn, const f32x16& bn, Frag (&kn)[2], Frag (&kl)[2], Frag (&vp)[2], Frag (&vl)[2], Frag (&qn)[2], uint32_t kl_off, uint32_t vl_off,
+    auto tile = [&](auto plain_c, uint32_t live, f32x16& sc, f32x16& sn, const f32x16& bn, Frag (&kn)[KS], Frag (&kl)[KS], Frag (&vp)[2], Frag (&vl)[2], Frag (&qn)[KS], uint32_t kl_off, uint32_t vl_off0, uint32_t vl_off1,
                     f32x16& op, float& lp) __attribute__((always_inline)) {
         Frag pc[2];
         f32x4 lt = {0.f, 0.f, 0.f, 0.f};
         float e0 = __builtin_amdgcn_exp2f(sc[0]), e1 = __builtin_amdgcn_exp2f(sc[1]);
 #pragma unroll
         for (int g = 0; g < 8; ++g) {
-            if (!decltype(plain_c)::value && g == 4 && live != 0xffffffffu) sn = mask_step(live, sn);
-            if (g == 1) lt = add_four(pf[0].w[0], pf[0].w[1], lt);
-            if (g == 3) lt = add_four(pf[0].w[2], pf[0].w[3], lt);
-            if (g == 5) lt = add_four(pf[1].w[0], pf[1].w[1], lt);
-            if (g == 7) lt = add_four(pf[1].w[2], pf[1].w[3], lt);
             if (g == 0) sn = mfma(kn[0].v, qn[0].v, bn);
-            if (g == 2) sn = mfma(kn[1].v, qn[1].v, sn);
+            if (KS > 1 && g == 2) sn = mfma(kn[KS - 1].v, qn[KS - 1].v, sn);
             if (g == 4) op = mfma(vp[0].v, pf[0].v, op);
             if (g == 6) op = mfma(vp[1].v, pf[1].v, op);
-            if (g == 1) {
-                vl[0].u = lds16(vl_off + rd_v);
-                vl[1].u = lds16(vl_off + (rd_v ^ 32u));
-            }
+            if (!decltype(plain_c)::value && g == 4 && live != 0xffffffffu) sn = mask_step(live, sn);
+            if (!ONES && (g & 1)) lt = add_four(pf[g >> 2].w[(g >> 1) % 2 * 2], pf[g >> 2].w[(g >> 1) % 2 * 2 + 1], lt);
             if (g == 0) {
                 kl[0].u = lds16(kl_off + rd_k);
-                kl[1].u = lds16(kl_off + (rd_k ^ 32u));
+                if (KS > 1) kl[KS - 1].u = lds16(kl_off + (rd_k ^ 32u));
+            }
+            if (g == 1) {
+                vl[0].u = lds16(ONES ? vl_off0 : vl_off0 + rd_v);
+                vl[1].u = lds16(ONES ? vl_off1 : vl_off0 + (rd_v ^ 32u));
             }
             float n0 = 0.f, n1 = 0.f;
             if (g < 7) {
@@ -300,7 +337,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_rows(AttnRowsArgs a) {
             e0 = n0;
             e1 = n1;
         }
-        lp += lt[0];
+        if (!ONES) lp += lt[0];
         pf[0] = pc[0];
         pf[1] = pc[1];
     };
@@ -315,6 +352,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_rows(AttnRowsArgs a) {
         const uint32_t cur = (uint32_t)(kt & (kRing - 1)) * STEP, nxt = (uint32_t)((kt + 1) & (kRing - 1)) * STEP;
         constexpr bool PLAIN = decltype(plain_c)::value;
         if constexpr (!PLAIN) fetch_live(kt + 1, live_n);
+        const uint32_t v0 = ONES ? rd_v + (cur & v_moves) : cur, v1 = ONES ? (rd_v ^ 32u) + (cur & v_moves) : cur;
 #pragma unroll
         for (int j = 0; j < NR; ++j) {
             constexpr int LAST = NR - 1;
@@ -324,12 +362,12 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_rows(AttnRowsArgs a) {
 #pragma unroll
                 for (int i = 0; i < NR; ++i) live_n[i] = __builtin_amdgcn_readfirstlane(live_n[i]);
             }
-            const uint32_t kl_off = j + 2 < NR ? cur + (uint32_t)(j + 2) * 2 * kTileBytes : nxt + (uint32_t)(j + 2 - NR) * 2 * kTileBytes;
-            const uint32_t vl_off = cur + (uint32_t)j * 2 * kTileBytes;
-            Frag(&qn)[2] = qf[j == LAST ? 0 : j + 1];
+            const uint32_t kl_off = j + 2 < NR ? cur + k_at(j + 2) : nxt + k_at(j + 2 - NR);
+            Frag(&qn)[KS] = qf[j == LAST ? 0 : j + 1];
             f32x16& op = o_acc[j == 0 ? LAST : j - 1];
             const f32x16& bt = j == LAST ? bn : bc;
-            tile(plain_c, j == LAST ? live_n[0] : live_c[j == LAST ? 0 : j + 1], s_acc[j & 1], s_acc[(j + 1) & 1], bt, kf[(j + 1) & 1], kf[j & 1], vf[(j + 1) & 1], vf[j & 1], qn, kl_off, vl_off, op, l_run[j == 0 ? LAST : j - 1]);
+            tile(plain_c, j == LAST ? live_n[0] : live_c[j == LAST ? 0 : j + 1], s_acc[j & 1], s_acc[(j + 1) & 1], bt, kf[(j + 1) & 1],
+                 kf[j & 1], vf[(j + 1) & 1], vf[j & 1], qn, kl_off, v0 + v_at(j), v1 + v_at(j), op, l_run[j == 0 ? LAST : j - 1]);
             if (j == LAST) load_bias(kt + 2, bc);
         }
         if constexpr (!PLAIN) {
@@ -342,13 +380,13 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_rows(AttnRowsArgs a) {
     fetch_live(0, live_c);
 #pragma unroll
     for (int j = 0; j < NR; ++j) live_c[j] = __builtin_amdgcn_readfirstlane(live_c[j]);
-    kf[0][0].u = lds16(rd_k);
-    kf[0][1].u = lds16(rd_k ^ 32u);
-    s_acc[0] = mfma(kf[0][0].v, qf[0][0].v, bias_a);
-    s_acc[0] = mfma(kf[0][1].v, qf[0][1].v, s_acc[0]);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        kf[0][s].u = lds16(rd_k ^ (32u * s));
+        s_acc[0] = mfma(kf[0][s].v, qf[0][s].v, s == 0 ? bias_a : s_acc[0]);
+        kf[1][s].u = lds16(k_at(1) + (rd_k ^ (32u * s)));
+    }
     s_acc[0] = mask_step(live_c[0], s_acc[0]);
-    kf[1][0].u = lds16(2 * kTileBytes + rd_k);
-    kf[1][1].u = lds16(2 * kTileBytes + (rd_k ^ 32u));
     // Steps before the first one that holds a masked (or missing) key have a loop of their own without the mask tests.
     int n_plain = nt;
     for (int i = 0; i < nt * NR && n_plain == nt; i += 64) {
@@ -370,28 +408,28 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_rows(AttnRowsArgs a) {
     }
     if (kt < nt) step(integral_constant<bool, false>{}, kt, bias_a, bias_b);
     o_acc[NR - 1] = mfma(vf[1][0].v, pf[0].v, o_acc[NR - 1]);
-    {
+    o_acc[NR - 1] = mfma(vf[1][1].v, pf[1].v, o_acc[NR - 1]);
+    if constexpr (!ONES) {
         f32x4 lt = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int c = 0; c < 4; ++c) lt = add_four(pf[c >> 1].w[2 * (c & 1)], pf[c >> 1].w[2 * (c & 1) + 1], lt);
         l_run[NR - 1] += lt[0];
     }
-    o_acc[NR - 1] = mfma(vf[1][1].v, pf[1].v, o_acc[NR - 1]);
 
     // ---- normalise, gate, store.  Lane = query, register v = element 8*(v/4) + 4*hf + v%4
     const int qi = 32 * qt + col;
-    auto load_gate = [&](int r, uint2 (&gr)[4]) __attribute__((always_inline)) {
-        const bf16_t* gp = a.g + ((size_t)r * a.H + h) * head_elems + (size_t)qt * 1024;
+    auto load_gate = [&](int r, uint2 (&gr)[D / 8]) __attribute__((always_inline)) {
+        const bf16_t* gp = a.g + ((size_t)r * a.H + h) * head_elems + (size_t)qt * (32 * D);
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-            gr[g] = *reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(gp + 8 * g) + (uint32_t)(col * 32 + 4 * hf) * 2);
+        for (int g = 0; g < D / 8; ++g)
+            gr[g] = *reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(gp + 8 * g) + (uint32_t)(col * D + 4 * hf) * 2);
     };
-    auto finish = [&](const f32x16& o, float l_tot, int r, const uint2 (&gate)[4]) __attribute__((always_inline)) {
+    auto finish = [&](const f32x16& o, float l_tot, int r, const uint2 (&gate)[D / 8]) __attribute__((always_inline)) {
         const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-        const size_t off = ((size_t)r * a.H + h) * head_elems + (size_t)qt * 1024;
-        uint32_t pk[8];
+        const size_t off = ((size_t)r * a.H + h) * head_elems + (size_t)qt * (32 * D);
+        uint32_t pk[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
+        for (int g = 0; g < D / 8; ++g) {
             const uint2 gr = gate[g];
             pk[2 * g] = pack2(o[4 * g] * inv * lo_f32(gr.x), o[4 * g + 1] * inv * hi_f32(gr.x));
             pk[2 * g + 1] = pack2(o[4 * g + 2] * inv * lo_f32(gr.y), o[4 * g + 3] * inv * hi_f32(gr.y));
@@ -400,21 +438,27 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_rows(AttnRowsArgs a) {
         merge_halves(pk[1], pk[3]);
         merge_halves(pk[4], pk[6]);      // lower: e 16..23, upper: e 24..31
         merge_halves(pk[5], pk[7]);
-        if (qi < a.L) {
+        if (qi < a.L && (D > 8 || hf == 0)) {
             char* op = reinterpret_cast<char*>(a.o + off) + q_lane;
             *reinterpret_cast<uint4*>(op) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
-            *reinterpret_cast<uint4*>(op + 32) = make_uint4(pk[4], pk[5], pk[6], pk[7]);
+            if (D == 32) *reinterpret_cast<uint4*>(op + 32) = make_uint4(pk[4], pk[5], pk[6], pk[7]);
         }
+    };
+    // the denominator of the lane's query: both halves' partial sums, or row D of the context
+    auto denominator = [&](const f32x16& o, float l) __attribute__((always_inline)) {
+        if constexpr (!ONES) return l + other_half(l);
+        const float x = o[ONES ? D / 2 : 0], y = other_half(x);      // (row D: register D / 2 of the lower half-wave)
+        return hf == 0 ? x : y;
     };
     // A denominator outside [2^-60, 2^96] (some weights overflowed, or all of them are tiny, or NaN): the row is done
     // again below with a running maximum.  0 is right where no key is attended to: redone as well, it costs nothing.
     int again = 0;
-    uint2 gate[NR][4];
+    uint2 gate[NR][D / 8];
 #pragma unroll
     for (int j = 0; j < NR; ++j) load_gate(row[j], gate[j]);
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
-        const float l_tot = l_run[j] + other_half(l_run[j]);
+        const float l_tot = denominator(o_acc[j], l_run[j]);
         const bool fine = l_tot >= 0x1p-60f && l_tot <= 0x1p96f;
         if (rb * NR + j >= a.rows) continue;
         if (__any(!fine && qi < a.L)) again |= 1 << j;
@@ -426,9 +470,12 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_rows(AttnRowsArgs a) {
         again &= again - 1;
         const int r = rb * NR + j;
         const size_t off = ((size_t)r * a.H + h) * head_elems;
-        Frag q0, q1;
-        q0.u = ldg16(a.q + off + (size_t)qt * 1024, q_lane);
-        q1.u = ldg16(a.q + off + (size_t)qt * 1024 + 16, q_lane);
+        Frag qs[KS];
+#pragma unroll
+        for (int i = 0; i < KS; ++i) {
+            qs[i].u = ldg16(a.q + off + (size_t)qt * (32 * D) + 16 * i, q_lane);
+            if (D == 8 && hf != 0) qs[i].u = make_uint4(0, 0, 0, 0);
+        }
         f32x16 o;
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[v] = 0.f;
@@ -438,14 +485,20 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_rows(AttnRowsArgs a) {
             if (live == 0) continue;
             f32x16 s;
             load_bias(kt, s);
-            Frag k0, k1, v0, v1;
-            const uint32_t kv = (uint32_t)(kperm * 32 + 8 * hf) * 2;
-            k0.u = ldg16(a.k + off + (size_t)kt * 1024, kv);
-            k1.u = ldg16(a.k + off + (size_t)kt * 1024 + 16, kv);
-            v0.u = ldg16(a.vt + off + (size_t)kt * 1024, q_lane);
-            v1.u = ldg16(a.vt + off + (size_t)kt * 1024 + 16, q_lane);
-            s = mfma(k0.v, q0.v, s);
-            s = mfma(k1.v, q1.v, s);
+            Frag vs[2];
+            const uint32_t kv = (uint32_t)(kperm * D + (D > 8 ? 8 * hf : 0)) * 2, ve = (uint32_t)((v_row ? col : 0) * 32 + 8 * hf) * 2;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                vs[c].u = ldg16(a.vt + off + (size_t)kt * (32 * D) + 16 * c, ve);
+                const uint32_t fill = col == D ? 0x3f803f80u : 0u;
+                if (!v_row) vs[c].u = make_uint4(fill, fill, fill, fill);
+            }
+#pragma unroll
+            for (int i = 0; i < KS; ++i) {
+                Frag k;
+                k.u = ldg16(a.k + off + (size_t)kt * (32 * D) + 16 * i, kv);
+                s = mfma(k.v, qs[i].v, s);
+            }
             s = mask_step(live, s);
             float mx = s[0];
 #pragma unroll
@@ -462,38 +515,47 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_rows(AttnRowsArgs a) {
                 p[g >> 2].w[g & 3] = pack2(__builtin_amdgcn_exp2f(s[2 * g] - m), __builtin_amdgcn_exp2f(s[2 * g + 1] - m));
                 l = add_pair(p[g >> 2].w[g & 3], l);
             }
-            o = mfma(v0.v, p[0].v, o);
-            o = mfma(v1.v, p[1].v, o);
+            o = mfma(vs[0].v, p[0].v, o);
+            o = mfma(vs[1].v, p[1].v, o);
         }
-        uint2 gr[4];
+        uint2 gr[D / 8];
         load_gate(r, gr);
-        finish(o, l + other_half(l), r, gr);
+        finish(o, denominator(o, l), r, gr);
     }
 }
 
-bool attn_rows_ok(int d, int L) { return d == 32 && L <= 16384; }
-
-template <int NR, int NW, bool HAS_BIAS>
+template <int D, int NR, int NW, bool HAS_BIAS>
 static ff_status launch(AttnRowsArgs a, hipStream_t st) {
     const int nt = (a.L + 31) / 32;
-    const size_t smem = (size_t)kRing * NR * 2 * kTileBytes + (size_t)((nt + 1) & ~1) * NR * 4;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_rows<NR, NW, HAS_BIAS>),
+    const size_t smem = (size_t)(kRing + (D < 32 ? 1 : 0)) * NR * 128 * D + (size_t)((nt + 1) & ~1) * NR * 4;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_rows<D, NR, NW, HAS_BIAS>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
     if (attr != hipSuccess) return fail(FF_EHIP, "k_attn_rows: dynamic LDS limit: %s", hipGetErrorString(attr));
     a.n_qb = (nt + NW - 1) / NW;
     a.n_rb = (a.rows + NR - 1) / NR;
     a.n_items = a.n_qb * a.n_rb * a.H;
-    hipLaunchKernelGGL((k_attn_rows<NR, NW, HAS_BIAS>), dim3((a.n_items + 7) / 8 * 8), dim3(NW * 64), smem, st, a);
+    hipLaunchKernelGGL((k_attn_rows<D, NR, NW, HAS_BIAS>), dim3((a.n_items + 7) / 8 * 8), dim3(NW * 64), smem, st, a);
     return FF_OK;
 }
 
-ff_status attn_rows_launch(const AttnRowsArgs& a, hipStream_t st) {
+template <int D>
+static ff_status launch_d(const AttnRowsArgs& a, hipStream_t st) {
     // Four rows per wavefront share a bias tile four ways.  Two rows where four would leave compute units with fewer than two
-    // blocks (128 x 128 triangle attention, the whole call: 32.5 us with four, 29.5 with two; 8 x 300 row attention: 43.8, 40.9).
+    // blocks (128 x 128 triangle attention, the whole call: 32.5 us with four, 29.5 with two; 8 x 300 row attention: 43.8,
+    // 40.9), and where there is no bias to share and the registers matter more (attn_rows_waves).
     const int nt = (a.L + 31) / 32;
-    const int64_t blocks4 = (int64_t)((nt + 3) / 4) * ((a.rows + 3) / 4) * a.H;
-    if (blocks4 < 2 * compute_units()) return a.bias ? launch<2, 4, true>(a, st) : launch<2, 4, false>(a, st);
-    return a.bias ? launch<4, 4, true>(a, st) : launch<4, 4, false>(a, st);
+    const bool few = (int64_t)((nt + 3) / 4) * ((a.rows + 3) / 4) * a.H < 2 * compute_units();
+    if (a.bias) return few ? launch<D, 2, 4, true>(a, st) : launch<D, 4, 4, true>(a, st);
+    if constexpr (D == 32) {
+        if (!few) return launch<D, 4, 4, false>(a, st);
+    }
+    return launch<D, 2, 4, false>(a, st);
+}
+
+ff_status attn_rows_launch(const AttnRowsArgs& a, int d, hipStream_t st) {
+    if (d == 8) return launch_d<8>(a, st);
+    if (d == 16) return launch_d<16>(a, st);
+    return launch_d<32>(a, st);
 }
 
 }  // namespace ff

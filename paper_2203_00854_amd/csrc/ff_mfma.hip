@@ -10,14 +10,12 @@
 //               step (operands split into bf16 hi + lo pairs) and the epilogue is a multiplication
 //               by rstd: q scaled, gate = sigmoid(. + b_g), q,k,gate head-major, v transposed,
 //               pair-bias columns as float32 [H][Lq][Lp]
-//   k_attn      flash-style attention at head dims 8 and 16 (32: k_attn_rows, ff_attn_rows.hip): S^T = K Q^T on the matrix cores with the bias tile as
-//               accumulator input; the key mask and the running reference maximum ride in
-//               two spare slots of the contraction, so the matrix core already returns
-//               s - m (+ -inf for masked keys) and the vector unit only exponentiates
+//   k_attn_rows (ff_attn_rows.hip) flash-style attention: S^T = K Q^T on the matrix cores with the bias tile as
+//               accumulator input, exponentials, O^T = V^T P^T; gate product
 //               (the paper's fused scale + mask + bias softmax, Section 5.2, without ever
-//               materialising the score tensor of Section 3.2); O^T = V^T P^T; gate product
+//               materialising the score tensor of Section 3.2)
 //   k_gemm<OUT> output projection + b_o, scattered to the caller's layout
-//   k_proj_attn sequences of 129..256 positions at head dimension 32: k_gemm<PROJ> and k_attn in one
+//   k_proj_attn sequences of 129..256 positions at head dimension 32: k_gemm<PROJ> and the attention in one
 //               kernel (a block = two batch rows x one head), q, k, v and gate never leave the chip
 //
 // Matrix-core operand layouts (wave64, 32x32x16, bf16 in, f32 out):
@@ -31,7 +29,7 @@
 // fetched, so nothing moves between the two contractions.
 //
 // Workspace layout of this family (Lp = Lq = L rounded up to 64, token p = rl*Lp + l):
-//   bias [H][Lq][Lp] float32 (times log2 e); for k_proj_attn and k_attn_rows the same elements in 32 x 32 tiles (bias_index)
+//   bias [H][Lq][Lp] float32 (times log2 e) in 32 x 32 tiles (bias_index)
 //   q, k, g, o [rows][H][Lp][D] bf16;  vt [rows][H][Lp/32][D][32] bf16
 //   prepared weights [(4*Hd + 32)][c] (+ [32][c_z] in row mode) bf16, their sums and offsets
 // Pad tokens (l in [L, Lp)) hold finite values everywhere; they are masked as keys.
@@ -299,12 +297,11 @@ __global__ __launch_bounds__(256) void k_prep(PrepArgs a) {
 // the first chunk) and the weight preparation in ONE launch (they do not depend on each other).  Blocks below bias_blocks take
 // 256 pairs each (one 32-pair tile per wavefront, the folded 32 x K weight tile built by the block
 // itself in LDS, same algebra as k_gemm's pair-bias tile); the blocks above them run prep_row.
-// Element (h, q, k) of the pair bias.  Plain: [H][Lq][Lp].  Tiled (for k_proj_attn and k_attn_rows): 32 x 32 tiles in
-// the register order of an S^T accumulator, [H][Lq/32][Lp/32][4][64 lanes][4]: lane = (q % 32) + 32 hf
+// Element (h, q, k) of the pair bias [H][Lq][Lp]: 32 x 32 tiles in the register order of an S^T accumulator,
+// [H][Lq/32][Lp/32][4][64 lanes][4]: lane = (q % 32) + 32 hf
 // holds the keys 16c + 8hf + 4i + e of the tile in element e of group 2c + i, so that a wavefront
 // fetches a tile with four loads of 1 KiB each.
-__device__ __forceinline__ size_t bias_index(bool tiled, int h, int q, int k, int Lq, int Lp) {
-    if (!tiled) return ((size_t)h * Lq + q) * Lp + k;
+__device__ __forceinline__ size_t bias_index(int h, int q, int k, int Lq, int Lp) {
     const int kk = k & 31;
     const int grp = 2 * (kk >> 4) + ((kk >> 2) & 1), hf = (kk >> 3) & 1;
     const size_t tile = ((size_t)h * (Lq >> 5) + (q >> 5)) * (Lp >> 5) + (k >> 5);
@@ -313,7 +310,6 @@ __device__ __forceinline__ size_t bias_index(bool tiled, int h, int q, int k, in
 
 struct PrepBiasArgs {
     PrepArgs prep;
-    int tiled;                   // layout of the output (bias_index)
     int bias_blocks;
     const bf16_t* z;             // pair (i, j) at z + (i*sr + j*sl)*K
     int64_t sr, sl;
@@ -421,7 +417,7 @@ __global__ __launch_bounds__(512) void k_prep_bias(PrepBiasArgs a) {
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa.v, xaug.v, acc, 0, 0, 0);
     }
     // lane = pair (qi, kj), register v = head 8*(v/4) + 4*hf + v%4
-    float* bp = a.bias + bias_index(a.tiled != 0, 0, qi, kj, a.Lq, a.Lp);
+    float* bp = a.bias + bias_index(0, qi, kj, a.Lq, a.Lp);
     const size_t plane = (size_t)a.Lq * a.Lp;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
@@ -430,16 +426,16 @@ __global__ __launch_bounds__(512) void k_prep_bias(PrepBiasArgs a) {
     }
 }
 
-// Rows q in [L, Lq) of the bias tensor [H][Lq][Lp] belong to pad queries: no kernel computes them, but
-// the attention kernel stages whole 64-query tiles.  Zeros there keep its lanes for pad queries (never
-// stored) on the common path whatever the caller's workspace held before.
-__global__ __launch_bounds__(256) void k_zero_bias_pad(float* bias, int L, int Lq, int Lp, int H, int tiled) {
+// Rows q in [L, Lq) of the bias tensor belong to pad queries: no kernel computes them, but k_proj_attn loads whole
+// tiles of 32 queries.  Zeros there keep its lanes for pad queries (never stored) on the common path whatever the
+// caller's workspace held before.  (k_attn_rows does not look at them.)
+__global__ __launch_bounds__(256) void k_zero_bias_pad(float* bias, int L, int Lq, int Lp, int H) {
     const int per_head = (Lq - L) * Lp;
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= per_head * H) return;
     const int h = i / per_head, r = i - h * per_head;
     const int q = L + r / Lp, k = r - (q - L) * Lp;
-    bias[bias_index(tiled != 0, h, q, k, Lq, Lp)] = 0.f;
+    bias[bias_index(h, q, k, Lq, Lp)] = 0.f;
 }
 
 // ====================================================================================
@@ -467,8 +463,7 @@ struct GemmArgs {
     float invD;            // 1 / D
     int nt_main;           // PROJ: 32-feature tiles of q|k|v|gate; tile nt_main is the pair-bias tile
     bf16_t *q, *k, *g, *vt;  // PROJ outputs
-    float* bias;             // PROJ pair-bias output [H][Lq][Lp], in the layout that tiled says (bias_index)
-    int tiled;
+    float* bias;             // PROJ pair-bias output, [H][Lq][Lp] elements in the tiles of bias_index
     bf16_t* out;             // OUT output, token (r,l) at (r*sr + l*sl)*N
     const bf16_t* res;       // OUT with RES: added to the output, laid out like out (may be out itself)
     int N;                   // OUT: features
@@ -706,7 +701,7 @@ __global__ __launch_bounds__(kGemmWaves * 64, 2) void k_gemm(GemmArgs a) {
             hlim = a.H - 4 * hf;
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt)
-                qk_off[tt] = bias_index(a.tiled != 0, 4 * hf, a.r0 + tok_rl[tt], tok_l[tt], a.Lq, a.Lp);
+                qk_off[tt] = bias_index(4 * hf, a.r0 + tok_rl[tt], tok_l[tt], a.Lq, a.Lp);
         }
         // value v of the lane: one multiplication by 1/std (the matrix core has already added the
         // LayerNorm mean and offset terms), the sigmoid for the gate, bf16
@@ -929,511 +924,8 @@ __global__ __launch_bounds__(kGemmWaves * 64, 2) void k_gemm(GemmArgs a) {
     else run_step(-1, kp, acc[1], acc[0], ra, s_w, ftp, ftp);
 }
 
-// ====================================================================================
-// Attention.  Block = RB wavefronts = RB batch rows, same head, same 64 queries: the bias
-// tile [64 queries x 64 keys] is staged once per block in LDS and used by all its rows;
-// K rows and V^T columns go straight from global memory into operand registers, one tile
-// ahead of their use.
-//
-// The q.k contraction has two extra slots.  Slot A multiplies 1 (key side) with -m_ref
-// (query side): the matrix core returns s - m_ref, m_ref being a per-query reference close
-// to the running maximum that is raised only when a tile exceeds it by more than kRaise
-// (then the accumulators are rescaled).  Slot B multiplies the mask term of the key (0 or
-// -inf) with 1.  The softmax denominator is summed by the vector unit from the rounded weights,
-// two at a time.
-struct AttnArgs {
-    const bf16_t *q, *k, *g, *vt;
-    bf16_t* o;
-    const float* bias;     // [H][Lq][Lp] or NULL
-    const float* mask;     // caller's mask or NULL
-    int64_t sr, sl;
-    int r0, rows, L, Lp, Lq, H, Hd;
-    float inv_nq, inv_nqh;   // 1 / (Lp / 64), 1 / (Lp / 64 * H): quotients of item indices below 2^22 without an integer division
-};
-
-// keys per bias tile in LDS (one barrier per tile): 64, or 128 for long sequences (GK template parameter)
-constexpr int kBiasPad = 4;      // floats added to an LDS bias row: conflict-free 16-byte reads
 constexpr float kRaise = 10.f;   // log2 units
 constexpr float kOver = 1048576.f;   // 2^20: partial denominator (16 keys) that triggers a raise of the reference
-
-// (bias-free 4-row blocks are held to 168 registers, three wavefronts per SIMD: d = 8 fits as it is, d = 16 spills
-// fifteen registers and is still 9 % faster; head dim 32 has k_attn_rows)
-template <int D, bool HAS_BIAS, int RB, int GK, bool PERSIST>
-__global__ __launch_bounds__(RB * 64, (RB == 4 && !HAS_BIAS) ? 3 : 2) void k_attn(AttnArgs a) {
-    static_assert(D == 8 || D == 16, "head dim 32 has a kernel of its own");
-    constexpr int PCX = D / 8;              // index of the 8-slot piece holding the two extra slots
-    constexpr int KS = PCX / 2 + 1;         // 16-wide contraction steps
-    constexpr int SX = PCX / 2, HX = PCX % 2;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr int TPG = GK / 32, kBiasPitch = GK + kBiasPad;
-    float* s_bias = reinterpret_cast<float*>(smem);                                  // [2][64][kBiasPitch]
-
-    const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, hf = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // (scalar: so is everything that places the wavefront's item)
-    // Work-groups are handed to the 8 XCDs round-robin and each XCD has its own L2.  The blocks
-    // that share K and V (same rows and head, different queries) get consecutive slots of ONE
-    // XCD, so K and V are fetched into one L2 once instead of once per query block.
-    // The grid is persistent: at most one block per set of RB wave slots of a compute unit, each
-    // taking the items (RB batch rows x one head x 64 queries) slot, slot + stride, ... of its XCD.
-    // The operands of an item's first tiles are fetched while the block still works on the last
-    // tile and the epilogue of the item before, so that only the first item of a block waits for
-    // memory before its first matrix instruction.
-    const int nq = a.Lp >> 6;
-    const int n_items = nq * a.H * ((a.rows + RB - 1) / RB);
-    const int per_xcd = (n_items + 7) >> 3;
-    const int slot_stride = gridDim.x >> 3;
-    int slot = blockIdx.x >> 3;
-    auto item_at = [&](int sl) __attribute__((always_inline)) -> int {                  // item of slot sl of this XCD, -1 if there is none
-        const int lg = (blockIdx.x & 7) * per_xcd + sl;
-        return (sl < per_xcd && lg < n_items) ? lg : -1;
-    };
-    int logical = item_at(slot);
-    if (logical < 0) return;                              // (whole block)
-    int rl, h, q0;                                        // of the item whose operands are fetched next
-    bool row_ok;
-    auto place = [&](int lg) __attribute__((always_inline)) {
-        // lg = (block of RB rows * H + head) * nq + query tile; float quotients, corrected by one
-        // where the rounding went the wrong way (exact for lg < 2^22, which the host checks)
-        const int nqh = nq * a.H;
-        int rb = (int)(((float)lg + 0.5f) * a.inv_nqh);
-        rb -= rb * nqh > lg;
-        rb += (rb + 1) * nqh <= lg;
-        const int rem = lg - rb * nqh;
-        int hh = (int)(((float)rem + 0.5f) * a.inv_nq);
-        hh -= hh * nq > rem;
-        hh += (hh + 1) * nq <= rem;
-        // (the float quotients pass through vector registers: back to scalar ones, so that every
-        // address built from them has a scalar base)
-        const int rl_raw = __builtin_amdgcn_readfirstlane(rb) * RB + wave;
-        row_ok = rl_raw < a.rows;
-        rl = row_ok ? rl_raw : a.rows - 1;
-        h = __builtin_amdgcn_readfirstlane(hh);
-        q0 = (rem - h * nq) * 64;
-    };
-    place(logical);
-    const bool xlane = hf == HX;            // this lane carries the extra slots in step SX
-    // Addresses: every tensor of this kernel has Lp*D elements per (batch row, head); item_off is
-    // that block's element offset (scalar), the per-lane parts are 32-bit byte offsets that never change.
-    size_t item_off = 0;
-    // permuted key of S^T row m = col: rows 8g + 4b + e hold key 16*(g/2) + 8b + 4*(g%2) + e
-    const int kperm = 16 * (col >> 4) + 8 * ((col >> 2) & 1) + 4 * ((col >> 3) & 1) + (col & 3);
-    const uint32_t qg_lane = (uint32_t)(col * D + 8 * hf) * 2;                       // q, o: query col, elements 8hf..
-    const uint32_t k_lane = (uint32_t)(kperm * D + 8 * hf) * 2;                      // k: key kperm of a tile
-    const uint32_t v_lane = (uint32_t)((col < D ? col : 0) * 32 + 8 * hf) * 2;       // v^T: element col, keys 8hf..
-    const uint32_t gate_lane = (uint32_t)(col * D + 4 * hf) * 2;                     // gate: query col, elements 4hf..
-
-    // ---- Q operand fragments: B operand, lane = query, 8 consecutive e
-    Frag qf[2][KS];
-    auto fetch_q = [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const bf16_t* qp = a.q + item_off + (size_t)(q0 + 32 * j) * D;      // (uniform; query q0 + 32j + col < Lp)
-#pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                qf[j][s].u = make_uint4(0, 0, 0, 0);
-                if (2 * s + hf < PCX) qf[j][s].u = ldg16(qp + 16 * s, qg_lane);
-            }
-        }
-    };
-
-    // ---- bias tile pipeline: [64 queries][GK keys]; GK/4 threads per row, RPP rows per pass
-    constexpr int TPR = GK / 4, RPP = RB * 64 / TPR, BP = 64 / RPP;
-    static_assert(BP == 2 || BP == 4, "bias tile passes");
-    const int b_row = tid / TPR, b_c4 = tid % TPR;
-    const float* bias_t = nullptr;            // (scalar) row q0 of the item's head
-    const uint32_t b_lane = (uint32_t)(b_row * a.Lp) * 4;
-    float* s_bias_t = s_bias + (size_t)b_row * kBiasPitch + 4 * b_c4;
-    // (named registers: an array captured by a lambda would be spilled to scratch)
-    float4 bq0, bq1, bq2, bq3;
-    auto load_bias = [&](int g) __attribute__((always_inline)) {
-        int colk = GK * g + 4 * b_c4;              // (a last group that is only half there repeats valid keys)
-        if (colk > a.Lp - 4) colk = a.Lp - 4;
-        const uint32_t off = b_lane + (uint32_t)colk * 4;
-        auto ld = [&](const float* base) __attribute__((always_inline)) {
-            return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(base) + off);
-        };
-        bq0 = ld(bias_t);
-        bq1 = ld(bias_t + (size_t)RPP * a.Lp);
-        if constexpr (BP > 2) {
-            bq2 = ld(bias_t + (size_t)(2 * RPP) * a.Lp);
-            bq3 = ld(bias_t + (size_t)(3 * RPP) * a.Lp);
-        }
-    };
-    auto store_bias = [&](int buf) __attribute__((always_inline)) {
-        float* sp = s_bias_t + (size_t)buf * 64 * kBiasPitch;
-        *reinterpret_cast<float4*>(sp) = bq0;
-        *reinterpret_cast<float4*>(sp + RPP * kBiasPitch) = bq1;
-        if constexpr (BP > 2) {
-            *reinterpret_cast<float4*>(sp + 2 * RPP * kBiasPitch) = bq2;
-            *reinterpret_cast<float4*>(sp + 3 * RPP * kBiasPitch) = bq3;
-        }
-    };
-
-    // k is [row][head][l][d], v^T is [row][head][l / 32][e][l % 32]: a 32-key tile of either is one
-    // contiguous block of 64*D bytes
-    const float* mp;
-    const bool has_mask = a.mask != nullptr;
-    const int msl = (int)a.sl;                     // (1 or n_b)
-    constexpr int kstep = 32 * D;
-    auto set_pointers = [&]() __attribute__((always_inline)) {             // operands of the item (rl, h, q0)
-        item_off = (size_t)(rl * a.H + h) * a.Lp * D;
-        mp = has_mask ? a.mask + (int64_t)(a.r0 + rl) * a.sr : nullptr;
-        if constexpr (HAS_BIAS) bias_t = a.bias + ((size_t)h * a.Lq + q0) * a.Lp;
-    };
-    set_pointers();
-    fetch_q();
-    if constexpr (HAS_BIAS) load_bias(0);      // (stored to LDS after the first K and V loads have been issued)
-
-    // Software pipeline over 32-key tiles i:
-    //   K(i+2), mask(i+2), V(i+1) are in flight (global -> registers) while
-    //   S^T(i+1) = K(i+1) Q^T runs on the matrix cores while
-    //   the vector unit takes the exponentials of tile i, followed by O^T += V^T(i) P^T(i).
-    // K and V use two register sets each (even / odd tiles); nothing looks at a loaded value
-    // before its use.  The bias tile in LDS covers 64 keys (an even and an odd tile).
-    Frag kb0[KS], kb1[KS], vb0[2], vb1[2];
-    float mv0 = 1.f, mv1 = 1.f;
-    auto fetch_k = [&](Frag (&kb)[KS], float& mv, int kt) __attribute__((always_inline)) {
-        // (the empty statement hides the lane offset from the loop optimiser, which would otherwise
-        // add it to the tile's base once and carry a 64-bit pointer per lane through the loop)
-        // and the tile index from being folded into an immediate offset that does not fit the instruction)
-        uint32_t lane_off = k_lane;
-        asm volatile("" : "+v"(lane_off));
-        int kts = kt;
-        asm volatile("" : "+s"(kts));
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            kb[s].u = make_uint4(0, 0, 0, 0);
-            if (2 * s + hf < PCX) kb[s].u = ldg16(a.k + item_off + (size_t)kts * kstep + 16 * s, lane_off);
-        }
-        // mask value of the lane's key (whoever uses mv pins it first, or the compiler compares it
-        // with zero right here and waits for every load just issued).  Keys beyond L - 1 read the
-        // entry of key L - 1; scalar base of the tile + 32-bit lane offset.
-        mv = 1.f;
-        if (has_mask) {
-            int k0 = 32 * kts;
-            if (k0 > ((a.L - 1) & ~31)) k0 = (a.L - 1) & ~31;
-            const int lk = kperm < a.L - 1 - k0 ? kperm : a.L - 1 - k0;          // >= 0
-            mv = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(mp + (int64_t)k0 * msl) +
-                                                 (uint32_t)(lk * msl) * 4u);
-        }
-    };
-    auto fetch_v = [&](Frag (&vb)[2], int kt) __attribute__((always_inline)) {
-        uint32_t lane_off = v_lane;
-        asm volatile("" : "+v"(lane_off));
-        int kts = kt;
-        asm volatile("" : "+s"(kts));
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            vb[c].u = make_uint4(0, 0, 0, 0);
-            if (col < D) vb[c].u = ldg16(a.vt + item_off + (size_t)kts * kstep + 16 * c, lane_off);
-        }
-    };
-
-    f32x16 o_acc[2];
-    float m_ref[2], l_run[2];
-    bool first = true;
-    int gbase = 0;          // bias groups staged so far (all items): group g of the item uses LDS buffer (gbase + g) & 1
-
-    // S^T of tile kt into sa in two parts: the bias tile as accumulator input (LDS reads, issued
-    // early: the loads of the next K and V tiles hide their latency), then the contraction, which
-    // returns whether any key of the tile is valid
-    auto qk_bias = [&](int kt, f32x16 (&sa)[2]) __attribute__((always_inline)) {
-        const float* sb = s_bias + (size_t)((kt / TPG + gbase) & 1) * 64 * kBiasPitch;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            if constexpr (HAS_BIAS) {
-                const float* br = sb + (size_t)(32 * j + col) * kBiasPitch + 32 * (kt % TPG) + 8 * hf;
-#pragma unroll
-                for (int c = 0; c < 2; ++c)
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        const float4 x4 = *reinterpret_cast<const float4*>(br + 16 * c + 4 * i);
-                        sa[j][8 * c + 4 * i] = x4.x; sa[j][8 * c + 4 * i + 1] = x4.y;
-                        sa[j][8 * c + 4 * i + 2] = x4.z; sa[j][8 * c + 4 * i + 3] = x4.w;
-                    }
-            }
-        }
-    };
-    auto qk_mma = [&](Frag (&kb)[KS], float mv, int kt, f32x16 (&sa)[2]) __attribute__((always_inline)) -> bool {
-        asm volatile("" : "+v"(mv));
-        const bool key_valid = (!has_mask || mv != 0.f) && 32 * kt + kperm < a.L;
-        if (!__any(key_valid)) return false;
-        if (xlane) kb[SX].w[0] = key_valid ? 0x00003f80u : 0xff803f80u;   // (1.0, mask term)
-        if constexpr (!HAS_BIAS) {          // (zero accumulator input: a constant operand of the first step)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) sa[j][v] = 0.f;
-        }
-        // the two query tiles alternate, so that no matrix-core instruction waits for the one before it
-#pragma unroll
-        for (int s = 0; s < KS; ++s)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                sa[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb[s].v, qf[j][s].v, sa[j], 0, 0, 0);
-        return true;
-    };
-    // Exponentials of tile sa and O^T update.
-    // FUSE = false: sn is the next tile, already issued with the old reference if sn_live.
-    // FUSE = true: the next tile's contraction S^T(ktn) = K Q^T (operands kbn, mask value mvn) is
-    // issued from in here, one matrix instruction after every other group of exponentials, so that
-    // the wavefront never queues behind its own matrix instructions (issued back to back, each waits
-    // for the matrix core to finish the one before, and the vector instructions behind them wait
-    // too).  Query tile 1 of the next tile is contracted while query tile 0 of this one is
-    // exponentiated and vice versa: when the reference of a query tile has to be raised, the next
-    // tile of that query tile is either complete (then it is corrected, as before) or not begun
-    // (then it sees the new reference in the Q operand).  Returns whether the next tile holds a
-    // valid key (FUSE) or sn_live.
-    auto soft_pv = [&](f32x16 (&sa)[2], Frag (&vb)[2], f32x16 (&sn)[2], bool sn_live, auto fuse_c, Frag (&kbn)[KS],
-                       float mvn, int ktn) __attribute__((always_inline)) -> bool {
-        constexpr bool FUSE = decltype(fuse_c)::value;
-        bool next_live = sn_live;
-        if constexpr (FUSE) {
-            asm volatile("" : "+v"(mvn));
-            const bool key_valid = (!has_mask || mvn != 0.f) && 32 * ktn + kperm < a.L;
-            next_live = __any(key_valid);           // (a tile without valid keys is still contracted: all -inf, never used)
-            if (xlane) kbn[SX].w[0] = key_valid ? 0x00003f80u : 0xff803f80u;   // (1.0, mask term)
-            if constexpr (!HAS_BIAS) {
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) sn[j][v] = 0.f;
-            }
-        }
-        // sa holds s - m_ref (masked keys: -inf).  Only the first tile takes the maximum; later tiles
-        // are exponentiated as they are and a partial denominator beyond kOver (some s - m_ref above
-        // about 16) sends the query tile through raise_ref afterwards: rare, and the common tile
-        // saves the sixteen max operations per query.  (For head dims below 32 a row of ones in V^T
-        // could let the matrix core sum the denominator, but an overflow would then already be
-        // accumulated, so every tile would need its maximum: 3 % slower at d = 8 in a same-box comparison.)
-        auto tile_max = [&](int j) __attribute__((always_inline)) -> float {
-            float mx = sa[j][0];
-#pragma unroll
-            for (int v = 1; v < 16; ++v) mx = fmaxf(mx, sa[j][v]);
-            return fmaxf(mx, other_half(mx));
-        };
-        auto raise_ref = [&](int j, float tmax, bool always, bool correct_next) __attribute__((always_inline)) {
-            const bool raise = always || tmax > kRaise;
-            const float new_ref = raise ? bf16_round(m_ref[j] + tmax) : m_ref[j];
-            const float delta = new_ref - m_ref[j];
-            m_ref[j] = new_ref;
-            const float sc = first ? 1.f : __builtin_amdgcn_exp2f(-delta);   // first: nothing accumulated yet
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                o_acc[j][v] *= sc;
-                sa[j][v] -= delta;
-            }
-            if (correct_next) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) sn[j][v] -= delta;
-            }
-            l_run[j] *= sc;
-            if (xlane) qf[j][SX].w[0] = pack2(-new_ref, 1.f);
-        };
-        if (first) {
-            const float t0 = tile_max(0), t1 = tile_max(1);
-            if (first || __any(t0 > kRaise || t1 > kRaise)) {
-                raise_ref(0, t0, first, !FUSE && sn_live);      // (FUSE: the next tile has not begun)
-                raise_ref(1, t1, first, !FUSE && sn_live);
-                first = false;
-            }
-        }
-        // matrix instruction m of the next tile's query tile jn (FUSE)
-        auto next_mma = [&](int jn, int m) __attribute__((always_inline)) {
-            sn[jn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kbn[m].v, qf[jn][m].v, sn[jn], 0, 0, 0);
-        };
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            Frag pf[2];
-            float lt = 0.f;
-            // eight groups of two exponentials, a pack and a partial denominator; with `weave` a
-            // matrix instruction of the other query tile follows every other group, and the fences
-            // keep the compiler from gathering them again
-            auto exponentiate = [&](auto weave_c) __attribute__((always_inline)) {
-                constexpr bool WEAVE = decltype(weave_c)::value;
-                lt = 0.f;
-                if constexpr (!WEAVE) {
-#pragma unroll
-                    for (int c = 0; c < 2; ++c)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const float p0 = __builtin_amdgcn_exp2f(sa[j][8 * c + 2 * i]);
-                            const float p1 = __builtin_amdgcn_exp2f(sa[j][8 * c + 2 * i + 1]);
-                            pf[c].w[i] = pack2(p0, p1);
-                            // denominator from the rounded weights, two per instruction
-                            lt = add_pair(pf[c].w[i], lt);
-                        }
-                } else {
-                    // (between two fences: the exponentials of group g + 1, then pack and partial
-                    // denominator of group g, whose exponentials have had a group's time to finish)
-                    float e0 = __builtin_amdgcn_exp2f(sa[j][0]), e1 = __builtin_amdgcn_exp2f(sa[j][1]);
-#pragma unroll
-                    for (int g = 0; g < 8; ++g) {
-                        float n0 = 0.f, n1 = 0.f;
-                        if (g < 7) {
-                            n0 = __builtin_amdgcn_exp2f(sa[j][2 * g + 2]);
-                            n1 = __builtin_amdgcn_exp2f(sa[j][2 * g + 3]);
-                            asm volatile("" : "+v"(n0), "+v"(n1));
-                        }
-                        uint32_t& w = pf[g >> 2].w[g & 3];
-                        w = pack2(e0, e1);
-                        lt = add_pair(w, lt);
-                        asm volatile("" : "+v"(w));
-                        if ((g & 1) && (g >> 1) < KS) next_mma(1 - j, g >> 1);
-                        __builtin_amdgcn_sched_barrier(0);
-                        e0 = n0;
-                        e1 = n1;
-                    }
-                }
-            };
-            exponentiate(std::integral_constant<bool, FUSE>{});
-            if (__any(!(lt <= kOver))) {
-                // (FUSE: the next tile of query tile 1 was issued during query tile 0, that of
-                // query tile 0 is issued during query tile 1)
-                raise_ref(j, tile_max(j), false, FUSE ? j == 1 : sn_live);
-                exponentiate(std::integral_constant<bool, false>{});
-            }
-            l_run[j] += lt;
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-                o_acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vb[c].v, pf[c].v, o_acc[j], 0, 0, 0);
-        }
-        return next_live;
-    };
-
-    const int nt = a.Lp >> 5;               // even
-    fetch_k(kb0, mv0, 0);
-    fetch_k(kb1, mv1, 1);
-    fetch_v(vb0, 0);
-    f32x16 s0[2], s1[2];
-    uint2 gate[2][4];       // gate values of the item's queries, fetched during its last tile
-  for (;;) {
-    // ---- an item begins: its Q, K(0), K(1), V(0) and first bias group are on their way or here
-    const int e_rl = rl, e_h = h, e_q0 = q0;        // the epilogue's copy: (rl, h, q0) move on to the next item before it
-    const bool e_row_ok = row_ok;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        m_ref[j] = 0.f;
-        l_run[j] = 0.f;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) o_acc[j][v] = 0.f;
-        if (xlane) qf[j][SX].w[0] = 0x3f800000u;        // (-m_ref = 0, 1.0)
-    }
-    first = true;
-    if constexpr (HAS_BIAS) {
-        // (group 0 goes to the buffer that the last group of the item before does not use; every
-        // wavefront finished with the group before that one when it passed the last barrier)
-        store_bias(gbase & 1);
-        if (TPG == 2 && nt > 2) load_bias(1);
-    }
-    __syncthreads();                        // bias group 0 is in LDS
-    qk_bias(0, s0);
-    bool live0 = qk_mma(kb0, mv0, 0, s0), live1 = false;
-    // (long sequences, PERSIST = false: one item per block.  There the start of an item is a few per
-    // cent of its time, and blocks handed out as compute units fall free even out the differences
-    // between compute units that a fixed share of 24 long items per block adds up: 3 % at 1024 keys)
-    const int next = PERSIST ? item_at(slot + slot_stride) : -1;
-    // The bias of key group g (TPG tiles) sits in LDS buffer (gbase + g) & 1.  It is loaded to registers one
-    // and a half iterations before tile g*TPG is first touched, stored and published (the only
-    // barrier of the group) at the end of the even half of the iteration before.
-    // (the last pair of tiles has a body of its own: the loop proper then holds no load that
-    // depends on a condition, which keeps the compiler's wait counts exact)
-    // The next tile's contraction is issued from inside the exponentials (soft_pv,
-    // FUSE).  Measured at 1024 keys, d = 8: 702 -> 671 us.
-    auto tile_pair = [&](int i, auto last_c) __attribute__((always_inline)) {
-        constexpr bool LAST = decltype(last_c)::value;
-        // ---- even tile i: K(i+2) -> set 0, V(i+1) -> set 1, S^T(i+1) -> s1, exponentials of s0
-        qk_bias(i + 1, s1);
-        if constexpr (!LAST) fetch_k(kb0, mv0, i + 2);
-        fetch_v(vb1, i + 1);
-        using std::integral_constant;
-        if constexpr (LAST) {
-            // no tile i+2.  The gate values of the epilogue set out, then the operands of the next
-            // item's first tiles as their registers fall free: K set 0 here, K set 1, V set 0, the
-            // bias registers and Q (its last matrix instruction has been issued; if the last
-            // exponentials still raise the reference, what they write into the Q operand is
-            // overwritten when the next item begins) half a pair later.  A block's last item
-            // fetches its own first tiles again instead: loads that do not depend on a condition
-            // keep the compiler's wait counts exact, so that the epilogue waits for the gate
-            // values only.
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const bf16_t* gp = a.g + item_off + (size_t)(q0 + 32 * j) * D;
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    gate[j][g] = make_uint2(0, 0);
-                    if (8 * g + 4 * hf < D) gate[j][g] = ldg8(gp + 8 * g, gate_lane);
-                }
-            }
-            if constexpr (PERSIST) {
-                place(next >= 0 ? next : logical);
-                set_pointers();
-                fetch_k(kb0, mv0, 0);
-            }
-        }
-        if (live0) live1 = soft_pv(s0, vb0, s1, false, integral_constant<bool, true>{}, kb1, mv1, i + 1);
-        else live1 = qk_mma(kb1, mv1, i + 1, s1);
-        if constexpr (HAS_BIAS && !LAST) {
-            if ((i + 2) % TPG == 0) {
-                store_bias(((i + 2) / TPG + gbase) & 1);
-                __syncthreads();
-            }
-        }
-        // ---- odd tile i+1: K(i+3) -> set 1, V(i+2) -> set 0, S^T(i+2) -> s0, exponentials of s1
-        live0 = false;
-        if constexpr (!LAST) {
-            qk_bias(i + 2, s0);
-            fetch_k(kb1, mv1, i + 3);
-            fetch_v(vb0, i + 2);
-            if constexpr (HAS_BIAS) {
-                if ((i + 4) % TPG == 0 && i + 4 < nt) load_bias((i + 4) / TPG);
-            }
-            if (live1) live0 = soft_pv(s1, vb1, s0, false, integral_constant<bool, true>{}, kb0, mv0, i + 2);
-            else live0 = qk_mma(kb0, mv0, i + 2, s0);
-        } else {
-            if constexpr (PERSIST) {
-                fetch_k(kb1, mv1, 1);
-                fetch_v(vb0, 0);
-                if constexpr (HAS_BIAS) load_bias(0);
-                fetch_q();
-            }
-            if (live1) soft_pv(s1, vb1, s0, false, integral_constant<bool, false>{}, kb0, mv0, 0);
-        }
-    };
-    for (int i = 0; i + 2 < nt; i += 2) tile_pair(i, std::integral_constant<bool, false>{});
-    tile_pair(nt - 2, std::integral_constant<bool, true>{});
-
-    // ---- epilogue: normalise, gate, store.  o_acc[j]: lane = query, register v = e = 8*(v/4) + 4*hf + v%4
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const float l_tot = l_run[j] + other_half(l_run[j]);
-        const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-        const int qi = e_q0 + 32 * j + col;                       // < Lp
-        // gate and context are head-major [row][head][l][d]: the wave's 32 queries are one
-        // contiguous block of 64*D bytes
-        bf16_t* op = a.o + (size_t)(e_rl * a.H + e_h) * a.Lp * D + (size_t)(e_q0 + 32 * j) * D;   // (uniform)
-        uint32_t pk[8];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const uint2 gr = gate[j][g];              // elements 8g + 4hf .. + 3 (zero beyond D)
-            pk[2 * g] = pack2(o_acc[j][4 * g] * inv * lo_f32(gr.x), o_acc[j][4 * g + 1] * inv * hi_f32(gr.x));
-            pk[2 * g + 1] = pack2(o_acc[j][4 * g + 2] * inv * lo_f32(gr.y), o_acc[j][4 * g + 3] * inv * hi_f32(gr.y));
-        }
-        merge_halves(pk[0], pk[2]);      // lower half-wave: e 0..7, upper: e 8..15
-        merge_halves(pk[1], pk[3]);
-        merge_halves(pk[4], pk[6]);      // lower: e 16..23, upper: e 24..31
-        merge_halves(pk[5], pk[7]);
-        if (e_row_ok && qi < a.L) {
-            if (8 * hf < D) stg16(op, qg_lane, make_uint4(pk[0], pk[1], pk[2], pk[3]));
-            if (16 + 8 * hf < D) stg16(op + 16, qg_lane, make_uint4(pk[4], pk[5], pk[6], pk[7]));
-        }
-    }
-    if (next < 0) break;
-    logical = next;
-    slot += slot_stride;
-    gbase += (nt + TPG - 1) / TPG;
-  }
-}
 
 // ====================================================================================
 // Projection and attention in one kernel, for sequences of at most 256 positions with head
@@ -1442,7 +934,7 @@ __global__ __launch_bounds__(RB * 64, (RB == 4 && !HAS_BIAS) ? 3 : 2) void k_att
 // that head's q, k, v and gate for all tokens of the two rows straight from the raw input (the
 // LayerNorm folded into the weights as in k_gemm) and attends at once.  q and the gate never
 // leave the registers, k and v^T live in LDS, so that of the five tensors k_gemm<PROJ> hands to
-// k_attn through HBM only the gated context is ever written.
+// the attention kernel through HBM only the gated context is ever written.
 //
 // Wavefront w owns tokens 32w .. 32w+31 of both rows: as projection tokens first, as queries
 // afterwards.  A projection tile leaves the matrix core with the lane = token, register =
@@ -1461,7 +953,7 @@ __global__ __launch_bounds__(RB * 64, (RB == 4 && !HAS_BIAS) ? 3 : 2) void k_att
 // of the compute unit's 160: one block of eight wavefronts per compute unit.
 //
 // Measured on the training crop of the row-wise attention (128 x 256 tokens, 8 heads): 50 us
-// against 34 + 31 us for k_gemm<PROJ> and k_attn.  No unit is saturated (LDS busy 22 %, matrix
+// against 34 + 31 us for k_gemm<PROJ> and an attention kernel.  No unit is saturated (LDS busy 22 %, matrix
 // pipe 25 %, vector unit 39 % of the kernel): in the projections every matrix instruction waits
 // for a fresh weight operand from LDS, the attention is paced by the exponentials, and two
 // wavefronts per SIMD with one dependent chain each leave a third of the issue slots empty.  Of
@@ -1713,7 +1205,7 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
             int lane_a = lane;
             asm volatile("" : "+v"(lane_a));
             const int col_a = lane_a & 31, hf_a = lane_a >> 5;
-            // permuted key of S^T row m = col (see k_attn): the lane's registers 8c .. 8c+7 then hold
+            // permuted key of S^T row m = col: rows 8g + 4b + e hold key 16*(g/2) + 8b + 4*(g%2) + e, so that the lane's registers 8c .. 8c+7 hold
             // the keys 16c + 8hf .. + 7 of the tile
             const int kperm_a = 16 * (col_a >> 4) + 8 * ((col_a >> 2) & 1) + 4 * ((col_a >> 3) & 1) + (col_a & 3);
             int lv[2];
@@ -1780,7 +1272,7 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
                     if (!live[j]) continue;
                     // sa holds s - m_ref (masked keys: -inf).  The first live tile sets the reference to
                     // its maximum; later tiles are exponentiated as they are, and a partial denominator
-                    // beyond kOver sends the tile through raise_ref (see k_attn)
+                    // beyond kOver sends the tile through raise_ref
                     auto tile_max = [&]() __attribute__((always_inline)) -> float {
                         float mx = sa[j][0];
 #pragma unroll
@@ -1919,24 +1411,11 @@ static int pick_split(int blocks_m, int tiles_n) {
     return split;
 }
 
-// Batch rows per block of k_attn (one wavefront each).  With a bias, 8 rows halve the bias traffic
-// of 4.  Without one nothing is shared inside a block, and for head dims below 32 the kernel needs
-// at most 168 registers: blocks of 4 wavefronts then fit three to a compute unit (three
-// wavefronts per SIMD) where a block of 8 leaves a third of the register file empty.
-static int attn_rows_per_block(const Problem& p, int rows) {
-    if (rows < 8) return 4;
-    return (!p.has_bias && p.d < 32) ? 4 : 8;
-}
-
-// work items of one attention launch over `rows` batch rows
-static int64_t attn_items(const Problem& p, int rows) {
-    const int rb = attn_rows_per_block(p, rows);
-    return (int64_t)(round_up(p.L, 64) / 64) * p.H * ((rows + rb - 1) / rb);
-}
-
 bool mfma_chunk_ok(const Problem& p, int chunk) {
-    // the attention kernel splits item indices with float reciprocals, exact below 2^22
-    return attn_items(p, chunk) < (1 << 22);
+    // work items of 64 queries of one head of eight batch rows (four without a bias below head dim 32): item indices
+    // and their products stay inside an int
+    const int rb = chunk < 8 || (!p.has_bias && p.d < 32) ? 4 : 8;
+    return (int64_t)(round_up(p.L, 64) / 64) * p.H * ((chunk + rb - 1) / rb) < (1 << 22);
 }
 
 static int query_compute_units() {
@@ -1952,37 +1431,7 @@ int compute_units() {
     return n;
 }
 
-// blocks of this attention instantiation that one compute unit holds at once
-template <int D, bool HAS_BIAS, int RB, int GK, bool PERSIST>
-static int attn_blocks_per_cu(size_t smem) {
-    int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(&k_attn<D, HAS_BIAS, RB, GK, PERSIST>),
-                                                     RB * 64, smem) != hipSuccess || nb < 1)
-        nb = 1;
-    return nb;
-}
-
-template <int D, bool HAS_BIAS, int RB, int GK, bool PERSIST>
-static ff_status launch_attn(int n_items, size_t smem, hipStream_t st, const AttnArgs& a) {
-    // (the LDS of an instantiation is fixed by its template parameters: at most 66 KiB, asked for once)
-    static const hipError_t attr =
-        GK > 64 ? allow_large_lds(&k_attn<D, HAS_BIAS, RB, GK, PERSIST>) : hipSuccess;
-    if (attr != hipSuccess) return fail(FF_EHIP, "k_attn: dynamic LDS limit: %s", hipGetErrorString(attr));
-    int n_blocks = n_items;
-    if constexpr (PERSIST) {
-        // persistent blocks: as many as the chip holds at once (registers and LDS of this
-        // instantiation decide how many fit a compute unit), each working through its share of the items
-        static const int per_cu = attn_blocks_per_cu<D, HAS_BIAS, RB, GK, PERSIST>(smem);
-        const int resident = compute_units() * per_cu;
-        if (n_blocks > resident) n_blocks = resident;
-    }
-    hipLaunchKernelGGL((k_attn<D, HAS_BIAS, RB, GK, PERSIST>), dim3(((n_blocks + 7) / 8) * 8), dim3(RB * 64), smem, st, a);
-    return FF_OK;
-}
-
 static bool fused_proj_attn(const Problem& p);
-// whether the pair bias is written in the tiles of bias_index: k_proj_attn and k_attn_rows read it so
-static bool tiled_bias(const Problem& p) { return fused_proj_attn(p) || attn_rows_ok(p.d, p.L); }
 
 static GemmArgs proj_args(const Problem& p, const MfmaWs& m, const Workspace& ws) {
     const int Lp = round_up(p.L, 64), Lq = round_up(p.L, 64);
@@ -1990,7 +1439,7 @@ static GemmArgs proj_args(const Problem& p, const MfmaWs& m, const Workspace& ws
     g.sr = p.sr; g.sl = p.sl; g.L = p.L; g.Lp = Lp; g.Lq = Lq; g.K = p.c; g.eps = p.eps;
     g.w = m.wp; g.aug = m.aug; g.Hd = p.Hd; g.H = p.H; g.D = p.d; g.invD = 1.f / (float)p.d; g.dsh = p.d == 8 ? 3 : (p.d == 16 ? 4 : 5);
     g.nt_main = 4 * p.Hd / 32;
-    g.q = m.q; g.k = m.k; g.g = m.g; g.vt = m.vt; g.bias = ws.bias; g.tiled = tiled_bias(p) ? 1 : 0;
+    g.q = m.q; g.k = m.k; g.g = m.g; g.vt = m.vt; g.bias = ws.bias;
     return g;
 }
 
@@ -2021,7 +1470,6 @@ ff_status mfma_prepare(const Problem& p, const ff_attn_weights& w, const void* x
             // triangle attention needs the bias of all rows before the first chunk
             PrepBiasArgs b{};
             b.prep = a;
-            b.tiled = tiled_bias(p) ? 1 : 0;
             b.bias_blocks = (p.L * (Lp / 32) + 7) / 8;
             b.w_b = (const bf16_t*)w.w_b;
             if (chunked_tri) {
@@ -2044,11 +1492,10 @@ ff_status mfma_prepare(const Problem& p, const ff_attn_weights& w, const void* x
             hipLaunchKernelGGL(k_prep, dim3((rows + 3) / 4), dim3(256), 0, st, a);
         }
     }
-    if (p.has_bias && Lq > p.L && (fused_proj_attn(p) || !attn_rows_ok(p.d, p.L))) {
+    if (p.has_bias && Lq > p.L && fused_proj_attn(p)) {
         const int n = (Lq - p.L) * Lp * p.H;
         Timed t(KK_PREP, st);
-        hipLaunchKernelGGL(k_zero_bias_pad, dim3((n + 255) / 256), dim3(256), 0, st, ws.bias, p.L, Lq, Lp, p.H,
-                           fused_proj_attn(p) ? 1 : 0);
+        hipLaunchKernelGGL(k_zero_bias_pad, dim3((n + 255) / 256), dim3(256), 0, st, ws.bias, p.L, Lq, Lp, p.H);
     }
     return check_launch("prepare (mfma)");
 }
@@ -2113,49 +1560,12 @@ ff_status mfma_chunk(const Problem& p, const ff_attn_weights& w, const void* x, 
         if (ls != FF_OK) return ls;
     }
 
-    AttnArgs a{};
-    a.q = m.q; a.k = m.k; a.g = m.g; a.vt = m.vt; a.o = m.o; a.bias = ws.bias; a.mask = mask;
-    a.sr = p.sr; a.sl = p.sl; a.r0 = r0; a.rows = rows; a.L = p.L; a.Lp = Lp; a.Lq = Lq; a.H = p.H; a.Hd = p.Hd;
-    a.inv_nq = 1.f / (float)(Lp / 64); a.inv_nqh = 1.f / (float)((Lp / 64) * p.H);
-    if (!fused && attn_rows_ok(p.d, p.L)) {
+    if (!fused) {
         AttnRowsArgs r{};
         r.q = m.q; r.k = m.k; r.g = m.g; r.vt = m.vt; r.o = m.o; r.bias = ws.bias; r.mask = mask;
         r.sr = p.sr; r.sl = p.sl; r.r0 = r0; r.rows = rows; r.L = p.L; r.Lp = Lp; r.Lq = Lq; r.H = p.H;
         Timed t(KK_ATTN, st);
-        const ff_status ls = attn_rows_launch(r, st);
-        if (ls != FF_OK) return ls;
-    } else if (!fused) {
-        Timed t(KK_ATTN, st);
-        ff_status ls = FF_OK;
-        const int rb = attn_rows_per_block(p, rows);
-        const int n_items = (int)attn_items(p, rows);          // < 2^22: mfma_chunk_ok
-        // keys per bias tile: 128 halve the barriers of long sequences, 64 keep the first tile of short ones small
-        const int gk = (p.has_bias && rb == 8 && Lp >= 512) ? 128 : 64;
-        // short sequences: persistent blocks, one per rb wave slots of a compute unit (the kernel
-        // keeps two wavefronts per SIMD), each working through its share of the items
-        const bool persist = Lp < 512;
-        const size_t bias_bytes = (size_t)2 * 64 * (gk + kBiasPad) * 4;   // two float tiles
-#define FF_ATTN3(DD, HB, RBV, GKV, SM)                                       \
-    do {                                                                     \
-        if (persist) ls = launch_attn<DD, HB, RBV, GKV, true>(n_items, SM, st, a);   \
-        else ls = launch_attn<DD, HB, RBV, GKV, false>(n_items, SM, st, a);          \
-    } while (0)
-#define FF_ATTN2(DD, RBV)                                                   \
-    do {                                                                    \
-        if (p.has_bias && gk == 128) ls = launch_attn<DD, true, 8, 128, false>(n_items, bias_bytes, st, a); \
-        else if (p.has_bias) FF_ATTN3(DD, true, RBV, 64, bias_bytes);                        \
-        else FF_ATTN3(DD, false, RBV, 64, 0);                                                \
-    } while (0)
-#define FF_ATTN(DD)                  \
-    do {                             \
-        if (rb == 8) FF_ATTN2(DD, 8); \
-        else FF_ATTN2(DD, 4);        \
-    } while (0)
-        if (p.d == 8) FF_ATTN(8);
-        else FF_ATTN(16);
-#undef FF_ATTN
-#undef FF_ATTN2
-#undef FF_ATTN3
+        const ff_status ls = attn_rows_launch(r, p.d, st);
         if (ls != FF_OK) return ls;
     }
 

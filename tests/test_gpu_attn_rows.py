@@ -1,4 +1,4 @@
-"""GPU parity of k_attn_rows (attention at head dimension 32 outside the sequences of k_proj_attn) against the float64 oracle.
+"""GPU parity of k_attn_rows (attention outside the sequences of k_proj_attn) against the float64 oracle.
 
 Sizes at its edges: one key, remainders of 32 keys, of four query tiles per block and of the two / four batch rows of a
 wavefront, more than eight row blocks, a last ring slot of every index; masks that empty whole key tiles or rows; logits
@@ -49,21 +49,23 @@ def check(case, got, what):
     (TE, 257, 257, 64, 2, 0, "none", 0),
     (TS, 275, 275, 128, 4, 0, "outer:0.95", 0),
 ])
-def test_shapes(mode, n_a, n_b, c, H, c_z, mask, chunk):
-    case = I.make_case(small_spec(mode, n_a, n_b, c, H, 32, c_z=c_z, dtype="bf16", mask=mask))
+@pytest.mark.parametrize("d", [8, 16, 32])
+def test_shapes(mode, n_a, n_b, c, H, c_z, mask, chunk, d):
+    H = H if H * d % 32 == 0 else 32 // d
+    case = I.make_case(small_spec(mode, n_a, n_b, c, H, d, c_z=c_z, dtype="bf16", mask=mask))
     check(case, run(case, chunk), case.spec.name)
 
 
-@pytest.mark.parametrize("n_a,n_b", [(3, 70), (300, 260)])
-def test_logits_far_from_zero(n_a, n_b):
+@pytest.mark.parametrize("n_a,n_b,d", [(3, 70, 32), (300, 260, 32), (5, 150, 8), (300, 100, 16)])
+def test_logits_far_from_zero(n_a, n_b, d):
     """The softmax runs without a reference while the denominator stays inside [2^-60, 2^96].  An offset of the pair bias moves all
     logits of a head by the same amount (which the softmax removes): heads at about -140, +140, -50 and +50 log2 units, the
     first two outside that range; one batch row is fully masked."""
-    case = I.make_case(small_spec(ROW, n_a, n_b, 64, 4, 32, c_z=16, dtype="bf16", mask="random:0.8"))
+    case = I.make_case(small_spec(ROW, n_a, n_b, 64, 4, d, c_z=16, dtype="bf16", mask="random:0.8"))
     case.mask[1, :] = 0.0
     case.weights["lnz_b"] = I.to_storage(np.full(16, 4.0), "bf16")
     wb = I.widen(case.weights["w_b"]).astype(np.float64)
     for h, shift in enumerate((-97.0, 97.0, -35.0, 35.0)):
         wb[h] += shift / 64.0
     case.weights["w_b"] = I.to_storage(wb, "bf16")
-    check(case, run(case), f"{n_a} x {n_b}")
+    check(case, run(case), f"{n_a} x {n_b}, d {d}")
