@@ -16,7 +16,7 @@
 //              projection value also holds its gate value; a and b leave channel-major, [c][N][Np], which makes every
 //              channel a dense N x N matrix for the next kernel.  The incoming form is the outgoing form
 //              on the transposed view of z (strides), so a[c][i][k] then holds a of pair (k, i).
-//   k_tm_mul   per channel t_c = A_c B_c^T: a batched N x N x N contraction, 128 x 128 or 256 x 256 tiles through
+//   k_tm_mul   per channel t_c = A_c B_c^T: a batched N x N x N contraction, even shares of up to 192 x 192 or 256 x 256 tiles through
 //              LDS; t leaves as [i][channel][j]
 //   k_tm_out   LayerNorm over the channels of t (read as 2-byte loads straight into operand fragments), output
 //              projection; the output gate g is computed here, from z, in float32 (it never exists in
@@ -26,6 +26,8 @@
 // columns 8*(l/32)..+7; B (16 x 32): lane l holds column l%32, rows 8*(l/32)..+7; D (32 x 32): lane l
 // holds column l%32, register v holds row 8*(v/4) + 4*(l/32) + v%4.
 #include "ff_common.h"
+
+#include <type_traits>
 
 namespace ff {
 namespace tm {
@@ -292,7 +294,7 @@ __global__ __launch_bounds__(512, 2) void k_tm_proj(TmProjArgs p) {
 
 // ====================================================================================
 // t_c[i][j] = sum_k A_c[i][k] B_c[j][k] for every channel c: block = WI x WJ wavefronts, each TI x TJ accumulator tiles
-// (block tile 128 x 128 with 2 x 2 wavefronts of 64 x 64, or 256 x 256 with 2 x 4 wavefronts of 128 x 64), the
+// (block tile 256 x 256 with 2 x 4 wavefronts of 128 x 64), the
 // contraction in chunks of 64 through double-buffered LDS.
 // Blocks are handed to the 8 XCDs round-robin; channel c goes to XCD c % 8 with all of its tiles, so a
 // channel's operands live in one L2.
@@ -305,9 +307,8 @@ struct TmMulArgs {
 constexpr int kMulPitch = 144;                          // bytes per 64-element row in LDS (128 + 16 padding)
 
 // Block tile (32 WI TI) x (32 WJ TJ) of one channel: WI x WJ wavefronts, each TI x TJ accumulator tiles of 32 x 32.
-// Per contraction step a wavefront reads TI + TJ operand fragments from LDS for TI TJ matrix instructions: the
-// LDS read rate is what bounds this kernel (1 KiB per instruction at 2 x 2), hence 4 x 2 tiles per wavefront (and a
-// 256 x 256 block tile, eight wavefronts, all of LDS) where the matrix is large enough to fill the chip with those.
+// Per contraction step a wavefront reads TI + TJ operand fragments from LDS for TI TJ matrix instructions; 4 x 2 tiles per
+// wavefront (a 256 x 256 block tile, eight wavefronts, all of LDS) where whole tiles of that size fill the chip.
 template <int WI, int WJ, int TI, int TJ>
 struct MulShape {
     static constexpr int NT = 64 * WI * WJ, BI = 32 * WI * TI, BJ = 32 * WJ * TJ;
@@ -452,6 +453,167 @@ __global__ __launch_bounds__(64 * WI * WJ, 2) void k_tm_mul(TmMulArgs p) {
             if (i < p.N && j < p.Np) *reinterpret_cast<uint4*>(xc + (size_t)i * xrow + j) = v;
         }
     }
+}
+
+// ------------------------------------------------------------------------------------
+// The same product for matrices that whole 256 x 256 tiles do not fit.  The nt = Np / 32 tile rows (columns) of a channel are
+// split evenly into blocks of at most six, and a block's among 2 x 2 wavefronts of at most 3 x 3 accumulator tiles, so that no
+// length computes more than its 32-row padding.  Both operands pass through a ring of three chunks of 32 positions of k in LDS,
+// filled by loads that write LDS directly while the two chunks before are worked on; two blocks per compute unit.
+// Bound at 701 positions x 128 channels (88 GFLOP): the operands' way from L2 (1.1 GB; 0.4 GB from and to HBM): 184 us with
+// 128 x 128 tiles staged through registers, 130 to 142 so.
+struct MulEven {
+    static constexpr int T = 3, MAXT = 6;                 // accumulator tiles of a wavefront, tiles of a block, per direction
+    static constexpr int SLOT = 2 * MAXT * 32 * 64;       // bytes of a ring slot: [a | b][192 rows][64 bytes]
+    static constexpr int RING = 3;
+    static constexpr size_t SMEM = (size_t)RING * SLOT;
+    static constexpr int OP = 208;                        // bytes per row of a staged output tile (32 x 96 and padding)
+    static_assert(4 * 32 * OP <= RING * SLOT, "the output tiles of the four wavefronts fit in the ring");
+};
+
+// (see k_attn_rows) 16 bytes per lane from base + lane_bytes straight into LDS at lds_base + 16 * lane; whoever reads the data
+// waits (vmcnt) and passes a barrier first
+__device__ __forceinline__ void load16_to_lds(const void* base, uint32_t lane_bytes, unsigned lds_base) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :
+                 : "v"(lane_bytes), "s"(base), "s"(lds_base)
+                 : "memory", "m0");
+}
+// at most n (0 .. 6) vector-memory operations of this wavefront left in flight
+__device__ __forceinline__ void wait_vmem(int n) {
+    switch (n) {
+        case 0: __builtin_amdgcn_s_waitcnt(0x0F70); break;
+        case 1: __builtin_amdgcn_s_waitcnt(0x0F71); break;
+        case 2: __builtin_amdgcn_s_waitcnt(0x0F72); break;
+        case 3: __builtin_amdgcn_s_waitcnt(0x0F73); break;
+        case 4: __builtin_amdgcn_s_waitcnt(0x0F74); break;
+        case 5: __builtin_amdgcn_s_waitcnt(0x0F75); break;
+        default: __builtin_amdgcn_s_waitcnt(0x0F76); break;
+    }
+}
+
+__global__ __launch_bounds__(256, 2) void k_tm_mul_even(TmMulArgs p) {
+    using Sh = MulEven;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, hf = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wi = wave >> 1, wj = wave & 1;
+    const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3, t2 = p.tiles_i * p.tiles_j;
+    const int ch = (idx / t2) * 8 + xcd, tile = idx % t2;
+    if (ch >= p.C) return;                              // (whole block)
+    const int nt = p.Np >> 5;
+    const int bi = tile / p.tiles_j, bj = tile - bi * p.tiles_j;
+    const int ti0 = bi * nt / p.tiles_i, nbi = (bi + 1) * nt / p.tiles_i - ti0;       // the block's tile rows
+    const int tj0 = bj * nt / p.tiles_j, nbj = (bj + 1) * nt / p.tiles_j - tj0;
+    const int ni0 = (nbi + 1) >> 1, nj0 = (nbj + 1) >> 1;                             // of them the first wavefront's
+    const int ni = wi == 0 ? ni0 : nbi - ni0, nj = wj == 0 ? nj0 : nbj - nj0;         // (0 .. 3)
+    const size_t plane = (size_t)p.N * p.Np;
+    const char* ac = reinterpret_cast<const char*>(p.a + (size_t)ch * plane);
+    const char* bc = reinterpret_cast<const char*>(p.b + (size_t)ch * plane);
+
+    // ---- loads: a KiB is 16 rows of one operand; lane i fills 16-byte slot i, row i / 4, and fetches the piece of the chunk
+    // that belongs there: piece q of row r sits at slot 4 r + (q ^ (r / 4) % 4), which spreads the operand reads over the banks.
+    // Rows beyond N repeat the last one: their products are never stored, or land in the padding of t.
+    const int n_load = 2 * (nbi + nbj);                  // (<= 24)
+    const int mine = (n_load - wave + 3) >> 2;           // KiB chunks wave, wave + 4, ... (<= 6)
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) void*)smem);
+    uint32_t src[6];
+    const char* base[6];
+    unsigned dst[6];
+#pragma unroll
+    for (int m = 0; m < 6; ++m) {
+        const int c = 4 * m + wave;
+        const bool is_a = c < 2 * nbi;
+        const int cc = is_a ? c : c - 2 * nbi;
+        int row = 32 * (is_a ? ti0 : tj0) + 16 * cc + (lane >> 2);
+        if (row > p.N - 1) row = p.N - 1;
+        src[m] = (uint32_t)row * (uint32_t)(p.Np * 2) + (uint32_t)(((lane & 3) ^ ((lane >> 4) & 3)) * 16);
+        base[m] = is_a ? ac : bc;
+        dst[m] = (unsigned)((is_a ? 0 : Sh::SLOT / 2) + cc * 1024);
+    }
+    auto stage = [&](int kc) __attribute__((always_inline)) {
+        const unsigned slot = lds0 + (unsigned)(kc % Sh::RING) * Sh::SLOT;
+#pragma unroll
+        for (int m = 0; m < 6; ++m)
+            if (m < mine) load16_to_lds(base[m] + (size_t)kc * 64, src[m], slot + dst[m]);
+    };
+    const int nk = nt;
+    stage(0);
+    if (nk > 1) stage(1);
+
+    // publishes chunk kc and sends chunk kc + 2 on its way, into the slot that was last read before the barrier
+    auto turn = [&](int kc) __attribute__((always_inline)) {
+        wait_vmem(kc + 1 < nk ? mine : 0);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (kc + 2 < nk) stage(kc + 2);
+    };
+    const uint32_t rd = (uint32_t)(col * 64 + ((hf ^ ((col >> 2) & 3)) * 16));
+    const uint32_t ra = rd + (uint32_t)(wi == 0 ? 0 : ni0) * 2048, rb = rd + Sh::SLOT / 2 + (uint32_t)(wj == 0 ? 0 : nj0) * 2048;
+    const int i0 = 32 * (ti0 + (wi == 0 ? 0 : ni0)), j0 = 32 * (tj0 + (wj == 0 ? 0 : nj0));
+
+    auto work = [&](auto ni_c, auto nj_c) __attribute__((always_inline)) {
+        constexpr int NI = decltype(ni_c)::value, NJ = decltype(nj_c)::value;
+        f32x16 acc[NJ][NI];     // lane = i, registers = j
+#pragma unroll
+        for (int tj = 0; tj < NJ; ++tj)
+#pragma unroll
+            for (int ti = 0; ti < NI; ++ti)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[tj][ti][v] = 0.f;
+        for (int kc = 0; kc < nk; ++kc) {
+            turn(kc);
+            const unsigned char* st = smem + (kc % Sh::RING) * Sh::SLOT;
+            Frag af[2][NI], bf[2][NJ];
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+                for (int ti = 0; ti < NI; ++ti) af[kk][ti].u = *reinterpret_cast<const uint4*>(st + ((ra ^ (32u * kk)) + ti * 2048));
+#pragma unroll
+                for (int tj = 0; tj < NJ; ++tj) bf[kk][tj].u = *reinterpret_cast<const uint4*>(st + ((rb ^ (32u * kk)) + tj * 2048));
+            }
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                for (int tj = 0; tj < NJ; ++tj)
+#pragma unroll
+                    for (int ti = 0; ti < NI; ++ti)
+                        acc[tj][ti] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[kk][tj].v, af[kk][ti].v, acc[tj][ti], 0, 0, 0);
+        }
+        __syncthreads();                                 // (the ring becomes the staging area of the output)
+        // t leaves as [i][channel][j] (see k_tm_mul): 32 rows at a time through the wavefront's own part of LDS, whose operations
+        // complete in order, as row segments of 64 NJ bytes
+        unsigned char* s_o = smem + wave * (32 * Sh::OP);
+        bf16_t* xc = p.x + (size_t)ch * p.Np;
+        const size_t xrow = (size_t)p.C * p.Np;
+#pragma unroll
+        for (int ti = 0; ti < NI; ++ti) {
+#pragma unroll
+            for (int tj = 0; tj < NJ; ++tj)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    *reinterpret_cast<uint2*>(s_o + col * Sh::OP + (32 * tj + 8 * g + 4 * hf) * 2) =
+                        make_uint2(pack2(acc[tj][ti][4 * g], acc[tj][ti][4 * g + 1]), pack2(acc[tj][ti][4 * g + 2], acc[tj][ti][4 * g + 3]));
+#pragma unroll
+            for (int n = 0; n < 2 * NJ; ++n) {
+                const int id = lane + 64 * n, row = id / (4 * NJ), pc = id - row * (4 * NJ);
+                const int i = i0 + 32 * ti + row;
+                const uint4 v = *reinterpret_cast<const uint4*>(s_o + row * Sh::OP + pc * 16);
+                if (i < p.N) *reinterpret_cast<uint4*>(xc + (size_t)i * xrow + j0 + pc * 8) = v;
+            }
+        }
+    };
+    using std::integral_constant;
+#define FF_MUL_CASE(NI, NJ) \
+    case 4 * NI + NJ: work(integral_constant<int, NI>{}, integral_constant<int, NJ>{}); break;
+    switch (4 * ni + nj) {
+        FF_MUL_CASE(3, 3) FF_MUL_CASE(3, 2) FF_MUL_CASE(3, 1) FF_MUL_CASE(2, 3) FF_MUL_CASE(2, 2) FF_MUL_CASE(2, 1) FF_MUL_CASE(1, 3)
+        FF_MUL_CASE(1, 2) FF_MUL_CASE(1, 1)
+        default:                                         // no tiles: only the share of the loads
+            for (int kc = 0; kc < nk; ++kc) turn(kc);
+            __syncthreads();
+    }
+#undef FF_MUL_CASE
 }
 
 // ====================================================================================
@@ -709,7 +871,22 @@ ff_status trimul_run(const ff_trimul_desc& d, const ff_trimul_weights& w, const 
     } while (0)
         // 256 x 256 block tiles once they fill the chip several times over (c channels x (N / 256)^2 blocks, one per CU)
         if ((int64_t)c * ((N + 255) / 256) * ((N + 255) / 256) >= 4 * compute_units() && N % 256 == 0) FF_TM_MUL(2, 4, 4, 2);
-        else FF_TM_MUL(2, 2, 2, 2);
+        else {
+            static const hipError_t once = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tm_mul_even),
+                                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)MulEven::SMEM);
+            attr = once;
+            // as few blocks per direction as six tiles each allow, or one more where that saves part of a last round of blocks (two per
+            // compute unit; the time of a block grows with its tiles per direction, plus about two for its loads and stores): 450
+            // positions of 64 channels 30.3 us in 3 x 3 blocks, 26.7 in 4 x 4; 192: 9.3 and 6.3; 701 of 128: 143 in 4 x 4, 155 in 5 x 5
+            const int nt = Np / 32, t0 = (nt + MulEven::MAXT - 1) / MulEven::MAXT;
+            auto cost = [&](int t) {
+                const int64_t slots = 2 * compute_units(), n = (int64_t)8 * ((c + 7) / 8) * t * t;
+                return (n + slots - 1) / slots * ((nt + t - 1) / t + 2);
+            };
+            a.tiles_i = a.tiles_j = t0 < nt && cost(t0 + 1) < cost(t0) ? t0 + 1 : t0;
+            const int blocks = 8 * ((c + 7) / 8) * a.tiles_i * a.tiles_j;
+            if (once == hipSuccess) hipLaunchKernelGGL(k_tm_mul_even, dim3(blocks), dim3(256), MulEven::SMEM, st, a);
+        }
 #undef FF_TM_MUL
         if (attr != hipSuccess) return fail(FF_EHIP, "k_tm_mul: dynamic LDS limit: %s", hipGetErrorString(attr));
     }

@@ -70,6 +70,13 @@ def test_ragged_shapes(incoming, n, c_z, c, mask):
     check(to_np(run(case)), oracle(case), spec.name)
 
 
+@pytest.mark.parametrize("n,c_z,c", [(161, 32, 32), (290, 32, 64), (321, 64, 128), (352, 32, 128)])
+def test_uneven_shares_of_the_product(n, c_z, c):
+    """6, 10 and 11 tile rows of 32: blocks of three to six of them, and wavefronts of one to three."""
+    case = I.make_trimul_case(I.TriMulSpec(f"t_tm_share_{n}_{c}", "bf16", n, c_z, c, False, "random:0.9"))
+    check(to_np(run(case)), oracle(case), f"n {n}, c {c}")
+
+
 @pytest.mark.parametrize("incoming", [False, True])
 def test_residual_form_and_in_place(incoming):
     spec = I.TriMulSpec(f"t_tm_res_{int(incoming)}", "bf16", 150, 128, 128, incoming, "random:0.9")
