@@ -177,6 +177,28 @@ __global__ __launch_bounds__(256) void k_tm_prep(TmPrepArgs a) {
     }
 }
 
+// rows x (2 KC + 1) 16-byte pieces of a folded weight matrix into LDS rows of 32 KC + 16 bytes, by 512 threads: the 2 KC pieces of a
+// row and the one of its extra contraction step in the padding.  Nine loads in flight per thread: one at a time, each waited
+// for before the next, the copy of a block took 8 to 17 memory round trips, half of these kernels at 256 positions.
+template <int KC>
+__device__ __forceinline__ void copy_weights(unsigned char* dst, const bf16_t* w, const bf16_t* ext, int rows, int tid) {
+    constexpr int PPR = 2 * KC + 1, U = 9;
+    const int total = rows * PPR;
+    for (int first = tid; first < total; first += 512 * U) {
+        uint4 v[U];
+        int off[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int id = first + 512 * u < total ? first + 512 * u : total - 1;      // (past the end: the last piece again)
+            const int row = id / PPR, pc = id - row * PPR;
+            v[u] = *reinterpret_cast<const uint4*>(pc < 2 * KC ? w + (size_t)row * (16 * KC) + pc * 8 : ext + (size_t)row * 8);
+            off[u] = row * (32 * KC + 16) + pc * 16;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) *reinterpret_cast<uint4*>(dst + off[u]) = v[u];
+    }
+}
+
 // ====================================================================================
 // Merged projection.  Block = 8 wavefronts, each owning one 32-token tile (tokens of one row of the view)
 // as register-resident operand fragments and sweeping the prepared weight matrix 64 rows (a "pair") at a
@@ -213,12 +235,7 @@ __global__ __launch_bounds__(512, 2) void k_tm_proj(TmProjArgs p) {
     // token tiles blockIdx.x * 8 + wave, + 8 * gridDim.x, ...: after this one barrier the wavefronts run
     // independently, so that one wavefront's matrix instructions overlap another's epilogue arithmetic on the
     // same SIMD, and the weights are read from L2 once per block, not once per 256 tokens.
-    for (int id = tid; id < 64 * p.ppb * (2 * KC + 1); id += 512) {
-        const int row = id / (2 * KC + 1), pc = id - row * (2 * KC + 1);
-        const bf16_t* src = pc < 2 * KC ? p.wp + (size_t)(64 * pr_first + row) * (16 * KC) + pc * 8
-                                        : p.ext + (size_t)(64 * pr_first + row) * 8;
-        *reinterpret_cast<uint4*>(s_w + row * PITCH + pc * 16) = *reinterpret_cast<const uint4*>(src);
-    }
+    copy_weights<KC>(s_w, p.wp + (size_t)64 * pr_first * (16 * KC), p.ext + (size_t)64 * pr_first * 8, 64 * p.ppb, tid);
     __syncthreads();                                    // (the only barrier)
 
     const size_t plane = (size_t)p.N * p.Np;
@@ -651,16 +668,8 @@ __global__ __launch_bounds__(512) void k_tm_out(TmOutArgs p) {
     int t = blockIdx.x * 8 + wave;
 
     // (a row's extra contraction step - see token_side - sits in the 16 bytes that pad it)
-    for (int id = tid; id < p.cz * (2 * KC + 1); id += 512) {
-        const int row = id / (2 * KC + 1), pc = id - row * (2 * KC + 1);
-        const bf16_t* src = pc < 2 * KC ? p.wp + (size_t)row * (16 * KC) + pc * 8 : p.ext + (size_t)row * 8;
-        *reinterpret_cast<uint4*>(s_wo + row * PC + pc * 16) = *reinterpret_cast<const uint4*>(src);
-    }
-    for (int id = tid; id < p.cz * (2 * KZ + 1); id += 512) {
-        const int row = id / (2 * KZ + 1), pc = id - row * (2 * KZ + 1);
-        const bf16_t* src = pc < 2 * KZ ? p.wg + (size_t)row * (16 * KZ) + pc * 8 : p.extg + (size_t)row * 8;
-        *reinterpret_cast<uint4*>(s_wg + row * PZ + pc * 16) = *reinterpret_cast<const uint4*>(src);
-    }
+    copy_weights<KC>(s_wo, p.wp, p.ext, p.cz, tid);
+    copy_weights<KZ>(s_wg, p.wg, p.extg, p.cz, tid);
     __syncthreads();                                        // (the only barrier)
 
     for (; t < tiles_m; t += nwaves) {
@@ -669,24 +678,32 @@ __global__ __launch_bounds__(512) void k_tm_out(TmOutArgs p) {
         {
             const int j = j0 + col;
             const bf16_t* zp = p.z + ((size_t)i * p.N + (j < p.N ? j : 0)) * p.cz;
+            // (no load sits under a condition: pieces beyond cz or C re-read the first one and are cleared below, so that
+            // the tile's loads are all in flight before the first one is waited for)
 #pragma unroll
-            for (int s = 0; s < KZ; ++s) {
-                za[s].u = make_uint4(0, 0, 0, 0);
-                if (16 * s + 8 * hf < p.cz) za[s].u = *reinterpret_cast<const uint4*>(zp + 16 * s + 8 * hf);
-            }
+            for (int s = 0; s < KZ; ++s) za[s].u = *reinterpret_cast<const uint4*>(zp + (16 * s < p.cz ? 16 * s : 0) + 8 * hf);
             // t is [i][channel][j]: the eight channels of an operand fragment are eight 2-byte loads, each of
-            // them 64 contiguous bytes across the half-wave (turning the tile in LDS instead, 16-byte loads and
-            // 2-byte LDS reads, measured the same)
-            const bf16_t* xp = p.x + (size_t)i * p.C * p.Np + j;
+            // them 64 contiguous bytes across the half-wave
+            const bf16_t* xp = p.x + (size_t)i * p.C * p.Np + j + (size_t)(8 * hf) * p.Np;
+            uint32_t xl[KC][8];
+#pragma unroll
+            for (int s = 0; s < KC; ++s)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) xl[s][e] = xp[(size_t)((16 * s < p.C ? 16 * s : 0) + e) * p.Np];
+            // (the compiler would otherwise pair up the first values, and wait for them, between the loads)
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int s = 0; s < KC; ++s)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(xl[s][e]));
+#pragma unroll
+            for (int s = 0; s < KZ; ++s)
+                if (16 * s >= p.cz) za[s].u = make_uint4(0, 0, 0, 0);
 #pragma unroll
             for (int s = 0; s < KC; ++s) {
-                xa[s].u = make_uint4(0, 0, 0, 0);
-                if (16 * s + 8 * hf < p.C) {
-                    const bf16_t* xc = xp + (size_t)(16 * s + 8 * hf) * p.Np;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        xa[s].w[e] = (uint32_t)xc[(size_t)(2 * e) * p.Np] | ((uint32_t)xc[(size_t)(2 * e + 1) * p.Np] << 16);
-                }
+                for (int e = 0; e < 4; ++e) xa[s].w[e] = xl[s][2 * e] | (xl[s][2 * e + 1] << 16);
+                if (16 * s >= p.C) xa[s].u = make_uint4(0, 0, 0, 0);
             }
         }
         float mean_z, rstd_z, istd_z, mean, rstd, istd;
