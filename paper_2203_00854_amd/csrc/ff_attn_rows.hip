@@ -29,11 +29,7 @@
 namespace ff {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
-typedef __attribute__((__vector_size__(4 * sizeof(short)))) short i16x4;
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef void __attribute__((address_space(3)))* lptr_t;
 
 namespace {
@@ -52,12 +48,6 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {   // a -> low half
 }
 __device__ __forceinline__ float lo_f32(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float hi_f32(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
-// Sum of the lane's own four bf16 values (w0, w1), added to every element of acc: a 4 x 4 x 4 matrix instruction (sixteen
-// independent blocks of four lanes) against ones.
-__device__ __forceinline__ f32x4 add_four(uint32_t w0, uint32_t w1, f32x4 acc) {
-    const i16x4 ones = __builtin_bit_cast(i16x4, make_uint2(0x3f803f80u, 0x3f803f80u));
-    return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_bit_cast(i16x4, make_uint2(w0, w1)), acc, 0, 0, 0);
-}
 // sum of the two bf16 halves of w, added to acc
 __device__ __forceinline__ float add_pair(uint32_t w, float acc) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), __builtin_bit_cast(bf16x2, 0x3f803f80u), acc,
@@ -293,13 +283,6 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, HAS_BIAS)) void k_attn_
     Frag kf[2][KS], vf[2][2], pf[2];
 #pragma unroll
     for (int c = 0; c < 2; ++c) pf[c].u = vf[1][c].u = make_uint4(0, 0, 0, 0);
-    // (query side of the mask step: a one against the key side's 0 or -inf)
-    const bf16x4 q_one = __builtin_bit_cast(bf16x4, make_uint2(hf == 0 ? 0x00003f80u : 0u, 0u));
-    auto mask_step = [&](uint32_t live, f32x16 s) __attribute__((always_inline)) {
-        const uint32_t term = (live >> kperm) & 1u ? 0u : 0x0000ff80u;
-        const bf16x4 k_mask = __builtin_bit_cast(bf16x4, make_uint2(hf == 0 ? term : 0u, 0u));
-        return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(i16x4, k_mask), __builtin_bit_cast(i16x4, q_one), s, 0, 0, 0);
-    };
     // One tile (row j of the step) of the software pipeline: the exponentials of tile t run while the matrix core forms
     // the scores of tile t + 1 (bias bn, query operand qn, keys kn) and the context of tile t - 1 (weights pp, values vp),
     // and the operands k of tile t + 2 and v^T of tile t come from LDS.
@@ -314,7 +297,7 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, HAS_BIAS)) void k_attn_
             if (KS > 1 && g == 2) sn = mfma(kn[KS - 1].v, qn[KS - 1].v, sn);
             if (g == 4) op = mfma(vp[0].v, pf[0].v, op);
             if (g == 6) op = mfma(vp[1].v, pf[1].v, op);
-            if (!decltype(plain_c)::value && g == 4 && live != 0xffffffffu) sn = mask_step(live, sn);
+            if (!decltype(plain_c)::value && g == 4 && live != 0xffffffffu) sn = mask_step(live, kperm, hf, sn);
             if (!ONES && (g & 1)) lt = add_four(pf[g >> 2].w[(g >> 1) % 2 * 2], pf[g >> 2].w[(g >> 1) % 2 * 2 + 1], lt);
             if (g == 0) {
                 kl[0].u = lds16(kl_off + rd_k);
@@ -386,7 +369,7 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, HAS_BIAS)) void k_attn_
         s_acc[0] = mfma(kf[0][s].v, qf[0][s].v, s == 0 ? bias_a : s_acc[0]);
         kf[1][s].u = lds16(k_at(1) + (rd_k ^ (32u * s)));
     }
-    s_acc[0] = mask_step(live_c[0], s_acc[0]);
+    s_acc[0] = mask_step(live_c[0], kperm, hf, s_acc[0]);
     // Steps before the first one that holds a masked (or missing) key have a loop of their own without the mask tests.
     int n_plain = nt;
     for (int i = 0; i < nt * NR && n_plain == nt; i += 64) {
@@ -499,7 +482,7 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, HAS_BIAS)) void k_attn_
                 k.u = ldg16(a.k + off + (size_t)kt * (32 * D) + 16 * i, kv);
                 s = mfma(k.v, qs[i].v, s);
             }
-            s = mask_step(live, s);
+            s = mask_step(live, kperm, hf, s);
             float mx = s[0];
 #pragma unroll
             for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);

@@ -29,7 +29,8 @@
 // fetched, so nothing moves between the two contractions.
 //
 // Workspace layout of this family (Lp = Lq = L rounded up to 64, token p = rl*Lp + l):
-//   bias [H][Lq][Lp] float32 (times log2 e) in 32 x 32 tiles (bias_index)
+//   bias [H][Lq][Lp] float32 (times log2 e) in 32 x 32 tiles (bias_index); rows of pad queries are never written, and
+//   only the lanes of those queries, which store nothing, see them
 //   q, k, g, o [rows][H][Lp][D] bf16;  vt [rows][H][Lp/32][D][32] bf16
 //   prepared weights [(4*Hd + 32)][c] (+ [32][c_z] in row mode) bf16, their sums and offsets
 // Pad tokens (l in [L, Lp)) hold finite values everywhere; they are masked as keys.
@@ -424,18 +425,6 @@ __global__ __launch_bounds__(512) void k_prep_bias(PrepBiasArgs a) {
         const int h = 8 * (v >> 2) + 4 * hf + (v & 3);
         if (h < a.H) bp[(size_t)h * plane] = acc[v] * rstd;
     }
-}
-
-// Rows q in [L, Lq) of the bias tensor belong to pad queries: no kernel computes them, but k_proj_attn loads whole
-// tiles of 32 queries.  Zeros there keep its lanes for pad queries (never stored) on the common path whatever the
-// caller's workspace held before.  (k_attn_rows does not look at them.)
-__global__ __launch_bounds__(256) void k_zero_bias_pad(float* bias, int L, int Lq, int Lp, int H) {
-    const int per_head = (Lq - L) * Lp;
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= per_head * H) return;
-    const int h = i / per_head, r = i - h * per_head;
-    const int q = L + r / Lp, k = r - (q - L) * Lp;
-    bias[bias_index(h, q, k, Lq, Lp)] = 0.f;
 }
 
 // ====================================================================================
@@ -924,9 +913,6 @@ __global__ __launch_bounds__(kGemmWaves * 64, 2) void k_gemm(GemmArgs a) {
     else run_step(-1, kp, acc[1], acc[0], ra, s_w, ftp, ftp);
 }
 
-constexpr float kRaise = 10.f;   // log2 units
-constexpr float kOver = 1048576.f;   // 2^20: partial denominator (16 keys) that triggers a raise of the reference
-
 // ====================================================================================
 // Projection and attention in one kernel, for sequences of at most 256 positions with head
 // dimension 32 (the row-wise and triangle attentions of the training crop, Section 5.2's merged
@@ -946,19 +932,20 @@ constexpr float kOver = 1048576.f;   // 2^20: partial denominator (16 keys) that
 // input for both rows.
 //
 // LDS: the head's four folded 32 x K weight tiles (row pitch 2K + 16 bytes), their extra pieces,
-// k [2][256][80 bytes] (four pieces of the contraction and the piece with 1 and the mask term),
-// v^T [2][32][528 bytes], 1/std of the tokens, one flag per (row, key tile) that tells whether
-// the tile holds a valid key, and 2 KiB per wavefront through which the raw tokens, fetched as
+// k [2][256][80 bytes], v^T [2][32][528 bytes], 1/std of the tokens, one word per (row, key tile) with a bit per
+// valid key, and 2 KiB per wavefront through which the raw tokens, fetched as
 // whole 128-byte lines, are turned into matrix-core operands.  With 256 channels that is 159 KiB
 // of the compute unit's 160: one block of eight wavefronts per compute unit.
 //
-// Measured on the training crop of the row-wise attention (128 x 256 tokens, 8 heads): 50 us
-// against 34 + 31 us for k_gemm<PROJ> and an attention kernel.  No unit is saturated (LDS busy 22 %, matrix
-// pipe 25 %, vector unit 39 % of the kernel): in the projections every matrix instruction waits
-// for a fresh weight operand from LDS, the attention is paced by the exponentials, and two
-// wavefronts per SIMD with one dependent chain each leave a third of the issue slots empty.  Of
-// the two wavefronts of a SIMD the older one is served first and finishes each phase about a
-// quarter earlier; the block waits for the younger one at both barriers.
+// The attention phase is the pipeline of k_attn_rows over two rows: no reference in the softmax, masked keys cost a matrix
+// instruction only in tiles that hold any, matrix instructions of the next and the previous tile between the exponentials.
+//
+// Measured on the training crop of the row-wise attention (128 x 256 tokens, 8 heads): 43.4 us (46.3 with a reference and dot
+// products in the softmax) against 34 + 31 us for k_gemm<PROJ> and an attention kernel; triangle attention at 256: 34.9 (36.7).
+// In the projections every matrix instruction waits for a fresh weight operand from LDS; of the two wavefronts of a SIMD
+// the older one is served first and finishes each phase about a quarter earlier, and the block waits for the younger one
+// at both barriers.
+
 struct FusedArgs {
     const bf16_t* x;       // raw input, token (r, l) at (r*sr + l*sl)*K
     int64_t sr, sl;        // token strides of x and of the mask
@@ -972,7 +959,7 @@ struct FusedArgs {
     bf16_t* o;             // gated context [rows][H][Lp][32]
 };
 
-constexpr int kFuKPitch = 80;       // bytes of a key row in LDS
+constexpr int kFuKPitch = 80;       // bytes of a key row in LDS (64 and a pad: conflict-free operand reads)
 constexpr int kFuVPitch = 528;      // bytes of a v^T row in LDS: 256 keys and a pad
 constexpr int kFuWaves = 8;
 
@@ -990,7 +977,7 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
     unsigned char* s_k = reinterpret_cast<unsigned char*>(s_aug + 128);         // [2][256][kFuKPitch]
     unsigned char* s_vt = s_k + 2 * 256 * kFuKPitch;                            // [2][32][kFuVPitch]
     float* s_stat = reinterpret_cast<float*>(s_vt + 2 * 32 * kFuVPitch);        // [wave][2][32]
-    int* s_live = reinterpret_cast<int*>(s_stat + kFuWaves * 2 * 32);           // [2][8]
+    int* s_live = reinterpret_cast<int*>(s_stat + kFuWaves * 2 * 32);           // [2][8]: bit = key of the tile is attended to
     unsigned char* s_st = reinterpret_cast<unsigned char*>(s_live + 16) + (threadIdx.x >> 6) * 2048;   // [wave][16][128]
 
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, hf = lane >> 5;
@@ -1075,7 +1062,7 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
         }
 
         // ---- projections: q and gate stay in registers, k and v^T go to LDS
-        Frag qf[2][3];          // (set and used by wavefronts with tokens only)
+        Frag qf[2][2];          // (set and used by wavefronts with tokens only)
         uint32_t gpk[2][8];
         if (active) {
 #pragma unroll
@@ -1146,8 +1133,8 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
                     s_stat[(wave * 2 + j) * 32 + col] = rstd;
                 }
                 const bool key_valid = tok_in && mval[j] != 0.f;
-                const bool any_valid = __any(key_valid);
-                if (lane == 0) s_live[j * 8 + wave] = any_valid ? 1 : 0;
+                const uint64_t live = __ballot(key_valid);           // (the two half-waves hold the same 32 tokens)
+                if (lane == 0) s_live[j * 8 + wave] = (int)(uint32_t)live;
                 {
                     Frag wq, wk, wv, wg;
                     wq.u = s_aug[col];
@@ -1159,8 +1146,7 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
                     av = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xaug.v, wv.v, av, 0, 0, 0);
                     ag = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wg.v, xaug.v, ag, 0, 0, 0);
                 }
-                // q: B operand of S^T, step s = registers 8s .. 8s+7; step 2 carries (-m_ref, 1)
-                // k: the same pieces into the token's LDS row, then (1, mask term)
+                // q: B operand of S^T, step s = registers 8s .. 8s+7; k: the same pieces into the token's LDS row
                 unsigned char* krow = s_k + (j * 256 + l_tok) * kFuKPitch;
 #pragma unroll
                 for (int s = 0; s < 2; ++s) {
@@ -1171,10 +1157,6 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
                         kw[i] = pack2(ak[8 * s + 2 * i] * rstd, ak[8 * s + 2 * i + 1] * rstd);
                     }
                     *reinterpret_cast<uint4*>(krow + (2 * s + hf) * 16) = make_uint4(kw[0], kw[1], kw[2], kw[3]);
-                }
-                qf[j][2].u = make_uint4(hf == 0 ? 0x3f800000u : 0u, 0u, 0u, 0u);            // (-m_ref = 0, 1.0)
-                if (hf == 0) {
-                    *reinterpret_cast<uint4*>(krow + 64) = make_uint4(key_valid ? 0x00003f80u : 0xff803f80u, 0u, 0u, 0u);   // (1.0, mask term)
                 }
                 // gate: the layout of O^T
 #pragma unroll
@@ -1208,21 +1190,12 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
             // permuted key of S^T row m = col: rows 8g + 4b + e hold key 16*(g/2) + 8b + 4*(g%2) + e, so that the lane's registers 8c .. 8c+7 hold
             // the keys 16c + 8hf .. + 7 of the tile
             const int kperm_a = 16 * (col_a >> 4) + 8 * ((col_a >> 2) & 1) + 4 * ((col_a >> 3) & 1) + (col_a & 3);
-            int lv[2];
+            const int nk = (a.L + 31) >> 5;                   // key tiles that hold keys
+            f32x16 o_acc[2], s_acc[2];
+            float l_run[2];
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                int bits = 0;
-                for (int t = 0; t < nt; ++t) bits |= s_live[j * 8 + t] << t;
-                lv[j] = __builtin_amdgcn_readfirstlane(bits);
-            }
-            f32x16 o_acc[2];
-            float m_ref[2], l_run[2];
-            bool first[2];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                m_ref[j] = 0.f;
                 l_run[j] = 0.f;
-                first[j] = true;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) o_acc[j][v] = 0.f;
             }
@@ -1231,6 +1204,7 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
             const uint32_t b_lane = (uint32_t)lane_a * 16;
             auto load_bias = [&](int kt, f32x16& bt) __attribute__((always_inline)) {
                 if constexpr (HAS_BIAS) {
+                    if (kt > nk - 1) kt = nk - 1;             // (past the end: a harmless repeat)
                     const char* bp = reinterpret_cast<const char*>(bh + 1024 * kt) + b_lane;
 #pragma unroll
                     for (int c = 0; c < 2; ++c)
@@ -1245,90 +1219,131 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
                     for (int v = 0; v < 16; ++v) bt[v] = 0.f;
                 }
             };
-            auto tile = [&](int kt, const f32x16& bt) __attribute__((always_inline)) {
-                f32x16 sa[2];
-                Frag vf[2][2];
-                bool live[2];
+            const uint32_t k_lane = (uint32_t)(kperm_a * kFuKPitch + hf_a * 16), v_lane = (uint32_t)(col_a * kFuVPitch + 16 * hf_a);
+            auto load_k = [&](int j, int kt, Frag (&kf)[2]) __attribute__((always_inline)) {
+                if (kt > nk - 1) kt = nk - 1;
+                const unsigned char* kr = s_k + (j * 256 + 32 * kt) * kFuKPitch + k_lane;
+                kf[0].u = *reinterpret_cast<const uint4*>(kr);
+                kf[1].u = *reinterpret_cast<const uint4*>(kr + 32);
+            };
+            auto load_v = [&](int j, int kt, Frag (&vf)[2]) __attribute__((always_inline)) {
+                const unsigned char* vr = s_vt + j * 32 * kFuVPitch + 64 * kt + v_lane;
+                vf[0].u = *reinterpret_cast<const uint4*>(vr);
+                vf[1].u = *reinterpret_cast<const uint4*>(vr + 32);
+            };
+            Frag kf[2][2], vf[2][2], pf[2];
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    live[j] = (lv[j] >> kt) & 1;
-                    if (live[j]) {
-                        const unsigned char* krow = s_k + (j * 256 + 32 * kt + kperm_a) * kFuKPitch;
-                        Frag kf[3];
-                        kf[0].u = *reinterpret_cast<const uint4*>(krow + hf_a * 16);
-                        kf[1].u = *reinterpret_cast<const uint4*>(krow + 32 + hf_a * 16);
-                        kf[2].u = make_uint4(0, 0, 0, 0);
-                        if (hf_a == 0) kf[2].u = *reinterpret_cast<const uint4*>(krow + 64);
-                        const unsigned char* vrow = s_vt + (j * 32 + col_a) * kFuVPitch + (32 * kt + 8 * hf_a) * 2;
-                        vf[j][0].u = *reinterpret_cast<const uint4*>(vrow);
-                        vf[j][1].u = *reinterpret_cast<const uint4*>(vrow + 32);
-                        sa[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0].v, qf[j][0].v, bt, 0, 0, 0);
-                        sa[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1].v, qf[j][1].v, sa[j], 0, 0, 0);
-                        sa[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[2].v, qf[j][2].v, sa[j], 0, 0, 0);
+            for (int c = 0; c < 2; ++c) pf[c].u = vf[1][c].u = make_uint4(0, 0, 0, 0);
+            // The pipeline of k_attn_rows over the tiles (kt, row 0), (kt, row 1), ...: the exponentials of a tile run while the
+            // matrix core forms the scores of the next one (bias bn, keys live_n) and the context and the denominator of the one before
+            auto tile = [&](uint32_t live_n, f32x16& sc, f32x16& sn, const f32x16& bn, Frag (&qn)[2], Frag (&kn)[2], Frag (&vp)[2],
+                            f32x16& op, float& lp, auto&& loads) __attribute__((always_inline)) {
+                Frag pc[2];
+                f32x4 lt = {0.f, 0.f, 0.f, 0.f};
+                float e0 = __builtin_amdgcn_exp2f(sc[0]), e1 = __builtin_amdgcn_exp2f(sc[1]);
+#pragma unroll
+                for (int g = 0; g < 8; ++g) {
+                    if (g == 0) sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kn[0].v, qn[0].v, bn, 0, 0, 0);
+                    if (g == 2) sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kn[1].v, qn[1].v, sn, 0, 0, 0);
+                    if (g == 4) op = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vp[0].v, pf[0].v, op, 0, 0, 0);
+                    if (g == 6) op = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vp[1].v, pf[1].v, op, 0, 0, 0);
+                    if (g == 4 && live_n != 0xffffffffu) sn = mask_step(live_n, kperm_a, hf_a, sn);
+                    if (g & 1) lt = add_four(pf[g >> 2].w[(g >> 1) % 2 * 2], pf[g >> 2].w[(g >> 1) % 2 * 2 + 1], lt);
+                    if (g == 0) loads();
+                    float n0 = 0.f, n1 = 0.f;
+                    if (g < 7) {
+                        n0 = __builtin_amdgcn_exp2f(sc[2 * g + 2]);
+                        n1 = __builtin_amdgcn_exp2f(sc[2 * g + 3]);
+                        asm volatile("" : "+v"(n0), "+v"(n1));
                     }
+                    uint32_t& w = pc[g >> 2].w[g & 3];
+                    w = pack2(e0, e1);
+                    asm volatile("" : "+v"(w));
+                    __builtin_amdgcn_sched_barrier(0);
+                    e0 = n0;
+                    e1 = n1;
                 }
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    if (!live[j]) continue;
-                    // sa holds s - m_ref (masked keys: -inf).  The first live tile sets the reference to
-                    // its maximum; later tiles are exponentiated as they are, and a partial denominator
-                    // beyond kOver sends the tile through raise_ref
-                    auto tile_max = [&]() __attribute__((always_inline)) -> float {
-                        float mx = sa[j][0];
-#pragma unroll
-                        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, sa[j][v]);
-                        return fmaxf(mx, other_half(mx));
-                    };
-                    auto raise_ref = [&](float tmax, bool always) __attribute__((always_inline)) {
-                        const bool raise = always || tmax > kRaise;
-                        const float new_ref = raise ? bf16_round(m_ref[j] + tmax) : m_ref[j];
-                        const float delta = new_ref - m_ref[j];
-                        m_ref[j] = new_ref;
-                        const float sc = first[j] ? 1.f : __builtin_amdgcn_exp2f(-delta);
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) {
-                            o_acc[j][v] *= sc;
-                            sa[j][v] -= delta;
-                        }
-                        l_run[j] *= sc;
-                        if (hf_a == 0) qf[j][2].w[0] = pack2(-new_ref, 1.f);
-                    };
-                    if (first[j]) {
-                        raise_ref(tile_max(), true);
-                        first[j] = false;
-                    }
-                    Frag pf[2];
-                    float lt;
-                    auto exponentiate = [&]() __attribute__((always_inline)) {
-                        lt = 0.f;
-#pragma unroll
-                        for (int c = 0; c < 2; ++c)
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) {
-                                const float p0 = __builtin_amdgcn_exp2f(sa[j][8 * c + 2 * i]);
-                                const float p1 = __builtin_amdgcn_exp2f(sa[j][8 * c + 2 * i + 1]);
-                                pf[c].w[i] = pack2(p0, p1);
-                                lt = add_pair(pf[c].w[i], lt);
-                            }
-                    };
-                    exponentiate();
-                    if (__any(!(lt <= kOver))) {
-                        raise_ref(tile_max(), false);
-                        exponentiate();
-                    }
-                    l_run[j] += lt;
-#pragma unroll
-                    for (int c = 0; c < 2; ++c)
-                        o_acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[j][c].v, pf[c].v, o_acc[j], 0, 0, 0);
-                }
+                lp += lt[0];
+                pf[0] = pc[0];
+                pf[1] = pc[1];
+            };
+            auto live_of = [&](int j, int kt) __attribute__((always_inline)) {
+                return (uint32_t)__builtin_amdgcn_readfirstlane(s_live[j * 8 + (kt < nk ? kt : nk - 1)]);
+            };
+            auto step = [&](int kt, f32x16& bc, f32x16& bn) __attribute__((always_inline)) {
+                const uint32_t l1 = live_of(1, kt), l0 = live_of(0, kt + 1);
+                tile(l1, s_acc[0], s_acc[1], bc, qf[1], kf[1], vf[1], o_acc[1], l_run[1], [&]() __attribute__((always_inline)) {
+                    load_k(0, kt + 1, kf[0]);
+                    load_v(0, kt, vf[0]);
+                });
+                tile(l0, s_acc[1], s_acc[0], bn, qf[0], kf[0], vf[0], o_acc[0], l_run[0], [&]() __attribute__((always_inline)) {
+                    load_k(1, kt + 1, kf[1]);
+                    load_v(1, kt, vf[1]);
+                    load_bias(kt + 2, bc);
+                });
             };
             f32x16 bA, bB;
             load_bias(0, bA);
-            for (int kt = 0; kt < nt; kt += 2) {
-                load_bias(kt + 1, bB);
-                tile(kt, bA);
-                load_bias(kt + 2 < nt ? kt + 2 : nt - 1, bA);        // (past the end: a harmless repeat)
-                tile(kt + 1, bB);
+            load_bias(1, bB);
+            load_k(0, 0, kf[0]);
+            load_k(1, 0, kf[1]);
+            s_acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0][0].v, qf[0][0].v, bA, 0, 0, 0);
+            s_acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0][1].v, qf[0][1].v, s_acc[0], 0, 0, 0);
+            s_acc[0] = mask_step(live_of(0, 0), kperm_a, hf_a, s_acc[0]);
+            int kt = 0;
+            for (; kt + 1 < nk; kt += 2) {
+                step(kt, bA, bB);
+                step(kt + 1, bB, bA);
+            }
+            if (kt < nk) step(kt, bA, bB);
+            {
+                f32x4 lt = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    o_acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[1][c].v, pf[c].v, o_acc[1], 0, 0, 0);
+                    lt = add_four(pf[c].w[0], pf[c].w[1], lt);
+                    lt = add_four(pf[c].w[2], pf[c].w[3], lt);
+                }
+                l_run[1] += lt[0];
+            }
+            // A denominator outside [2^-60, 2^96] (see k_attn_rows): the row is done again with a running maximum
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const float l_tot = l_run[j] + other_half(l_run[j]);
+                const bool fine = l_tot >= 0x1p-60f && l_tot <= 0x1p96f;
+                if (!__any(!fine && l_tok < a.L)) continue;
+                float m = -INFINITY;
+                l_run[j] = 0.f;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o_acc[j][v] = 0.f;
+                for (int t = 0; t < nk; ++t) {
+                    const uint32_t live = live_of(j, t);
+                    if (live == 0) continue;
+                    f32x16 s;
+                    Frag p[2];
+                    load_bias(t, s);
+                    load_k(j, t, kf[0]);
+                    load_v(j, t, vf[0]);
+                    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0][0].v, qf[j][0].v, s, 0, 0, 0);
+                    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0][1].v, qf[j][1].v, s, 0, 0, 0);
+                    s = mask_step(live, kperm_a, hf_a, s);
+                    float mx = s[0];
+#pragma unroll
+                    for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
+                    const float m_new = fmaxf(m, fmaxf(mx, other_half(mx)));       // (finite: the tile holds a live key)
+                    const float sc = __builtin_amdgcn_exp2f(m - m_new);
+                    m = m_new;
+                    l_run[j] *= sc;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) o_acc[j][v] *= sc;
+#pragma unroll
+                    for (int g = 0; g < 8; ++g) {
+                        p[g >> 2].w[g & 3] = pack2(__builtin_amdgcn_exp2f(s[2 * g] - m), __builtin_amdgcn_exp2f(s[2 * g + 1] - m));
+                        l_run[j] = add_pair(p[g >> 2].w[g & 3], l_run[j]);
+                    }
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) o_acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[0][c].v, p[c].v, o_acc[j], 0, 0, 0);
+                }
             }
 
             // ---- normalise, gate, store: o_acc[j]: lane = query, register v = e = 8*(v/4) + 4*hf + v%4
@@ -1491,11 +1506,6 @@ ff_status mfma_prepare(const Problem& p, const ff_attn_weights& w, const void* x
             Timed t(KK_PREP, st);
             hipLaunchKernelGGL(k_prep, dim3((rows + 3) / 4), dim3(256), 0, st, a);
         }
-    }
-    if (p.has_bias && Lq > p.L && fused_proj_attn(p)) {
-        const int n = (Lq - p.L) * Lp * p.H;
-        Timed t(KK_PREP, st);
-        hipLaunchKernelGGL(k_zero_bias_pad, dim3((n + 255) / 256), dim3(256), 0, st, ws.bias, p.L, Lq, Lp, p.H);
     }
     return check_launch("prepare (mfma)");
 }

@@ -56,11 +56,11 @@ def test_shapes(mode, n_a, n_b, c, H, c_z, mask, chunk, d):
     check(case, run(case, chunk), case.spec.name)
 
 
-@pytest.mark.parametrize("n_a,n_b,d", [(3, 70, 32), (300, 260, 32), (5, 150, 8), (300, 100, 16)])
+@pytest.mark.parametrize("n_a,n_b,d", [(3, 70, 32), (300, 260, 32), (5, 150, 8), (300, 100, 16), (7, 200, 32)])
 def test_logits_far_from_zero(n_a, n_b, d):
     """The softmax runs without a reference while the denominator stays inside [2^-60, 2^96].  An offset of the pair bias moves all
     logits of a head by the same amount (which the softmax removes): heads at about -140, +140, -50 and +50 log2 units, the
-    first two outside that range; one batch row is fully masked."""
+    first two outside that range; one batch row is fully masked.  (200 positions at d = 32: k_proj_attn, which does the same.)"""
     case = I.make_case(small_spec(ROW, n_a, n_b, 64, 4, d, c_z=16, dtype="bf16", mask="random:0.8"))
     case.mask[1, :] = 0.0
     case.weights["lnz_b"] = I.to_storage(np.full(16, 4.0), "bf16")
