@@ -9,10 +9,9 @@
 // The score matrix is never stored (Section 3.2): as in the forward pass it is recomputed tile by tile.
 // One wavefront per 32-query (or 32-key) tile, four consecutive tiles of one (row, head) per block; the tiles of the
 // other side, which all four contract with, are copied into LDS once per block, a tile ahead of the arithmetic:
-//   k_bwd_transpose  position-contiguous copies [d][L] of q, k and v for the operands whose contraction runs over
-//                positions (k_bwd_stats adds the one of dctx); the row of ones that stands in for no mask; and the
-//                bias times sqrt(d), tile by tile in the order of the accumulator registers, once with lane = query
-//                and once with lane = key, so that a bias tile is four 16-byte loads per lane in every kernel
+//   k_bwd_prepare  the bias times sqrt(d), tile by tile in the order of the accumulator registers, once with lane = query and
+//                once with lane = key, so that a bias tile is four 16-byte loads per lane in every kernel; the row of ones
+//                that stands in for no mask
 //   k_bwd_stats  forward recomputation with an online softmax: the logsumexp of every query (base 2), ctx,
 //                dg, dctx and delta
 //   k_bwd_dq     per query tile, over the key tiles: S^T = K Q^T and dP^T = V dctx^T (lane = query, so that
@@ -22,9 +21,10 @@
 //   k_bwd_dbias  per (head, patch of 4 x 4 tiles, chunk of batch rows), a wavefront per tile: dS summed in registers over the rows of the
 //                chunk, the chunks' partial sums added in a fixed order by a small second kernel (deterministic,
 //                no atomics)
-// Operands whose contraction runs over the head dim are 16-byte row reads; operands whose contraction runs
-// over keys or queries ("transposed" fragments: lane = channel) are two 8-byte reads of the position-contiguous
-// copies, taken in exactly the order in which the accumulator of the previous contraction leaves its values, so
+// Operands whose contraction runs over the head dim are 16-byte row reads of the staged tiles; operands whose contraction
+// runs over keys or queries (lane = channel) are transposing reads of the same tiles (ds_read_b64_tr_b16: no
+// position-contiguous copy of any tensor exists), taken in exactly the order in which the accumulator of the previous
+// contraction leaves its values, so
 // nothing moves between two contractions.  What is added to q.k and what is subtracted from dP enter through the
 // matrix core: the bias tile and -delta as the accumulators' starting values, the -inf of masked keys as one more
 // contraction step (key side 0 or -inf, query side 1).  A thread's share of the staging copies (which pieces,
@@ -66,13 +66,12 @@ struct Args {
     const float* mask;                       // [R][L] or NULL
     const float* mrow;                       // mask entry of (r, j): mrow[r * mstride + j] (without a mask: a row of ones, stride 0)
     int mstride;
-    float* ones;                             // workspace [Lp]: that row of ones (written by k_bwd_transpose)
+    float* ones;                             // workspace [Lp]: that row of ones (written by k_bwd_prepare)
     bf16_t *dq, *dk, *dv, *dg;               // [R][H][L][D]
     float* dbias;                            // [H][L][L] or NULL
     float* dbias_part;                       // workspace [row_chunks][H][L][L] (partial sums over the rows of a chunk)
     int row_chunks, rows_per_chunk;
     bf16_t* dctx;                            // workspace [R][H][L][D]
-    bf16_t *qT, *kT, *vT, *dctxT;            // workspace [R][H][D][Lp]: position-contiguous copies for the transposed operands
     float *lse, *delta;                      // workspace [R*H][Lp]
     float *biasA, *biasK;                    // workspace [H][Lp/32][Lp/32][4][64][4]: the bias, times sqrt(D), tile by tile in the
                                              // order of the accumulator registers (biasA: lane = query, biasK: lane = key)
@@ -95,78 +94,34 @@ __device__ __forceinline__ void load_rows(Frag (&f)[(D + 15) / 16], const bf16_t
     }
 }
 
-// Transposed fragments of the same 32 positions: lane (e, hf) holds x[n][e] for the eight positions that slot
-// u = 0..7 of half hf of contraction step s meets, n0 + 16 s + 4 hf + (u < 4 ? u : u + 4): the order in which a
-// 32 x 32 accumulator (register 8s + u of half hf) leaves its rows.  xT is the position-contiguous copy
-// [D][Lp] of the (row, head) (zeros beyond L), so these are two 8-byte loads per step; zeros for e >= D.
-template <int D>
-__device__ __forceinline__ void load_cols(Frag (&f)[2], const bf16_t* xT, int n0, int Lp, int col, int hf) {
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        f[s].u = make_uint4(0, 0, 0, 0);
-        if (col < D) {
-            const bf16_t* p = xT + (size_t)col * Lp + n0 + 16 * s + 4 * hf;
-            const uint2 lo = *reinterpret_cast<const uint2*>(p), hi = *reinterpret_cast<const uint2*>(p + 8);
-            f[s].u = make_uint4(lo.x, lo.y, hi.x, hi.y);
-        }
-    }
-}
-
-// xT[(row, head)][e][n] = x[(row, head)][n][e] for q, k and v (blockIdx.y picks the tensor), zeros for n in [L, Lp).
-// One wavefront per 32 positions: 16-byte row loads, 2-byte stores that are contiguous across the lanes.
-template <int D>
-__global__ __launch_bounds__(256) void k_bwd_transpose(Args a) {
+// The tiled copies of the bias (see Args) and the row of ones.  One wavefront per 32 x 32 tile of a head.
+__global__ __launch_bounds__(256) void k_bwd_prepare(Args a) {
     const int lane = threadIdx.x & 63, col = lane & 31, hf = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nt = a.Lp >> 5;
-    // blockIdx.y: with a bias 0 = the bias tiles (first, so that their chains of dependent loads run beside the
-    // copies), then q, k, v; without a bias q, k, v
-    const int which = a.bias ? (int)blockIdx.y - 1 : (int)blockIdx.y;
-    if (blockIdx.x == 0 && which == 0)
+    if (blockIdx.x == 0)
         for (int n = threadIdx.x; n < a.Lp; n += 256) a.ones[n] = 1.f;
     const int task = blockIdx.x * 4 + wave;
-    if (which < 0) {
-        // The bias tile (it, jt) of head h, times sqrt(D), as the accumulator of the logits holds it: float4 g of
-        // lane (col, hf) = entries 8 g + 4 hf .. + 3 along the register axis.  biasA: lane = query i0 + col, registers
-        // along the keys; biasK: lane = key j0 + col, registers along the queries.  Zeros outside [0, L)^2.
-        if (task >= a.H * nt * nt) return;
-        const int h = task / (nt * nt), rem = task - h * nt * nt, it = rem / nt, jt = rem - it * nt;
-        const float* bh = a.bias + (size_t)h * a.L * a.L;
-        float* ta = a.biasA + (size_t)task * 1024 + lane * 4;
-        float* tk = a.biasK + (size_t)task * 1024 + lane * 4;
+    if (!a.bias || task >= a.H * nt * nt) return;
+    // The bias tile (it, jt) of head h, times sqrt(D), as the accumulator of the logits holds it: float4 g of
+    // lane (col, hf) = entries 8 g + 4 hf .. + 3 along the register axis.  biasA: lane = query i0 + col, registers
+    // along the keys; biasK: lane = key j0 + col, registers along the queries.  Zeros outside [0, L)^2.
+    const int h = task / (nt * nt), rem = task - h * nt * nt, it = rem / nt, jt = rem - it * nt;
+    const float* bh = a.bias + (size_t)h * a.L * a.L;
+    float* ta = a.biasA + (size_t)task * 1024 + lane * 4;
+    float* tk = a.biasK + (size_t)task * 1024 + lane * 4;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            float va[4], vk[4];
+    for (int g = 0; g < 4; ++g) {
+        float va[4], vk[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int x = 8 * g + 4 * hf + e;
-                const int ia = it * 32 + col, ja = jt * 32 + x, ik = it * 32 + x, jk = jt * 32 + col;
-                va[e] = (ia < a.L && ja < a.L) ? bh[(size_t)ia * a.L + ja] * a.sqrt_d : 0.f;
-                vk[e] = (ik < a.L && jk < a.L) ? bh[(size_t)ik * a.L + jk] * a.sqrt_d : 0.f;
-            }
-            *reinterpret_cast<float4*>(ta + 256 * g) = make_float4(va[0], va[1], va[2], va[3]);
-            *reinterpret_cast<float4*>(tk + 256 * g) = make_float4(vk[0], vk[1], vk[2], vk[3]);
+        for (int e = 0; e < 4; ++e) {
+            const int x = 8 * g + 4 * hf + e;
+            const int ia = it * 32 + col, ja = jt * 32 + x, ik = it * 32 + x, jk = jt * 32 + col;
+            va[e] = (ia < a.L && ja < a.L) ? bh[(size_t)ia * a.L + ja] * a.sqrt_d : 0.f;
+            vk[e] = (ik < a.L && jk < a.L) ? bh[(size_t)ik * a.L + jk] * a.sqrt_d : 0.f;
         }
-        return;
-    }
-    if (task >= a.R * a.H * nt) return;
-    const int rh = task / nt, n0 = (task - rh * nt) * 32, n = n0 + col;
-    const bf16_t* src = which == 0 ? a.q : (which == 1 ? a.k : a.v);
-    bf16_t* dst = which == 0 ? a.qT : (which == 1 ? a.kT : a.vT);
-    // lane (n, hf) takes channels 8 hf + 16 s .. + 7 of position n
-#pragma unroll
-    for (int s = 0; s < (D + 15) / 16; ++s) {
-        const int e0 = 16 * s + 8 * hf;
-        if (e0 < D) {
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (n < a.L) v = *reinterpret_cast<const uint4*>(src + ((size_t)rh * a.L + n) * D + e0);
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                dst[((size_t)rh * D + e0 + 2 * i) * a.Lp + n] = (bf16_t)(w[i] & 0xffffu);
-                dst[((size_t)rh * D + e0 + 2 * i + 1) * a.Lp + n] = (bf16_t)(w[i] >> 16);
-            }
-        }
+        *reinterpret_cast<float4*>(ta + 256 * g) = make_float4(va[0], va[1], va[2], va[3]);
+        *reinterpret_cast<float4*>(tk + 256 * g) = make_float4(vk[0], vk[1], vk[2], vk[3]);
     }
 }
 
@@ -188,7 +143,7 @@ __device__ __forceinline__ f32x16 zero16() {
 // The logits enter the matrix core's accumulator already holding what is added to q.k: S = (q.k + B) * scale with
 // B[i][j] = bias[h][i][j] * sqrt(d) for a key that may be attended to and -inf for one that is masked or beyond L
 // (exp2 of the base-2 logit then gives weight 0 without any select).  The bias part comes from the copies that
-// k_bwd_transpose leaves in the order of the accumulator registers (four 16-byte loads per lane and tile, a
+// k_bwd_prepare leaves in the order of the accumulator registers (four 16-byte loads per lane and tile, a
 // contiguous KiB per instruction; bias_tile_fetch can run tiles ahead).  The -inf part is one more matrix
 // instruction: a contraction step whose key side holds 0 or -inf in its first slot and whose query side a one.
 __device__ __forceinline__ void bias_tile_fetch(float4 (&rows)[4], const float* tiles, int h, int nt, int it, int jt, int lane) {
@@ -216,57 +171,45 @@ __device__ __forceinline__ Frag one_side(int hf) {
 
 // ====================================================================================
 // Staging of a 32-position tile of one (row, head) for the four wavefronts of a block, which all contract with it:
-// the row-major tile of two tensors (x, y: [32][D]), their position-contiguous tiles (xT, yT: [D][32]) and two
-// float vectors of the 32 positions.  The block copies 16-byte pieces global -> registers -> LDS, one tile ahead
-// of the tile being worked on (two LDS stages, one barrier per tile); a wavefront reads its operand fragments
-// from LDS just before the matrix instructions that use them.
+// the row-major tile of two tensors (x, y: [32][D]) and two float vectors of the 32 positions.  The block copies 16-byte
+// pieces global -> registers -> LDS, one tile ahead of the tile being worked on (two LDS stages, one barrier per tile); a
+// wavefront reads its operand fragments from LDS just before the matrix instructions that use them.
 constexpr int kStPitch = 80;                          // bytes per staged row: 32 bf16 + 16 bytes, 16-byte aligned
-constexpr int kStRowsX = 0, kStRowsY = 32 * kStPitch, kStColsX = 64 * kStPitch, kStColsY = 96 * kStPitch;
-constexpr int kStVecA = 128 * kStPitch, kStVecB = kStVecA + 128, kStSpare = kStVecB + 128, kStBytes = kStSpare + 16;
+constexpr int kStRowsX = 0, kStRowsY = 32 * kStPitch;
+constexpr int kStVecA = 64 * kStPitch, kStVecB = kStVecA + 128, kStSpare = kStVecB + 128, kStBytes = kStSpare + 16;
 
 struct TileSrc {
-    const bf16_t *x, *y;         // [L][D] of the (row, head), or NULL (tile not needed: zeros)
-    const bf16_t *xT, *yT;       // [D][Lp] of the (row, head), or NULL
+    const bf16_t *x, *y;         // [L][D] of the (row, head)
     const float *va, *vb;        // [Lp] of the (row, head), or NULL
     int L, Lp;
 };
 
-// A thread moves up to three 16-byte pieces of every tile.  Which pieces, where they come from and where they go in the
+// A thread moves up to two 16-byte pieces of every tile.  Which pieces, where they come from and where they go in the
 // stage does not depend on the tile, so it is worked out once (StagePlan::init): per piece the address for tile
-// position 0, the bytes per position and the offset in the stage.  A piece nobody needs (its tensor is NULL, or the
-// thread has no third piece) asks for the start of x again and lands in a spare slot of the stage: every load and
+// position 0, the bytes per position and the offset in the stage.  A piece nobody needs (its vector is NULL, or the
+// thread has no second piece) asks for the start of x again and lands in a spare slot of the stage: every load and
 // every store of the loop is unconditional.
 template <int D, bool FULL>
 struct StagePlan {
-    const unsigned char *b0, *b1, *b2;     // piece address at tile position 0
-    int s0, s1, s2;                        // bytes per position
-    int d0, d1, d2;                        // offset in the stage
-    int n0_, n1_, n2_;                     // !FULL: position of a row piece within the tile (zeros beyond L), else a large negative number
+    const unsigned char *b0, *b1;          // piece address at tile position 0
+    int s0, s1;                            // bytes per position
+    int d0, d1;                            // offset in the stage
+    int n0_, n1_;                          // !FULL: position of a row piece within the tile (zeros beyond L), else a large negative number
 
     static __device__ __forceinline__ void piece(const TileSrc& t, int id, const unsigned char*& base, int& stride, int& dst, int& row) {
-        constexpr int PR = D / 8, NR = 32 * PR, NC = 4 * D, N = 2 * NR + 2 * NC + 16;
+        constexpr int PR = D / 8, NR = 32 * PR, N = 2 * NR + 16;
+        static_assert(N <= 512, "two pieces per thread");
         base = reinterpret_cast<const unsigned char*>(t.x); stride = 0; dst = kStSpare; row = -(1 << 30);
         if (id >= N) return;
         if (id < 2 * NR) {
             const bool second = id >= NR;
             const int k = second ? id - NR : id, n = k / PR, pc = k - n * PR;
             const bf16_t* src = second ? t.y : t.x;
-            if (!src) return;
             base = reinterpret_cast<const unsigned char*>(src + (size_t)n * D + 8 * pc); stride = 2 * D;
             dst = (second ? kStRowsY : kStRowsX) + n * kStPitch + pc * 16; row = n;
             return;
         }
         id -= 2 * NR;
-        if (id < 2 * NC) {
-            const bool second = id >= NC;
-            const int k = second ? id - NC : id, e = k >> 2, pc = k & 3;
-            const bf16_t* src = second ? t.yT : t.xT;
-            if (!src) return;
-            base = reinterpret_cast<const unsigned char*>(src + (size_t)e * t.Lp + 8 * pc); stride = 2;
-            dst = (second ? kStColsY : kStColsX) + e * kStPitch + pc * 16;
-            return;
-        }
-        id -= 2 * NC;
         const bool second = id >= 8;
         const int pc = second ? id - 8 : id;
         const float* src = second ? t.vb : t.va;
@@ -277,28 +220,25 @@ struct StagePlan {
     __device__ __forceinline__ void init(const TileSrc& t, int tid) {
         piece(t, tid, b0, s0, d0, n0_);
         piece(t, tid + 256, b1, s1, d1, n1_);
-        piece(t, tid + 512, b2, s2, d2, n2_);
     }
-    // the pieces of the tile at position n: requested from memory ...
-    __device__ __forceinline__ void fetch(int n, uint4& r0, uint4& r1, uint4& r2) const {
-        r0 = *reinterpret_cast<const uint4*>(b0 + (size_t)n * s0);
-        r1 = *reinterpret_cast<const uint4*>(b1 + (size_t)n * s1);
-        r2 = *reinterpret_cast<const uint4*>(b2 + (size_t)n * s2);
+    // the pieces of the tile at position n: requested from memory (rows at positions >= L: the last one again) ...
+    __device__ __forceinline__ void fetch(int n, int L, uint4& r0, uint4& r1) const {
+        const int m0 = FULL || n < L - n0_ ? n : L - 1 - n0_, m1 = FULL || n < L - n1_ ? n : L - 1 - n1_;
+        r0 = *reinterpret_cast<const uint4*>(b0 + (int64_t)m0 * s0);
+        r1 = *reinterpret_cast<const uint4*>(b1 + (int64_t)m1 * s1);
     }
     // ... and put into the stage (L: rows at positions n + row >= L are zeros)
-    __device__ __forceinline__ void store(unsigned char* stage, int n, int L, uint4 r0, uint4 r1, uint4 r2) const {
+    __device__ __forceinline__ void store(unsigned char* stage, int n, int L, uint4 r0, uint4 r1) const {
         const uint4 z = make_uint4(0, 0, 0, 0);
         if (!FULL) {
             if (n + n0_ >= L) r0 = z;
             if (n + n1_ >= L) r1 = z;
-            if (n + n2_ >= L) r2 = z;
         }
         *reinterpret_cast<uint4*>(stage + d0) = r0;
         *reinterpret_cast<uint4*>(stage + d1) = r1;
-        *reinterpret_cast<uint4*>(stage + d2) = r2;
     }
 };
-// operand fragments out of a stage: rows of the lane's position (as load_rows), channels of the lane (as load_cols)
+// operand fragments out of a stage: rows of the lane's position (as load_rows), channels of the lane (below)
 template <int D>
 __device__ __forceinline__ void staged_rows(Frag (&f)[(D + 15) / 16], const unsigned char* rows, int col, int hf) {
 #pragma unroll
@@ -307,16 +247,20 @@ __device__ __forceinline__ void staged_rows(Frag (&f)[(D + 15) / 16], const unsi
         if (16 * s + 8 * hf < D) f[s].u = *reinterpret_cast<const uint4*>(rows + col * kStPitch + (16 * s + 8 * hf) * 2);
     }
 }
-template <int D>
-__device__ __forceinline__ void staged_cols(Frag (&f)[2], const unsigned char* cols, int col, int hf) {
+// Lane (e, hf) gets x[n][e] for the eight positions that slot u = 0..7 of half hf of contraction step s meets, n = 16 s + 4 hf +
+// (u < 4 ? u : u + 4): the order in which a 32 x 32 accumulator (register 8s + u of half hf) leaves its rows.  Two
+// transposing 8-byte reads per step: of sixteen lanes, lane i asks for four channels 4 (i % 4) .. of position i / 4, and lane l
+// receives channel l of the four positions.  Lanes of channels beyond D receive what the rows' padding holds; it reaches only rows
+// of the result that nobody stores.
+typedef __attribute__((__vector_size__(4 * sizeof(short)))) short i16x4;
+typedef __attribute__((address_space(3))) i16x4* lds_i16x4;
+__device__ __forceinline__ void staged_cols(Frag (&f)[2], const unsigned char* rows, int lane) {
+    const unsigned char* p = rows + (4 * (lane >> 5) + ((lane >> 2) & 3)) * kStPitch + ((lane & 16) + 4 * (lane & 3)) * 2;
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-        f[s].u = make_uint4(0, 0, 0, 0);
-        if (col < D) {
-            const unsigned char* p = cols + col * kStPitch + (16 * s + 4 * hf) * 2;
-            const uint2 lo = *reinterpret_cast<const uint2*>(p), hi = *reinterpret_cast<const uint2*>(p + 16);
-            f[s].u = make_uint4(lo.x, lo.y, hi.x, hi.y);
-        }
+        const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4)(p + 16 * s * kStPitch)));
+        const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4)(p + (16 * s + 8) * kStPitch)));
+        f[s].u = make_uint4(lo.x, lo.y, hi.x, hi.y);
     }
 }
 
@@ -329,15 +273,15 @@ __device__ __forceinline__ void staged_cols(Frag (&f)[2], const unsigned char* c
 // tiles between a request to memory and its use (1 or 2)
 constexpr int kAhead = 1;
 #define FF_BWD_Q_PROLOGUE                                                                                        \
-    uint4 rs[2][3];                                                                                              \
+    uint4 rs[2][2];                                                                                              \
     float4 brow[2][4];                                                                                           \
     float mk[2] = {1.f, 1.f};                                                                                    \
     const int i0a = active ? i0 : 0;                                                                             \
     const float* mrow = a.mrow + (size_t)r * a.mstride;                                                          \
     {                                                                                                            \
         const int n1 = 32 < a.L ? 32 : 0;         /* (a single tile: fetched twice, the second copy unused) */   \
-        plan.fetch(0, rs[0][0], rs[0][1], rs[0][2]);                                         \
-        if (kAhead == 2) plan.fetch(n1, rs[1][0], rs[1][1], rs[1][2]);                       \
+        plan.fetch(0, a.L, rs[0][0], rs[0][1]);                                         \
+        if (kAhead == 2) plan.fetch(n1, a.L, rs[1][0], rs[1][1]);                       \
         if (BIAS) {                                                                                              \
             bias_tile_fetch(brow[0], a.biasA, h, nt, i0a >> 5, 0, lane);                                         \
             if (kAhead == 2) bias_tile_fetch(brow[1], a.biasA, h, nt, i0a >> 5, n1 >> 5, lane);                  \
@@ -345,7 +289,7 @@ constexpr int kAhead = 1;
         if (FULL || col < a.L) mk[0] = mrow[col];                                                                \
         if (kAhead == 2 && (FULL || n1 + col < a.L)) mk[1] = mrow[n1 + col];                                     \
     }                                                                                                            \
-    plan.store(s_stage, 0, a.L, rs[0][0], rs[0][1], rs[0][2]);                                    \
+    plan.store(s_stage, 0, a.L, rs[0][0], rs[0][1]);                                    \
     __syncthreads();
 // (bt and kx: what the accumulator of the logits starts from, see bias_tile_fetch.  Every load of the loop is issued on
 // every path - the last two tiles ask for themselves again - because a load under a condition makes the compiler
@@ -355,7 +299,7 @@ constexpr int kAhead = 1;
     const unsigned char* stage = s_stage + (P) * kStBytes;                                                       \
     constexpr int PF = kAhead == 2 ? (P) : 1 - (P);       /* the register set that receives what is requested now */ \
     const int jn = j0 + 32 * kAhead < a.L ? j0 + 32 * kAhead : j0;                                               \
-    plan.fetch(jn, rs[PF][0], rs[PF][1], rs[PF][2]);                                         \
+    plan.fetch(jn, a.L, rs[PF][0], rs[PF][1]);                                         \
     const Frag kx = key_side((FULL || j0 + col < a.L) && mk[P] != 0.f, hf);                                      \
     f32x16 bt;                                                                                                   \
     if (BIAS) rows_to_acc(bt, brow[P]);                                                                          \
@@ -364,11 +308,11 @@ constexpr int kAhead = 1;
     if (FULL || jn + col < a.L) mk[PF] = mrow[jn + col];
 #define FF_BWD_Q_TAIL(P)                                                                                         \
     if (j0 + 32 < a.L)                                                                                           \
-        plan.store(s_stage + (1 - (P)) * kStBytes, j0 + 32, a.L, rs[1 - (P)][0], rs[1 - (P)][1], rs[1 - (P)][2]); \
+        plan.store(s_stage + (1 - (P)) * kStBytes, j0 + 32, a.L, rs[1 - (P)][0], rs[1 - (P)][1]); \
     __syncthreads();
 
 // ====================================================================================
-// Block = four consecutive query tiles of one (row, head); the key-side tiles (k rows, v position-contiguous) are
+// Block = four consecutive query tiles of one (row, head); the key-side tiles (k and v rows) are
 // staged once per block and key tile; the bias rows and the key-mask entries of the next tile are requested
 // while this one is worked on.
 template <int D, bool FULL, bool BIAS>
@@ -383,7 +327,7 @@ __global__ __launch_bounds__(256) void k_bwd_stats(Args a) {
     const bool active = it < nt;
     const size_t base = (size_t)rh * a.L * D;
     TileSrc src;
-    src.x = a.k + base; src.y = nullptr; src.xT = nullptr; src.yT = a.vT + (size_t)rh * D * a.Lp;
+    src.x = a.k + base; src.y = a.v + base;
     src.va = nullptr; src.vb = nullptr; src.L = a.L; src.Lp = a.Lp;
     Frag qf[KS];
     load_rows<D, FULL>(qf, a.q + base, active ? i0 : 0, a.L, col, hf);
@@ -402,7 +346,7 @@ __global__ __launch_bounds__(256) void k_bwd_stats(Args a) {
         if (active) {                                                                                            \
             Frag kf[KS], vt[2], pf[2];                                                                           \
             staged_rows<D>(kf, stage + kStRowsX, col, hf);                                                       \
-            staged_cols<D>(vt, stage + kStColsY, col, hf);                                                       \
+            staged_cols(vt, stage + kStRowsY, lane);                                                             \
             f32x16 s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kx.v, one.v, bt, 0, 0, 0);                        \
             _Pragma("unroll") for (int t = 0; t < KS; ++t)                                                       \
                 s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t].v, qf[t].v, s, 0, 0, 0);                       \
@@ -444,13 +388,6 @@ __global__ __launch_bounds__(256) void k_bwd_stats(Args a) {
     const float lse = l_tot > 0.f ? m + __builtin_amdgcn_logf(l_tot) : INFINITY;
 
     float dl = 0.f;
-    if (i >= a.L) {         // pad queries: zeros in the position-contiguous copy of dctx
-#pragma unroll
-        for (int gq = 0; gq < 4; ++gq)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (8 * gq + 4 * hf + e < D) a.dctxT[((size_t)rh * D + 8 * gq + 4 * hf + e) * a.Lp + i] = 0;
-    }
     if (i < a.L) {
 #pragma unroll
         for (int gq = 0; gq < 4; ++gq) {
@@ -472,9 +409,6 @@ __global__ __launch_bounds__(256) void k_bwd_stats(Args a) {
                 }
                 *reinterpret_cast<uint2*>(a.dg + off) = make_uint2(pack2(dgv[0], dgv[1]), pack2(dgv[2], dgv[3]));
                 *reinterpret_cast<uint2*>(a.dctx + off) = make_uint2(pack2(dc[0], dc[1]), pack2(dc[2], dc[3]));
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    a.dctxT[((size_t)rh * D + e0 + e) * a.Lp + i] = (bf16_t)(pack2(dc[e], 0.f) & 0xffffu);
             }
         }
     }
@@ -486,7 +420,7 @@ __global__ __launch_bounds__(256) void k_bwd_stats(Args a) {
 }
 
 // ====================================================================================
-// Block = four consecutive query tiles of one (row, head); staged per key tile: k rows, v rows, k position-contiguous.
+// Block = four consecutive query tiles of one (row, head); staged per key tile: k rows and v rows.
 template <int D, bool FULL, bool BIAS>
 __global__ __launch_bounds__(256, 3) void k_bwd_dq(Args a) {
     constexpr int KS = (D + 15) / 16;
@@ -499,7 +433,7 @@ __global__ __launch_bounds__(256, 3) void k_bwd_dq(Args a) {
     const bool active = it < nt;
     const size_t base = (size_t)rh * a.L * D;
     TileSrc src;
-    src.x = a.k + base; src.y = a.v + base; src.xT = a.kT + (size_t)rh * D * a.Lp; src.yT = nullptr;
+    src.x = a.k + base; src.y = a.v + base;
     src.va = nullptr; src.vb = nullptr; src.L = a.L; src.Lp = a.Lp;
     Frag qf[KS], dcf[KS];
     load_rows<D, FULL>(qf, a.q + base, active ? i0 : 0, a.L, col, hf);
@@ -527,7 +461,7 @@ __global__ __launch_bounds__(256, 3) void k_bwd_dq(Args a) {
                 s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t].v, qf[t].v, s, 0, 0, 0);                       \
                 dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t].v, dcf[t].v, dp, 0, 0, 0);                    \
             }                                                                                                    \
-            staged_cols<D>(kt, stage + kStColsX, col, hf);                                                       \
+            staged_cols(kt, stage + kStRowsX, lane);                                                             \
             _Pragma("unroll") for (int v = 0; v < 16; ++v)                                                       \
                 s[v] = __builtin_amdgcn_exp2f(s[v] * a.qscale2 - lse) * dp[v];                                   \
             pack_rows(dsf, s);                                                                                   \
@@ -554,8 +488,8 @@ __global__ __launch_bounds__(256, 3) void k_bwd_dq(Args a) {
 }
 
 // ====================================================================================
-// Block = four consecutive key tiles of one (row, head); the query-side tiles (q, dctx, their position-contiguous
-// copies, logsumexp, delta) are staged once per block and query tile.
+// Block = four consecutive key tiles of one (row, head); the query-side tiles (q, dctx, logsumexp,
+// delta) are staged once per block and query tile.
 // (three wavefronts per SIMD where the lengths are whole tiles: at d = 32 with a bias that costs four spilled
 // registers, all outside the tile loop; in the variant with bounds checks one of them would land inside it, and a
 // reload inside the loop is waited for together with every load in flight)
@@ -572,7 +506,6 @@ __global__ __launch_bounds__(256, FULL ? 3 : 1) void k_bwd_dkv(Args a) {
     const size_t base = (size_t)rh * a.L * D;
     TileSrc src;
     src.x = a.q + base; src.y = a.dctx + base;
-    src.xT = a.qT + (size_t)rh * D * a.Lp; src.yT = a.dctxT + (size_t)rh * D * a.Lp;
     src.va = a.lse + (size_t)rh * a.Lp; src.vb = a.delta + (size_t)rh * a.Lp;
     src.L = a.L; src.Lp = a.Lp;
 
@@ -586,19 +519,19 @@ __global__ __launch_bounds__(256, FULL ? 3 : 1) void k_bwd_dkv(Args a) {
     const Frag kx = key_side(key_ok, hf), one = one_side(hf);
     const int jta = active ? jt : 0;
     float4 brow[2][4];
-    uint4 rs[2][3];
+    uint4 rs[2][2];
     StagePlan<D, FULL> plan;
     plan.init(src, tid);
     {
         const int n1 = 32 < a.L ? 32 : 0;
-        plan.fetch(0, rs[0][0], rs[0][1], rs[0][2]);
-        if (kAhead == 2) plan.fetch(n1, rs[1][0], rs[1][1], rs[1][2]);
+        plan.fetch(0, a.L, rs[0][0], rs[0][1]);
+        if (kAhead == 2) plan.fetch(n1, a.L, rs[1][0], rs[1][1]);
         if (BIAS) {
             bias_tile_fetch(brow[0], a.biasK, h, nt, 0, jta, lane);
             if (kAhead == 2) bias_tile_fetch(brow[1], a.biasK, h, nt, n1 >> 5, jta, lane);
         }
     }
-    plan.store(s_stage, 0, a.L, rs[0][0], rs[0][1], rs[0][2]);
+    plan.store(s_stage, 0, a.L, rs[0][0], rs[0][1]);
     __syncthreads();
 
     f32x16 dk = zero16(), dv = zero16();     // dk^T, dv^T: lane = key, register = channel
@@ -608,7 +541,7 @@ __global__ __launch_bounds__(256, FULL ? 3 : 1) void k_bwd_dkv(Args a) {
         const unsigned char* stage = s_stage + (P) * kStBytes;                                                   \
         constexpr int PF = kAhead == 2 ? (P) : 1 - (P);                                                          \
         const int in = i0 + 32 * kAhead < a.L ? i0 + 32 * kAhead : i0;    /* (the last tiles ask for themselves again) */ \
-        plan.fetch(in, rs[PF][0], rs[PF][1], rs[PF][2]);                                     \
+        plan.fetch(in, a.L, rs[PF][0], rs[PF][1]);                                     \
         f32x16 s;                                                                                                \
         if (BIAS) {                                                                                              \
             rows_to_acc(s, brow[P]);                                                                             \
@@ -630,8 +563,8 @@ __global__ __launch_bounds__(256, FULL ? 3 : 1) void k_bwd_dkv(Args a) {
                 s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[t].v, kf[t].v, s, 0, 0, 0);                       \
                 dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dcf[t].v, vf[t].v, dp, 0, 0, 0);                    \
             }                                                                                                    \
-            staged_cols<D>(qt, stage + kStColsX, col, hf);                                                       \
-            staged_cols<D>(dct, stage + kStColsY, col, hf);                                                      \
+            staged_cols(qt, stage + kStRowsX, lane);                                                             \
+            staged_cols(dct, stage + kStRowsY, lane);                                                            \
             _Pragma("unroll") for (int gq = 0; gq < 4; ++gq) {                                                   \
                 const float4 l4 = *reinterpret_cast<const float4*>(stage + kStVecA + (8 * gq + 4 * hf) * 4);     \
                 const float ls[4] = {l4.x, l4.y, l4.z, l4.w};                                                    \
@@ -652,7 +585,7 @@ __global__ __launch_bounds__(256, FULL ? 3 : 1) void k_bwd_dkv(Args a) {
             }                                                                                                    \
         }                                                                                                        \
         if (i0 + 32 < a.L)                                                                                       \
-            plan.store(s_stage + (1 - (P)) * kStBytes, i0 + 32, a.L, rs[1 - (P)][0], rs[1 - (P)][1], rs[1 - (P)][2]); \
+            plan.store(s_stage + (1 - (P)) * kStBytes, i0 + 32, a.L, rs[1 - (P)][0], rs[1 - (P)][1]); \
         __syncthreads();                                                                                         \
     }
     for (int tt = 0; 32 * tt < a.L; tt += 2) {
@@ -859,7 +792,7 @@ size_t core_backward_workspace(const ff_core_desc& d) {
     const size_t Lp = bwd::round_up(d.length, 32), rh = (size_t)d.rows * d.heads;
     const int chunks = dbias_chunks(d);
     return bwd::align256(Lp * 4) + 2 * bwd::align256(rh * Lp * 4) + bwd::align256(rh * d.length * d.head_dim * 2) +
-           4 * bwd::align256(rh * d.head_dim * Lp * 2) + 2 * bwd::align256((size_t)d.heads * Lp * Lp * 4) +
+           2 * bwd::align256((size_t)d.heads * Lp * Lp * 4) +
            (chunks > 1 ? bwd::align256((size_t)chunks * d.heads * d.length * d.length * 4) : 0);
 }
 
@@ -879,11 +812,6 @@ ff_status core_backward_run(const ff_core_desc& d, const void* q, const void* k,
     a.lse = (float*)p; p += align256(rh * a.Lp * 4);
     a.delta = (float*)p; p += align256(rh * a.Lp * 4);
     a.dctx = (bf16_t*)p; p += align256(rh * d.length * d.head_dim * 2);
-    const size_t tbytes = align256(rh * d.head_dim * a.Lp * 2);
-    a.qT = (bf16_t*)p; p += tbytes;
-    a.kT = (bf16_t*)p; p += tbytes;
-    a.vT = (bf16_t*)p; p += tbytes;
-    a.dctxT = (bf16_t*)p; p += tbytes;
     const size_t bbytes = align256((size_t)d.heads * a.Lp * a.Lp * 4);
     a.biasA = (float*)p; p += bbytes;
     a.biasK = (float*)p; p += bbytes;
@@ -897,7 +825,7 @@ ff_status core_backward_run(const ff_core_desc& d, const void* q, const void* k,
     a.scale = 1.f / sqrtf((float)d.head_dim);
     a.sqrt_d = sqrtf((float)d.head_dim);
     const int nt = a.Lp / 32;
-    const dim3 g1((unsigned)((rh * nt + 3) / 4)), g2((unsigned)((size_t)a.row_chunks * d.heads * ((nt + 3) / 4) * ((nt + 3) / 4)));
+    const dim3 g2((unsigned)((size_t)a.row_chunks * d.heads * ((nt + 3) / 4) * ((nt + 3) / 4)));
     const bool full = d.length % 32 == 0;        // nothing out of range: the kernels without bounds checks
 #define FF_BWD_D(KERNEL, GRID, DV)                                                                       \
     do {                                                                                                 \
@@ -913,13 +841,10 @@ ff_status core_backward_run(const ff_core_desc& d, const void* q, const void* k,
         else if (d.head_dim == 16) FF_BWD_D(KERNEL, GRID, 16);                                           \
         else FF_BWD_D(KERNEL, GRID, 32);                                                                 \
     } while (0)
-    const unsigned bias_blocks = (unsigned)(((size_t)d.heads * nt * nt + 3) / 4);
-    const dim3 gt(bias && bias_blocks > g1.x ? bias_blocks : g1.x, bias ? 4 : 3);      // q, k, v; the bias tiles
-    {
+    if (bias || !mask) {
         Timed t(KK_BWD_STATS, st);
-        if (d.head_dim == 8) hipLaunchKernelGGL((k_bwd_transpose<8>), gt, dim3(256), 0, st, a);
-        else if (d.head_dim == 16) hipLaunchKernelGGL((k_bwd_transpose<16>), gt, dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((k_bwd_transpose<32>), gt, dim3(256), 0, st, a);
+        const unsigned blocks = bias ? (unsigned)(((size_t)d.heads * nt * nt + 3) / 4) : 1u;
+        hipLaunchKernelGGL(k_bwd_prepare, dim3(blocks), dim3(256), 0, st, a);
     }
     const dim3 g4((unsigned)(rh * ((nt + 3) / 4)));          // blocks of four tiles of one (row, head)
     FF_BWD(k_bwd_stats, g4, KK_BWD_STATS);
