@@ -258,6 +258,15 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, HAS_BIAS)) void k_attn_
     const uint32_t v_moves = v_row ? 0xffffffffu : 0u;
     auto lds16 = [&](uint32_t off) __attribute__((always_inline)) { return *reinterpret_cast<const uint4*>(smem + off); };
 
+    // Steps before the first one that holds a masked (or missing) key have a loop of their own without the mask tests; steps behind the
+    // last one that holds a valid key are left out (and the content of padding there is irrelevant).
+    int n_plain = nt, n_live = 0;
+    for (int i = 0; i < nt * NR; i += 64) {
+        const uint32_t w = i + lane < nt * NR ? s_live[i + lane] : 0u;
+        const uint64_t part = __ballot(i + lane < nt * NR && w != 0xffffffffu), some = __ballot(w != 0u);
+        if (part && n_plain == nt) n_plain = (i + (int)__builtin_ctzll(part)) / NR;
+        if (some) n_live = (i + 63 - (int)__builtin_clzll(some)) / NR + 1;
+    }
     // publishes what set out a step ago and sends the next step on its way (the ring slot it fills was last read before
     // the barrier)
     auto turn = [&](int kt) __attribute__((always_inline)) {
@@ -265,10 +274,10 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, HAS_BIAS)) void k_attn_
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        if (kt + 3 < nt) stage(kt + 3);
+        if (kt + 3 < n_live) stage(kt + 3);
     };
     if (!active) {                                            // (no queries: only the share of the loads)
-        for (int kt = 0; kt < nt; ++kt) turn(kt);
+        for (int kt = 0; kt < n_live; ++kt) turn(kt);
         return;
     }
 
@@ -370,12 +379,6 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, HAS_BIAS)) void k_attn_
         kf[1][s].u = lds16(k_at(1) + (rd_k ^ (32u * s)));
     }
     s_acc[0] = mask_step(live_c[0], kperm, hf, s_acc[0]);
-    // Steps before the first one that holds a masked (or missing) key have a loop of their own without the mask tests.
-    int n_plain = nt;
-    for (int i = 0; i < nt * NR && n_plain == nt; i += 64) {
-        const uint64_t part = __ballot(i + lane < nt * NR && s_live[i + lane] != 0xffffffffu);
-        if (part) n_plain = (i + (int)__builtin_ctzll(part)) / NR;
-    }
     int kt = 0;
     using std::integral_constant;
     for (; kt + 2 < n_plain; kt += 2) {                       // (a step also forms the first scores of the next one)
@@ -385,11 +388,11 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, HAS_BIAS)) void k_attn_
     fetch_live(kt, live_c);
 #pragma unroll
     for (int j = 0; j < NR; ++j) live_c[j] = __builtin_amdgcn_readfirstlane(live_c[j]);
-    for (; kt + 1 < nt; kt += 2) {
+    for (; kt + 1 < n_live; kt += 2) {
         step(integral_constant<bool, false>{}, kt, bias_a, bias_b);
         step(integral_constant<bool, false>{}, kt + 1, bias_b, bias_a);
     }
-    if (kt < nt) step(integral_constant<bool, false>{}, kt, bias_a, bias_b);
+    if (kt < n_live) step(integral_constant<bool, false>{}, kt, bias_a, bias_b);
     o_acc[NR - 1] = mfma(vf[1][0].v, pf[0].v, o_acc[NR - 1]);
     o_acc[NR - 1] = mfma(vf[1][1].v, pf[1].v, o_acc[NR - 1]);
     if constexpr (!ONES) {

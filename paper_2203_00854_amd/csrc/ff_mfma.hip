@@ -1190,7 +1190,9 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
             // permuted key of S^T row m = col: rows 8g + 4b + e hold key 16*(g/2) + 8b + 4*(g%2) + e, so that the lane's registers 8c .. 8c+7 hold
             // the keys 16c + 8hf .. + 7 of the tile
             const int kperm_a = 16 * (col_a >> 4) + 8 * ((col_a >> 2) & 1) + 4 * ((col_a >> 3) & 1) + (col_a & 3);
-            const int nk = (a.L + 31) >> 5;                   // key tiles that hold keys
+            int nk = 1;                                       // key tiles up to the last one with a valid key in either row
+            for (int t = 1; t < nt; ++t)
+                if (__builtin_amdgcn_readfirstlane(s_live[t] | s_live[8 + t]) != 0) nk = t + 1;
             f32x16 o_acc[2], s_acc[2];
             float l_run[2];
 #pragma unroll

@@ -69,3 +69,21 @@ def test_logits_far_from_zero(n_a, n_b, d):
         wb[h] += shift / 64.0
     case.weights["w_b"] = I.to_storage(wb, "bf16")
     check(case, run(case), f"{n_a} x {n_b}, d {d}")
+
+
+@pytest.mark.parametrize("n_a,n_b,d,live", [(6, 160, 8, 64), (6, 160, 16, 96), (5, 128, 32, 32), (9, 320, 32, 288), (4, 256, 32, 192)])
+def test_content_of_masked_tail_tiles_is_irrelevant(n_a, n_b, d, live):
+    """NaN tokens in the last key tiles of 32, which hold no valid key in any row, and in a whole masked row: the other tokens'
+    results are those of finite tokens there, bit for bit."""
+    case = I.make_case(small_spec(ROW, n_a, n_b, 64, 4, d, c_z=16, dtype="bf16"))
+    case.mask = np.ones((n_a, n_b), np.float32)
+    case.mask[:, live:] = 0.0
+    case.mask[3, :] = 0.0
+    desc, w, x, z, mask = P.to_device(case, DEV)
+    a = P.ff_gated_attention(desc, w, x, z, mask)
+    x2 = x.clone()
+    x2[mask == 0] = float("nan")
+    b = P.ff_gated_attention(desc, w, x2, z, mask)
+    torch.cuda.synchronize()
+    assert P.ff_attention_last_path() == "mfma_bf16"
+    assert torch.isfinite(a).all() and torch.equal(a[mask != 0], b[mask != 0])
