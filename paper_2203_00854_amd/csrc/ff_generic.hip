@@ -456,6 +456,7 @@ __global__ __launch_bounds__(512) void k_attn_generic(GenericAttnArgs a) {
 #pragma unroll
     for (int i = 0; i < DG; ++i) qf[i] = load4<T, VEC>(base + (size_t)qc * N4, 8 * i + 4 * hf, a.d);
     const float* brow = a.bias ? a.bias + ((size_t)h * a.L + qc) * a.Lb : nullptr;
+    const float* mask_row = a.mask ? a.mask + (int64_t)(a.r0 + rl) * a.sr : nullptr;
     f32x16 acc[NE];
 #pragma unroll
     for (int n = 0; n < NE; ++n)
@@ -472,15 +473,17 @@ __global__ __launch_bounds__(512) void k_attn_generic(GenericAttnArgs a) {
             float4 kv = make_float4(0.f, 0.f, 0.f, 0.f), vv = kv;
             if (k < nk) {
                 const T* row = base + (size_t)(c0 + k) * N4;
+                const float mk = mask_row ? mask_row[(int64_t)(c0 + k) * a.sl] : 1.f;
                 kv = load4<T, VEC>(row + Hd, e, a.d);
                 vv = load4<T, VEC>(row + 2 * Hd, e, a.d);
+                vv = keep4(mk != 0.f, vv);           // (what a masked token holds may be anything, and 0 x NaN is NaN)
             }
             *reinterpret_cast<float4*>(s_k + k * KP + e) = kv;
             *reinterpret_cast<float4*>(s_v + k * DP + e) = vv;
         }
         for (int k = tid; k < nkp; k += nthreads) {
             bool ok = k < nk;
-            if (ok && a.mask) ok = a.mask[(int64_t)(a.r0 + rl) * a.sr + (int64_t)(c0 + k) * a.sl] != 0.f;
+            if (ok && mask_row) ok = mask_row[(int64_t)(c0 + k) * a.sl] != 0.f;
             s_m[k] = ok ? 0.f : -INFINITY;
         }
         __syncthreads();

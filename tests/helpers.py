@@ -29,3 +29,39 @@ def rel_l2(a, b):
     a = np.asarray(a, np.float64)
     b = np.asarray(b, np.float64)
     return float(np.linalg.norm(a - b) / max(np.linalg.norm(b), 1e-300))
+
+
+def patchy_mask(rows, length, seed=7):
+    """[rows, length] masks whose rows differ in where they have no valid key: a long tail, a long lead, a gap of whole tiles of
+    32, single keys at random, none at all, all but one key."""
+    rng = np.random.default_rng(seed)
+    m = np.ones((rows, length), np.float32)
+    for r in range(rows):
+        kind = r % 6
+        if kind == 0:
+            m[r, min(33, length - 1):] = 0.0
+        elif kind == 1:
+            m[r, :max(length - 40, 0)] = 0.0
+        elif kind == 2:
+            m[r, 31:min(97, length - 1)] = 0.0
+        elif kind == 3:
+            m[r] = rng.random(length) < 0.7
+        elif kind == 5:
+            m[r] = 0.0
+        if not m[r].any() or kind == 5:
+            m[r, length // 2] = 1.0
+    return m
+
+
+def poison_masked_tokens(case, mask):
+    """Sets the case's mask ([n_a, n_b]) and puts zeros into its masked tokens; returns x with NaN and infinities there instead
+    (storage type of the case)."""
+    case.mask = np.ascontiguousarray(mask, np.float32)
+    dead = case.mask == 0
+    case.x = case.x.copy()
+    case.x[dead] = 0
+    bad = case.x.copy()
+    n = int(dead.sum())
+    v = np.resize(np.array([np.nan, np.inf, -np.inf], np.float32), n)[:, None] * np.ones(case.x.shape[2], np.float32)
+    bad[dead] = I.to_storage(v, case.spec.dtype)
+    return bad

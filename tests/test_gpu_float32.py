@@ -12,7 +12,7 @@ import torch
 import paper_2203_00854_amd as P
 from oracle import evoformer_attention as O
 from paper_2203_00854_amd import inputs as I
-from helpers import f64_inputs, max_abs, rel_l2, small_spec
+from helpers import f64_inputs, max_abs, patchy_mask, poison_masked_tokens, rel_l2, small_spec
 
 pytestmark = pytest.mark.gpu
 ROW, COL, TS, TE = I.MODE_ROW, I.MODE_COL, I.MODE_TRI_START, I.MODE_TRI_END
@@ -51,3 +51,26 @@ def test_edges(dtype, mode, n_a, n_b, c, c_z, heads, d, mask, chunk):
         assert ma <= 1e-4
     else:
         assert ma <= 2e-2 and rl <= 1e-2
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("mode,n_a,n_b,c,heads,d", [(ROW, 13, 70, 32, 2, 12), (COL, 290, 7, 30, 2, 40), (ROW, 6, 5, 20, 1, 5), (TE, 75, 75, 36, 2, 20)])
+def test_content_of_masked_tokens_is_irrelevant(dtype, mode, n_a, n_b, c, heads, d):
+    """NaN and infinities in masked tokens, whole tiles of keys and single ones: a masked key has weight exactly 0, so every other
+    token's result is that of a finite token there."""
+    case = I.make_case(small_spec(mode, n_a, n_b, c, heads, d, c_z=12, dtype=dtype))
+    if mode == TE:
+        keep = patchy_mask(4, n_a)[3]
+        mask = np.outer(keep, keep)
+    else:
+        mask = patchy_mask(n_a, n_b) if mode == ROW else patchy_mask(n_b, n_a).T
+    bad = poison_masked_tokens(case, mask)
+    xf, zf, mf, wf = f64_inputs(case)
+    ref = O.gated_attention(mode, xf, zf, mf, wf, heads, case.spec.ln_eps)
+    case.x = bad
+    desc, w, x, z, m = P.to_device(case, "cuda:0")
+    got = P.ff_gated_attention(desc, w, x, z, m).float().cpu().numpy().astype(np.float64)
+    assert P.ff_attention_last_path() == "generic"
+    live = case.mask != 0
+    assert np.isfinite(got[live]).all()
+    assert max_abs(got[live], ref[live]) <= (1e-4 if dtype == "f32" else 2e-2)
