@@ -12,8 +12,8 @@
 // against four 32 x 32 x 16 matrix instructions (32 each) and four 4 x 4 x 4 ones for the denominator, so nothing else is
 // left in the loop:
 //  - no reference is subtracted from the scores.  float32 and bfloat16 keep their relative precision over the whole
-//    exponent range, so exp2(s) / sum exp2(s) needs none while the sum stays in range; a row of a
-//    wavefront whose sum does not is done again with a running maximum (end of the kernel).
+//    exponent range, so exp2(s) / sum exp2(s) needs none while the sums stay in range; a row of a
+//    wavefront whose sums do not is done again with a running maximum (softmax_stands, end of the kernel).
 //  - the denominator is summed from the rounded weights by 4 x 4 x 4 matrix instructions: eight v_dot2 per tile do not overlap
 //    with matrix instructions (bare loops of the tile's mix, two wavefronts per SIMD: 123 ns with dots, 104 so, 93
 //    without any denominator).
@@ -28,45 +28,10 @@
 
 namespace ff {
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 typedef void __attribute__((address_space(3)))* lptr_t;
 
 namespace {
 
-union Frag {
-    bf16x8 v;
-    uint4 u;
-    uint32_t w[4];
-};
-
-__device__ __forceinline__ uint32_t pack2(float a, float b) {   // a -> low half (first element)
-    bf16x2 t;
-    t[0] = (__bf16)a;
-    t[1] = (__bf16)b;
-    return __builtin_bit_cast(uint32_t, t);
-}
-__device__ __forceinline__ float lo_f32(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float hi_f32(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
-// sum of the two bf16 halves of w, added to acc
-__device__ __forceinline__ float add_pair(uint32_t w, float acc) {
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), __builtin_bit_cast(bf16x2, 0x3f803f80u), acc,
-                                           false);
-}
-// value of the other half-wave's lane (l ^ 32)
-__device__ __forceinline__ float other_half(float v) {
-    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return (threadIdx.x & 32) ? __uint_as_float(r[0]) : __uint_as_float(r[1]);
-}
-// (see ff_mfma.hip) two 4-element groups that are adjacent in memory end up in one lane
-__device__ __forceinline__ void merge_halves(uint32_t& a, uint32_t& b) {
-    auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-    a = r[0];
-    b = r[1];
-}
-__device__ __forceinline__ uint4 ldg16(const void* base, uint32_t lane_bytes) {
-    return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(base) + lane_bytes);
-}
 // 16 bytes per lane from base + lane_bytes straight into LDS at lds_base + 16 * lane (base and lds_base uniform).
 // Assembly, because the compiler would make every later LDS read wait for a load it knows to write LDS; whoever
 // reads the data waits (vmcnt) and passes a barrier first.
@@ -76,8 +41,6 @@ __device__ __forceinline__ void load16_to_lds(const void* base, uint32_t lane_by
                  : "v"(lane_bytes), "s"(base), "s"(lds_base)
                  : "memory", "m0");
 }
-constexpr int kWaitVmcnt0 = 0x0F70;      // s_waitcnt vmcnt(0), the other counters untouched
-
 constexpr int kRing = 4;                 // steps in the LDS ring
 
 __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
@@ -436,8 +399,7 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, HAS_BIAS)) void k_attn_
         const float x = o[ONES ? D / 2 : 0], y = other_half(x);      // (row D: register D / 2 of the lower half-wave)
         return hf == 0 ? x : y;
     };
-    // A denominator outside [2^-60, 2^96] (some weights overflowed, or all of them are tiny, or NaN): the row is done
-    // again below with a running maximum.  0 is right where no key is attended to: redone as well, it costs nothing.
+    // rows that do not stand (softmax_stands) are done again below
     int again = 0;
     uint2 gate[NR][D / 8];
 #pragma unroll
@@ -445,9 +407,8 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, HAS_BIAS)) void k_attn_
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
         const float l_tot = denominator(o_acc[j], l_run[j]);
-        const bool fine = l_tot >= 0x1p-60f && l_tot <= 0x1p96f;
         if (rb * NR + j >= a.rows) continue;
-        if (__any(!fine && qi < a.L)) again |= 1 << j;
+        if (__any(!softmax_stands<D / 2>(o_acc[j], l_tot) && qi < a.L)) again |= 1 << j;
         else finish(o_acc[j], l_tot, row[j], gate[j]);
     }
     // ---- the general softmax, one row after the other, operands straight from memory
@@ -474,39 +435,18 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, HAS_BIAS)) void k_attn_
             Frag vs[2];
             const uint32_t kv = (uint32_t)(kperm * D + (D > 8 ? 8 * hf : 0)) * 2, ve = (uint32_t)((v_row ? col : 0) * 32 + 8 * hf) * 2;
 #pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                vs[c].u = ldg16(a.vt + off + (size_t)kt * (32 * D) + 16 * c, ve);
-                const uint32_t fill = col == D ? 0x3f803f80u : 0u;
-                if (!v_row) vs[c].u = make_uint4(fill, fill, fill, fill);
-            }
+            for (int c = 0; c < 2; ++c) vs[c].u = ldg16(a.vt + off + (size_t)kt * (32 * D) + 16 * c, ve);      // (rows D .. 31 of the context: unused)
 #pragma unroll
             for (int i = 0; i < KS; ++i) {
                 Frag k;
                 k.u = ldg16(a.k + off + (size_t)kt * (32 * D) + 16 * i, kv);
                 s = mfma(k.v, qs[i].v, s);
             }
-            s = mask_step(live, kperm, hf, s);
-            float mx = s[0];
-#pragma unroll
-            for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
-            const float m_new = fmaxf(m, fmaxf(mx, other_half(mx)));       // (finite: the tile holds a live key)
-            const float sc = __builtin_amdgcn_exp2f(m - m_new);
-            m = m_new;
-            l *= sc;
-            Frag p[2];
-#pragma unroll
-            for (int v = 0; v < 16; ++v) o[v] *= sc;
-#pragma unroll
-            for (int g = 0; g < 8; ++g) {
-                p[g >> 2].w[g & 3] = pack2(__builtin_amdgcn_exp2f(s[2 * g] - m), __builtin_amdgcn_exp2f(s[2 * g + 1] - m));
-                l = add_pair(p[g >> 2].w[g & 3], l);
-            }
-            o = mfma(vs[0].v, p[0].v, o);
-            o = mfma(vs[1].v, p[1].v, o);
+            general_tile(s, vs, live, hf, o, m, l);
         }
         uint2 gr[D / 8];
         load_gate(r, gr);
-        finish(o, denominator(o, l), r, gr);
+        finish(o, l + other_half(l), r, gr);
     }
 }
 

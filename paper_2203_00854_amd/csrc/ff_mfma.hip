@@ -41,33 +41,11 @@
 
 namespace ff {
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
-
-union Frag {
-    bf16x8 v;
-    uint4 u;
-    uint32_t w[4];
-};
-
-__device__ __forceinline__ uint32_t pack2(float a, float b) {   // a -> low half (first element)
-    bf16x2 t;
-    t[0] = (__bf16)a;
-    t[1] = (__bf16)b;
-    return __builtin_bit_cast(uint32_t, t);
-}
-__device__ __forceinline__ float lo_f32(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float hi_f32(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 __device__ __forceinline__ float bf16_round(float f) { return lo_f32(pack2(f, 0.f)); }
 
 __device__ __forceinline__ uint4 ldg16(const void* p) { return *reinterpret_cast<const uint4*>(p); }
 __device__ __forceinline__ uint2 ldg8(const void* p) { return *reinterpret_cast<const uint2*>(p); }
-// The same loads and a store with the address split into a wave-uniform base (scalar registers)
-// and a 32-bit byte offset per lane: one instruction, no address arithmetic in the vector unit.
-__device__ __forceinline__ uint4 ldg16(const void* base, uint32_t lane_bytes) {
-    return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(base) + lane_bytes);
-}
+// (see ldg16 with a base and an offset per lane)
 __device__ __forceinline__ uint2 ldg8(const void* base, uint32_t lane_bytes) {
     return *reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(base) + lane_bytes);
 }
@@ -75,22 +53,9 @@ __device__ __forceinline__ void stg16(void* base, uint32_t lane_bytes, uint4 v) 
     *reinterpret_cast<uint4*>(reinterpret_cast<char*>(base) + lane_bytes) = v;
 }
 
-// sum of the two bf16 halves of w, added to acc (v_dot2c_f32_bf16)
-__device__ __forceinline__ float add_pair(uint32_t w, float acc) {
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), __builtin_bit_cast(bf16x2, 0x3f803f80u), acc,
-                                           false);
-}
-
 // sum of the squares of the two bf16 halves of w, added to acc (v_dot2c_f32_bf16: exact products)
 __device__ __forceinline__ float add_pair_sq(uint32_t w, float acc) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), __builtin_bit_cast(bf16x2, w), acc, false);
-}
-
-// value of the other half-wave's lane (l ^ 32)
-__device__ __forceinline__ float other_half(float v) {
-    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    // r[0] = {lower half of v, lower half of v}, r[1] = {upper half, upper half}
-    return (threadIdx.x & 32) ? __uint_as_float(r[0]) : __uint_as_float(r[1]);
 }
 
 // LayerNorm statistics of a token whose K channels lie in the KC fragments of the two lanes
@@ -116,15 +81,6 @@ __device__ __forceinline__ void token_stats(const Frag (&xa)[KC], int K, float e
     const float inv_k = 1.f / (float)K;
     mu = sum * inv_k;
     var = fmaxf(sq * inv_k - mu * mu, 0.f) + eps;
-}
-
-// After the call lanes of the lower half hold (a of lower lane, a of upper lane) and lanes of
-// the upper half hold (b of lower lane, b of upper lane): two 4-element groups that are
-// adjacent in memory end up in one lane.
-__device__ __forceinline__ void merge_halves(uint32_t& a, uint32_t& b) {
-    auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-    a = r[0];
-    b = r[1];
 }
 
 static inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -461,7 +417,6 @@ struct GemmArgs {
 };
 
 typedef void __attribute__((address_space(3)))* lptr_t;
-constexpr int kWaitVmcnt0 = 0x0F70;      // s_waitcnt vmcnt(0), the other counters untouched
 
 // Wait until at most n (rounded down to 8, 4, 2 or 0) vector-memory operations of this wavefront
 // are outstanding.  They complete in order, so with n = number of stores issued after a load this
@@ -1308,12 +1263,10 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
                 }
                 l_run[1] += lt[0];
             }
-            // A denominator outside [2^-60, 2^96] (see k_attn_rows): the row is done again with a running maximum
+            // rows that do not stand are done again with a running maximum
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const float l_tot = l_run[j] + other_half(l_run[j]);
-                const bool fine = l_tot >= 0x1p-60f && l_tot <= 0x1p96f;
-                if (!__any(!fine && l_tok < a.L)) continue;
+                if (!__any(!softmax_stands<16>(o_acc[j], l_run[j] + other_half(l_run[j])) && l_tok < a.L)) continue;
                 float m = -INFINITY;
                 l_run[j] = 0.f;
 #pragma unroll
@@ -1322,29 +1275,12 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
                     const uint32_t live = live_of(j, t);
                     if (live == 0) continue;
                     f32x16 s;
-                    Frag p[2];
                     load_bias(t, s);
                     load_k(j, t, kf[0]);
                     load_v(j, t, vf[0]);
                     s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0][0].v, qf[j][0].v, s, 0, 0, 0);
                     s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0][1].v, qf[j][1].v, s, 0, 0, 0);
-                    s = mask_step(live, kperm_a, hf_a, s);
-                    float mx = s[0];
-#pragma unroll
-                    for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
-                    const float m_new = fmaxf(m, fmaxf(mx, other_half(mx)));       // (finite: the tile holds a live key)
-                    const float sc = __builtin_amdgcn_exp2f(m - m_new);
-                    m = m_new;
-                    l_run[j] *= sc;
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) o_acc[j][v] *= sc;
-#pragma unroll
-                    for (int g = 0; g < 8; ++g) {
-                        p[g >> 2].w[g & 3] = pack2(__builtin_amdgcn_exp2f(s[2 * g] - m), __builtin_amdgcn_exp2f(s[2 * g + 1] - m));
-                        l_run[j] = add_pair(p[g >> 2].w[g & 3], l_run[j]);
-                    }
-#pragma unroll
-                    for (int c = 0; c < 2; ++c) o_acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[0][c].v, p[c].v, o_acc[j], 0, 0, 0);
+                    general_tile(s, vf[0], live, hf_a, o_acc[j], m, l_run[j]);
                 }
             }
 

@@ -11,7 +11,7 @@ import torch
 import paper_2203_00854_amd as P
 from oracle import evoformer_attention as O
 from paper_2203_00854_amd import inputs as I
-from helpers import small_spec, f64_inputs, max_abs, rel_l2
+from helpers import small_spec, f64_inputs, max_abs, patchy_mask, poison_masked_tokens, rel_l2
 
 pytestmark = pytest.mark.gpu
 
@@ -87,3 +87,43 @@ def test_content_of_masked_tail_tiles_is_irrelevant(n_a, n_b, d, live):
     torch.cuda.synchronize()
     assert P.ff_attention_last_path() == "mfma_bf16"
     assert torch.isfinite(a).all() and torch.equal(a[mask != 0], b[mask != 0])
+
+
+@pytest.mark.parametrize("mode,n_a,n_b,d", [(ROW, 14, 160, 8), (ROW, 14, 160, 16), (ROW, 14, 100, 32), (ROW, 300, 260, 32), (COL, 330, 9, 8), (ROW, 9, 160, 32),
+                                            (COL, 250, 13, 32), (TS, 300, 300, 32), (TE, 140, 140, 32), (TS, 90, 90, 16)])
+def test_content_of_masked_tokens_is_irrelevant(mode, n_a, n_b, d):
+    """NaN and infinities in masked tokens where the batch rows of a wavefront have their valid keys in different tiles: lead, gap,
+    tail and single keys (129 .. 256 positions at d = 32: k_proj_attn)."""
+    case = I.make_case(small_spec(mode, n_a, n_b, 64, 4, d, c_z=16, dtype="bf16"))
+    if mode in (TS, TE):
+        keep = patchy_mask(4, n_a)[3]
+        keep[32:64] = 0.0
+        mask = np.outer(keep, keep)
+    else:
+        mask = patchy_mask(n_a, n_b) if mode == ROW else patchy_mask(n_b, n_a).T
+    bad = poison_masked_tokens(case, mask)
+    x, z, m, w = f64_inputs(case)
+    ref = O.gated_attention(mode, x, z, m, w, 4, case.spec.ln_eps)
+    case.x = bad
+    live = case.mask != 0
+    got = run(case)[live]
+    assert np.isfinite(got).all()
+    assert max_abs(got, ref[live]) <= 2e-2 and rel_l2(got, ref[live]) <= 1e-2
+
+
+@pytest.mark.parametrize("n_a,n_b,d", [(6, 70, 32), (5, 150, 8), (9, 100, 16), (7, 200, 32)])
+def test_values_that_overflow_unnormalised_sums(n_a, n_b, d):
+    """Weights up to 2^85 or so, which pass as they are, times values of about 2^60: the sum over the keys leaves float32 although
+    the weighted mean does not."""
+    case = I.make_case(small_spec(ROW, n_a, n_b, 64, 4, d, c_z=16, dtype="bf16", mask="random:0.8"))
+    case.weights["lnz_b"] = I.to_storage(np.full(16, 4.0), "bf16")
+    wb = I.widen(case.weights["w_b"]).astype(np.float64)
+    for h, shift in enumerate((50.0, 45.0, -30.0, 0.0)):
+        wb[h] += shift / 64.0
+    case.weights["w_b"] = I.to_storage(wb, "bf16")
+    case.weights["w_v"] = I.to_storage(I.widen(case.weights["w_v"]).astype(np.float64) * 2.0 ** 60, "bf16")
+    got = run(case) * 2.0 ** -60
+    x, z, m, w = f64_inputs(case)
+    ref = O.gated_attention(ROW, x, z, m, w, 4, case.spec.ln_eps) * 2.0 ** -60
+    assert np.isfinite(got).all()
+    assert max_abs(got, ref) <= 2e-2 and rel_l2(got, ref) <= 1e-2
