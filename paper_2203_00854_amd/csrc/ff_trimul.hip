@@ -178,12 +178,12 @@ __global__ __launch_bounds__(256) void k_tm_prep(TmPrepArgs a) {
 }
 
 // rows x (2 KC + 1) 16-byte pieces of a folded weight matrix into LDS rows of 32 KC + 16 bytes, by 512 threads: the 2 KC pieces of a
-// row and the one of its extra contraction step in the padding.  Nine loads in flight per thread: one at a time, each waited
-// for before the next, the copy of a block took 8 to 17 memory round trips, half of these kernels at 256 positions.
-template <int KC>
-__device__ __forceinline__ void copy_weights(unsigned char* dst, const bf16_t* w, const bf16_t* ext, int rows, int tid) {
-    constexpr int PPR = 2 * KC + 1, U = 9;
-    const int total = rows * PPR;
+// row and the one of its extra contraction step in the padding.  Up to nine loads in flight per thread: one at a time, each waited
+// for before the next, the copy of a block took 8 to 17 memory round trips, half of these kernels at 256 positions.  As many as
+// the matrix has pieces for: nine in every case made these kernels 10 to 20 % slower at 32 channels, where one or two do.
+template <int KC, int U>
+__device__ __forceinline__ void copy_weights_by(unsigned char* dst, const bf16_t* w, const bf16_t* ext, int total, int tid) {
+    constexpr int PPR = 2 * KC + 1;
     for (int first = tid; first < total; first += 512 * U) {
         uint4 v[U];
         int off[U];
@@ -197,6 +197,14 @@ __device__ __forceinline__ void copy_weights(unsigned char* dst, const bf16_t* w
 #pragma unroll
         for (int u = 0; u < U; ++u) *reinterpret_cast<uint4*>(dst + off[u]) = v[u];
     }
+}
+template <int KC>
+__device__ __forceinline__ void copy_weights(unsigned char* dst, const bf16_t* w, const bf16_t* ext, int rows, int tid) {
+    const int total = rows * (2 * KC + 1);
+    if (total <= 512) copy_weights_by<KC, 1>(dst, w, ext, total, tid);
+    else if (total <= 2 * 512) copy_weights_by<KC, 2>(dst, w, ext, total, tid);
+    else if (total <= 5 * 512) copy_weights_by<KC, 5>(dst, w, ext, total, tid);
+    else copy_weights_by<KC, 9>(dst, w, ext, total, tid);
 }
 
 // ====================================================================================
