@@ -41,7 +41,8 @@ __device__ __forceinline__ void load16_to_lds(const void* base, uint32_t lane_by
                  : "v"(lane_bytes), "s"(base), "s"(lds_base)
                  : "memory", "m0");
 }
-constexpr int kRing = 4;                 // steps in the LDS ring
+// steps in the LDS ring: blocks of two wavefronts take sequences of at most two steps (launch_d), which are in LDS from the start
+constexpr int ring_of(int NW) { return NW == 2 ? 2 : 4; }
 
 __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
@@ -49,15 +50,18 @@ __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
 
 }  // namespace
 
-// wavefronts per SIMD the registers of an instantiation are held to.  Without a bias and below head dim 32 two rows fit 128
-// registers: four wavefronts per SIMD, where the exponentials of a wavefront hide another's waits (1024-sequence column
-// attention at d = 8, the whole call: 438 us; three wavefronts 456; four rows and three wavefronts 499, two 469).
-constexpr int attn_rows_waves(int D, bool has_bias) { return D == 32 || has_bias ? 2 : 4; }
+// wavefronts per SIMD the registers of an instantiation are held to.  Without a bias and below head dim 32 two rows are held to 128
+// registers (five spilled, none inside the step loops): four wavefronts per SIMD, where the exponentials of a wavefront hide
+// another's waits (1024-sequence column attention at d = 8, the whole call: 438 us; three wavefronts 456; four rows and
+// three wavefronts 499, two 469).  Blocks of two wavefronts: three per SIMD fit without spills (64 x 384 columns at d = 8:
+// 8.1 us, with four 10.4).
+constexpr int attn_rows_waves(int D, int NW, bool has_bias) { return has_bias ? 2 : (NW == 2 ? 3 : (D == 32 ? 2 : 4)); }
 
 template <int D, int NR, int NW, bool HAS_BIAS>
-__global__ __launch_bounds__(NW * 64, attn_rows_waves(D, HAS_BIAS)) void k_attn_rows(AttnRowsArgs a) {
+__global__ __launch_bounds__(NW * 64, attn_rows_waves(D, NW, HAS_BIAS)) void k_attn_rows(AttnRowsArgs a) {
     static_assert((D == 8 || D == 16 || D == 32) && (NR == 2 || NR == 4), "head dimension, rows per wavefront");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int kRing = ring_of(NW);
     constexpr int TILE = 64 * D;                    // bytes of a tile of 32 keys: k as [key][D], v^T as [D][key]
     constexpr int KS = D / 16 > 0 ? D / 16 : 1;     // contraction steps of S^T
     constexpr int STEP = NR * 2 * TILE;             // bytes of a ring slot; k and v^T of its row j:
@@ -150,7 +154,7 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, HAS_BIAS)) void k_attn_
     load_mask(wave);
     stage(0);
     if (nt > 1) stage(1);
-    if (nt > 2) stage(2);
+    if (kRing > 2 && nt > 2) stage(2);
 
     // ---- q: B operand of S^T (lane = query, 8 consecutive elements)
     Frag qf[NR][KS];
@@ -237,7 +241,7 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, HAS_BIAS)) void k_attn_
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        if (kt + 3 < n_live) stage(kt + 3);
+        if (kRing > 2 && kt + 3 < n_live) stage(kt + 3);
     };
     if (!active) {                                            // (no queries: only the share of the loads)
         for (int kt = 0; kt < n_live; ++kt) turn(kt);
@@ -453,7 +457,7 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, HAS_BIAS)) void k_attn_
 template <int D, int NR, int NW, bool HAS_BIAS>
 static ff_status launch(AttnRowsArgs a, hipStream_t st) {
     const int nt = (a.L + 31) / 32;
-    const size_t smem = (size_t)(kRing + (D < 32 ? 1 : 0)) * NR * 128 * D + (size_t)((nt + 1) & ~1) * NR * 4;
+    const size_t smem = (size_t)(ring_of(NW) + (D < 32 ? 1 : 0)) * NR * 128 * D + (size_t)((nt + 1) & ~1) * NR * 4;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_rows<D, NR, NW, HAS_BIAS>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
     if (attr != hipSuccess) return fail(FF_EHIP, "k_attn_rows: dynamic LDS limit: %s", hipGetErrorString(attr));
@@ -469,7 +473,12 @@ static ff_status launch_d(const AttnRowsArgs& a, hipStream_t st) {
     // Four rows per wavefront share a bias tile four ways.  Two rows where four would leave compute units with fewer than two
     // blocks (128 x 128 triangle attention, the whole call: 32.5 us with four, 29.5 with two; 8 x 300 row attention: 43.8,
     // 40.9), and where there is no bias to share and the registers matter more (attn_rows_waves).
+    //
+    // Up to 64 positions a row has one or two query tiles: blocks of two wavefronts and two rows, instead of four of which half hold
+    // no queries (kernel time of column attention, 64 x 1024 at d = 32: 43.0 -> 33.9 us, 64 x 384 at d = 8: 12.6 -> 8.1; 512 x 64 row
+    // attention 22.9 -> 20.1).
     const int nt = (a.L + 31) / 32;
+    if (nt <= 2) return a.bias ? launch<D, 2, 2, true>(a, st) : launch<D, 2, 2, false>(a, st);
     const bool few = (int64_t)((nt + 3) / 4) * ((a.rows + 3) / 4) * a.H < 2 * compute_units();
     if (a.bias) return few ? launch<D, 2, 4, true>(a, st) : launch<D, 4, 4, true>(a, st);
     if constexpr (D == 32) {

@@ -56,6 +56,16 @@ def test_shapes(mode, n_a, n_b, c, H, c_z, mask, chunk, d):
     check(case, run(case, chunk), case.spec.name)
 
 
+@pytest.mark.parametrize("mode,n_a,n_b,mask,chunk", [
+    (COL, 1, 7, "none", 0), (COL, 32, 9, "tail:3", 0), (COL, 33, 6, "random:0.6", 0), (COL, 64, 301, "tail:40", 0), (COL, 63, 5, "none", 2),
+    (ROW, 7, 64, "random:0.8", 0), (ROW, 6, 33, "tail:1", 0), (TS, 64, 64, "outer:0.9", 15), (TE, 50, 50, "none", 0)])
+@pytest.mark.parametrize("d", [8, 16, 32])
+def test_one_or_two_query_tiles(mode, n_a, n_b, mask, chunk, d):
+    """Up to 64 positions: blocks of two wavefronts, a ring of two steps."""
+    case = I.make_case(small_spec(mode, n_a, n_b, 64, 4, d, c_z=16, dtype="bf16", mask=mask))
+    check(case, run(case, chunk), case.spec.name)
+
+
 @pytest.mark.parametrize("n_a,n_b,d", [(3, 70, 32), (300, 260, 32), (5, 150, 8), (300, 100, 16), (7, 200, 32)])
 def test_logits_far_from_zero(n_a, n_b, d):
     """The softmax runs without a reference while the denominator stays inside [2^-60, 2^96].  An offset of the pair bias moves all
