@@ -3,7 +3,8 @@ more than one LDS portion, head dimensions around the 8- and 32-channel groups, 
 of 32, rows that are no multiple of four elements, LayerNorm rows in and beyond registers.
 
 Tolerance: max-abs 1e-4, the benchmark definition's for float32 (measured: below 2e-6).  The bfloat16 cases run the
-same kernels on bfloat16 storage, shapes the bfloat16 matrix-core family does not take: max-abs 2e-2, relative L2 1e-2.
+same kernels on bfloat16 storage (shapes the bfloat16 matrix-core family does not take, or a token pointer that is not
+16-byte aligned): max-abs 2e-2, relative L2 1e-2.
 """
 import numpy as np
 import pytest
@@ -31,16 +32,15 @@ def test_edges(dtype, mode, n_a, n_b, c, c_z, heads, d, mask, chunk):
     spec = small_spec(mode, n_a, n_b, c, heads, d, c_z=c_z, dtype=dtype, mask=mask, chunk_rows=chunk)
     case = I.make_case(spec)
     desc, w, x, z, m = P.to_device(case, "cuda:0")
+    if P.ff_attention_path(desc) != "generic":        # (the bfloat16 matrix-core family wants 16-byte aligned pointers)
+        x = torch.cat([x.new_zeros(4), x.flatten()])[4:].view_as(x)
     ws = torch.full((P.ff_attention_workspace_bytes(desc, chunk),), 0xFF, dtype=torch.uint8, device="cuda:0")   # NaN patterns
     if chunk:
         got = P.ff_attention_chunked(desc, w, x, z, m, chunk_rows=chunk, ws=ws)
     else:
         got = P.ff_gated_attention(desc, w, x, z, m, ws=ws)
     torch.cuda.synchronize()
-    if dtype == "f32":
-        assert P.ff_attention_last_path() == "generic"
-    elif P.ff_attention_last_path() != "generic":
-        pytest.skip("a shape of the bfloat16 matrix-core family")
+    assert P.ff_attention_last_path() == "generic"
     xf, zf, mf, wf = f64_inputs(case)
     ref = O.gated_attention(mode, xf, zf, mf, wf, heads, spec.ln_eps)
     g = got.float().cpu().numpy().astype(np.float64)
