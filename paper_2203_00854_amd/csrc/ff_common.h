@@ -32,6 +32,17 @@ template <typename T> __device__ __forceinline__ T from_f32(float v);
 template <> __device__ __forceinline__ float from_f32<float>(float v) { return v; }
 template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float v) { return f32_to_bf16(v); }
 
+// ---- loads that write LDS directly -----------------------------------------------------
+// 16 bytes per lane from base + lane_bytes straight into LDS at lds_base + 16 * lane (base and lds_base uniform).
+// Assembly, because the compiler would make every later LDS read wait for a load it knows to write LDS; whoever
+// reads the data waits (vmcnt) and passes a barrier first.
+__device__ __forceinline__ void load16_to_lds(const void* base, uint32_t lane_bytes, unsigned lds_base) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :
+                 : "v"(lane_bytes), "s"(base), "s"(lds_base)
+                 : "memory", "m0");
+}
+
 // ---- wave64 reductions --------------------------------------------------------------
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll

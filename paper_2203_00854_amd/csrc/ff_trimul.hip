@@ -496,24 +496,17 @@ struct MulEven {
     static_assert(4 * 32 * OP <= RING * SLOT, "the output tiles of the four wavefronts fit in the ring");
 };
 
-// (see k_attn_rows) 16 bytes per lane from base + lane_bytes straight into LDS at lds_base + 16 * lane; whoever reads the data
-// waits (vmcnt) and passes a barrier first
-__device__ __forceinline__ void load16_to_lds(const void* base, uint32_t lane_bytes, unsigned lds_base) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :
-                 : "v"(lane_bytes), "s"(base), "s"(lds_base)
-                 : "memory", "m0");
-}
-// at most n (0 .. 6) vector-memory operations of this wavefront left in flight
-__device__ __forceinline__ void wait_vmem(int n) {
+// at most n (0 .. 6) vector-memory operations of this wavefront left in flight, and none of its LDS reads: the slot that they
+// read is filled again after the barrier that follows
+__device__ __forceinline__ void wait_loads(int n) {
     switch (n) {
-        case 0: __builtin_amdgcn_s_waitcnt(0x0F70); break;
-        case 1: __builtin_amdgcn_s_waitcnt(0x0F71); break;
-        case 2: __builtin_amdgcn_s_waitcnt(0x0F72); break;
-        case 3: __builtin_amdgcn_s_waitcnt(0x0F73); break;
-        case 4: __builtin_amdgcn_s_waitcnt(0x0F74); break;
-        case 5: __builtin_amdgcn_s_waitcnt(0x0F75); break;
-        default: __builtin_amdgcn_s_waitcnt(0x0F76); break;
+        case 0: __builtin_amdgcn_s_waitcnt(0x0070); break;
+        case 1: __builtin_amdgcn_s_waitcnt(0x0071); break;
+        case 2: __builtin_amdgcn_s_waitcnt(0x0072); break;
+        case 3: __builtin_amdgcn_s_waitcnt(0x0073); break;
+        case 4: __builtin_amdgcn_s_waitcnt(0x0074); break;
+        case 5: __builtin_amdgcn_s_waitcnt(0x0075); break;
+        default: __builtin_amdgcn_s_waitcnt(0x0076); break;
     }
 }
 
@@ -567,7 +560,7 @@ __global__ __launch_bounds__(256, 2) void k_tm_mul_even(TmMulArgs p) {
 
     // publishes chunk kc and sends chunk kc + 2 on its way, into the slot that was last read before the barrier
     auto turn = [&](int kc) __attribute__((always_inline)) {
-        wait_vmem(kc + 1 < nk ? mine : 0);
+        wait_loads(kc + 1 < nk ? mine : 0);
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
@@ -894,7 +887,9 @@ ff_status trimul_run(const ff_trimul_desc& d, const ff_trimul_weights& w, const 
         const int blocks = 8 * ((c + 7) / 8) * a.tiles_i * a.tiles_j;                                            \
         if (once == hipSuccess) hipLaunchKernelGGL((k_tm_mul<WI, WJ, TI, TJ>), dim3(blocks), dim3(Sh::NT), Sh::SMEM, st, a); \
     } while (0)
-        // 256 x 256 block tiles once they fill the chip several times over (c channels x (N / 256)^2 blocks, one per CU)
+        // 256 x 256 block tiles where whole ones fill the chip several times over (c channels x (N / 256)^2 blocks, one per CU); the whole
+        // call against even shares: 1024 x 128 channels 735 us, 765 with even shares; 1280 1227, 1270; 1536 1879, 1906; 2048 3870,
+        // 3990; 1024 x 64 353, 374; 768 x 128, the smallest, 391, 388
         if ((int64_t)c * ((N + 255) / 256) * ((N + 255) / 256) >= 4 * compute_units() && N % 256 == 0) FF_TM_MUL(2, 4, 4, 2);
         else {
             static const hipError_t once = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tm_mul_even),
