@@ -1365,8 +1365,9 @@ static int pick_split(int blocks_m, int tiles_n) {
 }
 
 bool mfma_chunk_ok(const Problem& p, int chunk) {
-    // work items of 64 queries of one head of eight batch rows (four without a bias below head dim 32): item indices
-    // and their products stay inside an int
+    // units of 64 queries of one head of eight batch rows (four without a bias below head dim 32): below 2^22 of them the padded
+    // tokens of the chunk (rows x Lp) and the threads of k_attn_rows' grid (blocks of 64 to 128 queries of one head of two or
+    // four rows: at most four blocks of 128 threads or two of 256 per unit) are less than 2^31, and the kernels count both in an int
     const int rb = chunk < 8 || (!p.has_bias && p.d < 32) ? 4 : 8;
     return (int64_t)(round_up(p.L, 64) / 64) * p.H * ((chunk + rb - 1) / rb) < (1 << 22);
 }
