@@ -187,7 +187,7 @@ def kernel_rooflines(sp, kernels, steps, measured=None):
         "k_gemm<PROJ>": (fl["proj"] + (fl["bias"] if tri_fused else 0.0),
                          tok * sp.c * 2 + w_main,
                          tok * (sp.c + 4 * hd) * 2 + w_main + (bias_out if tri_fused else 0), "mfma"),
-        "k_attn": (fl["attn"], None,
+        "k_attn_rows": (fl["attn"], None,
                    tok * 5 * hd * 2 + (bias_out * (R // rows_per_launch) if sp.mode != 1 else 0), "alu"),
         # sequences of at most 256 positions at head dim 32: projections and attention in one kernel, which
         # reads x, the weights and the bias and writes the gated context only
@@ -203,7 +203,7 @@ def kernel_rooflines(sp, kernels, steps, measured=None):
     # element: exp2 at half rate (2), half a pack (two elements per instruction) and half a
     # partial-denominator instruction (two elements per dot instruction); the maximum is taken for the
     # first key tile only
-    alu_per_step = {"k_attn": R * sp.heads * L * L * 3.0}
+    alu_per_step = {"k_attn_rows": R * sp.heads * L * L * 3.0}
     traffic = traffic_bytes(sp.name)
     rows = []
     for name, (ms, cnt) in kernels.items():

@@ -17,7 +17,7 @@ static std::mutex g_prof_mu;
 struct ProfRec { int kind; hipEvent_t a, b; };
 static std::vector<ProfRec> g_prof;
 static std::vector<hipEvent_t> g_prof_pool;
-static const char* kKindNames[KK_COUNT] = {"k_prep", "pair bias pass", "k_gemm<PROJ>", "k_attn",
+static const char* kKindNames[KK_COUNT] = {"k_prep", "pair bias pass", "k_gemm<PROJ>", "k_attn_rows",
                                            "k_gemm<OUT>", "k_layernorm", "generic family", "probe: mfma loop",
                                            "probe: copy", "k_tm_prep", "k_tm_proj", "k_tm_mul", "k_tm_out",
                                            "k_gca_kv", "k_gca_softmax", "k_gca_out",
