@@ -313,11 +313,13 @@ __global__ __launch_bounds__(256) void k_gemm_generic(GenericGemmArgs g) {
             *reinterpret_cast<float4*>(&Bs[buf][row * 32 + ((pc ^ (row & 7)) << 2)]) = keep4(bok[i], rb[i].value(k, g.K));
         }
     };
-    f32x16 acc[NT];
+    // two sums per output, of the even and of the odd ones of every four contraction steps, added at the end: half as many roundings
+    // in a row, none of which costs the matrix core anything
+    f32x16 acc[NT], odd[NT];
 #pragma unroll
     for (int n = 0; n < NT; ++n)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[n][v] = 0.f;
+        for (int v = 0; v < 16; ++v) acc[n][v] = odd[n][v] = 0.f;
     const int wt = WM == 4 ? wave : wave >> 1, wn = WM == 4 ? 0 : (wave & 1);
     fetch(0);
     stash(0, 0);
@@ -336,21 +338,23 @@ __global__ __launch_bounds__(256) void k_gemm_generic(GenericGemmArgs g) {
 #pragma unroll
             for (int n = 0; n < NT; ++n) bv[n] = *reinterpret_cast<const float4*>(br + 32 * 32 * n + at);
 #pragma unroll
-            for (int n = 0; n < NT; ++n) {
-                acc[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x, bv[n].x, acc[n], 0, 0, 0);
-            }
+            for (int n = 0; n < NT; ++n) acc[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x, bv[n].x, acc[n], 0, 0, 0);
 #pragma unroll
-            for (int n = 0; n < NT; ++n) acc[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.y, bv[n].y, acc[n], 0, 0, 0);
+            for (int n = 0; n < NT; ++n) odd[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.y, bv[n].y, odd[n], 0, 0, 0);
 #pragma unroll
             for (int n = 0; n < NT; ++n) acc[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.z, bv[n].z, acc[n], 0, 0, 0);
 #pragma unroll
-            for (int n = 0; n < NT; ++n) acc[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.w, bv[n].w, acc[n], 0, 0, 0);
+            for (int n = 0; n < NT; ++n) odd[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.w, bv[n].w, odd[n], 0, 0, 0);
         }
         if (more) {
             stash(buf ^ 1, k0 + 32);              // (read last in the round before, and that round's barrier has passed)
             __syncthreads();
         }
     }
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[n][v] += odd[n][v];
     // lane = feature, register v = token 8 (v / 4) + 4 hf + v % 4 of the wavefront's 32: 128-byte runs per token.  FULL: all
     // of its tokens exist (the checks are branches around every store otherwise)
     const int tw = t0 + 32 * wt;
@@ -422,8 +426,9 @@ __global__ __launch_bounds__(256) void k_gemm_generic(GenericGemmArgs g) {
 // then every load of the block is in flight together and two barriers are all it needs).  S^T = K Q^T puts a query
 // in a lane: maximum and sum are lane-local but for one exchange between the halves, and register v of the
 // exponentiated tile is the B operand of instruction v of O^T = V^T P^T as it stands (its two halves hold the keys
-// 8 (v / 4) + v % 4 and that + 4).  The bias tile is the accumulator's starting value, the key mask (0 or -inf) an
-// addend.  Online softmax; a query without any unmasked key gets zero context.  Output o = gate * context.
+// 8 (v / 4) + v % 4 and that + 4).  The bias is added to the finished products (as the accumulator's starting value it was rounded
+// with every one of them), the key mask (0 or -inf) selects.  Online softmax; a query without any unmasked key gets
+// zero context.  Output o = gate * context.
 struct GenericAttnArgs {
     const void* qkvg;
     const float* bias;       // [H][L][Lb] or NULL
@@ -491,12 +496,13 @@ __global__ __launch_bounds__(512) void k_attn_generic(GenericAttnArgs a) {
         for (int kt = 0; kt < nkp; kt += 32) {
             // lane = query, register 4 g + e = key kt + 8 g + 4 hf + e
             f32x16 s;
+            float4 bias[4];
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const int k = kt + 8 * g + 4 * hf;
-                float4 b4 = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (brow && c0 + k < a.Lb) b4 = *reinterpret_cast<const float4*>(brow + c0 + k);
-                s[4 * g] = b4.x; s[4 * g + 1] = b4.y; s[4 * g + 2] = b4.z; s[4 * g + 3] = b4.w;
+                bias[g] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (brow && c0 + k < a.Lb) bias[g] = *reinterpret_cast<const float4*>(brow + c0 + k);
+                s[4 * g] = s[4 * g + 1] = s[4 * g + 2] = s[4 * g + 3] = 0.f;
             }
             const float* kr = s_k + (kt + col) * KP + 4 * hf;
 #pragma unroll
@@ -512,10 +518,10 @@ __global__ __launch_bounds__(512) void k_attn_generic(GenericAttnArgs a) {
             for (int g = 0; g < 4; ++g) {
                 const float4 m4 = *reinterpret_cast<const float4*>(s_m + kt + 8 * g + 4 * hf);
                 // (a select, not a sum: what the padded end of a bias row holds may be anything)
-                s[4 * g] = m4.x == 0.f ? s[4 * g] : m4.x;
-                s[4 * g + 1] = m4.y == 0.f ? s[4 * g + 1] : m4.y;
-                s[4 * g + 2] = m4.z == 0.f ? s[4 * g + 2] : m4.z;
-                s[4 * g + 3] = m4.w == 0.f ? s[4 * g + 3] : m4.w;
+                s[4 * g] = m4.x == 0.f ? s[4 * g] + bias[g].x : m4.x;
+                s[4 * g + 1] = m4.y == 0.f ? s[4 * g + 1] + bias[g].y : m4.y;
+                s[4 * g + 2] = m4.z == 0.f ? s[4 * g + 2] + bias[g].z : m4.z;
+                s[4 * g + 3] = m4.w == 0.f ? s[4 * g + 3] + bias[g].w : m4.w;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) tmax = fmaxf(tmax, s[4 * g + e]);
             }
@@ -530,17 +536,22 @@ __global__ __launch_bounds__(512) void k_attn_generic(GenericAttnArgs a) {
                 part += s[v];
             }
             sum = sum * alpha + part;
+            f32x16 pv[NE];                           // the tile's own sums, so that 32 keys and the tiles round, not all keys in a row
 #pragma unroll
             for (int n = 0; n < NE; ++n)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[n][v] *= alpha;
+                for (int v = 0; v < 16; ++v) pv[n][v] = 0.f;
             // lane = channel 32 n + col (channels beyond DP read the row's neighbours and are dropped), half: keys + 4
             const float* vr = s_v + (kt + 4 * hf) * DP + (DP < 32 ? (col < DP ? col : 0) : col);
 #pragma unroll
             for (int v = 0; v < 16; ++v)
 #pragma unroll
                 for (int n = 0; n < NE; ++n)
-                    acc[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[(8 * (v >> 2) + (v & 3)) * DP + 32 * n], s[v], acc[n], 0, 0, 0);
+                    pv[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[(8 * (v >> 2) + (v & 3)) * DP + 32 * n], s[v], pv[n], 0, 0, 0);
+#pragma unroll
+            for (int n = 0; n < NE; ++n)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[n][v] = fmaf(acc[n][v], alpha, pv[n][v]);
         }
     }
     if (!active || qi >= a.L) return;

@@ -74,3 +74,21 @@ def test_content_of_masked_tokens_is_irrelevant(dtype, mode, n_a, n_b, c, heads,
     live = case.mask != 0
     assert np.isfinite(got[live]).all()
     assert max_abs(got[live], ref[live]) <= (1e-4 if dtype == "f32" else 2e-2)
+
+
+@pytest.mark.parametrize("mode,n_a,n_b,c,c_z,heads,d,limit", [
+    (ROW, 8, 32, 32, 16, 4, 8, 2.30e-7), (ROW, 16, 200, 64, 32, 4, 16, 2.65e-7), (ROW, 40, 155, 256, 128, 8, 32, 4.85e-7),
+    (TE, 96, 96, 256, 0, 8, 32, 4.92e-7), (TS, 120, 120, 32, 0, 4, 8, 2.42e-7)])
+def test_rounding_of_the_float32_sums(mode, n_a, n_b, c, c_z, heads, d, limit):
+    """Relative error against float64.  limit: that of vector multiply-adds, a chain per output and the keys of a query spread over 64
+    lanes (measured with such kernels on these inputs); one chain per output on the matrix instruction, with the bias
+    as its starting value and all keys in a row, has 2.56, 3.48, 5.61, 5.61 and 2.97e-7."""
+    spec = small_spec(mode, n_a, n_b, c, heads, d, c_z=c_z, dtype="f32")
+    case = I.make_case(spec)
+    desc, w, x, z, m = P.to_device(case, "cuda:0")
+    got = P.ff_gated_attention(desc, w, x, z, m).cpu().numpy().astype(np.float64)
+    assert P.ff_attention_last_path() == "generic"
+    xf, zf, mf, wf = f64_inputs(case)
+    rl = rel_l2(got, O.gated_attention(mode, xf, zf, mf, wf, heads, spec.ln_eps))
+    print(f"{spec.name}: rel_l2={rl:.3e}", flush=True)
+    assert rl <= limit
