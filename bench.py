@@ -201,8 +201,8 @@ def kernel_rooflines(sp, kernels, steps, measured=None):
     }
     # vector-unit work of the attention kernel that no design can avoid, in lane-operations per score
     # element: exp2 at half rate (2), half a pack (two elements per instruction) and half a
-    # partial-denominator instruction (two elements per dot instruction); the maximum is taken for the
-    # first key tile only
+    # partial-denominator instruction (two elements per dot instruction; k_attn_rows sums it on the matrix
+    # cores); no maximum is taken
     alu_per_step = {"k_attn_rows": R * sp.heads * L * L * 3.0}
     traffic = traffic_bytes(sp.name)
     rows = []
