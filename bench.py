@@ -441,7 +441,7 @@ def time_backward(name, steps, warmup, measured):
     kernels = P.ff_profile_collect()
     P.ff_profile_enable(False)
     pair = 2.0 * sp.rows * sp.heads * sp.length * sp.length * sp.head_dim      # one L x L x d contraction over all (row, head)
-    executed = {"k_bwd_stats": 2 * pair, "k_bwd_dq": 3 * pair, "k_bwd_dkv": 4 * pair, "k_bwd_dbias": 2 * pair}
+    executed = {"k_bwd_rows": 7 * pair, "k_bwd_stats": 2 * pair, "k_bwd_dq": 3 * pair, "k_bwd_dkv": 4 * pair, "k_bwd_dbias": 2 * pair}
     rows = []
     for kname, (kms, cnt) in kernels.items():
         r = {"kernel": kname, "avg_us": kms / cnt * 1e3}

@@ -7,18 +7,18 @@
 //   dq[i] = scale sum_j dS[i,j] k[j];  dk[j] = scale sum_i dS[i,j] q[i];  dbias[h,i,j] = sum_r dS[r,h,i,j]
 //
 // The score matrix is never stored (Section 3.2): as in the forward pass it is recomputed tile by tile.
-// One wavefront per 32-query (or 32-key) tile, four consecutive tiles of one (row, head) per block; the tiles of the
-// other side, which all four contract with, are copied into LDS once per block, a tile ahead of the arithmetic:
+// Launches:
 //   k_bwd_prepare  the bias times sqrt(d), tile by tile in the order of the accumulator registers, once with lane = query and
-//                once with lane = key, so that a bias tile is four 16-byte loads per lane in every kernel; the row of ones
-//                that stands in for no mask
-//   k_bwd_stats  forward recomputation with an online softmax: the logsumexp of every query (base 2), ctx,
-//                dg, dctx and delta
-//   k_bwd_dq     per query tile, over the key tiles: S^T = K Q^T and dP^T = V dctx^T (lane = query, so that
-//                logsumexp and delta are lane-local), dS^T, dq^T += K^T dS^T
-//   k_bwd_dkv    per key tile, over the query tiles: S = Q K^T and dP = dctx V^T (lane = key), P and dS,
-//                dv^T += dctx^T P, dk^T += Q^T dS
-//   k_bwd_dbias  per (head, patch of 4 x 4 tiles, chunk of batch rows), a wavefront per tile: dS summed in registers over the rows of the
+//                once with lane = key, so that a bias tile is four 16-byte loads per lane in every kernel; the key masks as bits
+//   k_bwd_rows   up to 512 positions: a block per (row, head), everything but the bias gradient:
+//                forward recomputation with an online softmax (the logsumexp of every query, base 2, ctx, dg and delta), then P and dS once
+//                for dq, dk and dv
+//   k_bwd_stats, k_bwd_dq, k_bwd_dkv   longer sequences: the same in three kernels, one wavefront per 32-query (or 32-key) tile, four
+//                consecutive tiles of one (row, head) per block; the tiles of the other side, which all four contract with, are copied into LDS
+//                once per block, a tile ahead of the arithmetic.  dq: S^T = K Q^T and dP^T = V dctx^T (lane = query, so that
+//                logsumexp and delta are lane-local), dS^T, dq^T += K^T dS^T; dkv: S = Q K^T and dP = dctx V^T (lane = key), P and
+//                dS, dv^T += dctx^T P, dk^T += Q^T dS
+//   k_bwd_dbias  per (head, patch of 4 x 4 tiles, chunk of batch rows): dS summed in registers over the rows of the
 //                chunk, the chunks' partial sums added in a fixed order by a small second kernel (deterministic,
 //                no atomics)
 // Operands whose contraction runs over the head dim are 16-byte row reads of the staged tiles; operands whose contraction
@@ -69,10 +69,11 @@ struct Args {
     float* ones;                             // workspace [Lp]: that row of ones (written by k_bwd_prepare)
     bf16_t *dq, *dk, *dv, *dg;               // [R][H][L][D]
     float* dbias;                            // [H][L][L] or NULL
-    float* dbias_part;                       // workspace [row_chunks][H][L][L] (partial sums over the rows of a chunk)
+    float* dbias_part;                       // workspace [row_chunks][H][Lp/32][Lp/32][4][64][4]: partial sums over the rows of a chunk, ordered as biasA
     int row_chunks, rows_per_chunk;
     bf16_t* dctx;                            // workspace [R][H][L][D]
-    float *lse, *delta;                      // workspace [R*H][Lp]
+    float *lse, *delta;                      // workspace [R*H][2][Lp]: logsumexp and delta of a (row, head) side by side (delta = lse + Lp)
+    uint32_t* live;                          // workspace [R][Lp/32]: bit = key is attended to (written by k_bwd_prepare when there is a bias)
     float *biasA, *biasK;                    // workspace [H][Lp/32][Lp/32][4][64][4]: the bias, times sqrt(D), tile by tile in the
                                              // order of the accumulator registers (biasA: lane = query, biasK: lane = key)
     int R, H, L, Lp;
@@ -102,7 +103,16 @@ __global__ __launch_bounds__(256) void k_bwd_prepare(Args a) {
     if (blockIdx.x == 0)
         for (int n = threadIdx.x; n < a.Lp; n += 256) a.ones[n] = 1.f;
     const int task = blockIdx.x * 4 + wave;
-    if (!a.bias || task >= a.H * nt * nt) return;
+    if (!a.bias) return;
+    if (task >= a.H * nt * nt) {                     // the wavefronts behind the tiles: the key masks of two tiles of a batch row as bits
+        const int pairs = (nt + 1) >> 1, w = task - a.H * nt * nt;
+        const int r = w / pairs, jt = 2 * (w - r * pairs), j = 32 * jt + lane;
+        if (r >= a.R) return;
+        const uint64_t bits = __ballot(j < a.L && (a.mask == nullptr || a.mask[(size_t)r * a.L + (j < a.L ? j : 0)] != 0.f));
+        if (lane == 0) a.live[(size_t)r * nt + jt] = (uint32_t)bits;
+        if (lane == 0 && jt + 1 < nt) a.live[(size_t)r * nt + jt + 1] = (uint32_t)(bits >> 32);
+        return;
+    }
     // The bias tile (it, jt) of head h, times sqrt(D), as the accumulator of the logits holds it: float4 g of
     // lane (col, hf) = entries 8 g + 4 hf .. + 3 along the register axis.  biasA: lane = query i0 + col, registers
     // along the keys; biasK: lane = key j0 + col, registers along the queries.  Zeros outside [0, L)^2.
@@ -147,9 +157,10 @@ __device__ __forceinline__ f32x16 zero16() {
 // contiguous KiB per instruction; bias_tile_fetch can run tiles ahead).  The -inf part is one more matrix
 // instruction: a contraction step whose key side holds 0 or -inf in its first slot and whose query side a one.
 __device__ __forceinline__ void bias_tile_fetch(float4 (&rows)[4], const float* tiles, int h, int nt, int it, int jt, int lane) {
-    const float* p = tiles + (((size_t)h * nt + it) * nt + jt) * 1024 + lane * 4;
+    const char* p = reinterpret_cast<const char*>(tiles + (((size_t)h * nt + it) * nt + jt) * 1024);     // (uniform)
+    const uint32_t off = (uint32_t)lane * 16;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) rows[g] = *reinterpret_cast<const float4*>(p + 256 * g);
+    for (int g = 0; g < 4; ++g) rows[g] = *reinterpret_cast<const float4*>(p + 1024 * g + off);
 }
 __device__ __forceinline__ void rows_to_acc(f32x16& b, const float4 (&rows)[4]) {
 #pragma unroll
@@ -414,8 +425,8 @@ __global__ __launch_bounds__(256) void k_bwd_stats(Args a) {
     }
     dl += other_half(dl);
     if (hf == 0) {       // (Lp slots per (row, head): queries beyond L get a defined value too)
-        a.lse[(size_t)rh * a.Lp + i] = i < a.L ? lse : INFINITY;
-        a.delta[(size_t)rh * a.Lp + i] = dl;
+        a.lse[(size_t)rh * 2 * a.Lp + i] = i < a.L ? lse : INFINITY;
+        a.delta[(size_t)rh * 2 * a.Lp + i] = dl;
     }
 }
 
@@ -438,7 +449,7 @@ __global__ __launch_bounds__(256, 3) void k_bwd_dq(Args a) {
     Frag qf[KS], dcf[KS];
     load_rows<D, FULL>(qf, a.q + base, active ? i0 : 0, a.L, col, hf);
     load_rows<D, FULL>(dcf, a.dctx + base, active ? i0 : 0, a.L, col, hf);
-    const float lse = a.lse[(size_t)rh * a.Lp + (active ? i : col)], delta = a.delta[(size_t)rh * a.Lp + (active ? i : col)];
+    const float lse = a.lse[(size_t)rh * 2 * a.Lp + (active ? i : col)], delta = a.delta[(size_t)rh * 2 * a.Lp + (active ? i : col)];
     StagePlan<D, FULL> plan;
     plan.init(src, tid);
     FF_BWD_Q_PROLOGUE
@@ -506,7 +517,7 @@ __global__ __launch_bounds__(256, FULL ? 3 : 1) void k_bwd_dkv(Args a) {
     const size_t base = (size_t)rh * a.L * D;
     TileSrc src;
     src.x = a.q + base; src.y = a.dctx + base;
-    src.va = a.lse + (size_t)rh * a.Lp; src.vb = a.delta + (size_t)rh * a.Lp;
+    src.va = a.lse + (size_t)rh * 2 * a.Lp; src.vb = a.delta + (size_t)rh * 2 * a.Lp;
     src.L = a.L; src.Lp = a.Lp;
 
     Frag kf[KS], vf[KS];
@@ -608,167 +619,487 @@ __global__ __launch_bounds__(256, FULL ? 3 : 1) void k_bwd_dkv(Args a) {
 }
 
 // ====================================================================================
-// dbias: block = 16 wavefronts = a patch of 4 x 4 tiles of one head and one chunk of batch rows; wavefront (wi, wj)
-// sums dS of tile (it0 + wi, jt0 + wj) over the rows of the chunk in registers.  Per batch row the patch needs the
-// q and dctx rows of four query tiles and the k and v rows of four key tiles (16 operand tiles, 2 KiB per result
-// tile instead of the 8 KiB a wavefront on its own would fetch), logsumexp and delta of its 128 queries and the mask
-// entries of its 128 keys.  The block copies them global -> registers -> LDS (two stages, one barrier per row); a
-// thread's share is two 16-byte pieces and one float per row, so that a row is requested two iterations before it is
-// needed at the price of nine registers.
-constexpr int kDbOperand = 32 * kStPitch;                 // bytes of a staged operand tile [32][D]
-constexpr int kDbVec = 16 * kDbOperand;                   // then logsumexp [128], delta [128], key mask [128] (floats)
-constexpr int kDbStage = kDbVec + 3 * 128 * 4;
+// Up to 512 positions: statistics, dq, dk and dv of one (row, head) in one block, so that every tensor passes memory once and the
+// weights are recomputed once for dq, dk and dv together.  q, k, v and later dctx of the (row, head) stay in LDS.  There is a wavefront per
+// 32 positions: wavefront w owns query tile w while the statistics are formed (as k_bwd_stats), then key tile w (as
+// k_bwd_dkv) and dq of query tile w.  In step s of the second phase wavefront w works on query tile (w + s) mod nt: its
+// tile of dS goes to LDS (in the place of v, which is in registers by then), and after a barrier the owner of that query tile contracts it with
+// the key rows of the wavefront it comes from.  The wavefronts work on different query tiles, so every one of
+// them has exactly one such contraction per step.
+// What bounds it: the instructions that the wavefronts of a SIMD can issue (about 130 per tile for the statistics, 190 in the second phase),
+// at four wavefronts per SIMD, hence at most 128 registers; then the bytes.  Two tiles per wavefront and two wavefronts per SIMD need fewer
+// LDS reads, but took 96 us at 128 rows x 8 heads x 256 x 32 with a bias; now 77, the three kernels 117 (46 + 32 + 40).  Without its tile
+// loops it takes 39 us there for the 168 MB that it moves.
+// Rows are 64 bytes whatever the head dim, the 16-byte piece p of row n at p ^ (n / 4) % 4: operand reads of rows and transposing reads alike
+// then spread over the banks.  Masked keys and positions beyond L are zeros; their dk and dv are not taken from the
+// accumulators, and their weights are cleared from dS.
+constexpr int kRowsTiles = 16;                         // at most: 32 positions per wavefront
+__device__ __forceinline__ int piece_swizzle(int n) { return (n >> 2) & 3; }
 
-template <int D, bool FULL>
-__global__ __launch_bounds__(1024) void k_bwd_dbias(Args a) {
-    constexpr int KS = (D + 15) / 16, PR = D / 8, NP = 16 * 32 * PR;      // 16-byte row pieces per batch row
+// operand fragments of a swizzled tile: rows of the lane's position, lane_off = rows_lane(col, hf) ...
+__device__ __forceinline__ int rows_lane(int col, int hf) { return col * 64 + ((hf ^ piece_swizzle(col)) << 4); }
+template <int D>
+__device__ __forceinline__ void rows_frag(Frag (&f)[(D + 15) / 16], const unsigned char* tile, int lane_off, int hf) {
+#pragma unroll
+    for (int s = 0; s < (D + 15) / 16; ++s) f[s].u = *reinterpret_cast<const uint4*>(tile + (lane_off ^ (32 * s)));
+    if (D == 8 && hf) f[0].u = make_uint4(0, 0, 0, 0);
+}
+// ... and channels of the lane over the positions 16 s + 4 hf + (u < 4 ? u : u + 4) (see staged_cols), lane_off = cols_lane(lane)
+__device__ __forceinline__ int cols_lane(int lane) {
+    const int hf = lane >> 5, chunk = ((lane & 16) >> 2) + (lane & 3);
+    return (4 * hf + ((lane >> 2) & 3)) * 64 + (((chunk >> 1) ^ hf) << 4) + (chunk & 1) * 8;
+}
+__device__ __forceinline__ uint2 read_tr(const unsigned char* p) {
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4)p));
+}
+__device__ __forceinline__ void cols_frag(Frag (&f)[2], const unsigned char* tile, int lane_off) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const uint2 lo = read_tr(tile + lane_off + 1024 * s), hi = read_tr(tile + (lane_off ^ 32) + 1024 * s + 512);
+        f[s].u = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    }
+}
+// A transposed result tile (lane = position, register v = channel 8 (v / 4) + 4 hf + v % 4) as 16-byte pieces: words lo, hi of channel groups
+// g and g + 1 (channels 4 hf .. + 1 and + 2 .. + 3) become the eight channels of group g + hf.
+__device__ __forceinline__ uint4 merge_groups(uint32_t lo0, uint32_t hi0, uint32_t lo1, uint32_t hi1) {
+    const auto l = __builtin_amdgcn_permlane32_swap(lo0, lo1, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi0, hi1, false, false);
+    return make_uint4(l[0], h[0], l[1], h[1]);
+}
+// x [D] of the lane's position, packed words w[2 g], w[2 g + 1] of channel group g
+template <int D>
+__device__ __forceinline__ void store_position(bf16_t* x, const uint32_t* w, int hf) {
+    if constexpr (D == 8) {
+        *reinterpret_cast<uint2*>(x + 4 * hf) = make_uint2(w[0], w[1]);
+    } else {
+#pragma unroll
+        for (int g = 0; g < D / 8; g += 2)
+            *reinterpret_cast<uint4*>(x + 8 * (g + hf)) = make_uint4(w[2 * g], w[2 * g + 1], w[2 * g + 2], w[2 * g + 3]);
+    }
+}
+// the words of store_position from an accumulator (all lanes take part)
+template <int D>
+__device__ __forceinline__ void pack_position(uint32_t (&w)[8], const f32x16& a, float scale) {
+#pragma unroll
+    for (int g = 0; g < D / 8; ++g) {
+        w[2 * g] = pack2(a[4 * g] * scale, a[4 * g + 1] * scale);
+        w[2 * g + 1] = pack2(a[4 * g + 2] * scale, a[4 * g + 3] * scale);
+    }
+    if constexpr (D > 8)
+#pragma unroll
+        for (int g = 0; g < D / 8; g += 2) {
+            const uint4 u = merge_groups(w[2 * g], w[2 * g + 1], w[2 * g + 2], w[2 * g + 3]);
+            w[2 * g] = u.x; w[2 * g + 1] = u.y; w[2 * g + 2] = u.z; w[2 * g + 3] = u.w;
+        }
+}
+
+__device__ __forceinline__ uint4 only_if(bool c, uint4 v) {
+    const uint32_t m = c ? 0xffffffffu : 0u;
+    return make_uint4(v.x & m, v.y & m, v.z & m, v.w & m);
+}
+// products of two pairs of bf16 values, rounded to bf16
+__device__ __forceinline__ uint32_t mul_pairs(uint32_t a, uint32_t b) { return pack2(lo_f32(a) * lo_f32(b), hi_f32(a) * hi_f32(b)); }
+
+template <int D, bool BIAS>
+__global__ __launch_bounds__(64 * kRowsTiles, 4) void k_bwd_rows(Args a) {
+    constexpr int KS = (D + 15) / 16, PR = D / 8, NG = D / 8;      // contraction steps, 16-byte pieces of a row, channel groups
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, hf = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = a.Lp >> 5;
+    const int rh = blockIdx.x, r = rh / a.H, h = rh - r * a.H;
+    const size_t base = (size_t)rh * a.L * D;
+    unsigned char *s_q = smem, *s_k = smem + nt * 2048, *s_v = smem + nt * 4096, *s_d = smem + nt * 6144;
+    float *s_lse = reinterpret_cast<float*>(smem + nt * 8192), *s_nd = s_lse + 32 * nt;       // logsumexp and -delta of the queries
+    const int n = 32 * wave + col, nc = n < a.L ? n : a.L - 1;     // the lane's query, later its key
+    const float* mrow = a.mask ? a.mask + (size_t)r * a.L : nullptr;
+
+    // ---- q, k, v and dctx = dout * g (rounded to bf16) into LDS, everything in flight at once (a wavefront copies its own 32 positions)
+    {
+        constexpr int NL = (32 * PR + 63) / 64;                    // pieces per lane
+        uint4 tq[NL], tk[NL], tv[NL], td[NL], tg[NL];
+        float mk[NL];
+#pragma unroll
+        for (int x = 0; x < NL; ++x) {
+            const int id = (lane + 64 * x) % (32 * PR), row = 32 * wave + id / PR, rc = row < a.L ? row : a.L - 1;
+            const size_t at = base + (size_t)rc * D + 8 * (id % PR);
+            tq[x] = *reinterpret_cast<const uint4*>(a.q + at);
+            tk[x] = *reinterpret_cast<const uint4*>(a.k + at);
+            tv[x] = *reinterpret_cast<const uint4*>(a.v + at);
+            td[x] = *reinterpret_cast<const uint4*>(a.dout + at);
+            tg[x] = *reinterpret_cast<const uint4*>(a.g + at);
+            mk[x] = mrow ? mrow[rc] : 1.f;
+        }
+#pragma unroll
+        for (int x = 0; x < NL; ++x) {
+            const int id = (lane + 64 * x) % (32 * PR), row = 32 * wave + id / PR;
+            const bool in = row < a.L, key = in && mk[x] != 0.f;
+            const int at = row * 64 + (((id % PR) ^ piece_swizzle(row)) << 4);
+            *reinterpret_cast<uint4*>(s_q + at) = only_if(in, tq[x]);
+            *reinterpret_cast<uint4*>(s_k + at) = only_if(key, tk[x]);
+            *reinterpret_cast<uint4*>(s_v + at) = only_if(key, tv[x]);
+            const uint4 dc = make_uint4(mul_pairs(td[x].x, tg[x].x), mul_pairs(td[x].y, tg[x].y), mul_pairs(td[x].z, tg[x].z), mul_pairs(td[x].w, tg[x].w));
+            *reinterpret_cast<uint4*>(s_d + at) = only_if(in, dc);
+            if (BIAS && in) *reinterpret_cast<uint4*>(a.dctx + base + (size_t)row * D + 8 * (id % PR)) = dc;
+        }
+    }
+    const uint32_t keep = n < a.L && (!mrow || mrow[nc] != 0.f) ? 0xffffffffu : 0u;      // all ones if the lane's key is attended to
+    // (which keys are attended to, one bit per key: in the place of the statistics, which come later)
+    uint32_t* s_live = reinterpret_cast<uint32_t*>(s_lse);
+    {
+        const uint32_t bits = (uint32_t)__ballot(keep != 0u);
+        if (lane == 0) s_live[wave] = bits;
+    }
+    const int row_off = rows_lane(col, hf), col_off = cols_lane(lane);
+    f32x16 b = zero16();
+    auto fetch_bias = [&](const float* tiles, int it, int jt) __attribute__((always_inline)) {
+        float4 rows[4];
+        bias_tile_fetch(rows, tiles, h, nt, it, jt, lane);
+        rows_to_acc(b, rows);
+    };
+    if (BIAS) fetch_bias(a.biasA, wave, 0);
+    __syncthreads();
+
+    // ---- statistics (see k_bwd_stats)
+    float lse, delta;
+    {
+        Frag qf[KS];
+        rows_frag<D>(qf, s_q + wave * 2048, row_off, hf);
+        const Frag one = one_side(hf);
+        constexpr float kSlack = 8.f;
+        float m = -1e30f, l = 0.f;
+        f32x16 ctx = zero16();
+        for (int jt = 0; jt < nt; ++jt) {
+            Frag kf[KS], vt[2], pf[2];
+            rows_frag<D>(kf, s_k + jt * 2048, row_off, hf);
+            const Frag kx = key_side((s_live[jt] >> col) & 1u, hf);
+            f32x16 s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kx.v, one.v, b, 0, 0, 0);
+            if (BIAS) fetch_bias(a.biasA, wave, jt + 1 < nt ? jt + 1 : jt);
+#pragma unroll
+            for (int t = 0; t < KS; ++t) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t].v, qf[t].v, s, 0, 0, 0);
+            cols_frag(vt, s_v + jt * 2048, col_off);
+            float tmax = s[0];
+#pragma unroll
+            for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, s[v]);
+            tmax *= a.qscale2;
+            if (__builtin_amdgcn_ballot_w64(tmax > m + kSlack) != 0) {
+                const float m_new = fmaxf(m, fmaxf(tmax, other_half(tmax)));
+                const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+#pragma unroll
+                for (int v = 0; v < 16; ++v) ctx[v] *= alpha;
+                l *= alpha;
+                m = m_new;
+            }
+            float lt = 0.f;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                s[v] = __builtin_amdgcn_exp2f(s[v] * a.qscale2 - m);
+                lt += s[v];
+            }
+            l += lt;
+            pack_rows(pf, s);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) ctx = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vt[t].v, pf[t].v, ctx, 0, 0, 0);
+        }
+        // dout of the lane's query once more (it was read a moment ago)
+        uint2 dov[NG], dcv[NG];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            dov[g] = *reinterpret_cast<const uint2*>(a.dout + base + (size_t)nc * D + 8 * g + 4 * hf);
+            dcv[g] = *reinterpret_cast<const uint2*>(s_d + n * 64 + ((g ^ piece_swizzle(n)) << 4) + 8 * hf);
+        }
+        // (all lanes take part in what follows: the two lanes of a query exchange halves; only queries below L are stored)
+        const float l_tot = l + other_half(l), inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+        // a query without unmasked keys: logsumexp = +inf makes every recomputed weight exp2(s - inf) = 0
+        lse = l_tot > 0.f && n < a.L ? m + __builtin_amdgcn_logf(l_tot) : INFINITY;
+        float dl = 0.f;          // delta uses the very dctx values the other contractions read
+        uint32_t wg[8];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const float d_o[4] = {lo_f32(dov[g].x), hi_f32(dov[g].x), lo_f32(dov[g].y), hi_f32(dov[g].y)};
+            const float dc[4] = {lo_f32(dcv[g].x), hi_f32(dcv[g].x), lo_f32(dcv[g].y), hi_f32(dcv[g].y)};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float c = ctx[4 * g + e] * inv;
+                dl += dc[e] * c;
+                ctx[4 * g + e] = d_o[e] * c;
+            }
+        }
+        delta = dl + other_half(dl);
+        pack_position<D>(wg, ctx, 1.f);
+        if (n < a.L) store_position<D>(a.dg + base + (size_t)n * D, wg, hf);
+        if (BIAS && hf == 0) {
+            a.lse[(size_t)rh * 2 * a.Lp + n] = lse;
+            a.delta[(size_t)rh * 2 * a.Lp + n] = delta;
+        }
+    }
+    // ---- dq, dk, dv
+    Frag vf[KS];
+    rows_frag<D>(vf, s_v + wave * 2048, row_off, hf);
+    if (BIAS) fetch_bias(a.biasK, wave, wave);
+    __syncthreads();                 // (the key masks and v have been read)
+    if (hf == 0) {
+        s_lse[n] = lse;
+        s_nd[n] = -delta;
+    }
+    __syncthreads();
+    f32x16 dk = zero16(), dv = zero16(), dq = zero16();
+    unsigned char* s_ds = s_v;       // [wavefront][32 keys][32 queries]
+    const int row_lane = row_off, col_lane = col_off;
+    int it = wave, from = wave;      // (wave + step) mod nt, (wave - step) mod nt
+    for (int step = 0; step < nt; ++step) {
+        // (opaque: else every LDS address of the loop is worked out before it, and some of them wait in scratch memory)
+        int row_off = row_lane, col_off = col_lane;
+        asm volatile("" : "+v"(row_off), "+v"(col_off));
+        Frag dsf[2];
+        {
+            Frag qr[KS], dr[KS], kf[KS], pf[2], ft[2];
+            rows_frag<D>(qr, s_q + it * 2048, row_off, hf);
+            rows_frag<D>(kf, s_k + wave * 2048, row_off, hf);
+#pragma unroll
+            for (int c = 0; c < KS; ++c) b = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qr[c].v, kf[c].v, b, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);       // (else the operands of both contractions are in registers together, and others in scratch memory)
+            f32x16 dp;               // lane = key, register v = query 8 (v / 4) + 4 hf + v % 4; starts from -delta
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float4 d4 = *reinterpret_cast<const float4*>(s_nd + 32 * it + 8 * g + 4 * hf);
+                dp[4 * g] = d4.x; dp[4 * g + 1] = d4.y; dp[4 * g + 2] = d4.z; dp[4 * g + 3] = d4.w;
+            }
+            rows_frag<D>(dr, s_d + it * 2048, row_off, hf);
+#pragma unroll
+            for (int c = 0; c < KS; ++c) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dr[c].v, vf[c].v, dp, 0, 0, 0);
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float4 l4 = *reinterpret_cast<const float4*>(s_lse + 32 * it + 8 * g + 4 * hf);
+                const float ls[4] = {l4.x, l4.y, l4.z, l4.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    b[4 * g + e] = __builtin_amdgcn_exp2f(b[4 * g + e] * a.qscale2 - ls[e]);
+                    dp[4 * g + e] *= b[4 * g + e];
+                }
+            }
+            pack_rows(pf, b);
+            pack_rows(dsf, dp);
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) dsf[c].w[i] &= keep;
+            const int itn = it + 1 < nt ? it + 1 : 0;
+            if (BIAS) fetch_bias(a.biasK, itn, wave);
+            else b = zero16();
+            cols_frag(ft, s_d + it * 2048, col_off);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) dv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ft[c].v, pf[c].v, dv, 0, 0, 0);
+            cols_frag(ft, s_q + it * 2048, col_off);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) dk = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ft[c].v, dsf[c].v, dk, 0, 0, 0);
+            it = itn;
+        }
+        __syncthreads();             // (the dS tiles of the previous step have been read)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                *reinterpret_cast<uint2*>(s_ds + wave * 2048 + col * 64 + (((2 * c + u) ^ piece_swizzle(col)) << 4) + 8 * hf) =
+                    make_uint2(dsf[c].w[2 * u], dsf[c].w[2 * u + 1]);
+        __syncthreads();
+        // dS of the wavefront's own query tile comes from wavefront (wave - step) mod nt this time
+        Frag ds[2], kc[2];
+        cols_frag(ds, s_ds + from * 2048, col_off);
+        cols_frag(kc, s_k + from * 2048, col_off);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) dq = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kc[c].v, ds[c].v, dq, 0, 0, 0);
+        from = from > 0 ? from - 1 : nt - 1;
+    }
+    uint32_t wq[8], wk[8], wv[8];
+    pack_position<D>(wq, dq, a.scale);
+    pack_position<D>(wk, dk, a.scale);
+    pack_position<D>(wv, dv, 1.f);
+#pragma unroll
+    for (int i = 0; i < 2 * NG; ++i) {
+        wk[i] &= keep;
+        wv[i] &= keep;
+    }
+    if (n < a.L) {
+        store_position<D>(a.dq + base + (size_t)n * D, wq, hf);
+        store_position<D>(a.dk + base + (size_t)n * D, wk, hf);
+        store_position<D>(a.dv + base + (size_t)n * D, wv, hf);
+    }
+}
+
+// ====================================================================================
+// dbias: block = eight wavefronts = a patch of 4 x 4 tiles of one head and one chunk of batch rows; wavefront (wi, wj) sums dS of
+// the tiles (it0 + wi, jt0 + 2 wj), (it0 + wi, jt0 + 2 wj + 1) over the rows of the chunk in registers.  Per batch row the patch
+// needs the q and dctx rows of four query tiles, the k and v rows of four key tiles and logsumexp and delta of its
+// 128 queries: 33 KiB for 16 tiles, by loads that write LDS directly (rows swizzled by the source address) into a ring of
+// kDbRing rows, kDbRing - 1 rows ahead, one barrier per row.  Positions beyond L are the last one again: their entries
+// are not stored.
+constexpr int kDbRing = 4;
+constexpr int kDbStage = 16 * 2048 + 1024;                // 16 operand tiles [32][64 bytes], then logsumexp [128] and delta [128]
+typedef void __attribute__((address_space(3)))* lds_void;
+
+// byte offset of an operand fragment in a staged tile of rows of 2 D bytes (its second step: ^ 32)
+template <int D>
+__device__ __forceinline__ int db_rows_lane(int col, int hf) {
+    if (D == 32) return rows_lane(col, hf);
+    return D == 16 ? col * 32 + ((hf ^ ((col >> 3) & 1)) << 4) : col * 16;
+}
+template <int D>
+__global__ __launch_bounds__(512, 2) void k_bwd_dbias(Args a) {
+    constexpr int KS = (D + 15) / 16, TILE = 64 * D, STAGE = 16 * TILE + 1024;
+    constexpr int NLW = D / 8;                             // loads of 1 KiB per wavefront and batch row (16 tiles, eight wavefronts)
+    static_assert(STAGE <= kDbStage, "a batch row fits its place in the ring");
     extern __shared__ __attribute__((aligned(16))) unsigned char s_db[];
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, hf = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wi = wave >> 2, wj = wave & 3;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wi = wave >> 1, wj = wave & 1;
     const int nt = a.Lp >> 5, np = (nt + 3) >> 2;
     const int chunk = blockIdx.x / (a.H * np * np), rem = blockIdx.x - chunk * a.H * np * np;
     const int h = rem / (np * np), pp = rem - h * np * np, it0 = 4 * (pp / np), jt0 = 4 * (pp - (pp / np) * np);
-    const int it = it0 + wi, jt = jt0 + wj;
+    const int it = it0 + wi, jt = jt0 + 2 * wj;            // (the wavefront's tiles: (it, jt), (it, jt + 1))
     const bool active = it < nt && jt < nt;
     const int r_begin = chunk * a.rows_per_chunk;
     const int r_end = r_begin + a.rows_per_chunk < a.R ? r_begin + a.rows_per_chunk : a.R;
-    const int i0 = it * 32, j0 = jt * 32, i = i0 + col;
     if (r_begin >= r_end) return;                          // (whole block)
 
-    // ---- the thread's pieces: address for batch row 0, offset in a stage; rows beyond L are staged as zeros
-    const size_t row_stride = (size_t)a.H * a.L * D;       // elements from a batch row to the next
-    // (piece tid + 1024, which exists at D = 32 only, is the same row and piece of the operand eight further on)
-    constexpr bool TWO = NP > 1024;
-    static_assert(NP == 2048 || NP <= 1024, "one or two pieces for every thread");
-    const bf16_t *pb0, *pb1;
-    int pd0;
-    bool pz0, pz1;
-    {
-        auto plan = [&](int p, const bf16_t*& base, int& dst, bool& zero) {
-            const bool has = p < NP;
-            const int pq = has ? p : 0;
-            const int o = pq / (32 * PR), n = (pq - o * 32 * PR) / PR, pc = pq - (pq / PR) * PR;
-            const bf16_t* t = o < 4 ? a.q : (o < 8 ? a.dctx : (o < 12 ? a.k : a.v));
-            const int pos = ((o & 3) + (o < 8 ? it0 : jt0)) * 32 + n;
-            const bool ok = pos < a.L;
-            base = t + ((size_t)h * a.L + (ok ? pos : 0)) * D + 8 * pc;
-            dst = has ? o * kDbOperand + n * kStPitch + pc * 16 : -1;
-            zero = !ok;
-        };
-        int unused;
-        plan(tid, pb0, pd0, pz0);
-        plan(TWO ? tid + 1024 : tid, pb1, unused, pz1);
-    }
-    // threads 0 .. 383: one float of logsumexp | delta | key mask per row
-    const float* vb = a.lse;
-    int vstride = 0;                                       // (floats from a batch row to the next: below 2^31)
-    int vd = -1;
-    bool vz = false;
-    if (tid < 384) {
-        const int kind = tid >> 7, x = tid & 127;
-        if (kind < 2) {
-            const int q = it0 * 32 + x;
-            vb = (kind == 0 ? a.lse : a.delta) + (size_t)h * a.Lp + (q < a.Lp ? q : 0);
-            vstride = a.H * a.Lp;
-        } else {
-            const int j = jt0 * 32 + x;
-            vz = j >= a.L;
-            vb = a.mrow + (vz ? 0 : j);
-            vstride = a.mstride;
-        }
-        vd = kDbVec + kind * 512 + x * 4;
-    }
-#define FF_DB_FETCH(R, ROW)                                                                         \
-    {                                                                                               \
-        const int rr_ = (ROW) < r_end ? (ROW) : r_end - 1;      /* (past the end: the last row again) */ \
-        R##a = *reinterpret_cast<const uint4*>(pb0 + (size_t)rr_ * row_stride);                     \
-        if (TWO) R##b = *reinterpret_cast<const uint4*>(pb1 + (size_t)rr_ * row_stride);            \
-        R##v = vb[rr_ * vstride];                                                                   \
-    }
-#define FF_DB_STORE(R, STAGE)                                                                       \
-    {                                                                                               \
-        /* (through opaque registers: pieces that go from a load straight to an LDS store end up in scratch memory otherwise) */ \
-        uint32_t a0_ = R##a.x, a1_ = R##a.y, a2_ = R##a.z, a3_ = R##a.w, b0_ = R##b.x, b1_ = R##b.y, b2_ = R##b.z, b3_ = R##b.w; \
-        asm volatile("" : "+v"(a0_), "+v"(a1_), "+v"(a2_), "+v"(a3_), "+v"(b0_), "+v"(b1_), "+v"(b2_), "+v"(b3_));      \
-        if (pz0) a0_ = a1_ = a2_ = a3_ = 0u;                                                        \
-        if (pz1) b0_ = b1_ = b2_ = b3_ = 0u;                                                        \
-        if (pd0 >= 0) *reinterpret_cast<uint4*>((STAGE) + pd0) = make_uint4(a0_, a1_, a2_, a3_);    \
-        if (TWO) *reinterpret_cast<uint4*>((STAGE) + pd0 + 8 * kDbOperand) = make_uint4(b0_, b1_, b2_, b3_); \
-        if (vd >= 0) *reinterpret_cast<float*>((STAGE) + vd) = vz ? 0.f : R##v;                     \
-    }
-    // two register sets, by name (a copy from one set to another would have to wait for the load that fills it; a
-    // third set spilled, and a spilled load result is waited for at once, which undoes the whole pipeline)
-    uint4 rAa, rAb = make_uint4(0, 0, 0, 0), rBa, rBb = make_uint4(0, 0, 0, 0);
-    float rAv, rBv;
-    FF_DB_FETCH(rA, r_begin)
-    FF_DB_FETCH(rB, r_begin + 1)
-
-    f32x16 bt = zero16();           // bias tile times sqrt(d) (the same for every batch row; the key mask is not)
-    if (active) {
-        float4 rows[4];
-        bias_tile_fetch(rows, a.biasA, h, nt, it, jt, lane);
-        rows_to_acc(bt, rows);
-    }
-    const Frag one = one_side(hf);
-    f32x16 acc = zero16();          // lane = query i, register v = key j0 + 8(v/4) + 4hf + v%4
-    FF_DB_STORE(rA, s_db)
-    __syncthreads();
-    // Row r: the set FREE (its row is in the stage) asks for row r + 2, the stage is worked on, the set NEXT (row r + 1,
-    // requested one row ago) goes into the other stage.
-#define FF_DB_ROW(FREE, NEXT)                                                                                    \
-    {                                                                                                            \
-        const unsigned char* stage = s_db + ((r - r_begin) & 1) * kDbStage;                                      \
-        FF_DB_FETCH(FREE, r + 2)                                                                                 \
-        if (active) {                                                                                            \
-            Frag qf[KS], dcf[KS], kf[KS], vf[KS];                                                                \
-            staged_rows<D>(qf, stage + wi * kDbOperand, col, hf);                                                \
-            staged_rows<D>(dcf, stage + (4 + wi) * kDbOperand, col, hf);                                         \
-            staged_rows<D>(kf, stage + (8 + wj) * kDbOperand, col, hf);                                          \
-            staged_rows<D>(vf, stage + (12 + wj) * kDbOperand, col, hf);                                         \
-            const float lse = *reinterpret_cast<const float*>(stage + kDbVec + (wi * 32 + col) * 4);             \
-            const float delta = *reinterpret_cast<const float*>(stage + kDbVec + 512 + (wi * 32 + col) * 4);     \
-            const float mk = *reinterpret_cast<const float*>(stage + kDbVec + 1024 + (wj * 32 + col) * 4);       \
-            const Frag kx = key_side(mk != 0.f, hf);                                                             \
-            /* the accumulators start from the bias tile (and -inf for this row's masked keys) and -delta */      \
-            f32x16 s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kx.v, one.v, bt, 0, 0, 0), dp;                    \
-            _Pragma("unroll") for (int v = 0; v < 16; ++v) dp[v] = -delta;                                       \
-            _Pragma("unroll") for (int t = 0; t < KS; ++t) {                                                     \
-                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t].v, qf[t].v, s, 0, 0, 0);                       \
-                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t].v, dcf[t].v, dp, 0, 0, 0);                    \
-            }                                                                                                    \
-            _Pragma("unroll") for (int v = 0; v < 16; ++v)                                                       \
-                acc[v] += __builtin_amdgcn_exp2f(s[v] * a.qscale2 - lse) * dp[v];                                \
-        }                                                                                                        \
-        if (r + 1 < r_end) FF_DB_STORE(NEXT, s_db + ((r + 1 - r_begin) & 1) * kDbStage)                          \
-        __syncthreads();                                                                                         \
-        ++r;                                                                                                     \
-    }
-    for (int r = r_begin; r < r_end;) {
-        FF_DB_ROW(rA, rB)
-        if (r >= r_end) break;
-        FF_DB_ROW(rB, rA)
-    }
-#undef FF_DB_ROW
-#undef FF_DB_FETCH
-#undef FF_DB_STORE
-    if (active && i < a.L) {
-        float* out = a.row_chunks > 1 ? a.dbias_part + (size_t)chunk * a.H * a.L * a.L : a.dbias;
-        float* drow = out + ((size_t)h * a.L + i) * a.L;
+    // ---- the wavefront's loads: lane i of a load fills 16-byte slot i of its KiB of the stage
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lds_void)s_db);
+    const char* ld_src[NLW];                               // (scalar) tensor at batch row 0 and this head
+    uint32_t ld_lane[NLW];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int j = j0 + 8 * (v >> 2) + 4 * hf + (v & 3);
-            if (j < a.L) drow[j] = acc[v];
+    for (int i = 0; i < NLW; ++i) {
+        const int c = 8 * i + wave;                        // KiB of the stage: half a tile, a tile or two tiles
+        const int o = D == 32 ? c >> 1 : (D == 16 ? c : 2 * c);
+        const bf16_t* t = o < 4 ? a.q : (o < 8 ? a.dctx : (o < 12 ? a.k : a.v));
+        ld_src[i] = reinterpret_cast<const char*>(t + (size_t)h * a.L * D);
+        const int row = D == 32 ? 16 * (c & 1) + (lane >> 2) : (D == 16 ? lane >> 1 : lane & 31);
+        const int piece = D == 32 ? (lane & 3) ^ ((lane >> 4) & 3) : (D == 16 ? (lane & 1) ^ ((lane >> 4) & 1) : 0);
+        const int tile = (o & 3) + (D == 8 ? lane >> 5 : 0) + (o < 8 ? it0 : jt0);
+        const int pos = 32 * tile + row < a.L ? 32 * tile + row : a.L - 1;
+        ld_lane[i] = (uint32_t)(pos * 2 * D + piece * 16);
+    }
+    // (logsumexp by lanes 0 .. 31, delta by lanes 32 .. 63, in wavefront 0)
+    const int vq = 32 * it0 + 4 * col < a.Lp ? 32 * it0 + 4 * col : a.Lp - 4;
+    const char* vec_src = reinterpret_cast<const char*>(a.lse + (size_t)h * 2 * a.Lp);
+    const uint32_t vec_lane = (uint32_t)((hf * a.Lp + vq) * 4);
+    const size_t row_bytes = (size_t)a.H * a.L * D * 2, vec_row_bytes = (size_t)a.H * 2 * a.Lp * 4;
+    auto stage = [&](int r) __attribute__((always_inline)) {
+        const int rr = r < r_end ? r : r_end - 1;          // (past the end: the last row again, into a slot that nobody reads)
+        const unsigned dst = lds0 + (unsigned)((r - r_begin) % kDbRing) * STAGE;
+#pragma unroll
+        for (int i = 0; i < NLW; ++i) load16_to_lds(ld_src[i] + rr * row_bytes, ld_lane[i], dst + (8 * i + wave) * 1024);
+        if (wave == 0) load16_to_lds(vec_src + rr * vec_row_bytes, vec_lane, dst + 16 * TILE);
+    };
+    f32x16 bt[2], acc[2];           // bias tiles times sqrt(d), the same for every batch row; lane = query i, register v = key 8 (v / 4) + 4 hf + v % 4
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        float4 rows[4];
+        bias_tile_fetch(rows, a.biasA, h, nt, it < nt ? it : nt - 1, jt + t < nt ? jt + t : nt - 1, lane);
+        rows_to_acc(bt[t], rows);
+        acc[t] = zero16();
+    }
+    // (through the scalar cache: a vector load would count among the loads of stage())
+    typedef const uint32_t __attribute__((address_space(4)))* scalar_words;
+    const scalar_words live = (scalar_words)(uintptr_t)(a.live + (jt < nt ? jt : nt - 1));
+    const int live1 = jt + 1 < nt ? 1 : 0;
+    uint32_t lv0 = live[(size_t)r_begin * nt], lv1 = live[(size_t)r_begin * nt + live1];
+    __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0): from here on the counter counts the loads of stage() alone
+#pragma unroll
+    for (int x = 0; x < kDbRing - 1; ++x) stage(r_begin + x);
+    const Frag one = one_side(hf);
+    const int off = db_rows_lane<D>(col, hf);
+    for (int r = r_begin; r < r_end; ++r) {
+        // row r has arrived when at most the loads of rows r + 1 .. r + kDbRing - 2 are on their way
+        constexpr int N0 = (kDbRing - 2) * (NLW + 1), N = (kDbRing - 2) * NLW;
+        static_assert(N0 < 16, "fits the low bits of the wait count");
+        // (and lgkmcnt(0): the wavefront's reads of row r - 1, whose slot is filled next, are complete)
+        if (wave == 0) __builtin_amdgcn_s_waitcnt(0x0070 | N0);
+        else __builtin_amdgcn_s_waitcnt(0x0070 | N);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        stage(r + kDbRing - 1);
+        const uint32_t cur0 = lv0, cur1 = lv1;
+        const size_t rn = (size_t)(r + 1 < r_end ? r + 1 : r) * nt;
+        lv0 = live[rn];
+        lv1 = live[rn + live1];
+        if (active) {
+            const unsigned char* st = s_db + ((r - r_begin) % kDbRing) * STAGE;
+            Frag qf[KS], dcf[KS], kf[2][KS], vf[2][KS];
+            auto frag = [&](Frag (&f)[KS], int o) __attribute__((always_inline)) {
+#pragma unroll
+                for (int c = 0; c < KS; ++c) f[c].u = *reinterpret_cast<const uint4*>(st + o * TILE + (off ^ (32 * c)));
+                if (D == 8 && hf) f[0].u = make_uint4(0, 0, 0, 0);
+            };
+            frag(qf, wi);
+            frag(kf[0], 8 + 2 * wj);
+            frag(kf[1], 9 + 2 * wj);
+            frag(dcf, 4 + wi);
+            frag(vf[0], 12 + 2 * wj);
+            frag(vf[1], 13 + 2 * wj);
+            const float lse = *reinterpret_cast<const float*>(st + 16 * TILE + (wi * 32 + col) * 4);
+            const float delta = *reinterpret_cast<const float*>(st + 16 * TILE + 512 + (wi * 32 + col) * 4);
+            const Frag kx[2] = {key_side((cur0 >> col) & 1u, hf), key_side((cur1 >> col) & 1u, hf)};
+            f32x16 s[2], dp[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kx[t].v, one.v, bt[t], 0, 0, 0);
+                dp[t] = zero16();
+            }
+#pragma unroll
+            for (int c = 0; c < KS; ++c)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t][c].v, qf[c].v, s[t], 0, 0, 0);
+                    dp[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t][c].v, dcf[c].v, dp[t], 0, 0, 0);
+                }
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[t][v] += __builtin_amdgcn_exp2f(s[t][v] * a.qscale2 - lse) * (dp[t][v] - delta);
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);                    // (no load may write LDS after the block has ended)
+    if (!active) return;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        if (jt + t >= nt) break;
+        if (a.row_chunks > 1) {
+            float* part = a.dbias_part + ((((size_t)chunk * a.H + h) * nt + it) * nt + jt + t) * 1024 + lane * 4;
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                *reinterpret_cast<float4*>(part + 256 * g) = make_float4(acc[t][4 * g], acc[t][4 * g + 1], acc[t][4 * g + 2], acc[t][4 * g + 3]);
+        } else {
+            const int i = 32 * it + col;
+            float* drow = a.dbias + ((size_t)h * a.L + i) * a.L;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int j = 32 * (jt + t) + 8 * (v >> 2) + 4 * hf + (v & 3);
+                if (i < a.L && j < a.L) drow[j] = acc[t][v];
+            }
         }
     }
 }
 
-// dbias = sum over the row chunks of the partial sums, in chunk order (deterministic)
+// dbias = sum over the row chunks of the partial sums, in chunk order (deterministic).  A block per tile: eight threads take the 32
+// entries of a row, so that 128 bytes of a row are written together; entry 8 g + 4 hf .. of row i lies at lane 32 hf + i of group g.
 __global__ __launch_bounds__(256) void k_bwd_dbias_reduce(Args a) {
-    const size_t n = (size_t)a.H * a.L * a.L;
-    for (size_t x = (size_t)blockIdx.x * 256 + threadIdx.x; x < n; x += (size_t)gridDim.x * 256) {
-        float t = 0.f;
-        for (int c = 0; c < a.row_chunks; ++c) t += a.dbias_part[(size_t)c * n + x];
-        a.dbias[x] = t;
+    const int nt = a.Lp >> 5, tile = blockIdx.x, h = tile / (nt * nt), rem = tile - h * nt * nt;
+    const int x = threadIdx.x >> 3, c = threadIdx.x & 7, i = 32 * (rem / nt) + x, j = 32 * (rem % nt) + 4 * c;
+    const size_t n = (size_t)a.H * nt * nt * 1024;
+    const float* p = a.dbias_part + (size_t)tile * 1024 + 256 * (c >> 1) + (32 * (c & 1) + x) * 4;
+    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int k = 0; k < a.row_chunks; ++k) {
+        const float4 y = *reinterpret_cast<const float4*>(p + k * n);
+        t.x += y.x; t.y += y.y; t.z += y.z; t.w += y.w;
+    }
+    if (i >= a.L) return;
+    float* d = a.dbias + ((size_t)h * a.L + i) * a.L + j;
+    if ((a.L & 3) == 0) {
+        if (j < a.L) *reinterpret_cast<float4*>(d) = t;
+    } else {
+        const float e[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (j + k < a.L) d[k] = e[k];
     }
 }
 
@@ -791,9 +1122,9 @@ static int dbias_chunks(const ff_core_desc& d) {
 size_t core_backward_workspace(const ff_core_desc& d) {
     const size_t Lp = bwd::round_up(d.length, 32), rh = (size_t)d.rows * d.heads;
     const int chunks = dbias_chunks(d);
-    return bwd::align256(Lp * 4) + 2 * bwd::align256(rh * Lp * 4) + bwd::align256(rh * d.length * d.head_dim * 2) +
-           2 * bwd::align256((size_t)d.heads * Lp * Lp * 4) +
-           (chunks > 1 ? bwd::align256((size_t)chunks * d.heads * d.length * d.length * 4) : 0);
+    return bwd::align256(Lp * 4) + bwd::align256(2 * rh * Lp * 4) + bwd::align256((size_t)d.rows * (Lp / 32) * 4) +
+           bwd::align256(rh * d.length * d.head_dim * 2) + 2 * bwd::align256((size_t)d.heads * Lp * Lp * 4) +
+           (chunks > 1 ? bwd::align256((size_t)chunks * d.heads * Lp * Lp * 4) : 0);
 }
 
 ff_status core_backward_run(const ff_core_desc& d, const void* q, const void* k, const void* v, const void* g, const float* bias,
@@ -809,8 +1140,9 @@ ff_status core_backward_run(const ff_core_desc& d, const void* q, const void* k,
     a.ones = (float*)p; p += align256((size_t)a.Lp * 4);
     a.mrow = mask ? mask : a.ones;
     a.mstride = mask ? d.length : 0;
-    a.lse = (float*)p; p += align256(rh * a.Lp * 4);
-    a.delta = (float*)p; p += align256(rh * a.Lp * 4);
+    a.lse = (float*)p; p += align256(2 * rh * a.Lp * 4);
+    a.delta = a.lse + a.Lp;
+    a.live = (uint32_t*)p; p += align256((size_t)d.rows * (a.Lp / 32) * 4);
     a.dctx = (bf16_t*)p; p += align256(rh * d.length * d.head_dim * 2);
     const size_t bbytes = align256((size_t)d.heads * a.Lp * a.Lp * 4);
     a.biasA = (float*)p; p += bbytes;
@@ -825,7 +1157,6 @@ ff_status core_backward_run(const ff_core_desc& d, const void* q, const void* k,
     a.scale = 1.f / sqrtf((float)d.head_dim);
     a.sqrt_d = sqrtf((float)d.head_dim);
     const int nt = a.Lp / 32;
-    const dim3 g2((unsigned)((size_t)a.row_chunks * d.heads * ((nt + 3) / 4) * ((nt + 3) / 4)));
     const bool full = d.length % 32 == 0;        // nothing out of range: the kernels without bounds checks
 #define FF_BWD_D(KERNEL, GRID, DV)                                                                       \
     do {                                                                                                 \
@@ -841,39 +1172,59 @@ ff_status core_backward_run(const ff_core_desc& d, const void* q, const void* k,
         else if (d.head_dim == 16) FF_BWD_D(KERNEL, GRID, 16);                                           \
         else FF_BWD_D(KERNEL, GRID, 32);                                                                 \
     } while (0)
-    if (bias || !mask) {
+    const bool in_lds = nt <= kRowsTiles;                   // (longer sequences: the three kernels that pass the other side through LDS)
+    if (bias || (!mask && !in_lds)) {
         Timed t(KK_BWD_STATS, st);
-        const unsigned blocks = bias ? (unsigned)(((size_t)d.heads * nt * nt + 3) / 4) : 1u;
-        hipLaunchKernelGGL(k_bwd_prepare, dim3(blocks), dim3(256), 0, st, a);
+        const size_t tasks = bias ? (size_t)d.heads * nt * nt + (size_t)d.rows * ((nt + 1) / 2) : 1;
+        hipLaunchKernelGGL(k_bwd_prepare, dim3((unsigned)((tasks + 3) / 4)), dim3(256), 0, st, a);
     }
-    const dim3 g4((unsigned)(rh * ((nt + 3) / 4)));          // blocks of four tiles of one (row, head)
-    FF_BWD(k_bwd_stats, g4, KK_BWD_STATS);
-    FF_BWD(k_bwd_dq, g4, KK_BWD_DQ);
-    FF_BWD(k_bwd_dkv, g4, KK_BWD_DKV);
+    hipError_t attr = hipSuccess;
+    if (in_lds) {
+        Timed t(KK_BWD_ROWS, st);
+        constexpr int lds_tile = 4 * 2048 + 2 * 128;         // q, k, v, dctx, logsumexp and delta of 32 positions
+#define FF_BWD_ROWS(DV, BV)                                                                                      \
+    do {                                                                                                         \
+        static const hipError_t once = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bwd_rows<DV, BV>),  \
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, kRowsTiles * lds_tile); \
+        attr = once;                                                                                             \
+        if (once == hipSuccess) hipLaunchKernelGGL((k_bwd_rows<DV, BV>), dim3((unsigned)rh), dim3(64 * nt), nt * lds_tile, st, a); \
+    } while (0)
+        if (d.head_dim == 8) { if (bias) FF_BWD_ROWS(8, true); else FF_BWD_ROWS(8, false); }
+        else if (d.head_dim == 16) { if (bias) FF_BWD_ROWS(16, true); else FF_BWD_ROWS(16, false); }
+        else { if (bias) FF_BWD_ROWS(32, true); else FF_BWD_ROWS(32, false); }
+#undef FF_BWD_ROWS
+        if (attr != hipSuccess) return fail(FF_EHIP, "k_bwd_rows: dynamic LDS limit: %s", hipGetErrorString(attr));
+    } else {
+        const dim3 g4((unsigned)(rh * ((nt + 3) / 4)));      // blocks of four tiles of one (row, head)
+        FF_BWD(k_bwd_stats, g4, KK_BWD_STATS);
+        FF_BWD(k_bwd_dq, g4, KK_BWD_DQ);
+        FF_BWD(k_bwd_dkv, g4, KK_BWD_DKV);
+    }
+#undef FF_BWD
+#undef FF_BWD_D
     if (bias) {
         {
             Timed t(KK_BWD_DBIAS, st);
-            hipError_t attr = hipSuccess;
-#define FF_BWD_DB(DV, FV)                                                                                        \
+            const dim3 g2((unsigned)((size_t)a.row_chunks * d.heads * ((nt + 3) / 4) * ((nt + 3) / 4)));
+#define FF_BWD_DB(DV)                                                                                            \
     do {                                                                                                         \
-        static const hipError_t once = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bwd_dbias<DV, FV>), \
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kDbStage); \
+        constexpr int lds = kDbRing * (16 * 64 * DV + 1024);                                                     \
+        static const hipError_t once = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bwd_dbias<DV>),     \
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);    \
         attr = once;                                                                                             \
-        if (once == hipSuccess) hipLaunchKernelGGL((k_bwd_dbias<DV, FV>), g2, dim3(1024), 2 * kDbStage, st, a);  \
+        if (once == hipSuccess) hipLaunchKernelGGL((k_bwd_dbias<DV>), g2, dim3(512), lds, st, a);               \
     } while (0)
-            if (d.head_dim == 8) { if (full) FF_BWD_DB(8, true); else FF_BWD_DB(8, false); }
-            else if (d.head_dim == 16) { if (full) FF_BWD_DB(16, true); else FF_BWD_DB(16, false); }
-            else { if (full) FF_BWD_DB(32, true); else FF_BWD_DB(32, false); }
+            if (d.head_dim == 8) FF_BWD_DB(8);
+            else if (d.head_dim == 16) FF_BWD_DB(16);
+            else FF_BWD_DB(32);
 #undef FF_BWD_DB
             if (attr != hipSuccess) return fail(FF_EHIP, "k_bwd_dbias: dynamic LDS limit: %s", hipGetErrorString(attr));
         }
         if (a.row_chunks > 1) {
             Timed t(KK_BWD_DBIAS, st);
-            hipLaunchKernelGGL(k_bwd_dbias_reduce, dim3(1024), dim3(256), 0, st, a);
+            hipLaunchKernelGGL(k_bwd_dbias_reduce, dim3((unsigned)((size_t)d.heads * nt * nt)), dim3(256), 0, st, a);
         }
     }
-#undef FF_BWD
-#undef FF_BWD_D
     return check_launch("attention core backward");
 }
 

@@ -77,6 +77,19 @@ def test_ragged_shapes(rows, heads, length, d, bias, mask):
     check_all(case, run(case), oracle(case), spec.name)
 
 
+@pytest.mark.parametrize("rows,heads,length,d,bias,mask", [
+    (2, 2, 32, 32, True, "tail:3"),                                                   # one wavefront
+    (2, 1, 257, 8, True, "random:0.8"), (1, 2, 320, 16, False, "tail:40"), (2, 1, 479, 32, True, "random:0.7"),
+    (1, 2, 512, 32, True, "tail:33"),                                                # the longest that one block takes whole
+    (1, 1, 513, 32, True, "random:0.9"), (1, 1, 540, 16, False, "tail:9"),          # the kernels for longer sequences
+])
+def test_lengths_around_the_limits_of_a_block(rows, heads, length, d, bias, mask):
+    """Up to 512 positions a block holds a whole (row, head), a wavefront per 32 positions; beyond, three kernels pass tiles."""
+    spec = I.CoreSpec(f"t_core_limits_{rows}_{heads}_{length}_{d}_{int(bias)}_{mask}", rows, heads, length, d, bias, mask)
+    case = I.make_core_case(spec)
+    check_all(case, run(case), oracle(case), spec.name)
+
+
 def test_fully_masked_rows_have_zero_gradients():
     spec = I.CoreSpec("t_core_dead", 4, 2, 50, 32, True, "random:0.8")
     case = I.make_core_case(spec)
