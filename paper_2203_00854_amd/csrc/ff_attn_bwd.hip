@@ -114,24 +114,30 @@ __global__ __launch_bounds__(256) void k_bwd_prepare(Args a) {
         return;
     }
     // The bias tile (it, jt) of head h, times sqrt(D), as the accumulator of the logits holds it: float4 g of
-    // lane (col, hf) = entries 8 g + 4 hf .. + 3 along the register axis.  biasA: lane = query i0 + col, registers
-    // along the keys; biasK: lane = key j0 + col, registers along the queries.  Zeros outside [0, L)^2.
+    // lane (col, hf) = entries 8 g + 4 hf .. + 3 along the register axis.  biasK: lane = key j0 + col, registers
+    // along the queries, as the rows are read (128 bytes of a row per half-wave); biasA: lane = query i0 + col, registers along the
+    // keys, through the wavefront's own LDS tile.  Zeros outside [0, L)^2.
+    __shared__ float s_t[4][32 * 33];
     const int h = task / (nt * nt), rem = task - h * nt * nt, it = rem / nt, jt = rem - it * nt;
     const float* bh = a.bias + (size_t)h * a.L * a.L;
     float* ta = a.biasA + (size_t)task * 1024 + lane * 4;
     float* tk = a.biasK + (size_t)task * 1024 + lane * 4;
+    float* t = s_t[wave];
+    float vk[16];
+    const int j = jt * 32 + col, jc = j < a.L ? j : a.L - 1;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int i = it * 32 + 8 * (v >> 2) + 4 * hf + (v & 3);
+        const float x = bh[(size_t)(i < a.L ? i : a.L - 1) * a.L + jc];
+        vk[v] = i < a.L && j < a.L ? x * a.sqrt_d : 0.f;
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) t[(8 * (v >> 2) + 4 * hf + (v & 3)) * 33 + col] = vk[v];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-        float va[4], vk[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int x = 8 * g + 4 * hf + e;
-            const int ia = it * 32 + col, ja = jt * 32 + x, ik = it * 32 + x, jk = jt * 32 + col;
-            va[e] = (ia < a.L && ja < a.L) ? bh[(size_t)ia * a.L + ja] * a.sqrt_d : 0.f;
-            vk[e] = (ik < a.L && jk < a.L) ? bh[(size_t)ik * a.L + jk] * a.sqrt_d : 0.f;
-        }
-        *reinterpret_cast<float4*>(ta + 256 * g) = make_float4(va[0], va[1], va[2], va[3]);
-        *reinterpret_cast<float4*>(tk + 256 * g) = make_float4(vk[0], vk[1], vk[2], vk[3]);
+        *reinterpret_cast<float4*>(tk + 256 * g) = make_float4(vk[4 * g], vk[4 * g + 1], vk[4 * g + 2], vk[4 * g + 3]);
+        const float* u = t + col * 33 + 8 * g + 4 * hf;
+        *reinterpret_cast<float4*>(ta + 256 * g) = make_float4(u[0], u[1], u[2], u[3]);
     }
 }
 
@@ -711,7 +717,9 @@ __global__ __launch_bounds__(64 * kRowsTiles, 4) void k_bwd_rows(Args a) {
     unsigned char *s_q = smem, *s_k = smem + nt * 2048, *s_v = smem + nt * 4096, *s_d = smem + nt * 6144;
     float *s_lse = reinterpret_cast<float*>(smem + nt * 8192), *s_nd = s_lse + 32 * nt;       // logsumexp and -delta of the queries
     const int n = 32 * wave + col, nc = n < a.L ? n : a.L - 1;     // the lane's query, later its key
-    const float* mrow = a.mask ? a.mask + (size_t)r * a.L : nullptr;
+    // (without a mask a stand-in is read and not looked at: a load under a condition is a branch and a wait of its own)
+    const bool has_mask = a.mask != nullptr;
+    const float* mrow = has_mask ? a.mask + (size_t)r * a.L : reinterpret_cast<const float*>(a.q + base);
 
     // ---- q, k, v and dctx = dout * g (rounded to bf16) into LDS, everything in flight at once (a wavefront copies its own 32 positions)
     {
@@ -727,12 +735,12 @@ __global__ __launch_bounds__(64 * kRowsTiles, 4) void k_bwd_rows(Args a) {
             tv[x] = *reinterpret_cast<const uint4*>(a.v + at);
             td[x] = *reinterpret_cast<const uint4*>(a.dout + at);
             tg[x] = *reinterpret_cast<const uint4*>(a.g + at);
-            mk[x] = mrow ? mrow[rc] : 1.f;
+            mk[x] = mrow[rc];
         }
 #pragma unroll
         for (int x = 0; x < NL; ++x) {
             const int id = (lane + 64 * x) % (32 * PR), row = 32 * wave + id / PR;
-            const bool in = row < a.L, key = in && mk[x] != 0.f;
+            const bool in = row < a.L, key = in && (!has_mask || mk[x] != 0.f);
             const int at = row * 64 + (((id % PR) ^ piece_swizzle(row)) << 4);
             *reinterpret_cast<uint4*>(s_q + at) = only_if(in, tq[x]);
             *reinterpret_cast<uint4*>(s_k + at) = only_if(key, tk[x]);
@@ -742,7 +750,7 @@ __global__ __launch_bounds__(64 * kRowsTiles, 4) void k_bwd_rows(Args a) {
             if (BIAS && in) *reinterpret_cast<uint4*>(a.dctx + base + (size_t)row * D + 8 * (id % PR)) = dc;
         }
     }
-    const uint32_t keep = n < a.L && (!mrow || mrow[nc] != 0.f) ? 0xffffffffu : 0u;      // all ones if the lane's key is attended to
+    const uint32_t keep = n < a.L && (!has_mask || mrow[nc] != 0.f) ? 0xffffffffu : 0u;      // all ones if the lane's key is attended to
     // (which keys are attended to, one bit per key: in the place of the statistics, which come later)
     uint32_t* s_live = reinterpret_cast<uint32_t*>(s_lse);
     {
@@ -927,12 +935,13 @@ __global__ __launch_bounds__(64 * kRowsTiles, 4) void k_bwd_rows(Args a) {
 }
 
 // ====================================================================================
-// dbias: block = eight wavefronts = a patch of 4 x 4 tiles of one head and one chunk of batch rows; wavefront (wi, wj) sums dS of
-// the tiles (it0 + wi, jt0 + 2 wj), (it0 + wi, jt0 + 2 wj + 1) over the rows of the chunk in registers.  Per batch row the patch
-// needs the q and dctx rows of four query tiles, the k and v rows of four key tiles and logsumexp and delta of its
-// 128 queries: 33 KiB for 16 tiles, by loads that write LDS directly (rows swizzled by the source address) into a ring of
-// kDbRing rows, kDbRing - 1 rows ahead, one barrier per row.  Positions beyond L are the last one again: their entries
-// are not stored.
+// dbias: block = sixteen wavefronts = a patch of 4 x 4 tiles of one head and one chunk of batch rows; wavefront (wi, wj) sums dS of
+// tile (it0 + wi, jt0 + wj) over the rows of the chunk in registers.  Per batch row the patch needs the q and dctx rows of
+// four query tiles, the k and v rows of four key tiles and logsumexp and delta of its 128 queries: 33 KiB for 16 tiles, by
+// loads that write LDS directly (rows swizzled by the source address) into a ring of kDbRing rows, kDbRing - 1 rows ahead, one
+// barrier per row.  Positions beyond L are the last one again: their entries are not stored.
+// At 128 rows x 8 heads x 256 x 32 it takes 27 us (two tiles per wavefront, two wavefronts per SIMD: 31): about 1.05 us per batch row and block,
+// 85 vector instructions per tile at four wavefronts per SIMD, and at the same time 33 KiB per block and row out of L2.
 constexpr int kDbRing = 4;
 constexpr int kDbStage = 16 * 2048 + 1024;                // 16 operand tiles [32][64 bytes], then logsumexp [128] and delta [128]
 typedef void __attribute__((address_space(3)))* lds_void;
@@ -944,17 +953,21 @@ __device__ __forceinline__ int db_rows_lane(int col, int hf) {
     return D == 16 ? col * 32 + ((hf ^ ((col >> 3) & 1)) << 4) : col * 16;
 }
 template <int D>
-__global__ __launch_bounds__(512, 2) void k_bwd_dbias(Args a) {
+__global__ __launch_bounds__(1024, 4) void k_bwd_dbias(Args a) {
     constexpr int KS = (D + 15) / 16, TILE = 64 * D, STAGE = 16 * TILE + 1024;
-    constexpr int NLW = D / 8;                             // loads of 1 KiB per wavefront and batch row (16 tiles, eight wavefronts)
+    constexpr int NLW = D / 16;                            // loads of 1 KiB per wavefront and batch row; D = 8: one by each of the first eight wavefronts
+    constexpr int NL = D == 8 ? 1 : NLW;
     static_assert(STAGE <= kDbStage, "a batch row fits its place in the ring");
     extern __shared__ __attribute__((aligned(16))) unsigned char s_db[];
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, hf = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wi = wave >> 1, wj = wave & 1;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wi = wave >> 2, wj = wave & 3;
     const int nt = a.Lp >> 5, np = (nt + 3) >> 2;
-    const int chunk = blockIdx.x / (a.H * np * np), rem = blockIdx.x - chunk * a.H * np * np;
+    // (an XCD takes a contiguous range of the order chunk, head, patch: the patches of a head that share operand rows share its L2)
+    const int per_xcd = (int)(gridDim.x >> 3), item = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if (item >= a.row_chunks * a.H * np * np) return;      // (whole block)
+    const int chunk = item / (a.H * np * np), rem = item - chunk * a.H * np * np;
     const int h = rem / (np * np), pp = rem - h * np * np, it0 = 4 * (pp / np), jt0 = 4 * (pp - (pp / np) * np);
-    const int it = it0 + wi, jt = jt0 + 2 * wj;            // (the wavefront's tiles: (it, jt), (it, jt + 1))
+    const int it = it0 + wi, jt = jt0 + wj;
     const bool active = it < nt && jt < nt;
     const int r_begin = chunk * a.rows_per_chunk;
     const int r_end = r_begin + a.rows_per_chunk < a.R ? r_begin + a.rows_per_chunk : a.R;
@@ -962,119 +975,118 @@ __global__ __launch_bounds__(512, 2) void k_bwd_dbias(Args a) {
 
     // ---- the wavefront's loads: lane i of a load fills 16-byte slot i of its KiB of the stage
     const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lds_void)s_db);
-    const char* ld_src[NLW];                               // (scalar) tensor at batch row 0 and this head
-    uint32_t ld_lane[NLW];
+    const char* ld_src[NL];                                // (scalar) tensor at this head of the next batch row to request
+    uint32_t ld_lane[NL];
 #pragma unroll
-    for (int i = 0; i < NLW; ++i) {
-        const int c = 8 * i + wave;                        // KiB of the stage: half a tile, a tile or two tiles
+    for (int i = 0; i < NL; ++i) {
+        const int c = D == 8 ? wave & 7 : 16 * i + wave;                  // KiB of the stage: half a tile, a tile or two tiles
         const int o = D == 32 ? c >> 1 : (D == 16 ? c : 2 * c);
         const bf16_t* t = o < 4 ? a.q : (o < 8 ? a.dctx : (o < 12 ? a.k : a.v));
-        ld_src[i] = reinterpret_cast<const char*>(t + (size_t)h * a.L * D);
+        ld_src[i] = reinterpret_cast<const char*>(t + ((size_t)r_begin * a.H + h) * a.L * D);
         const int row = D == 32 ? 16 * (c & 1) + (lane >> 2) : (D == 16 ? lane >> 1 : lane & 31);
         const int piece = D == 32 ? (lane & 3) ^ ((lane >> 4) & 3) : (D == 16 ? (lane & 1) ^ ((lane >> 4) & 1) : 0);
         const int tile = (o & 3) + (D == 8 ? lane >> 5 : 0) + (o < 8 ? it0 : jt0);
         const int pos = 32 * tile + row < a.L ? 32 * tile + row : a.L - 1;
         ld_lane[i] = (uint32_t)(pos * 2 * D + piece * 16);
     }
-    // (logsumexp by lanes 0 .. 31, delta by lanes 32 .. 63, in wavefront 0)
+    // (logsumexp by lanes 0 .. 31, delta by lanes 32 .. 63, in the last wavefront)
     const int vq = 32 * it0 + 4 * col < a.Lp ? 32 * it0 + 4 * col : a.Lp - 4;
-    const char* vec_src = reinterpret_cast<const char*>(a.lse + (size_t)h * 2 * a.Lp);
+    const char* vec_src = reinterpret_cast<const char*>(a.lse + ((size_t)r_begin * a.H + h) * 2 * a.Lp);
     const uint32_t vec_lane = (uint32_t)((hf * a.Lp + vq) * 4);
     const size_t row_bytes = (size_t)a.H * a.L * D * 2, vec_row_bytes = (size_t)a.H * 2 * a.Lp * 4;
-    auto stage = [&](int r) __attribute__((always_inline)) {
-        const int rr = r < r_end ? r : r_end - 1;          // (past the end: the last row again, into a slot that nobody reads)
-        const unsigned dst = lds0 + (unsigned)((r - r_begin) % kDbRing) * STAGE;
+    // Requests the next batch row (past the end: the last one again, into a slot that nobody reads).  Everything moves on by additions: a CU has
+    // one scalar unit for its sixteen wavefronts, and products of row numbers and strides took it half of a row's time.
+    unsigned to_slot = 0;                                  // offset of the ring slot that is filled next
+    int to_row = r_begin;
+    auto stage = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < NLW; ++i) load16_to_lds(ld_src[i] + rr * row_bytes, ld_lane[i], dst + (8 * i + wave) * 1024);
-        if (wave == 0) load16_to_lds(vec_src + rr * vec_row_bytes, vec_lane, dst + 16 * TILE);
+        for (int i = 0; i < NL; ++i)
+            if (D > 8 || wave < 8) load16_to_lds(ld_src[i], ld_lane[i], lds0 + to_slot + (16 * i + wave) * 1024);
+        if (wave == 15) load16_to_lds(vec_src, vec_lane, lds0 + to_slot + 16 * TILE);
+        to_slot = to_slot + STAGE < kDbRing * STAGE ? to_slot + STAGE : 0;
+        if (++to_row < r_end) {
+#pragma unroll
+            for (int i = 0; i < NL; ++i) ld_src[i] += row_bytes;
+            vec_src += vec_row_bytes;
+        }
     };
-    f32x16 bt[2], acc[2];           // bias tiles times sqrt(d), the same for every batch row; lane = query i, register v = key 8 (v / 4) + 4 hf + v % 4
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    f32x16 bt, acc = zero16();      // bias tile times sqrt(d), the same for every batch row; lane = query i, register v = key 8 (v / 4) + 4 hf + v % 4
+    {
         float4 rows[4];
-        bias_tile_fetch(rows, a.biasA, h, nt, it < nt ? it : nt - 1, jt + t < nt ? jt + t : nt - 1, lane);
-        rows_to_acc(bt[t], rows);
-        acc[t] = zero16();
+        bias_tile_fetch(rows, a.biasA, h, nt, it < nt ? it : nt - 1, jt < nt ? jt : nt - 1, lane);
+        rows_to_acc(bt, rows);
     }
     // (through the scalar cache: a vector load would count among the loads of stage())
     typedef const uint32_t __attribute__((address_space(4)))* scalar_words;
-    const scalar_words live = (scalar_words)(uintptr_t)(a.live + (jt < nt ? jt : nt - 1));
-    const int live1 = jt + 1 < nt ? 1 : 0;
-    uint32_t lv0 = live[(size_t)r_begin * nt], lv1 = live[(size_t)r_begin * nt + live1];
+    scalar_words live = (scalar_words)(uintptr_t)(a.live + (size_t)r_begin * nt + (jt < nt ? jt : nt - 1));
+    uint32_t lv = *live;
     __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0): from here on the counter counts the loads of stage() alone
 #pragma unroll
-    for (int x = 0; x < kDbRing - 1; ++x) stage(r_begin + x);
+    for (int x = 0; x < kDbRing - 1; ++x) stage();
     const Frag one = one_side(hf);
     const int off = db_rows_lane<D>(col, hf);
-    for (int r = r_begin; r < r_end; ++r) {
-        // row r has arrived when at most the loads of rows r + 1 .. r + kDbRing - 2 are on their way
-        constexpr int N0 = (kDbRing - 2) * (NLW + 1), N = (kDbRing - 2) * NLW;
-        static_assert(N0 < 16, "fits the low bits of the wait count");
-        // (and lgkmcnt(0): the wavefront's reads of row r - 1, whose slot is filled next, are complete)
-        if (wave == 0) __builtin_amdgcn_s_waitcnt(0x0070 | N0);
-        else __builtin_amdgcn_s_waitcnt(0x0070 | N);
+    // the wavefront's operands of one batch row, read from LDS while the previous row's weights are formed
+    Frag qf[KS], dcf[KS], kf[KS], vf[KS];
+    float lse, delta;
+    const unsigned char* st = s_db;                       // slot of the next row to read
+    auto read = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < KS; ++c) {
+            qf[c].u = *reinterpret_cast<const uint4*>(st + wi * TILE + (off ^ (32 * c)));
+            kf[c].u = *reinterpret_cast<const uint4*>(st + (8 + wj) * TILE + (off ^ (32 * c)));
+            dcf[c].u = *reinterpret_cast<const uint4*>(st + (4 + wi) * TILE + (off ^ (32 * c)));
+            vf[c].u = *reinterpret_cast<const uint4*>(st + (12 + wj) * TILE + (off ^ (32 * c)));
+        }
+        if (D == 8 && hf) qf[0].u = kf[0].u = dcf[0].u = vf[0].u = make_uint4(0, 0, 0, 0);
+        lse = *reinterpret_cast<const float*>(st + 16 * TILE + (wi * 32 + col) * 4);
+        delta = *reinterpret_cast<const float*>(st + 16 * TILE + 512 + (wi * 32 + col) * 4);
+        st = st + STAGE < s_db + kDbRing * STAGE ? st + STAGE : s_db;
+    };
+    // Row r has arrived when at most the loads of the AHEAD rows behind it are on their way.  (And lgkmcnt(0): the wavefront's reads of the
+    // row before, whose slot is filled next, are complete.)
+    constexpr int AHEAD = kDbRing - 2;
+    auto arrived = [&]() __attribute__((always_inline)) {
+        if (wave == 15) __builtin_amdgcn_s_waitcnt(0x0070 | AHEAD * (NLW + 1));
+        else __builtin_amdgcn_s_waitcnt(0x0070 | AHEAD * NL);
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        stage(r + kDbRing - 1);
-        const uint32_t cur0 = lv0, cur1 = lv1;
-        const size_t rn = (size_t)(r + 1 < r_end ? r + 1 : r) * nt;
-        lv0 = live[rn];
-        lv1 = live[rn + live1];
+    };
+    arrived();
+    stage();
+    if (active) read();
+    for (int r = r_begin; r < r_end; ++r) {
+        arrived();                                         // row r + 1; row r has been read by everybody
+        stage();
         if (active) {
-            const unsigned char* st = s_db + ((r - r_begin) % kDbRing) * STAGE;
-            Frag qf[KS], dcf[KS], kf[2][KS], vf[2][KS];
-            auto frag = [&](Frag (&f)[KS], int o) __attribute__((always_inline)) {
+            const Frag kx = key_side((lv >> col) & 1u, hf);
+            f32x16 s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kx.v, one.v, bt, 0, 0, 0), dp = zero16();
 #pragma unroll
-                for (int c = 0; c < KS; ++c) f[c].u = *reinterpret_cast<const uint4*>(st + o * TILE + (off ^ (32 * c)));
-                if (D == 8 && hf) f[0].u = make_uint4(0, 0, 0, 0);
-            };
-            frag(qf, wi);
-            frag(kf[0], 8 + 2 * wj);
-            frag(kf[1], 9 + 2 * wj);
-            frag(dcf, 4 + wi);
-            frag(vf[0], 12 + 2 * wj);
-            frag(vf[1], 13 + 2 * wj);
-            const float lse = *reinterpret_cast<const float*>(st + 16 * TILE + (wi * 32 + col) * 4);
-            const float delta = *reinterpret_cast<const float*>(st + 16 * TILE + 512 + (wi * 32 + col) * 4);
-            const Frag kx[2] = {key_side((cur0 >> col) & 1u, hf), key_side((cur1 >> col) & 1u, hf)};
-            f32x16 s[2], dp[2];
+            for (int c = 0; c < KS; ++c) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[c].v, qf[c].v, s, 0, 0, 0);
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kx[t].v, one.v, bt[t], 0, 0, 0);
-                dp[t] = zero16();
-            }
+            for (int c = 0; c < KS; ++c) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[c].v, dcf[c].v, dp, 0, 0, 0);
+            const float l0 = lse, d0 = delta;
+            read();                                        // (past the end: a slot that holds the last row again)
+            if (r + 1 < r_end) live += nt;
+            lv = *live;
 #pragma unroll
-            for (int c = 0; c < KS; ++c)
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t][c].v, qf[c].v, s[t], 0, 0, 0);
-                    dp[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t][c].v, dcf[c].v, dp[t], 0, 0, 0);
-                }
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[t][v] += __builtin_amdgcn_exp2f(s[t][v] * a.qscale2 - lse) * (dp[t][v] - delta);
+            for (int v = 0; v < 16; ++v) acc[v] += __builtin_amdgcn_exp2f(s[v] * a.qscale2 - l0) * (dp[v] - d0);
         }
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);                    // (no load may write LDS after the block has ended)
     if (!active) return;
+    if (a.row_chunks > 1) {
+        float* part = a.dbias_part + ((((size_t)chunk * a.H + h) * nt + it) * nt + jt) * 1024 + lane * 4;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        if (jt + t >= nt) break;
-        if (a.row_chunks > 1) {
-            float* part = a.dbias_part + ((((size_t)chunk * a.H + h) * nt + it) * nt + jt + t) * 1024 + lane * 4;
+        for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<float4*>(part + 256 * g) = make_float4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
+    } else {
+        const int i = 32 * it + col;
+        float* drow = a.dbias + ((size_t)h * a.L + i) * a.L;
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
-                *reinterpret_cast<float4*>(part + 256 * g) = make_float4(acc[t][4 * g], acc[t][4 * g + 1], acc[t][4 * g + 2], acc[t][4 * g + 3]);
-        } else {
-            const int i = 32 * it + col;
-            float* drow = a.dbias + ((size_t)h * a.L + i) * a.L;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int j = 32 * (jt + t) + 8 * (v >> 2) + 4 * hf + (v & 3);
-                if (i < a.L && j < a.L) drow[j] = acc[t][v];
-            }
+        for (int v = 0; v < 16; ++v) {
+            const int j = 32 * jt + 8 * (v >> 2) + 4 * hf + (v & 3);
+            if (i < a.L && j < a.L) drow[j] = acc[v];
         }
     }
 }
@@ -1087,6 +1099,7 @@ __global__ __launch_bounds__(256) void k_bwd_dbias_reduce(Args a) {
     const size_t n = (size_t)a.H * nt * nt * 1024;
     const float* p = a.dbias_part + (size_t)tile * 1024 + 256 * (c >> 1) + (32 * (c & 1) + x) * 4;
     float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
     for (int k = 0; k < a.row_chunks; ++k) {
         const float4 y = *reinterpret_cast<const float4*>(p + k * n);
         t.x += y.x; t.y += y.y; t.z += y.z; t.w += y.w;
@@ -1205,14 +1218,14 @@ ff_status core_backward_run(const ff_core_desc& d, const void* q, const void* k,
     if (bias) {
         {
             Timed t(KK_BWD_DBIAS, st);
-            const dim3 g2((unsigned)((size_t)a.row_chunks * d.heads * ((nt + 3) / 4) * ((nt + 3) / 4)));
+            const dim3 g2((unsigned)(((size_t)a.row_chunks * d.heads * ((nt + 3) / 4) * ((nt + 3) / 4) + 7) / 8 * 8));
 #define FF_BWD_DB(DV)                                                                                            \
     do {                                                                                                         \
         constexpr int lds = kDbRing * (16 * 64 * DV + 1024);                                                     \
         static const hipError_t once = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bwd_dbias<DV>),     \
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);    \
         attr = once;                                                                                             \
-        if (once == hipSuccess) hipLaunchKernelGGL((k_bwd_dbias<DV>), g2, dim3(512), lds, st, a);               \
+        if (once == hipSuccess) hipLaunchKernelGGL((k_bwd_dbias<DV>), g2, dim3(1024), lds, st, a);               \
     } while (0)
             if (d.head_dim == 8) FF_BWD_DB(8);
             else if (d.head_dim == 16) FF_BWD_DB(16);
