@@ -475,10 +475,7 @@ static ff_status launch_d(const AttnRowsArgs& a, hipStream_t st) {
     if (nt <= 2) return a.bias ? launch<D, 2, 2, true>(a, st) : launch<D, 2, 2, false>(a, st);
     const bool few = (int64_t)((nt + 3) / 4) * ((a.rows + 3) / 4) * a.H < 2 * compute_units();
     if (a.bias) return few ? launch<D, 2, 4, true>(a, st) : launch<D, 4, 4, true>(a, st);
-    if constexpr (D == 32) {
-        if (!few) return launch<D, 4, 4, false>(a, st);
-    }
-    return launch<D, 2, 4, false>(a, st);
+    return launch<D, 2, 4, false>(a, st);                     // (at d = 32: 166 registers, three wavefronts per SIMD; four rows: 220, two)
 }
 
 ff_status attn_rows_launch(const AttnRowsArgs& a, int d, hipStream_t st) {

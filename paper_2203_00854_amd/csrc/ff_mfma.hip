@@ -28,7 +28,7 @@
 // 32-key tile is permuted; the same permutation is applied when K rows and V^T columns are
 // fetched, so nothing moves between the two contractions.
 //
-// Workspace layout of this family (Lp = Lq = L rounded up to 64, token p = rl*Lp + l):
+// Workspace layout of this family (Lp = Lq = L rounded up to 32, token p = rl*Lp + l):
 //   bias [H][Lq][Lp] float32 (times log2 e) in 32 x 32 tiles (bias_index); rows of pad queries are never written, and
 //   only the lanes of those queries, which store nothing, see them
 //   q, k, g, o [rows][H][Lp][D] bf16;  vt [rows][H][Lp/32][D][32] bf16
@@ -36,6 +36,8 @@
 // Pad tokens (l in [L, Lp)) hold finite values everywhere; they are masked as keys.
 #include "ff_attn_rows.h"
 #include "ff_common.h"
+
+#include <math.h>
 
 #include <type_traits>
 
@@ -94,7 +96,7 @@ struct MfmaWs {
 };
 
 static MfmaWs split_ws(const Problem& p, int chunk, const Workspace& ws) {
-    const size_t Lp = round_up(p.L, 64);
+    const size_t Lp = round_up(p.L, 32);
     const size_t n = (size_t)chunk * Lp * p.Hd;   // elements per tensor
     MfmaWs m;
     m.q = (bf16_t*)ws.qkvg;
@@ -124,7 +126,7 @@ bool mfma_supported(const Problem& p) {
 }
 
 size_t mfma_workspace(const Problem& p, int chunk, Workspace* ws, void* base) {
-    const size_t Lp = round_up(p.L, 64), Lq = round_up(p.L, 64);
+    const size_t Lp = round_up(p.L, 32), Lq = round_up(p.L, 32);
     size_t off = 0;
     char* b = (char*)base;
     ws->bias = nullptr;
@@ -384,12 +386,17 @@ __global__ __launch_bounds__(512) void k_prep_bias(PrepBiasArgs a) {
 }
 
 // ====================================================================================
-// GEMM with the whole contraction length (<= 256) resident: a wavefront owns TT 32-token
-// tiles as register-resident operand fragments and sweeps over 32-feature tiles of the
-// weight matrix.  The block streams those tiles through LDS with loads that write LDS
-// directly (global_load_lds_dwordx4: lane i of a wavefront deposits its 16 bytes at the
-// wave-uniform LDS base + 16 i), NS tiles per step, double buffered: the tiles of step i+1
-// are in flight while the matrix cores work on step i.
+// GEMM with the whole contraction length (<= 256) resident: a wavefront owns a 32-token tile as register-resident operand fragments
+// and sweeps over 32-feature tiles of the weight matrix, which the block keeps in LDS: all of them where they fit (no barrier after the
+// first, the wavefronts of the grid walk over the token tiles by themselves), else two halves of NS tiles each, one being
+// worked on while the other is filled (global_load_lds_dwordx4: lane i of a wavefront deposits its 16 bytes at the
+// wave-uniform LDS base + 16 i).
+// What bounds it is the number of instructions a wavefront can issue (one every eight cycles or so, whatever the others do): about 60 per
+// 32 x 32 tile beside KC + 1 matrix instructions.  So the registers are held to 128, sixteen wavefronts per compute unit, and a wavefront finishes a
+// tile before it begins the next one: the matrix instructions of one hide behind the epilogues of the other three of its SIMD.A kernel of
+// eight wavefronts with 186 to 250 registers that alternated the matrix instructions of a tile with the epilogue of the one before took
+// 150 to 200 instructions per tile: projections of 64 x 2048 tokens of 128 channels 46 -> 38 us, of 333 x 333 50 -> 40, of 60 x 300 of 256 channels 34 -> 29.5.
+// No instance may spill: a kernel that uses scratch memory starts 2.5 us later (8 x 48 row attention, projections 11.7 -> 9.2 us).
 //
 // LDS image of a tile: 32 rows of P = 2 KC 16-byte pieces, piece p of row r at slot
 // r P + (p ^ g(r)); g spreads 16 consecutive rows over the 16 slots of a 256-byte LDS line, so
@@ -412,182 +419,140 @@ struct GemmArgs {
     bf16_t* out;             // OUT output, token (r,l) at (r*sr + l*sl)*N
     const bf16_t* res;       // OUT with RES: added to the output, laid out like out (may be out itself)
     int N;                   // OUT: features
-    int ft_first, ft_count;  // range of feature tiles of this launch
+    int ft_count;            // feature tiles of this launch
     int tiles_per_split;     // tiles per blockIdx.y
 };
 
 typedef void __attribute__((address_space(3)))* lptr_t;
 
 // Wait until at most n (rounded down to 8, 4, 2 or 0) vector-memory operations of this wavefront
-// are outstanding.  They complete in order, so with n = number of stores issued after a load this
+// are outstanding, and none of its LDS reads.  They complete in order, so with n = number of stores issued after a load this
 // waits for the load but not for those stores.
 __device__ __forceinline__ void wait_vmem_but_last(int n) {
-    if (n >= 8) __builtin_amdgcn_s_waitcnt(0x0F78);
-    else if (n >= 4) __builtin_amdgcn_s_waitcnt(0x0F74);
-    else if (n >= 2) __builtin_amdgcn_s_waitcnt(0x0F72);
-    else __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    if (n >= 8) __builtin_amdgcn_s_waitcnt(0x0078);
+    else if (n >= 4) __builtin_amdgcn_s_waitcnt(0x0074);
+    else if (n >= 2) __builtin_amdgcn_s_waitcnt(0x0072);
+    else __builtin_amdgcn_s_waitcnt(0x0070);
 }
 
-// 16 bytes per lane from global memory straight into LDS at lds_base + 16 * lane (lds_base wave-uniform).
-// Written as assembly on purpose: the compiler would make every later LDS read wait for a load it
-// knows to write LDS, also those of the other half of the ring.  The kernel waits for these loads
-// itself (s_waitcnt vmcnt(0) before the barrier that publishes the tile).
-__device__ __forceinline__ void load16_to_lds(const void* gsrc, unsigned lds_base) {
-    const unsigned base = __builtin_amdgcn_readfirstlane(lds_base);
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(gsrc), "s"(base) : "memory", "m0");
-}
+constexpr int gemm_waves(int kc) { return kc >= 16 ? 12 : 16; }    // wavefronts per compute unit: four per SIMD, three where the tokens take 64 registers
+constexpr int gemm_half(int kc) { return kc >= 16 ? 4 : 9; }       // NS: weight tiles per half of the ring
 
-constexpr int kGemmWaves = 8;      // wavefronts per block: two per SIMD
-
-// dynamic LDS of k_gemm: weight ring, LayerNorm statistics, per-feature sums and offsets
-static size_t gemm_smem_bytes(int kc, int tt, int ns, int tiles_per_split) {
-    return (size_t)2 * ns * 32 * 2 * kc * 16 + (size_t)kGemmWaves * tt * 64 * 4 + (size_t)tiles_per_split * 32 * (4 + 16);
+// dynamic LDS of k_gemm: weight tiles, 1/std of the wavefronts' tokens, per-feature offsets and extra pieces
+static size_t gemm_smem_bytes(int kc, int tiles) {
+    const int held = tiles < 2 * gemm_half(kc) ? tiles : 2 * gemm_half(kc);
+    return (size_t)held * kc * 1024 + (size_t)gemm_waves(kc) * 32 * 4 + (size_t)tiles * 32 * (4 + 16);
 }
 
 // tile kinds of k_gemm (q and k share their epilogue)
 enum { TK_Q = 0, TK_K = 1, TK_V = 2, TK_GATE = 3, TK_BIAS = 4, TK_OUT = 5 };
 
-template <int KC, bool PROJ, int TT, int NS, bool RES>
-__global__ __launch_bounds__(kGemmWaves * 64, 2) void k_gemm(GemmArgs a) {
+template <int KC, bool PROJ, bool RES>
+__global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gemm(GemmArgs a) {
     static_assert(!(PROJ && RES), "the residual belongs to the output projection");
-    constexpr int NW = kGemmWaves;
+    constexpr int NS = gemm_half(KC);
     constexpr int P = 2 * KC;                           // 16-byte pieces per weight row
     constexpr int STAGE = 32 * P * 16;                  // bytes of one 32-feature tile in LDS
     constexpr int RSH = P >= 16 ? 0 : (P == 8 ? 1 : 2);
     constexpr int GM = (P >= 16 ? 16 : P) - 1;          // g(r) = (r >> RSH) & GM
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    unsigned char* s_w = smem;                                              // [2][NS][STAGE]
-    float* s_stat = reinterpret_cast<float*>(smem + 2 * NS * STAGE);        // [wave][tt][2][32]: 1/std of the wave's tokens in [1]
-    float* s_cn = s_stat + NW * TT * 64;                                     // OUT: [tiles_per_split][32] output bias
-    uint4* s_aug = reinterpret_cast<uint4*>(s_cn + a.tiles_per_split * 32);  // PROJ: [tiles_per_split][32] extra piece per feature
+    const int ft_begin = blockIdx.y * a.tiles_per_split;
+    const int ft_end = ft_begin + a.tiles_per_split < a.ft_count ? ft_begin + a.tiles_per_split : a.ft_count;
+    const int n_ft = ft_end - ft_begin;
+    const int NW = blockDim.x >> 6;                     // eight, or gemm_waves(KC)
+    const int tiles_m = a.rows * (a.Lp >> 5);
+    if (n_ft <= 0 || (int)blockIdx.x * NW >= tiles_m) return;            // (whole block)
+    const bool whole = n_ft <= 2 * NS;                                    // all of the block's weights are in LDS at once
+    unsigned char* s_w = smem;                                            // [min(n_ft, 2 NS)][STAGE]
+    uint4* s_aug = reinterpret_cast<uint4*>(smem + (whole ? n_ft : 2 * NS) * STAGE);      // PROJ: [n_ft][32] extra piece per feature
+    float* s_cn = reinterpret_cast<float*>(s_aug + n_ft * 32);            // OUT: [n_ft][32] output bias
+    float* s_rstd = s_cn + n_ft * 32;                                     // [wave][32]: 1/std of the wavefront's tokens
 
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, hf = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int K = a.K;
-    const int tiles_m = a.rows * (a.Lp >> 5);
-    const int ft_begin = a.ft_first + blockIdx.y * a.tiles_per_split;
-    int ft_end = ft_begin + a.tiles_per_split;
-    if (ft_end > a.ft_first + a.ft_count) ft_end = a.ft_first + a.ft_count;
-    if (ft_begin >= ft_end) return;     // (whole block)
 
     // ---- token operand fragments, raw (issued first: they come from HBM)
-    Frag xa[TT][KC];
-    bool tok_valid[TT], tile_off[TT];     // tile_off (wave-uniform): a repeated tile that must not be stored
-    int tok_rl[TT], tok_l[TT];            // batch row (wave-uniform) and position of this lane's token
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-        // (token tiles beyond the last one repeat it: the same values are stored twice)
-        int tg = (blockIdx.x * NW + wave) * TT + tt;
-        const bool repeated = tg > tiles_m - 1;
-        if (repeated) tg = tiles_m - 1;
-        const int p = tg * 32 + col;
-        const int rl = p / a.Lp, l = p - rl * a.Lp;
-        tok_rl[tt] = __builtin_amdgcn_readfirstlane(rl);       // a tile lies inside one batch row
-        tok_l[tt] = l;
-        // (with a residual that may be the output itself a tile must be added and stored once only)
-        tile_off[tt] = RES && repeated;
-        tok_valid[tt] = l < a.L && !tile_off[tt];
-        const bf16_t* sp = a.src + ((int64_t)(a.r0 + rl) * a.sr + (int64_t)l * a.sl) * K;
+    Frag xa[KC];
+    int rl = 0, l = 0;                    // batch row (wave-uniform) and position of this lane's token
+    bool valid = false;
+    uint32_t ahead[2] = {0u, 0u};
+    const int LpD = a.Lp * a.D;           // every tensor of this family has Lp*Hd elements per batch row
+    auto load_tokens = [&](int unit) __attribute__((always_inline)) {
+        const int tg = unit < tiles_m ? unit : tiles_m - 1;
+        // (a tile lies inside one batch row; neighbouring wavefronts take tokens that are neighbours in memory)
+        const int by = a.sl > a.sr ? a.rows : a.Lp >> 5, major = __builtin_amdgcn_readfirstlane(tg / by), minor = tg - major * by;
+        rl = a.sl > a.sr ? minor : major;
+        l = 32 * (a.sl > a.sr ? major : minor) + col;
+        valid = l < a.L;
+        // (no load sits under a condition: pad tokens repeat the last one, pieces beyond K the last one of the token, and are cleared below)
+        const int lc = valid ? l : a.L - 1;
+        const bf16_t* sp = PROJ ? a.src + ((int64_t)(a.r0 + rl) * a.sr + (int64_t)lc * a.sl) * K : nullptr;
+        const bf16_t* ctx = PROJ ? nullptr : a.src + (size_t)rl * a.H * LpD;
+        int half = hf;
+        asm volatile("" : "+v"(half));                                    // (the offsets below: worked out anew for every tile, not kept, or spilled)
 #pragma unroll
         for (int s = 0; s < KC; ++s) {
-            xa[tt][s].u = make_uint4(0, 0, 0, 0);
-            const int f = 16 * s + 8 * hf;
-            if constexpr (PROJ) {
-                if (tok_valid[tt] && f < K) xa[tt][s].u = ldg16(sp + f);
-            } else {
-                // gated context, head-major [row][head][l][d]
-                const int hh = (int)(((float)f + 0.5f) * a.invD);
-                if (tok_valid[tt] && f < K)
-                    xa[tt][s].u = ldg16(a.src + ((size_t)(rl * a.H + hh) * a.Lp + l) * a.D + (f - hh * a.D));
+            const int f = 16 * s + 8 * half < K ? 16 * s + 8 * half : K - 8;
+            const int hh = f >> a.dsh;                                    // OUT: gated context, head-major [row][head][l][d]
+            if constexpr (PROJ) xa[s].u = ldg16(sp + f);
+            else xa[s].u = ldg16(ctx, (uint32_t)(hh * LpD + lc * a.D + (f - (hh << a.dsh))) * 2);
+        }
+        if (l - col + 32 > a.L || K != 16 * KC) {                        // (wave-uniform)
+#pragma unroll
+            for (int s = 0; s < KC; ++s) {
+                const uint32_t m = valid && 16 * s + 8 * hf < K ? 0xffffffffu : 0u;
+                xa[s].u = make_uint4(xa[s].u.x & m, xa[s].u.y & m, xa[s].u.z & m, xa[s].u.w & m);
             }
         }
-    }
-
-    // ---- weight tiles: each wavefront moves KC/NW chunks of 64 pieces (1 KiB) of a tile.
-    // Pieces beyond K re-read the last valid piece (the token operand is zero there).
-    constexpr int IPW = KC >= NW ? KC / NW : 1;
-    int goff[IPW];
+        if constexpr (RES) {
+            // the residual's lines of the token tile into L2, a load per line (N <= 256: at most four per token): the
+            // loads below come one feature tile ahead of their use, too late for memory
 #pragma unroll
-    for (int j = 0; j < IPW; ++j) {
-        int chunk = j * NW + wave;
-        if (KC < NW && chunk >= KC) chunk = 0;
-        const int ps = chunk * 64 + lane, row = ps / P, pp = ps % P;
-        int kk = (pp ^ ((row >> RSH) & GM)) * 8;
-        if (kk > K - 8) kk = K - 8;
-        goff[j] = row * K + kk;
-    }
-    const unsigned s_w_lds = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lptr_t)s_w);
-    auto issue_tile = [&](int ft, int stage) {
-        const bf16_t* wt = a.w + (size_t)ft * 32 * K;
-#pragma unroll
-        for (int j = 0; j < IPW; ++j) {
-            const int chunk = j * NW + wave;
-            if (KC >= NW || chunk < KC) load16_to_lds(wt + goff[j], s_w_lds + stage * STAGE + chunk * 1024);
+            for (int i = 0; i < 2; ++i) {
+                const int line = (lane >> 5) + 2 * i, at = 64 * line < a.N ? 64 * line : 0;
+                ahead[i] = *reinterpret_cast<const uint32_t*>(a.res + (size_t)(((int64_t)(a.r0 + rl) * a.sr + (int64_t)lc * a.sl) * a.N) + at);
+            }
         }
     };
-    // steps 0 and 1 fill the two halves of the ring
-#pragma unroll
-    for (int n = 0; n < 2 * NS; ++n)
-        if (ft_begin + n < ft_end) issue_tile(ft_begin + n, n);
-    // per-feature sums / offsets of this block's tiles
-    for (int i = tid; i < (ft_end - ft_begin) * 32; i += NW * 64) {
-        if constexpr (PROJ) {
-            s_aug[i] = a.aug[ft_begin * 32 + i];
-        } else {
-            s_cn[i] = bf16_to_f32(a.bvec[ft_begin * 32 + i]);
+    int unit = blockIdx.x * NW + wave;
+    load_tokens(unit);
+
+    // ---- weight tiles: KC chunks of 64 pieces (1 KiB) each, shared out over the wavefronts: chunk c of a half goes to
+    // wavefront c % NW.  Pieces beyond K re-read the last valid piece (the token operand is zero there).
+    const unsigned s_w_lds = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(lptr_t)s_w);
+    auto issue = [&](int first, int count, int slot) __attribute__((always_inline)) {      // tiles first .. + count - 1 into the slots slot ..
+        for (int c = wave; c < count * KC; c += NW) {
+            const int ft = c / KC, ps = (c - ft * KC) * 64 + lane, row = ps / P;
+            int kk = ((ps % P) ^ ((row >> RSH) & GM)) * 8;
+            if (kk > K - 8) kk = K - 8;
+            ff::load16_to_lds(a.w + (size_t)(ft_begin + first + ft) * 32 * K, (uint32_t)(row * K + kk) * 2,
+                              s_w_lds + (unsigned)((slot + ft) * STAGE + (c - ft * KC) * 1024));
         }
+    };
+    issue(0, n_ft < 2 * NS ? n_ft : 2 * NS, 0);
+    // per-feature offsets of this block's tiles
+    for (int i = tid; i < n_ft * 32; i += NW * 64) {
+        if constexpr (PROJ) s_aug[i] = a.aug[ft_begin * 32 + i];
+        else s_cn[i] = bf16_to_f32(a.bvec[ft_begin * 32 + i]);
     }
     // operand read: piece 2s + hf of row col sits at byte rd0 ^ (32 s) of its tile
     const unsigned rd0 = (unsigned)col * (P * 16) + 16u * (unsigned)((((col >> RSH) & GM)) ^ hf);
-
-    // ---- epilogue addressing: every tensor of this family has Lp*Hd elements per batch row
-    const int LpD = a.Lp * a.D;
-    size_t row_base[TT];      // PROJ: element offset of the batch row in q, k, gate, v^T; OUT: of the token in out
-    int l0v[TT];
-    unsigned t_lane[TT];      // q, k, gate, out: this lane's part of the element offset (the same for every tile)
-    bool any_valid[TT];       // some token of the tile is a real one
-    // v^T: lane = feature col of a 32-feature tile that starts at a multiple of 32 inside v
-    const unsigned v_lane = (unsigned)(col >> a.dsh) * LpD + (unsigned)(col & (a.D - 1)) * 32 + 8 * hf;
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-        if constexpr (PROJ) row_base[tt] = (size_t)tok_rl[tt] * a.H * LpD;
-        else {
-            // (pad tokens take the address of the last real one: they load the residual, never store)
-            const int lc = tok_l[tt] < a.L ? tok_l[tt] : a.L - 1;
-            row_base[tt] = (size_t)(((int64_t)(a.r0 + tok_rl[tt]) * a.sr + (int64_t)lc * a.sl) * a.N);
-        }
-        if constexpr (PROJ) t_lane[tt] = (unsigned)tok_l[tt] * a.D + (a.D >= 16 ? 8 * hf : hf * LpD);
-        else t_lane[tt] = 8 * hf;
-        const int l0 = __builtin_amdgcn_readfirstlane(tok_l[tt] - col);
-        l0v[tt] = l0 * a.D;                                                   // (l0 / 32) * D * 32
-        any_valid[tt] = l0 < a.L && !tile_off[tt];
-    }
-    float rstd[TT];           // 1 / standard deviation of this lane's token
-    Frag xaug[TT];            // its extra piece of the contraction: (-mean, standard deviation) as bf16 pairs (see k_prep)
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-        rstd[tt] = 0.f;
-        xaug[tt].u = make_uint4(0, 0, 0, 0);
-    }
+    // lane's part of the places of a tile's two stores (see there): token or feature lane % 16 of the first or second sixteen, piece
+    const int t16 = lane & 15, piece8 = 8 * (2 * ((lane >> 4) & 1) + hf);
+    const unsigned t_lane = a.D == 32 ? (unsigned)t16 * 32 + piece8 : (unsigned)col * a.D + (a.D == 16 ? 8 * hf : hf * LpD);
+    const unsigned t_second = a.D == 32 ? 16 * 32 : (unsigned)(16 >> a.dsh) * LpD;
+    const unsigned v_lane = (unsigned)(t16 >> a.dsh) * LpD + (unsigned)(t16 & (a.D - 1)) * 32 + piece8;
+    const unsigned v_second = (unsigned)((16 >> a.dsh) * LpD + (16 & (a.D - 1)) * 32);
+    const int64_t o_lane = (int64_t)t16 * a.sl * a.N + piece8;
 
     // ---- residual (RES): the matrix core adds it.  Two more contraction steps multiply a
     // selection matrix (feature f of the tile picks slot f, then f - 16) with the residual
     // values of 16 features per token: 1.0 * bf16 into the float32 accumulator is exact, the
     // operand is the token's row as it lies in memory (16 bytes per lane, the very bytes the
     // lane stores later, so the output may replace the residual in place), and the sum is
-    // rounded to bf16 once.  ra feeds the first tile of a pipeline step, rb the second; each is
-    // reloaded for the next step as soon as its matrix instructions have been issued.
-    Frag sel[2];
-    Frag ra[TT][2], rb[TT][2];
-    auto load_res = [&](Frag (&r)[TT][2], int ft) {
-        if (ft > ft_end - 1) ft = ft_end - 1;            // (past the end: a harmless repeat)
-#pragma unroll
-        for (int tt = 0; tt < TT; ++tt) {
-            const bf16_t* rp = a.res + row_base[tt] + (size_t)ft * 32 + 8 * hf;
-            r[tt][0].u = ldg16(rp);
-            r[tt][1].u = ldg16(rp + 16);
-        }
-    };
+    // rounded to bf16 once.
+    Frag sel[2], rn[2];
     if constexpr (RES) {
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
@@ -596,276 +561,175 @@ __global__ __launch_bounds__(kGemmWaves * 64, 2) void k_gemm(GemmArgs a) {
             for (int i = 0; i < 4; ++i)
                 sel[m].w[i] = (k >> 1) == i ? ((k & 1) ? 0x3f800000u : 0x00003f80u) : 0u;
         }
-        load_res(ra, ft_begin);
-        load_res(rb, ft_begin + 1);
     }
 
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     __syncthreads();
 
-    // Software pipeline inside every wavefront: the matrix-core instructions of tile i alternate,
-    // one contraction step at a time, with the vector instructions of the epilogue of tile i-1
-    // (a wavefront issues a vector instruction only every eight cycles or so and a 32x32x16
-    // matrix instruction lasts 32: the epilogue fits into the shadow of the matrix core).
-    // Two accumulator sets alternate between the roles "being computed" and "being stored".
-    constexpr int VPC = 16 / KC > 0 ? 16 / KC : 1;      // epilogue values per contraction step
-    constexpr int AHEAD = KC < 4 ? KC : 4;              // operand reads in flight (LDS latency is about two steps)
-    const int LpD2 = LpD;
-    int n_stores = 0;                     // stores and residual loads issued in this step (a lower bound)
-    f32x16 acc[2][TT];
-
-    // matrix part of tile ftn (weights at st) into an[], epilogue of tile ftp (kind KP) from ap[]
-    auto tile_step = [&](auto vt_c, auto kp_c, auto next_c, f32x16 (&an)[TT], f32x16 (&ap)[TT], Frag (&rn)[TT][2],
-                         const unsigned char* st, int ftn, int ftp) {
-        constexpr bool VT = decltype(vt_c)::value;
-        constexpr int KP = decltype(kp_c)::value;
-        constexpr bool NEXT = decltype(next_c)::value;
-        // ---- epilogue state of tile ftp
-        const int nbp = ftp * 32;
-        const int so = (ftp - ft_begin) * 32;
-        // OUT: bias of four features, V: 1/std of four tokens; the group after the one in use is
-        // already on its way from LDS (c4n, rs4n), so that no step waits for it
-        float4 c4 = make_float4(0.f, 0.f, 0.f, 0.f), c4n = c4;
-        float4 rs4[TT], rs4n[TT];
-        auto fetch_group = [&](int g) {
-            if constexpr (KP == TK_OUT) {
-                c4n = *reinterpret_cast<const float4*>(s_cn + so + 8 * g + 4 * hf);
-            } else if constexpr (KP == TK_V) {
-#pragma unroll
-                for (int tt = 0; tt < TT; ++tt)
-                    rs4n[tt] = *reinterpret_cast<const float4*>(s_stat + (wave * TT + tt) * 64 + 32 + 8 * g + 4 * hf);
-            }
-        };
-        if constexpr (KP == TK_OUT || KP == TK_V) fetch_group(0);
-        uint32_t pk[TT][8];
-        float pend[TT];
-        size_t qk_off[TT];
-        int hlim = 0;
-        if constexpr (KP == TK_BIAS) {
-            hlim = a.H - 4 * hf;
-#pragma unroll
-            for (int tt = 0; tt < TT; ++tt)
-                qk_off[tt] = bias_index(4 * hf, a.r0 + tok_rl[tt], tok_l[tt], a.Lq, a.Lp);
-        }
-        // value v of the lane: one multiplication by 1/std (the matrix core has already added the
-        // LayerNorm mean and offset terms), the sigmoid for the gate, bf16
-        auto epi_value = [&](int v) {
-            const int g = v >> 2, e = v & 3;
-            if constexpr (KP == TK_OUT || KP == TK_V) {
-                if (e == 0) {
-                    c4 = c4n;
-#pragma unroll
-                    for (int tt = 0; tt < TT; ++tt) rs4[tt] = rs4n[tt];
-                    if (g < 3) fetch_group(g + 1);
-                }
-            }
-#pragma unroll
-            for (int tt = 0; tt < TT; ++tt) {
-                float t;
-                if constexpr (KP == TK_OUT) {
-                    t = ap[tt][v] + (e == 0 ? c4.x : (e == 1 ? c4.y : (e == 2 ? c4.z : c4.w)));
-                } else if constexpr (KP == TK_V) {
-                    // lane = feature, value = token 8g + 4hf + e
-                    t = ap[tt][v] * (e == 0 ? rs4[tt].x : (e == 1 ? rs4[tt].y : (e == 2 ? rs4[tt].z : rs4[tt].w)));
-                } else {
-                    t = ap[tt][v] * rstd[tt];
-                }
-                if constexpr (KP == TK_GATE) t = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-t * kLog2e));
-                if constexpr (KP == TK_BIAS) {
-                    // pair bias: feature = head, token (rl, l) = pair (q, k)
-                    const int hu = 8 * g + e;                    // head of the lower half-wave
-                    if (hu < hlim) a.bias[qk_off[tt] + (size_t)hu * a.Lq * a.Lp] = t;
-                } else {
-                    // (the empty statements pin the arithmetic to this contraction step: the
-                    // compiler would otherwise sink it below the matrix-core instructions)
-                    if (v & 1) {
-                        pk[tt][v >> 1] = pack2(pend[tt], t);
-                        asm volatile("" : "+v"(pk[tt][v >> 1]));
-                    } else {
-                        pend[tt] = t;
-                        asm volatile("" : "+v"(pend[tt]));
-                    }
-                }
-            }
-        };
-        // ---- the pipeline: KC steps over the weight tile, then the extra piece (PROJ)
-        Frag wf[KC];
-        Frag waug;
-        if constexpr (NEXT) {
-#pragma unroll
-            for (int s = 0; s < AHEAD; ++s) wf[s].u = *reinterpret_cast<const uint4*>(st + (rd0 ^ (32u * s)));
-            if constexpr (PROJ) waug.u = s_aug[(ftn - ft_begin) * 32 + col];
-        }
-#pragma unroll
-        for (int s = 0; s < KC; ++s) {
-            if constexpr (NEXT) {
-                if (s + AHEAD < KC) wf[s + AHEAD].u = *reinterpret_cast<const uint4*>(st + (rd0 ^ (32u * (s + AHEAD))));
-#pragma unroll
-                for (int tt = 0; tt < TT; ++tt) {
-                    f32x16 c = an[tt];
-                    if (s == 0) {
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) c[v] = 0.f;
-                    }
-                    if constexpr (VT) an[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[tt][s].v, wf[s].v, c, 0, 0, 0);
-                    else an[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[s].v, xa[tt][s].v, c, 0, 0, 0);
-                }
-            }
-            if constexpr (KP != -1) {
-#pragma unroll
-                for (int vv = 0; vv < VPC; ++vv) epi_value(s * VPC + vv);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if constexpr (NEXT && PROJ) {
-#pragma unroll
-            for (int tt = 0; tt < TT; ++tt) {
-                if constexpr (VT) an[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xaug[tt].v, waug.v, an[tt], 0, 0, 0);
-                else an[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(waug.v, xaug[tt].v, an[tt], 0, 0, 0);
-            }
-        }
-        if constexpr (NEXT && RES) {
-#pragma unroll
-            for (int tt = 0; tt < TT; ++tt) {
-                an[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sel[0].v, rn[tt][0].v, an[tt], 0, 0, 0);
-                an[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sel[1].v, rn[tt][1].v, an[tt], 0, 0, 0);
-            }
-        }
-        // ---- stores of tile ftp
-        if constexpr (KP == TK_V) {
-            const size_t head_off = (size_t)((nbp - 2 * a.Hd) >> a.dsh) * LpD2;
-#pragma unroll
-            for (int tt = 0; tt < TT; ++tt) {
-                merge_halves(pk[tt][0], pk[tt][2]);
-                merge_halves(pk[tt][1], pk[tt][3]);
-                merge_halves(pk[tt][4], pk[tt][6]);
-                merge_halves(pk[tt][5], pk[tt][7]);
-                // v^T tiled by 32 keys: [row][head][l / 32][e][l % 32]
-                bf16_t* tile = a.vt + (row_base[tt] + head_off + (size_t)l0v[tt]);
-                *reinterpret_cast<uint4*>(tile + v_lane) = make_uint4(pk[tt][0], pk[tt][1], pk[tt][2], pk[tt][3]);
-                *reinterpret_cast<uint4*>(tile + v_lane + 16) = make_uint4(pk[tt][4], pk[tt][5], pk[tt][6], pk[tt][7]);
-            }
-            n_stores += 2 * TT;
-        } else if constexpr (KP == TK_Q || KP == TK_GATE || KP == TK_OUT) {
-            // features f .. f+7 and f+16 .. f+23 (f = first feature of the tile + 8 hf): uniform part of their place
-            size_t u0 = (size_t)nbp, u1 = (size_t)nbp + 16;               // out: [token][N]
-            bf16_t* base = a.out;
-            if constexpr (PROJ) {                                          // q, k, gate: [row][head][l][d]
-                const int kind = (nbp >= a.Hd) + (nbp >= 2 * a.Hd) + (nbp >= 3 * a.Hd);
-                const int f = nbp - kind * a.Hd;
-                u0 = (size_t)(f >> a.dsh) * LpD2 + (f & (a.D - 1));
-                u1 = (size_t)((f + 16) >> a.dsh) * LpD2 + ((f + 16) & (a.D - 1));
-                base = kind == 0 ? a.q : (kind == 1 ? a.k : a.g);
-            }
-#pragma unroll
-            for (int tt = 0; tt < TT; ++tt) {
-                merge_halves(pk[tt][0], pk[tt][2]);
-                merge_halves(pk[tt][1], pk[tt][3]);
-                merge_halves(pk[tt][4], pk[tt][6]);
-                merge_halves(pk[tt][5], pk[tt][7]);
-                bf16_t* rowp = base + row_base[tt];
-                if (PROJ || tok_valid[tt]) {
-                    *reinterpret_cast<uint4*>(rowp + u0 + t_lane[tt]) = make_uint4(pk[tt][0], pk[tt][1], pk[tt][2], pk[tt][3]);
-                    *reinterpret_cast<uint4*>(rowp + u1 + t_lane[tt]) = make_uint4(pk[tt][4], pk[tt][5], pk[tt][6], pk[tt][7]);
-                }
-                if (PROJ || any_valid[tt]) n_stores += 2;     // (wave-uniform: the instructions were issued)
-            }
-        }
-    };
-    // kind of tile ft: q and k share their epilogue
-    auto kind_of = [&](int ft) -> int {
-        if constexpr (!PROJ) return TK_OUT;
-        if (ft >= a.nt_main) return TK_BIAS;
-        const int k = (ft * 32 >= a.Hd) + (ft * 32 >= 2 * a.Hd) + (ft * 32 >= 3 * a.Hd);
-        return k == TK_K ? TK_Q : k;
-    };
-    using std::integral_constant;
-    auto run_step = [&](int kn, int kp, f32x16 (&an)[TT], f32x16 (&ap)[TT], Frag (&rn)[TT][2], const unsigned char* st,
-                        int ftn, int ftp) {
-#define FF_STEP(KPV)                                                                                                         \
-    do {                                                                                                                     \
-        if (kn < 0) tile_step(integral_constant<bool, false>{}, integral_constant<int, KPV>{},                               \
-                              integral_constant<bool, false>{}, an, ap, rn, st, ftn, ftp);                                        \
-        else if (kn == TK_V) tile_step(integral_constant<bool, true>{}, integral_constant<int, KPV>{},                       \
-                                       integral_constant<bool, true>{}, an, ap, rn, st, ftn, ftp);                                \
-        else tile_step(integral_constant<bool, false>{}, integral_constant<int, KPV>{}, integral_constant<bool, true>{}, an, \
-                       ap, rn, st, ftn, ftp);                                                                                     \
-    } while (0)
+    for (;; load_tokens(unit)) {
+        const bool run = unit < tiles_m;                      // (wave-uniform; without whole weights a wavefront without tokens still takes its share of the loads)
+        float rstd = 0.f;         // 1 / standard deviation of this lane's token
+        Frag xaug;                // its extra piece of the contraction: (-mean, standard deviation) as bf16 pairs (see k_prep)
+        xaug.u = make_uint4(0, 0, 0, 0);
         if constexpr (PROJ) {
-            switch (kp) {
-                case TK_Q: FF_STEP(TK_Q); break;
-                case TK_V: FF_STEP(TK_V); break;
-                case TK_GATE: FF_STEP(TK_GATE); break;
-                case TK_BIAS: FF_STEP(TK_BIAS); break;
-                default: FF_STEP(-1); break;
-            }
-        } else {
-            if (kp == TK_OUT) FF_STEP(TK_OUT);
-            else FF_STEP(-1);
-        }
-#undef FF_STEP
-    };
-
-    if constexpr (PROJ) {
-        // LayerNorm statistics of the raw rows (token_stats)
-#pragma unroll
-        for (int tt = 0; tt < TT; ++tt) {
+            // LayerNorm statistics of the raw rows (token_stats)
             float mu, var;
-            token_stats<KC>(xa[tt], K, a.eps, mu, var);
-            rstd[tt] = tok_valid[tt] ? rsqrtf(var) : 0.f;
-            const float m = tok_valid[tt] ? -mu : 0.f, r = var * rstd[tt];
+            token_stats<KC>(xa, K, a.eps, mu, var);
+            rstd = valid ? rsqrtf(var) : 0.f;
+            const float m = valid ? -mu : 0.f, r = var * rstd;
             const float m_hi = bf16_round(m), m_lo = bf16_round(m - m_hi);
             const float r_hi = bf16_round(r), r_lo = bf16_round(r - r_hi);
             if (hf == 0) {
-                xaug[tt].u = make_uint4(pack2(m_hi, m_hi), pack2(m_lo, r_hi), pack2(r_hi, r_lo), 0u);
-                s_stat[((wave * TT + tt) * 2 + 1) * 32 + col] = rstd[tt];
+                xaug.u = make_uint4(pack2(m_hi, m_hi), pack2(m_lo, r_hi), pack2(r_hi, r_lo), 0u);
+                s_rstd[wave * 32 + col] = rstd;
             }
         }
-    }
-
-    const int n_it = (ft_end - ft_begin + NS - 1) / NS;
-    int kp = -1, ftp = ft_begin;
-    bool last_in_1 = false;
-    for (int it = 0; it < n_it; ++it) {
-        const int ftb = ft_begin + it * NS;
-        const bool two = ftb + 1 < ft_end;
-        const unsigned char* st = s_w + ((it & 1) * NS) * STAGE;
-        run_step(kind_of(ftb), kp, acc[0], acc[1], ra, st, ftb, ftp);
-        kp = kind_of(ftb);
-        ftp = ftb;
-        last_in_1 = false;
-        if constexpr (RES) {
-            load_res(ra, ftb + NS);
-            n_stores += 2 * TT;
-        }
-        if (two) {
-            run_step(kind_of(ftb + 1), kp, acc[1], acc[0], rb, st + STAGE, ftb + 1, ftp);
-            kp = kind_of(ftb + 1);
-            ftp = ftb + 1;
-            last_in_1 = true;
-            if constexpr (RES) {
-                load_res(rb, ftb + 1 + NS);
-                n_stores += 2 * TT;
-            }
-        }
-        if (it + 1 >= n_it) break;
-        // Order of this wavefront's memory operations: ... L(i+1), S, L(i+2), S, ... (L = tile loads
-        // of a step, S = the stores issued during one step).  The next step needs L(it+1):
-        // everything but the stores issued after it, those of this step, must have completed.
-        // After the barrier all wavefronts have their share of L(it+1) in LDS and have finished
-        // reading this step's half of the ring, which the loads of step it+2 then overwrite.
-        wait_vmem_but_last(__builtin_amdgcn_readfirstlane(n_stores));
-        __syncthreads();
+        // q, k, gate, v^T of the token tile's batch row; RES: the lane's token in out (pad tokens: the last real one, they load the residual and
+        // never store)
+        const size_t row_base = PROJ ? (size_t)rl * a.H * LpD
+                                     : (size_t)(((int64_t)(a.r0 + rl) * a.sr + (int64_t)(valid ? l : a.L - 1) * a.sl) * a.N);
+        const int l0 = __builtin_amdgcn_readfirstlane(l - col);
+        auto load_res = [&](int ft) __attribute__((always_inline)) {
+            if (ft > ft_end - 1) ft = ft_end - 1;            // (past the end: a harmless repeat)
+            const bf16_t* rp = a.res + row_base + (size_t)ft * 32 + 8 * hf;
+            rn[0].u = ldg16(rp);
+            rn[1].u = ldg16(rp + 16);
+        };
+        if constexpr (RES) load_res(ft_begin);
+        int n_ops = 0;            // stores and residual loads issued since the last weight loads (a lower bound)
+        for (int n = 0; n < n_ft; ++n) {
+            const int ft = ft_begin + n, nb = ft * 32;
+            if (run) {
+                const unsigned char* st = s_w + (whole ? n : n % (2 * NS)) * STAGE;
+                // q and k share their epilogue
+                const int kind = !PROJ ? TK_OUT : (ft >= a.nt_main ? TK_BIAS : (nb >= a.Hd) + (nb >= 2 * a.Hd) + (nb >= 3 * a.Hd));
+                f32x16 acc;
 #pragma unroll
-        for (int n = 0; n < NS; ++n) {
-            const int ft = ft_begin + (it + 2) * NS + n;
-            if (ft < ft_end) issue_tile(ft, (it & 1) * NS + n);
+                for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+                uint32_t pk[8];
+                // (opaque and fenced: else the operand addresses of all steps, and all operands, are in registers at once, and others in scratch memory)
+                unsigned rd = rd0;
+                asm volatile("" : "+v"(rd));
+                auto contract = [&](auto&& mac) __attribute__((always_inline)) {
+                    constexpr int AHEAD = KC >= 16 ? 3 : (KC < 4 ? KC : 4);              // operand reads in flight
+                    Frag wf[AHEAD];
+#pragma unroll
+                    for (int s = 0; s < AHEAD; ++s) wf[s].u = *reinterpret_cast<const uint4*>(st + (rd ^ (32u * s)));
+#pragma unroll
+                    for (int s = 0; s < KC; ++s) {
+                        mac(s, wf[s % AHEAD]);
+                        if (s + AHEAD < KC) wf[s % AHEAD].u = *reinterpret_cast<const uint4*>(st + (rd ^ (32u * (s + AHEAD))));
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                };
+                if (PROJ && kind == TK_V) {
+                    // lane = feature, value v = token 8 (v / 4) + 4 hf + v % 4
+                    contract([&](int s, const Frag& w) __attribute__((always_inline)) { acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[s].v, w.v, acc, 0, 0, 0); });
+                    Frag wx;
+                    wx.u = s_aug[n * 32 + col];
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xaug.v, wx.v, acc, 0, 0, 0);
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const float4 rs = *reinterpret_cast<const float4*>(s_rstd + wave * 32 + 8 * g + 4 * hf);
+                        pk[2 * g] = pack2(acc[4 * g] * rs.x, acc[4 * g + 1] * rs.y);
+                        pk[2 * g + 1] = pack2(acc[4 * g + 2] * rs.z, acc[4 * g + 3] * rs.w);
+                    }
+                } else {
+                    // lane = token, value v = feature 8 (v / 4) + 4 hf + v % 4
+                    contract([&](int s, const Frag& w) __attribute__((always_inline)) { acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w.v, xa[s].v, acc, 0, 0, 0); });
+                    if constexpr (PROJ) {
+                        Frag wx;
+                        wx.u = s_aug[n * 32 + col];
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wx.v, xaug.v, acc, 0, 0, 0);
+                    }
+                    if constexpr (RES) {
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sel[0].v, rn[0].v, acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sel[1].v, rn[1].v, acc, 0, 0, 0);
+                        load_res(ft + 1);
+                        n_ops += 2;
+                    }
+                    if constexpr (!PROJ) {
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) {
+                            const float4 c = *reinterpret_cast<const float4*>(s_cn + n * 32 + 8 * g + 4 * hf);
+                            pk[2 * g] = pack2(acc[4 * g] + c.x, acc[4 * g + 1] + c.y);
+                            pk[2 * g + 1] = pack2(acc[4 * g + 2] + c.z, acc[4 * g + 3] + c.w);
+                        }
+                    } else if (kind == TK_GATE) {
+                        const float nr = -kLog2e * rstd;
+#pragma unroll
+                        for (int i = 0; i < 8; ++i)
+                            pk[i] = pack2(__builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(acc[2 * i] * nr)),
+                                          __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(acc[2 * i + 1] * nr)));
+                    } else if (kind == TK_BIAS) {
+                        // pair bias: feature = head, token (rl, l) = pair (q, k)
+                        int lq = l;
+                        asm volatile("" : "+v"(lq));                           // (the sixteen addresses: not before the loop)
+                        float* bp = a.bias + bias_index(4 * hf, a.r0 + rl, lq, a.Lq, a.Lp);
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) {
+                            const int hu = 8 * (v >> 2) + (v & 3);               // head of the lower half-wave
+                            if (hu < a.H - 4 * hf) bp[(size_t)hu * a.Lq * a.Lp] = acc[v] * rstd;
+                        }
+                        continue;                                              // (the last tile)
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) pk[i] = pack2(acc[2 * i] * rstd, acc[2 * i + 1] * rstd);
+                    }
+                }
+                // A lane holds the 16-byte pieces hf and 2 + hf of its token's (v: feature's) 64 bytes.  Where these are 64 bytes of memory too
+                // they are exchanged so that the first store has all four pieces of the first sixteen tokens, piece 2 (row % 2) + row / 2 in
+                // the row of sixteen lanes, and the second those of the others: each writes whole 64-byte rows (halves of 32 rows: 42 us instead of
+                // 38 for the projections of 64 x 2048 tokens).
+                merge_halves(pk[0], pk[2]);
+                merge_halves(pk[1], pk[3]);
+                merge_halves(pk[4], pk[6]);
+                merge_halves(pk[5], pk[7]);
+                if (!PROJ || kind == TK_V || a.D == 32)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const auto sw = __builtin_amdgcn_permlane16_swap(pk[i], pk[4 + i], false, false);
+                    pk[i] = sw[0];
+                    pk[4 + i] = sw[1];
+                }
+                const uint4 lo = make_uint4(pk[0], pk[1], pk[2], pk[3]), hi = make_uint4(pk[4], pk[5], pk[6], pk[7]);
+                if (PROJ && kind == TK_V) {
+                    // v^T tiled by 32 keys: [row][head][l / 32][e][l % 32]
+                    bf16_t* tile = a.vt + (row_base + (size_t)((nb - 2 * a.Hd) >> a.dsh) * LpD + (size_t)l0 * a.D);
+                    *reinterpret_cast<uint4*>(tile + v_lane) = lo;
+                    *reinterpret_cast<uint4*>(tile + v_lane + v_second) = hi;
+                    n_ops += 2;
+                } else if constexpr (PROJ) {                       // q, k, gate: [row][head][l][d]
+                    bf16_t* base = (kind == TK_Q ? a.q : (kind == TK_K ? a.k : a.g)) + row_base + (size_t)((nb - kind * a.Hd) >> a.dsh) * LpD + (size_t)l0 * a.D;
+                    *reinterpret_cast<uint4*>(base + t_lane) = lo;
+                    *reinterpret_cast<uint4*>(base + t_lane + t_second) = hi;
+                    n_ops += 2;
+                } else {                                           // out: [token][N]
+                    bf16_t* base = a.out + (size_t)(((int64_t)(a.r0 + rl) * a.sr + (int64_t)l0 * a.sl) * a.N + nb);
+                    if (l0 + (lane & 15) < a.L) *reinterpret_cast<uint4*>(base + o_lane) = lo;
+                    if (l0 + 16 + (lane & 15) < a.L) *reinterpret_cast<uint4*>(base + o_lane + 16 * a.sl * a.N) = hi;
+                    if (l0 < a.L) n_ops += l0 + 16 < a.L ? 2 : 1;  // (wave-uniform: the instructions were issued)
+                }
+            }
+            if (!whole && (n + 1) % NS == 0 && n + 1 < n_ft) {
+                // Order of this wavefront's memory operations: ... L(i+1), S, L(i+2), S, ... (L = loads of a half, S = the stores
+                // issued during one half).  The next half needs L(i+1): everything but the stores issued after it must have completed.
+                // After the barrier all wavefronts have their share of L(i+1) in LDS and have finished
+                // reading this half, which the loads of the half after next then overwrite.
+                wait_vmem_but_last(__builtin_amdgcn_readfirstlane(n_ops));
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                n_ops = 0;
+                const int next = n + 1 + NS;
+                if (next < n_ft) issue(next, n_ft - next < NS ? n_ft - next : NS, next % (2 * NS));
+            }
         }
-        n_stores = 0;
+        if constexpr (RES) asm volatile("" : : "v"(ahead[0]), "v"(ahead[1]));
+        if (!whole) break;
+        unit += gridDim.x * NW;
+        if (unit >= tiles_m) break;
     }
-    // epilogue of the last tile
-    if (last_in_1) run_step(-1, kp, acc[0], acc[1], ra, s_w, ftp, ftp);
-    else run_step(-1, kp, acc[1], acc[0], ra, s_w, ftp, ftp);
 }
 
 // ====================================================================================
@@ -937,7 +801,7 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
 
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, hf = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nt = a.Lp >> 5;                               // 32-token tiles of a row: even, at most 8
+    const int nt = a.Lp >> 5;                               // 32-token tiles of a row, at most 8
     const bool active = wave < nt;                          // (wave-uniform)
     // Work-groups go to the 8 XCDs round-robin and each XCD has its own L2: the heads of a row
     // pair run on one XCD at about the same time, so the rows of x come from HBM once.  Item
@@ -1310,19 +1174,6 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
 
 // ====================================================================================
 // host side
-// token tiles per wavefront: two halve the LDS traffic per MFMA, one keeps the register count at
-// two wavefronts per SIMD when the contraction is long
-// (and one when two would leave compute units without a block)
-static int gemm_tt(bool proj, int K, int tiles_m) {
-    return (K > (proj ? 64 : 128) || tiles_m < 2 * kGemmWaves * 256) ? 1 : 2;
-}
-constexpr int kGemmNS = 2;      // weight tiles per pipeline step
-
-static int gemm_blocks_m(bool proj, int tiles_m, int K) {
-    const int per_block = kGemmWaves * gemm_tt(proj, K, tiles_m);
-    return (tiles_m + per_block - 1) / per_block;
-}
-
 // More than 64 KiB of dynamic LDS has to be asked for once per kernel.  The request is the
 // initialiser of a function-local static: the language runs it exactly once, also when several
 // threads make their first call together, and every caller sees its result.
@@ -1332,36 +1183,45 @@ static hipError_t allow_large_lds(Kernel kernel) {
                                96 * 1024);
 }
 
-template <int KC, bool PROJ, int TT, bool RES>
-static ff_status launch_gemm_inst(const GemmArgs& a, dim3 grid, hipStream_t st) {
-    const size_t smem = gemm_smem_bytes(KC, TT, kGemmNS, a.tiles_per_split);
-    static const hipError_t attr = allow_large_lds(&k_gemm<KC, PROJ, TT, kGemmNS, RES>);
+template <int KC, bool PROJ, bool RES>
+static ff_status launch_gemm_inst(GemmArgs a, int tiles_m, hipStream_t st) {
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm<KC, PROJ, RES>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return fail(FF_EHIP, "k_gemm: dynamic LDS limit: %s", hipGetErrorString(attr));
-    hipLaunchKernelGGL((k_gemm<KC, PROJ, TT, kGemmNS, RES>), grid, dim3(kGemmWaves * 64), smem, st, a);
+    // Blocks of eight wavefronts or of all that a compute unit holds, one token tile each, and the feature tiles shared out over `split` such blocks: what
+    // makes the rounds of blocks times the time of a block least.  A block takes its tiles and about ten more for its tokens and first
+    // weights, an eighth longer per wavefront and SIMD (128 x 128 triangle attention, projections: split in 1, 2, 3, 4, 6, 9, 17 29.5, 20.0, 17.8, 17.2,
+    // 15.5, 19.6, 27.6 us, the last two in a second round).  The blocks along the tokens are rounded up to a multiple of the 8 XCDs where
+    // they are split, so that the shares of the same tokens run on one XCD and fetch them into one L2.
+    const int cu = compute_units();
+    int blocks = 1, split = 1, waves = 8;
+    double least = 1e300;
+    for (int nw : {8, gemm_waves(KC)}) {
+        const int along = (tiles_m + nw - 1) / nw;
+        for (int t = 1; t <= a.ft_count; t += t < 8 ? 1 : t / 4) {
+            const int per = (a.ft_count + t - 1) / t, n = (a.ft_count + per - 1) / per;
+            const int fit = 2 * nw <= gemm_waves(KC) && 2 * gemm_smem_bytes(KC, per) <= 160 * 1024 ? 2 : 1;          // blocks per compute unit
+            int b = n > 1 ? (along + 7) / 8 * 8 : along;
+            const double cost = ceil((double)b * n / (cu * fit)) * (10 + per) * (24 + nw * fit);
+            if (cost >= least) continue;
+            least = cost;
+            // (whole weights: no more blocks than are resident, each takes more tokens)
+            if (per <= 2 * gemm_half(KC) && (double)b * n > cu * fit) b = (cu * fit + n - 1) / n;
+            blocks = b; split = n; waves = nw;
+            a.tiles_per_split = per;
+        }
+    }
+    hipLaunchKernelGGL((k_gemm<KC, PROJ, RES>), dim3(blocks, split), dim3(waves * 64), gemm_smem_bytes(KC, a.tiles_per_split), st, a);
     return FF_OK;
 }
 
 template <bool PROJ, bool RES>
-static ff_status launch_gemm(const GemmArgs& a, int K, dim3 grid, hipStream_t st) {
-    const int kc = K / 16;
-    if (gemm_tt(PROJ, K, a.rows * (a.Lp >> 5)) == 1) {
-        if (kc <= 2) return launch_gemm_inst<2, PROJ, 1, RES>(a, grid, st);
-        if (kc <= 4) return launch_gemm_inst<4, PROJ, 1, RES>(a, grid, st);
-        if (kc <= 8) return launch_gemm_inst<8, PROJ, 1, RES>(a, grid, st);
-        return launch_gemm_inst<16, PROJ, 1, RES>(a, grid, st);
-    }
-    if (kc <= 2) return launch_gemm_inst<2, PROJ, 2, RES>(a, grid, st);
-    if (kc <= 4) return launch_gemm_inst<4, PROJ, 2, RES>(a, grid, st);
-    if constexpr (!PROJ) return launch_gemm_inst<8, PROJ, 2, RES>(a, grid, st);
-    return fail(FF_EUNSUPPORTED, "k_gemm: no instantiation for K = %d with two token tiles", K);
-}
-
-// blocks along the feature axis: at least one block (eight wavefronts) per compute unit
-static int pick_split(int blocks_m, int tiles_n) {
-    int split = 1;
-    while (blocks_m * split < 256 && split < tiles_n) ++split;
-    while (tiles_n % split != 0) ++split;      // equal shares
-    return split;
+static ff_status launch_gemm(const GemmArgs& a, hipStream_t st) {
+    const int tiles_m = a.rows * (a.Lp >> 5);
+    if (a.K <= 32) return launch_gemm_inst<2, PROJ, RES>(a, tiles_m, st);
+    if (a.K <= 64) return launch_gemm_inst<4, PROJ, RES>(a, tiles_m, st);
+    if (a.K <= 128) return launch_gemm_inst<8, PROJ, RES>(a, tiles_m, st);
+    return launch_gemm_inst<16, PROJ, RES>(a, tiles_m, st);
 }
 
 bool mfma_chunk_ok(const Problem& p, int chunk) {
@@ -1388,7 +1248,7 @@ int compute_units() {
 static bool fused_proj_attn(const Problem& p);
 
 static GemmArgs proj_args(const Problem& p, const MfmaWs& m, const Workspace& ws) {
-    const int Lp = round_up(p.L, 64), Lq = round_up(p.L, 64);
+    const int Lp = round_up(p.L, 32), Lq = round_up(p.L, 32);
     GemmArgs g{};
     g.sr = p.sr; g.sl = p.sl; g.L = p.L; g.Lp = Lp; g.Lq = Lq; g.K = p.c; g.eps = p.eps;
     g.w = m.wp; g.aug = m.aug; g.Hd = p.Hd; g.H = p.H; g.D = p.d; g.invD = 1.f / (float)p.d; g.dsh = p.d == 8 ? 3 : (p.d == 16 ? 4 : 5);
@@ -1400,7 +1260,7 @@ static GemmArgs proj_args(const Problem& p, const MfmaWs& m, const Workspace& ws
 ff_status mfma_prepare(const Problem& p, const ff_attn_weights& w, const void* x, const void* z, const Workspace& ws,
                        hipStream_t st) {
     const MfmaWs m = split_ws(p, ws.chunk, ws);
-    const int Lp = round_up(p.L, 64), Lq = round_up(p.L, 64);
+    const int Lp = round_up(p.L, 32), Lq = round_up(p.L, 32);
     const float qscale = kLog2e / sqrtf((float)p.d);
     const bool tri = p.mode == FF_TRI_START || p.mode == FF_TRI_END;
     {
@@ -1474,11 +1334,9 @@ static ff_status launch_fused(const FusedArgs& a, hipStream_t st) {
 
 ff_status mfma_chunk(const Problem& p, const ff_attn_weights& w, const void* x, const float* mask, const void* res,
                      void* out, const Workspace& ws, int r0, int rows, hipStream_t st) {
-    const int Lp = round_up(p.L, 64), Lq = round_up(p.L, 64);
+    const int Lp = round_up(p.L, 32), Lq = round_up(p.L, 32);
     const MfmaWs m = split_ws(p, ws.chunk, ws);
     const bool tri = p.mode == FF_TRI_START || p.mode == FF_TRI_END;
-    const int tiles_m = rows * (Lp / 32);
-    const int blocks_m = gemm_blocks_m(true, tiles_m, p.c);
     const bool fused = fused_proj_attn(p);
     if (fused) {
         FusedArgs f{};
@@ -1501,11 +1359,9 @@ ff_status mfma_chunk(const Problem& p, const ff_attn_weights& w, const void* x, 
         g.src = (const bf16_t*)x; g.r0 = r0; g.rows = rows;
         // one chunk covering every row: the pair-bias tile rides along with the projections
         const bool fused_bias = tri && ws.chunk >= p.R;
-        const int split = pick_split(blocks_m, g.nt_main);
-        g.ft_first = 0; g.ft_count = g.nt_main + (fused_bias ? 1 : 0);
-        g.tiles_per_split = (g.ft_count + split - 1) / split;
+        g.ft_count = g.nt_main + (fused_bias ? 1 : 0);
         Timed t(KK_PROJ, st);
-        const ff_status ls = launch_gemm<true, false>(g, p.c, dim3(blocks_m, split), st);
+        const ff_status ls = launch_gemm<true, false>(g, st);
         if (ls != FF_OK) return ls;
     }
 
@@ -1523,15 +1379,10 @@ ff_status mfma_chunk(const Problem& p, const ff_attn_weights& w, const void* x, 
     o.K = p.Hd; o.w = (const bf16_t*)w.w_o; o.bvec = (const bf16_t*)w.b_o;
     o.Hd = p.Hd; o.H = p.H; o.D = p.d; o.invD = 1.f / (float)p.d; o.dsh = p.d == 8 ? 3 : (p.d == 16 ? 4 : 5); o.out = (bf16_t*)out; o.N = p.c;
     {
-        const int tiles_n = o.N / 32;
-        const int blocks_o = gemm_blocks_m(false, tiles_m, p.Hd);
-        const int split = pick_split(blocks_o, tiles_n);
-        o.ft_first = 0; o.ft_count = tiles_n;
-        o.tiles_per_split = tiles_n / split;
+        o.ft_count = o.N / 32;
         Timed t(KK_OUT, st);
         o.res = (const bf16_t*)res;
-        const ff_status ls = res ? launch_gemm<false, true>(o, p.Hd, dim3(blocks_o, split), st)
-                                 : launch_gemm<false, false>(o, p.Hd, dim3(blocks_o, split), st);
+        const ff_status ls = res ? launch_gemm<false, true>(o, st) : launch_gemm<false, false>(o, st);
         if (ls != FF_OK) return ls;
     }
     return check_launch("attention chunk (mfma)");
