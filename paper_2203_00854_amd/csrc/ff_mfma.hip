@@ -393,7 +393,7 @@ __global__ __launch_bounds__(512) void k_prep_bias(PrepBiasArgs a) {
 // wave-uniform LDS base + 16 i).
 // What bounds it is the number of instructions a wavefront can issue (one every eight cycles or so, whatever the others do): about 60 per
 // 32 x 32 tile beside KC + 1 matrix instructions.  So the registers are held to 128, sixteen wavefronts per compute unit, and a wavefront finishes a
-// tile before it begins the next one: the matrix instructions of one hide behind the epilogues of the other three of its SIMD.A kernel of
+// tile before it begins the next one: the matrix instructions of one hide behind the epilogues of the other three of its SIMD.  A kernel of
 // eight wavefronts with 186 to 250 registers that alternated the matrix instructions of a tile with the epilogue of the one before took
 // 150 to 200 instructions per tile: projections of 64 x 2048 tokens of 128 channels 46 -> 38 us, of 333 x 333 50 -> 40, of 60 x 300 of 256 channels 34 -> 29.5.
 // No instance may spill: a kernel that uses scratch memory starts 2.5 us later (8 x 48 row attention, projections 11.7 -> 9.2 us).
@@ -1203,7 +1203,8 @@ static ff_status launch_gemm_inst(GemmArgs a, int tiles_m, hipStream_t st) {
             const int fit = 2 * nw <= gemm_waves(KC) && 2 * gemm_smem_bytes(KC, per) <= 160 * 1024 ? 2 : 1;          // blocks per compute unit
             int b = n > 1 ? (along + 7) / 8 * 8 : along;
             const double cost = ceil((double)b * n / (cu * fit)) * (10 + per) * (24 + nw * fit);
-            if (cost >= least) continue;
+            // (65 to 128 channels: more than 22 tiles with their offsets and extra pieces do not fit beside the ring)
+            if (cost >= least || gemm_smem_bytes(KC, per) > 160 * 1024) continue;
             least = cost;
             // (whole weights: no more blocks than are resident, each takes more tokens)
             if (per <= 2 * gemm_half(KC) && (double)b * n > cu * fit) b = (cu * fit + n - 1) / n;

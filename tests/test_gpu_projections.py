@@ -25,6 +25,8 @@ DEV = "cuda:0"
     (I.MODE_ROW, 90, 129, 256, 8, 16, 16, "random:0.9"),
     (I.MODE_TRI_START, 65, 65, 128, 4, 32, 0, "none"),        # the pair-bias tile as a share of its own
     (I.MODE_TRI_END, 290, 290, 64, 2, 16, 0, "outer:0.9"),
+    (I.MODE_COL, 30, 2200, 128, 8, 32, 0, "tail:3"),          # 32 feature tiles at 128 channels, many tokens: all in one block would not fit LDS
+    (I.MODE_TRI_START, 290, 290, 96, 16, 16, 0, "none"),      # 33 of them with the pair-bias tile
 ])
 @pytest.mark.parametrize("residual", [False, True])
 def test_shapes(mode, n_a, n_b, c, H, d, c_z, mask, residual):
