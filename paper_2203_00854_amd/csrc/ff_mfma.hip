@@ -1200,7 +1200,9 @@ static ff_status launch_gemm_inst(GemmArgs a, int tiles_m, hipStream_t st) {
         const int along = (tiles_m + nw - 1) / nw;
         for (int t = 1; t <= a.ft_count; t += t < 8 ? 1 : t / 4) {
             const int per = (a.ft_count + t - 1) / t, n = (a.ft_count + per - 1) / per;
-            const int fit = 2 * nw <= gemm_waves(KC) && 2 * gemm_smem_bytes(KC, per) <= 160 * 1024 ? 2 : 1;          // blocks per compute unit
+            // blocks per compute unit (the output projections hold at most 128 registers at 256 channels too: two of eight wavefronts; 128 x 256
+            // row attention, the whole call: 67.6 us with two shares in one block per unit each, 62.6 with four)
+            const int fit = 2 * nw <= (PROJ ? gemm_waves(KC) : 16) && 2 * gemm_smem_bytes(KC, per) <= 160 * 1024 ? 2 : 1;
             int b = n > 1 ? (along + 7) / 8 * 8 : along;
             const double cost = ceil((double)b * n / (cu * fit)) * (10 + per) * (24 + nw * fit);
             // (65 to 128 channels: more than 22 tiles with their offsets and extra pieces do not fit beside the ring)
