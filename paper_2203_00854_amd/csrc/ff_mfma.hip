@@ -693,16 +693,14 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gem
                     pk[4 + i] = sw[1];
                 }
                 const uint4 lo = make_uint4(pk[0], pk[1], pk[2], pk[3]), hi = make_uint4(pk[4], pk[5], pk[6], pk[7]);
-                if (PROJ && kind == TK_V) {
-                    // v^T tiled by 32 keys: [row][head][l / 32][e][l % 32]
-                    bf16_t* tile = a.vt + (row_base + (size_t)((nb - 2 * a.Hd) >> a.dsh) * LpD + (size_t)l0 * a.D);
-                    *reinterpret_cast<uint4*>(tile + v_lane) = lo;
-                    *reinterpret_cast<uint4*>(tile + v_lane + v_second) = hi;
-                    n_ops += 2;
-                } else if constexpr (PROJ) {                       // q, k, gate: [row][head][l][d]
-                    bf16_t* base = (kind == TK_Q ? a.q : (kind == TK_K ? a.k : a.g)) + row_base + (size_t)((nb - kind * a.Hd) >> a.dsh) * LpD + (size_t)l0 * a.D;
-                    *reinterpret_cast<uint4*>(base + t_lane) = lo;
-                    *reinterpret_cast<uint4*>(base + t_lane + t_second) = hi;
+                if constexpr (PROJ) {
+                    // q, k, gate: [row][head][l][d]; v^T tiled by 32 keys: [row][head][l / 32][e][l % 32].  One place for all of them: of two
+                    // the compiler merges the ends, and writes the second store in pieces of 4 and 12 bytes
+                    bf16_t* to = kind == TK_Q ? a.q : (kind == TK_K ? a.k : (kind == TK_V ? a.vt : a.g));
+                    to += row_base + (size_t)((nb - kind * a.Hd) >> a.dsh) * LpD + (size_t)l0 * a.D;
+                    const unsigned at = kind == TK_V ? v_lane : t_lane;
+                    *reinterpret_cast<uint4*>(to + at) = lo;
+                    *reinterpret_cast<uint4*>(to + at + (kind == TK_V ? v_second : t_second)) = hi;
                     n_ops += 2;
                 } else {                                           // out: [token][N]
                     bf16_t* base = a.out + (size_t)(((int64_t)(a.r0 + rl) * a.sr + (int64_t)l0 * a.sl) * a.N + nb);
