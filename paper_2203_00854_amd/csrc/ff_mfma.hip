@@ -420,7 +420,8 @@ struct GemmArgs {
     const bf16_t* res;       // OUT with RES: added to the output, laid out like out (may be out itself)
     int N;                   // OUT: features
     int ft_count;            // feature tiles of this launch
-    int tiles_per_split;     // tiles per blockIdx.y
+    int tiles_per_split;     // feature tiles of a share
+    int along, split;        // blocks along the tokens, shares of the feature tiles
 };
 
 typedef void __attribute__((address_space(3)))* lptr_t;
@@ -456,12 +457,18 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gem
     constexpr int RSH = P >= 16 ? 0 : (P == 8 ? 1 : 2);
     constexpr int GM = (P >= 16 ? 16 : P) - 1;          // g(r) = (r >> RSH) & GM
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const int ft_begin = blockIdx.y * a.tiles_per_split;
+    // Work-groups go to the 8 XCDs round-robin and each XCD has its own L2: an XCD takes a contiguous range of the order (token block,
+    // share), so that the shares of the same tokens run on one XCD at the same time and every XCD has its eighth of the blocks.  (With
+    // the blocks along the tokens rounded up to a multiple of 8 instead, 8 x 48 tokens were two of eight: everything ran on two XCDs
+    // behind three empty blocks for each that had work.)
+    const int item = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+    const int block = (int)((unsigned)item / (unsigned)a.split), share = item - block * a.split;
+    const int ft_begin = share * a.tiles_per_split;
     const int ft_end = ft_begin + a.tiles_per_split < a.ft_count ? ft_begin + a.tiles_per_split : a.ft_count;
     const int n_ft = ft_end - ft_begin;
     const int NW = blockDim.x >> 6;                     // eight, or gemm_waves(KC)
     const int tiles_m = a.rows * (a.Lp >> 5);
-    if (n_ft <= 0 || (int)blockIdx.x * NW >= tiles_m) return;            // (whole block)
+    if (block >= a.along) return;                       // (whole block)
     const bool whole = n_ft <= 2 * NS;                                    // all of the block's weights are in LDS at once
     unsigned char* s_w = smem;                                            // [min(n_ft, 2 NS)][STAGE]
     uint4* s_aug = reinterpret_cast<uint4*>(smem + (whole ? n_ft : 2 * NS) * STAGE);      // PROJ: [n_ft][32] extra piece per feature
@@ -515,7 +522,7 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gem
             }
         }
     };
-    int unit = blockIdx.x * NW + wave;
+    int unit = block * NW + wave;
     load_tokens(unit);
 
     // ---- weight tiles: KC chunks of 64 pieces (1 KiB) each, shared out over the wavefronts: chunk c of a half goes to
@@ -725,7 +732,7 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gem
         }
         if constexpr (RES) asm volatile("" : : "v"(ahead[0]), "v"(ahead[1]));
         if (!whole) break;
-        unit += gridDim.x * NW;
+        unit += a.along * NW;
         if (unit >= tiles_m) break;
     }
 }
@@ -1189,10 +1196,9 @@ static ff_status launch_gemm_inst(GemmArgs a, int tiles_m, hipStream_t st) {
     // Blocks of eight wavefronts or of all that a compute unit holds, one token tile each, and the feature tiles shared out over `split` such blocks: what
     // makes the rounds of blocks times the time of a block least.  A block takes its tiles and about ten more for its tokens and first
     // weights, an eighth longer per wavefront and SIMD (128 x 128 triangle attention, projections: split in 1, 2, 3, 4, 6, 9, 17 29.5, 20.0, 17.8, 17.2,
-    // 15.5, 19.6, 27.6 us, the last two in a second round).  The blocks along the tokens are rounded up to a multiple of the 8 XCDs where
-    // they are split, so that the shares of the same tokens run on one XCD and fetch them into one L2.
+    // 15.5, 19.6, 27.6 us, the last two in a second round).
     const int cu = compute_units();
-    int blocks = 1, split = 1, waves = 8;
+    int waves = 8;
     double least = 1e300;
     for (int nw : {8, gemm_waves(KC)}) {
         const int along = (tiles_m + nw - 1) / nw;
@@ -1201,18 +1207,18 @@ static ff_status launch_gemm_inst(GemmArgs a, int tiles_m, hipStream_t st) {
             // blocks per compute unit (the output projections hold at most 128 registers at 256 channels too: two of eight wavefronts; 128 x 256
             // row attention, the whole call: 67.6 us with two shares in one block per unit each, 62.6 with four)
             const int fit = 2 * nw <= (PROJ ? gemm_waves(KC) : 16) && 2 * gemm_smem_bytes(KC, per) <= 160 * 1024 ? 2 : 1;
-            int b = n > 1 ? (along + 7) / 8 * 8 : along;
+            int b = along;
             const double cost = ceil((double)b * n / (cu * fit)) * (10 + per) * (24 + nw * fit);
             // (65 to 128 channels: more than 22 tiles with their offsets and extra pieces do not fit beside the ring)
             if (cost >= least || gemm_smem_bytes(KC, per) > 160 * 1024) continue;
             least = cost;
             // (whole weights: no more blocks than are resident, each takes more tokens)
             if (per <= 2 * gemm_half(KC) && (double)b * n > cu * fit) b = (cu * fit + n - 1) / n;
-            blocks = b; split = n; waves = nw;
-            a.tiles_per_split = per;
+            a.along = b; a.split = n; a.tiles_per_split = per;
+            waves = nw;
         }
     }
-    hipLaunchKernelGGL((k_gemm<KC, PROJ, RES>), dim3(blocks, split), dim3(waves * 64), gemm_smem_bytes(KC, a.tiles_per_split), st, a);
+    hipLaunchKernelGGL((k_gemm<KC, PROJ, RES>), dim3((a.along * a.split + 7) / 8 * 8), dim3(waves * 64), gemm_smem_bytes(KC, a.tiles_per_split), st, a);
     return FF_OK;
 }
 
