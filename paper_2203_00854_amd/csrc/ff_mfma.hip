@@ -513,11 +513,11 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gem
             }
         }
         if constexpr (RES) {
-            // the residual's lines of the token tile into L2, a load per line (N <= 256: at most four per token): the
+            // the residual's lines of the share into L2, a load per line (N <= 256: at most four per token): the
             // loads below come one feature tile ahead of their use, too late for memory
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                const int line = (lane >> 5) + 2 * i, at = 64 * line < a.N ? 64 * line : 0;
+                const int line = (lane >> 5) + 2 * i, at = ft_begin * 32 + 64 * line < ft_end * 32 ? ft_begin * 32 + 64 * line : ft_begin * 32;
                 ahead[i] = *reinterpret_cast<const uint32_t*>(a.res + (size_t)(((int64_t)(a.r0 + rl) * a.sr + (int64_t)lc * a.sl) * a.N) + at);
             }
         }
