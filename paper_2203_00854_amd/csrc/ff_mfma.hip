@@ -402,6 +402,12 @@ __global__ __launch_bounds__(512) void k_prep_bias(PrepBiasArgs a) {
 // r P + (p ^ g(r)); g spreads 16 consecutive rows over the 16 slots of a 256-byte LDS line, so
 // the operand reads (lane = row, all lanes the same piece) are conflict free without padding.
 struct GemmArgs {
+    int along, split;        // blocks along the tokens, shares of the feature tiles
+    uint32_t split_inv;      // 2^32 / split rounded up (split > 1): item / split as a product
+    int per_xcd;             // blocks of an XCD
+    int waves;               // wavefronts of a block: eight, or gemm_waves(KC)
+    int ft_count;            // feature tiles of this launch
+    int tiles_per_split;     // feature tiles of a share
     const bf16_t* src;     // PROJ: x or z (strided tokens); OUT: o [rows][H][Lp][D]
     int64_t sr, sl;        // token strides of src (PROJ) / out (OUT)
     int r0, rows, L, Lp, Lq;
@@ -419,9 +425,6 @@ struct GemmArgs {
     bf16_t* out;             // OUT output, token (r,l) at (r*sr + l*sl)*N
     const bf16_t* res;       // OUT with RES: added to the output, laid out like out (may be out itself)
     int N;                   // OUT: features
-    int ft_count;            // feature tiles of this launch
-    int tiles_per_split;     // feature tiles of a share
-    int along, split;        // blocks along the tokens, shares of the feature tiles
 };
 
 typedef void __attribute__((address_space(3)))* lptr_t;
@@ -461,12 +464,15 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gem
     // share), so that the shares of the same tokens run on one XCD at the same time and every XCD has its eighth of the blocks.  (With
     // the blocks along the tokens rounded up to a multiple of 8 instead, 8 x 48 tokens were two of eight: everything ran on two XCDs
     // behind three empty blocks for each that had work.)
-    const int item = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
-    const int block = (int)((unsigned)item / (unsigned)a.split), share = item - block * a.split;
+    // (all arguments are on their way before the first one is waited for: a small call waits for little else than its chain of loads)
+    asm volatile("" : : "s"(a.src), "s"(a.sr), "s"(a.sl), "s"(a.r0), "s"(a.rows), "s"(a.L), "s"(a.Lp), "s"(a.K), "s"(a.w), "s"(a.aug), "s"(a.bvec),
+                 "s"(a.Hd), "s"(a.H), "s"(a.D), "s"(a.dsh));
+    const int item = (int)(blockIdx.x & 7) * a.per_xcd + (int)(blockIdx.x >> 3);
+    const int block = a.split > 1 ? (int)__umulhi((unsigned)item, a.split_inv) : item, share = item - block * a.split;
     const int ft_begin = share * a.tiles_per_split;
     const int ft_end = ft_begin + a.tiles_per_split < a.ft_count ? ft_begin + a.tiles_per_split : a.ft_count;
     const int n_ft = ft_end - ft_begin;
-    const int NW = blockDim.x >> 6;                     // eight, or gemm_waves(KC)
+    const int NW = a.waves;
     const int tiles_m = a.rows * (a.Lp >> 5);
     if (block >= a.along) return;                       // (whole block)
     const bool whole = n_ft <= 2 * NS;                                    // all of the block's weights are in LDS at once
@@ -488,11 +494,12 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gem
     auto load_tokens = [&](int unit) __attribute__((always_inline)) {
         const int tg = unit < tiles_m ? unit : tiles_m - 1;
         // (a tile lies inside one batch row; neighbouring wavefronts take tokens that are neighbours in memory)
-        const int by = a.sl > a.sr ? a.rows : a.Lp >> 5, major = __builtin_amdgcn_readfirstlane(tg / by), minor = tg - major * by;
+        const unsigned by = (unsigned)(a.sl > a.sr ? a.rows : a.Lp >> 5);
+        const int major = (int)((unsigned)tg / by), minor = tg - major * (int)by;
         rl = a.sl > a.sr ? minor : major;
         l = 32 * (a.sl > a.sr ? major : minor) + col;
         valid = l < a.L;
-        // (no load sits under a condition: pad tokens repeat the last one, pieces beyond K the last one of the token, and are cleared below)
+        // (no load sits under a condition: pad tokens repeat the last one, pieces beyond K the last one of the token; clear_pad drops them)
         const int lc = valid ? l : a.L - 1;
         const bf16_t* sp = PROJ ? a.src + ((int64_t)(a.r0 + rl) * a.sr + (int64_t)lc * a.sl) * K : nullptr;
         const bf16_t* ctx = PROJ ? nullptr : a.src + (size_t)rl * a.H * LpD;
@@ -505,13 +512,6 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gem
             if constexpr (PROJ) xa[s].u = ldg16(sp + f);
             else xa[s].u = ldg16(ctx, (uint32_t)(hh * LpD + lc * a.D + (f - (hh << a.dsh))) * 2);
         }
-        if (l - col + 32 > a.L || K != 16 * KC) {                        // (wave-uniform)
-#pragma unroll
-            for (int s = 0; s < KC; ++s) {
-                const uint32_t m = valid && 16 * s + 8 * hf < K ? 0xffffffffu : 0u;
-                xa[s].u = make_uint4(xa[s].u.x & m, xa[s].u.y & m, xa[s].u.z & m, xa[s].u.w & m);
-            }
-        }
         if constexpr (RES) {
             // the residual's lines of the share into L2, a load per line (N <= 256: at most four per token): the
             // loads below come one feature tile ahead of their use, too late for memory
@@ -519,6 +519,16 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gem
             for (int i = 0; i < 2; ++i) {
                 const int line = (lane >> 5) + 2 * i, at = ft_begin * 32 + 64 * line < ft_end * 32 ? ft_begin * 32 + 64 * line : ft_begin * 32;
                 ahead[i] = *reinterpret_cast<const uint32_t*>(a.res + (size_t)(((int64_t)(a.r0 + rl) * a.sr + (int64_t)lc * a.sl) * a.N) + at);
+            }
+        }
+    };
+    // (where the tokens are waited for anyway: between their loads and those of the weights it would put one memory latency behind the other)
+    auto clear_pad = [&]() __attribute__((always_inline)) {
+        if (l - col + 32 > a.L || K != 16 * KC) {                        // (wave-uniform)
+#pragma unroll
+            for (int s = 0; s < KC; ++s) {
+                const uint32_t m = valid && 16 * s + 8 * hf < K ? 0xffffffffu : 0u;
+                xa[s].u = make_uint4(xa[s].u.x & m, xa[s].u.y & m, xa[s].u.z & m, xa[s].u.w & m);
             }
         }
     };
@@ -574,6 +584,8 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gem
     __syncthreads();
 
     for (;; load_tokens(unit)) {
+        clear_pad();
+        if constexpr (RES) asm volatile("" : : "v"(ahead[0]), "v"(ahead[1]));      // (they set out with the tokens)
         const bool run = unit < tiles_m;                      // (wave-uniform; without whole weights a wavefront without tokens still takes its share of the loads)
         float rstd = 0.f;         // 1 / standard deviation of this lane's token
         Frag xaug;                // its extra piece of the contraction: (-mean, standard deviation) as bf16 pairs (see k_prep)
@@ -730,7 +742,6 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gem
                 if (next < n_ft) issue(next, n_ft - next < NS ? n_ft - next : NS, next % (2 * NS));
             }
         }
-        if constexpr (RES) asm volatile("" : : "v"(ahead[0]), "v"(ahead[1]));
         if (!whole) break;
         unit += a.along * NW;
         if (unit >= tiles_m) break;
@@ -1198,7 +1209,7 @@ static ff_status launch_gemm_inst(GemmArgs a, int tiles_m, hipStream_t st) {
     // weights, an eighth longer per wavefront and SIMD (128 x 128 triangle attention, projections: split in 1, 2, 3, 4, 6, 9, 17 29.5, 20.0, 17.8, 17.2,
     // 15.5, 19.6, 27.6 us, the last two in a second round).
     const int cu = compute_units();
-    int waves = 8;
+    a.waves = 8;
     double least = 1e300;
     for (int nw : {8, gemm_waves(KC)}) {
         const int along = (tiles_m + nw - 1) / nw;
@@ -1210,15 +1221,18 @@ static ff_status launch_gemm_inst(GemmArgs a, int tiles_m, hipStream_t st) {
             int b = along;
             const double cost = ceil((double)b * n / (cu * fit)) * (10 + per) * (24 + nw * fit);
             // (65 to 128 channels: more than 22 tiles with their offsets and extra pieces do not fit beside the ring)
-            if (cost >= least || gemm_smem_bytes(KC, per) > 160 * 1024) continue;
+            // (nor, at any size that memory holds, more blocks than split_inv divides exactly)
+            if (cost >= least || gemm_smem_bytes(KC, per) > 160 * 1024 || (n > 1 && (int64_t)along * n * n >= ((int64_t)1 << 31))) continue;
             least = cost;
             // (whole weights: no more blocks than are resident, each takes more tokens)
             if (per <= 2 * gemm_half(KC) && (double)b * n > cu * fit) b = (cu * fit + n - 1) / n;
             a.along = b; a.split = n; a.tiles_per_split = per;
-            waves = nw;
+            a.waves = nw;
         }
     }
-    hipLaunchKernelGGL((k_gemm<KC, PROJ, RES>), dim3((a.along * a.split + 7) / 8 * 8), dim3(waves * 64), gemm_smem_bytes(KC, a.tiles_per_split), st, a);
+    a.split_inv = a.split > 1 ? (uint32_t)((((uint64_t)1 << 32) + a.split - 1) / a.split) : 0u;
+    a.per_xcd = (a.along * a.split + 7) / 8;
+    hipLaunchKernelGGL((k_gemm<KC, PROJ, RES>), dim3(8 * a.per_xcd), dim3(a.waves * 64), gemm_smem_bytes(KC, a.tiles_per_split), st, a);
     return FF_OK;
 }
 
