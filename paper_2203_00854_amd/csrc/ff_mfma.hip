@@ -101,8 +101,8 @@ static MfmaWs split_ws(const Problem& p, int chunk, const Workspace& ws) {
     MfmaWs m;
     m.q = (bf16_t*)ws.qkvg;
     m.k = m.q + n;
-    m.g = m.k + n;
-    m.vt = m.g + n;
+    m.vt = m.k + n;        // (the order of the feature tiles: k_gemm steps from one tensor to the next)
+    m.g = m.vt + n;
     m.o = (bf16_t*)ws.o;
     char* pr = (char*)ws.prep;
     const size_t rows_main = 4 * (size_t)p.Hd + 32;
@@ -391,11 +391,12 @@ __global__ __launch_bounds__(512) void k_prep_bias(PrepBiasArgs a) {
 // first, the wavefronts of the grid walk over the token tiles by themselves), else two halves of NS tiles each, one being
 // worked on while the other is filled (global_load_lds_dwordx4: lane i of a wavefront deposits its 16 bytes at the
 // wave-uniform LDS base + 16 i).
-// What bounds it is the number of instructions a wavefront can issue (one every eight cycles or so, whatever the others do): about 60 per
-// 32 x 32 tile beside KC + 1 matrix instructions.  So the registers are held to 128, sixteen wavefronts per compute unit, and a wavefront finishes a
-// tile before it begins the next one: the matrix instructions of one hide behind the epilogues of the other three of its SIMD.  A kernel of
-// eight wavefronts with 186 to 250 registers that alternated the matrix instructions of a tile with the epilogue of the one before took
-// 150 to 200 instructions per tile: projections of 64 x 2048 tokens of 128 channels 46 -> 38 us, of 333 x 333 50 -> 40, of 60 x 300 of 256 channels 34 -> 29.5.
+// What bounds it is the number of instructions a wavefront can issue (one every eight cycles or so, whatever the others do): a q or k tile at 128
+// channels passes 170, 9 of them matrix instructions, 82 vector, LDS and memory instructions, the rest scalar ones, waits and branches.  So the
+// registers are held to 128, sixteen wavefronts per compute unit, and a wavefront finishes a
+// tile before it begins the next one: the matrix instructions of one hide behind the epilogues of the other three of its SIMD.  (A kernel of
+// eight wavefronts with 186 to 250 registers that alternated the matrix instructions of a tile with the epilogue of the one before: whole calls of
+// triangle attention at 333 117 us, now 104; 60 x 300 row attention 75, now 60; 300 x 48 columns 52, now 46.)
 // No instance may spill: a kernel that uses scratch memory starts 2.5 us later (8 x 48 row attention, projections 11.7 -> 9.2 us).
 //
 // LDS image of a tile: 32 rows of P = 2 KC 16-byte pieces, piece p of row r at slot
@@ -418,9 +419,10 @@ struct GemmArgs {
     const bf16_t* bvec;    // OUT: b_o [N]
     int Hd, H, D;
     int dsh;               // log2(D), D in {8, 16, 32}
-    float invD;            // 1 / D
+    int odd_step, even_step; // OUT: elements from an even contraction step of 16 channels to the odd one behind it, and from that to the next even one
     int nt_main;           // PROJ: 32-feature tiles of q|k|v|gate; tile nt_main is the pair-bias tile
-    bf16_t *q, *k, *g, *vt;  // PROJ outputs
+    bf16_t* q;               // PROJ outputs: q, then k, v^T and gate, each `tensor` elements behind the one before
+    int64_t tensor;
     float* bias;             // PROJ pair-bias output, [H][Lq][Lp] elements in the tiles of bias_index
     bf16_t* out;             // OUT output, token (r,l) at (r*sr + l*sl)*N
     const bf16_t* res;       // OUT with RES: added to the output, laid out like out (may be out itself)
@@ -466,7 +468,7 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gem
     // behind three empty blocks for each that had work.)
     // (all arguments are on their way before the first one is waited for: a small call waits for little else than its chain of loads)
     asm volatile("" : : "s"(a.src), "s"(a.sr), "s"(a.sl), "s"(a.r0), "s"(a.rows), "s"(a.L), "s"(a.Lp), "s"(a.K), "s"(a.w), "s"(a.aug), "s"(a.bvec),
-                 "s"(a.Hd), "s"(a.H), "s"(a.D), "s"(a.dsh));
+                 "s"(a.Hd), "s"(a.H), "s"(a.D), "s"(a.dsh), "s"(a.odd_step), "s"(a.even_step));
     const int item = (int)(blockIdx.x & 7) * a.per_xcd + (int)(blockIdx.x >> 3);
     const int block = a.split > 1 ? (int)__umulhi((unsigned)item, a.split_inv) : item, share = item - block * a.split;
     const int ft_begin = share * a.tiles_per_split;
@@ -499,18 +501,41 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gem
         rl = a.sl > a.sr ? minor : major;
         l = 32 * (a.sl > a.sr ? major : minor) + col;
         valid = l < a.L;
-        // (no load sits under a condition: pad tokens repeat the last one, pieces beyond K the last one of the token; clear_pad drops them)
+        // (pad tokens load the last one again: clear_pad drops it)
         const int lc = valid ? l : a.L - 1;
-        const bf16_t* sp = PROJ ? a.src + ((int64_t)(a.r0 + rl) * a.sr + (int64_t)lc * a.sl) * K : nullptr;
-        const bf16_t* ctx = PROJ ? nullptr : a.src + (size_t)rl * a.H * LpD;
-        int half = hf;
-        asm volatile("" : "+v"(half));                                    // (the offsets below: worked out anew for every tile, not kept, or spilled)
+        // (K is a multiple of 16, so a contraction step has both of its pieces or none: what depends on the step is uniform.  Worked out step by
+        // step, from an opaque K: the offsets of all steps at once do not fit the scalar registers)
+        int k = K;
+        asm volatile("" : "+s"(k));
+        if constexpr (PROJ) {
+            const bf16_t* sp = a.src + ((int64_t)(a.r0 + rl) * a.sr + (int64_t)lc * a.sl) * K + 8 * hf;
+            if (k == 16 * KC) {
 #pragma unroll
-        for (int s = 0; s < KC; ++s) {
-            const int f = 16 * s + 8 * half < K ? 16 * s + 8 * half : K - 8;
-            const int hh = f >> a.dsh;                                    // OUT: gated context, head-major [row][head][l][d]
-            if constexpr (PROJ) xa[s].u = ldg16(sp + f);
-            else xa[s].u = ldg16(ctx, (uint32_t)(hh * LpD + lc * a.D + (f - (hh << a.dsh))) * 2);
+                for (int s = 0; s < KC; ++s) xa[s].u = ldg16(sp + 16 * s);
+            } else {
+#pragma unroll
+                for (int s = 0; s < KC; ++s) {
+                    if (16 * s < k) xa[s].u = ldg16(sp + 16 * s);
+                    else xa[s].u = make_uint4(0, 0, 0, 0);
+                }
+            }
+        } else {                                                          // gated context, head-major [row][head][l][d]
+            const bf16_t* ctx = a.src + (size_t)rl * a.H * LpD;
+            const uint32_t lane_at = (uint32_t)(lc * a.D + (a.D == 8 ? hf * LpD : 8 * hf)) * 2;
+            if (k == 16 * KC) {
+#pragma unroll
+                for (int s = 0; s < KC; ++s) {
+                    xa[s].u = ldg16(ctx, lane_at);
+                    ctx += s & 1 ? a.even_step : a.odd_step;
+                }
+            } else {
+#pragma unroll
+                for (int s = 0; s < KC; ++s) {
+                    if (16 * s < k) xa[s].u = ldg16(ctx, lane_at);
+                    else xa[s].u = make_uint4(0, 0, 0, 0);
+                    ctx += s & 1 ? a.even_step : a.odd_step;
+                }
+            }
         }
         if constexpr (RES) {
             // the residual's lines of the share into L2, a load per line (N <= 256: at most four per token): the
@@ -524,12 +549,10 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gem
     };
     // (where the tokens are waited for anyway: between their loads and those of the weights it would put one memory latency behind the other)
     auto clear_pad = [&]() __attribute__((always_inline)) {
-        if (l - col + 32 > a.L || K != 16 * KC) {                        // (wave-uniform)
+        if (l - col + 32 > a.L) {                                        // (wave-uniform)
+            const uint32_t m = valid ? 0xffffffffu : 0u;
 #pragma unroll
-            for (int s = 0; s < KC; ++s) {
-                const uint32_t m = valid && 16 * s + 8 * hf < K ? 0xffffffffu : 0u;
-                xa[s].u = make_uint4(xa[s].u.x & m, xa[s].u.y & m, xa[s].u.z & m, xa[s].u.w & m);
-            }
+            for (int s = 0; s < KC; ++s) xa[s].u = make_uint4(xa[s].u.x & m, xa[s].u.y & m, xa[s].u.z & m, xa[s].u.w & m);
         }
     };
     int unit = block * NW + wave;
@@ -562,6 +585,12 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gem
     const unsigned v_lane = (unsigned)(t16 >> a.dsh) * LpD + (unsigned)(t16 & (a.D - 1)) * 32 + piece8;
     const unsigned v_second = (unsigned)((16 >> a.dsh) * LpD + (16 & (a.D - 1)) * 32);
     const int64_t o_lane = (int64_t)t16 * a.sl * a.N + piece8;
+
+    // the share's first tile (see the loop): its kind, the tiles left of that kind, its place in the outputs of a batch row
+    const int per_kind = a.nt_main >> 2, tile_step = (32 >> a.dsh) * LpD;
+    const int kind0 = PROJ ? (ft_begin >= per_kind) + (ft_begin >= 2 * per_kind) + (ft_begin >= 3 * per_kind) + (ft_begin >= a.nt_main) : (int)TK_OUT;
+    const int kind_left0 = (kind0 + 1) * per_kind - ft_begin;
+    const int64_t to0 = kind0 * a.tensor + (per_kind - kind_left0) * tile_step;
 
     // ---- residual (RES): the matrix core adds it.  Two more contraction steps multiply a
     // selection matrix (feature f of the tile picks slot f, then f - 16) with the residual
@@ -616,12 +645,17 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gem
         };
         if constexpr (RES) load_res(ft_begin);
         int n_ops = 0;            // stores and residual loads issued since the last weight loads (a lower bound)
+        // What a tile needs of its place moves on by additions: its slot in LDS, the tiles left of its half of the ring, its kind, the tiles left of
+        // that kind, and where its tokens (l0 .. l0 + 31 of the batch row) begin in the tensor of that kind.  (Worked out per tile it was
+        // half of the tile's instructions.)
+        const unsigned char* st = s_w;
+        int ring = NS;
+        int kind = kind0, kind_left = kind_left0;
+        bf16_t* to = PROJ ? a.q + row_base + (size_t)l0 * a.D + to0
+                          : a.out + (size_t)(((int64_t)(a.r0 + rl) * a.sr + (int64_t)l0 * a.sl) * a.N + ft_begin * 32);
         for (int n = 0; n < n_ft; ++n) {
-            const int ft = ft_begin + n, nb = ft * 32;
+            const int ft = ft_begin + n;
             if (run) {
-                const unsigned char* st = s_w + (whole ? n : n % (2 * NS)) * STAGE;
-                // q and k share their epilogue
-                const int kind = !PROJ ? TK_OUT : (ft >= a.nt_main ? TK_BIAS : (nb >= a.Hd) + (nb >= 2 * a.Hd) + (nb >= 3 * a.Hd));
                 f32x16 acc;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[v] = 0.f;
@@ -685,10 +719,12 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gem
                         int lq = l;
                         asm volatile("" : "+v"(lq));                           // (the sixteen addresses: not before the loop)
                         float* bp = a.bias + bias_index(4 * hf, a.r0 + rl, lq, a.Lq, a.Lp);
+                        int plane = a.Lq * a.Lp;
+                        asm volatile("" : "+s"(plane));                        // (and the sixteen multiples of it)
 #pragma unroll
                         for (int v = 0; v < 16; ++v) {
                             const int hu = 8 * (v >> 2) + (v & 3);               // head of the lower half-wave
-                            if (hu < a.H - 4 * hf) bp[(size_t)hu * a.Lq * a.Lp] = acc[v] * rstd;
+                            if (hu < a.H - 4 * hf) bp[(size_t)hu * plane] = acc[v] * rstd;
                         }
                         continue;                                              // (the last tile)
                     } else {
@@ -715,20 +751,30 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gem
                 if constexpr (PROJ) {
                     // q, k, gate: [row][head][l][d]; v^T tiled by 32 keys: [row][head][l / 32][e][l % 32].  One place for all of them: of two
                     // the compiler merges the ends, and writes the second store in pieces of 4 and 12 bytes
-                    bf16_t* to = kind == TK_Q ? a.q : (kind == TK_K ? a.k : (kind == TK_V ? a.vt : a.g));
-                    to += row_base + (size_t)((nb - kind * a.Hd) >> a.dsh) * LpD + (size_t)l0 * a.D;
                     const unsigned at = kind == TK_V ? v_lane : t_lane;
                     *reinterpret_cast<uint4*>(to + at) = lo;
                     *reinterpret_cast<uint4*>(to + at + (kind == TK_V ? v_second : t_second)) = hi;
                     n_ops += 2;
                 } else {                                           // out: [token][N]
-                    bf16_t* base = a.out + (size_t)(((int64_t)(a.r0 + rl) * a.sr + (int64_t)l0 * a.sl) * a.N + nb);
-                    if (l0 + (lane & 15) < a.L) *reinterpret_cast<uint4*>(base + o_lane) = lo;
-                    if (l0 + 16 + (lane & 15) < a.L) *reinterpret_cast<uint4*>(base + o_lane + 16 * a.sl * a.N) = hi;
+                    if (l0 + (lane & 15) < a.L) *reinterpret_cast<uint4*>(to + o_lane) = lo;
+                    if (l0 + 16 + (lane & 15) < a.L) *reinterpret_cast<uint4*>(to + o_lane + 16 * a.sl * a.N) = hi;
                     if (l0 < a.L) n_ops += l0 + 16 < a.L ? 2 : 1;  // (wave-uniform: the instructions were issued)
                 }
             }
-            if (!whole && (n + 1) % NS == 0 && n + 1 < n_ft) {
+            st = st + STAGE < s_w + 2 * NS * STAGE ? st + STAGE : s_w;
+            if constexpr (PROJ) {
+                to += tile_step;
+                if (--kind_left == 0) {
+                    asm volatile("");                         // (a branch: seldom taken)
+                    ++kind;
+                    kind_left = per_kind;
+                    to += a.tensor - a.H * LpD;
+                }
+            } else {
+                to += 32;
+            }
+            if (--ring == 0 && !whole && n + 1 < n_ft) {
+                ring = NS;
                 // Order of this wavefront's memory operations: ... L(i+1), S, L(i+2), S, ... (L = loads of a half, S = the stores
                 // issued during one half).  The next half needs L(i+1): everything but the stores issued after it must have completed.
                 // After the barrier all wavefronts have their share of L(i+1) in LDS and have finished
@@ -1272,9 +1318,9 @@ static GemmArgs proj_args(const Problem& p, const MfmaWs& m, const Workspace& ws
     const int Lp = round_up(p.L, 32), Lq = round_up(p.L, 32);
     GemmArgs g{};
     g.sr = p.sr; g.sl = p.sl; g.L = p.L; g.Lp = Lp; g.Lq = Lq; g.K = p.c; g.eps = p.eps;
-    g.w = m.wp; g.aug = m.aug; g.Hd = p.Hd; g.H = p.H; g.D = p.d; g.invD = 1.f / (float)p.d; g.dsh = p.d == 8 ? 3 : (p.d == 16 ? 4 : 5);
+    g.w = m.wp; g.aug = m.aug; g.Hd = p.Hd; g.H = p.H; g.D = p.d; g.dsh = p.d == 8 ? 3 : (p.d == 16 ? 4 : 5);
     g.nt_main = 4 * p.Hd / 32;
-    g.q = m.q; g.k = m.k; g.g = m.g; g.vt = m.vt; g.bias = ws.bias;
+    g.q = m.q; g.tensor = m.k - m.q; g.bias = ws.bias;
     return g;
 }
 
@@ -1398,7 +1444,8 @@ ff_status mfma_chunk(const Problem& p, const ff_attn_weights& w, const void* x, 
     GemmArgs o{};
     o.src = m.o; o.sr = p.sr; o.sl = p.sl; o.r0 = r0; o.rows = rows; o.L = p.L; o.Lp = Lp; o.Lq = Lq;
     o.K = p.Hd; o.w = (const bf16_t*)w.w_o; o.bvec = (const bf16_t*)w.b_o;
-    o.Hd = p.Hd; o.H = p.H; o.D = p.d; o.invD = 1.f / (float)p.d; o.dsh = p.d == 8 ? 3 : (p.d == 16 ? 4 : 5); o.out = (bf16_t*)out; o.N = p.c;
+    o.Hd = p.Hd; o.H = p.H; o.D = p.d; o.dsh = p.d == 8 ? 3 : (p.d == 16 ? 4 : 5); o.out = (bf16_t*)out; o.N = p.c;
+    o.odd_step = p.d == 32 ? 16 : Lp * 16; o.even_step = p.d == 32 ? Lp * 32 - 16 : o.odd_step;
     {
         o.ft_count = o.N / 32;
         Timed t(KK_OUT, st);

@@ -30,6 +30,22 @@ DEV = "cuda:0"
 ])
 @pytest.mark.parametrize("residual", [False, True])
 def test_shapes(mode, n_a, n_b, c, H, d, c_z, mask, residual):
+    check(mode, n_a, n_b, c, H, d, c_z, mask, residual)
+
+
+@pytest.mark.parametrize("mode,n_a,n_b,c,H,d,c_z,mask", [
+    (I.MODE_COL, 5, 70, 96, 12, 8, 0, "none"),                # two of 128 channels' steps missing in both contractions, heads of 8 channels
+    (I.MODE_ROW, 7, 40, 160, 10, 16, 32, "tail:7"),           # six of sixteen, heads of 16
+    (I.MODE_ROW, 9, 33, 224, 7, 32, 32, "random:0.8"),        # two of sixteen, heads of 32
+    (I.MODE_TRI_END, 37, 37, 32, 1, 32, 0, "none"),           # two steps, one tile of each kind
+])
+@pytest.mark.parametrize("residual", [False, True])
+def test_contraction_lengths(mode, n_a, n_b, c, H, d, c_z, mask, residual):
+    """Channels and head channels that leave steps of the contraction empty, at each head dim (the step to the next operand differs)."""
+    check(mode, n_a, n_b, c, H, d, c_z, mask, residual)
+
+
+def check(mode, n_a, n_b, c, H, d, c_z, mask, residual):
     case = I.make_case(small_spec(mode, n_a, n_b, c, H, d, c_z=c_z, dtype="bf16", mask=mask))
     desc, w, x, z, m = P.to_device(case, DEV)
     ws = torch.full((P.ff_attention_workspace_bytes(desc, 0),), 0xFF, dtype=torch.uint8, device=DEV)      # (NaN patterns)
