@@ -442,6 +442,7 @@ __device__ __forceinline__ void wait_vmem_but_last(int n) {
 }
 
 constexpr int gemm_waves(int kc) { return kc >= 16 ? 12 : 16; }    // wavefronts per compute unit: four per SIMD, three where the tokens take 64 registers
+constexpr int gemm_fit(int kc, bool proj) { return proj ? gemm_waves(kc) : 16; }   // and of several blocks: the output projections keep to 128 registers at 256 channels too
 constexpr int gemm_half(int kc) { return kc >= 16 ? 4 : 9; }       // NS: weight tiles per half of the ring
 
 // dynamic LDS of k_gemm: weight tiles, 1/std of the wavefronts' tokens, per-feature offsets and extra pieces
@@ -454,7 +455,7 @@ static size_t gemm_smem_bytes(int kc, int tiles) {
 enum { TK_Q = 0, TK_K = 1, TK_V = 2, TK_GATE = 3, TK_BIAS = 4, TK_OUT = 5 };
 
 template <int KC, bool PROJ, bool RES>
-__global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_waves(KC) / 4) void k_gemm(GemmArgs a) {
+__global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_fit(KC, PROJ) / 4) void k_gemm(GemmArgs a) {
     static_assert(!(PROJ && RES), "the residual belongs to the output projection");
     constexpr int NS = gemm_half(KC);
     constexpr int P = 2 * KC;                           // 16-byte pieces per weight row
@@ -1251,28 +1252,35 @@ static ff_status launch_gemm_inst(GemmArgs a, int tiles_m, hipStream_t st) {
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return fail(FF_EHIP, "k_gemm: dynamic LDS limit: %s", hipGetErrorString(attr));
     // Blocks of eight wavefronts or of all that a compute unit holds, one token tile each, and the feature tiles shared out over `split` such blocks: what
-    // makes the rounds of blocks times the time of a block least.  A block takes its tiles and about ten more for its tokens and first
-    // weights, an eighth longer per wavefront and SIMD (128 x 128 triangle attention, projections: split in 1, 2, 3, 4, 6, 9, 17 29.5, 20.0, 17.8, 17.2,
-    // 15.5, 19.6, 27.6 us, the last two in a second round).
+    // makes the rounds of blocks times the time of a block least.  A block takes its tiles and about five more for its tokens and first
+    // weights, each the longer the more wavefronts its compute unit really holds (fewer than fit where the grid does not fill the chip), and a seventh
+    // more through the ring with its barriers.  The constants lie where the regret over all splits of 160 launches is least (both kernels of 94 calls from
+    // 8 x 48 to 2048 x 2048 tokens, 32 to 256 channels): 0.2 % of the call on average and 4 % at most above the best split, 93 % of
+    // them within 1 %.  (Charging every block for the wavefronts that could share its unit, ten tiles and 24 wavefronts: 1.2 % on average, 11 % at most -
+    // twelve wavefronts for the outputs of 32 x 64 tokens of 256 channels, 27.1 us the call, eight 25.4; projections of 384 x 384 tokens
+    // in 288 blocks, two rounds, 161.5, in two shares 149.)
     const int cu = compute_units();
     a.waves = 8;
     double least = 1e300;
-    for (int nw : {8, gemm_waves(KC)}) {
+    constexpr bool large_first = KC > 4;                     // (of equals the larger blocks, which load the weights less often; where those are short the smaller ones)
+    for (int nw : {large_first ? gemm_waves(KC) : 8, large_first ? 8 : gemm_waves(KC)}) {
         const int along = (tiles_m + nw - 1) / nw;
-        for (int t = 1; t <= a.ft_count; t += t < 8 ? 1 : t / 4) {
+        for (int t = 1, next; t <= a.ft_count; t = t < a.ft_count && next > a.ft_count ? a.ft_count : next) {
+            next = t + (t < 8 ? 1 : t / 4);
             const int per = (a.ft_count + t - 1) / t, n = (a.ft_count + per - 1) / per;
-            // blocks per compute unit (the output projections hold at most 128 registers at 256 channels too: two of eight wavefronts; 128 x 256
-            // row attention, the whole call: 67.6 us with two shares in one block per unit each, 62.6 with four)
-            const int fit = 2 * nw <= (PROJ ? gemm_waves(KC) : 16) && 2 * gemm_smem_bytes(KC, per) <= 160 * 1024 ? 2 : 1;
-            int b = along;
-            const double cost = ceil((double)b * n / (cu * fit)) * (10 + per) * (24 + nw * fit);
             // (65 to 128 channels: more than 22 tiles with their offsets and extra pieces do not fit beside the ring)
             // (nor, at any size that memory holds, more blocks than split_inv divides exactly)
-            if (cost >= least || gemm_smem_bytes(KC, per) > 160 * 1024 || (n > 1 && (int64_t)along * n * n >= ((int64_t)1 << 31))) continue;
+            if (gemm_smem_bytes(KC, per) > 160 * 1024 || (n > 1 && (int64_t)along * n * n >= ((int64_t)1 << 31))) continue;
+            // blocks per compute unit (gemm_fit: what the registers allow)
+            const int fit = 2 * nw <= gemm_fit(KC, PROJ) && 2 * gemm_smem_bytes(KC, per) <= 160 * 1024 ? 2 : 1;
+            const double blocks = (double)along * n;
+            const bool whole = per <= 2 * gemm_half(KC);
+            const double cost = ceil(blocks / (cu * fit)) * (5 + per) * (8 + nw * fmin(fit, ceil(blocks / cu))) * (whole ? 1 : 1.15);
+            if (cost >= least) continue;
             least = cost;
             // (whole weights: no more blocks than are resident, each takes more tokens)
-            if (per <= 2 * gemm_half(KC) && (double)b * n > cu * fit) b = (cu * fit + n - 1) / n;
-            a.along = b; a.split = n; a.tiles_per_split = per;
+            a.along = whole && blocks > cu * fit ? (cu * fit + n - 1) / n : along;
+            a.split = n; a.tiles_per_split = per;
             a.waves = nw;
         }
     }

@@ -45,6 +45,19 @@ def test_contraction_lengths(mode, n_a, n_b, c, H, d, c_z, mask, residual):
     check(mode, n_a, n_b, c, H, d, c_z, mask, residual)
 
 
+@pytest.mark.parametrize("mode,n_a,n_b,c,H,d,c_z,mask", [
+    (I.MODE_ROW, 8, 48, 256, 8, 32, 32, "tail:3"),            # shares of one tile; two blocks along the tokens on eight XCDs
+    (I.MODE_TRI_START, 43, 43, 128, 4, 32, 0, "outer:0.9"),   # seventeen tiles, the last share the pair bias alone
+    (I.MODE_COL, 100, 100, 256, 8, 32, 0, "tail:9"),          # five shares of seven tiles: they begin inside q, k, v and gate
+    (I.MODE_ROW, 3, 500, 256, 8, 16, 16, "none"),             # a token block that is mostly empty
+    (I.MODE_COL, 40, 830, 256, 8, 32, 0, "none"),             # more token tiles than resident wavefronts, in shares
+])
+@pytest.mark.parametrize("residual", [False, True])
+def test_shares(mode, n_a, n_b, c, H, d, c_z, mask, residual):
+    """How the feature tiles are shared out over blocks, and the blocks over the XCDs."""
+    check(mode, n_a, n_b, c, H, d, c_z, mask, residual)
+
+
 def check(mode, n_a, n_b, c, H, d, c_z, mask, residual):
     case = I.make_case(small_spec(mode, n_a, n_b, c, H, d, c_z=c_z, dtype="bf16", mask=mask))
     desc, w, x, z, m = P.to_device(case, DEV)
