@@ -10,10 +10,10 @@
 // Launches:
 //   k_bwd_prepare  the bias times sqrt(d), tile by tile in the order of the accumulator registers, once with lane = query and
 //                once with lane = key, so that a bias tile is four 16-byte loads per lane in every kernel; the key masks as bits
-//   k_bwd_rows   up to 512 positions: a block per (row, head), everything but the bias gradient:
+//   k_bwd_rows   up to 512 positions of enough (row, head)s (rows_in_lds): a block per (row, head), everything but the bias gradient:
 //                forward recomputation with an online softmax (the logsumexp of every query, base 2, ctx, dg and delta), then P and dS once
 //                for dq, dk and dv
-//   k_bwd_stats, k_bwd_dq, k_bwd_dkv   longer sequences: the same in three kernels, one wavefront per 32-query (or 32-key) tile, four
+//   k_bwd_stats, k_bwd_dq, k_bwd_dkv   longer sequences, and few (row, head)s of more than 320 positions: the same in three kernels, one wavefront per 32-query (or 32-key) tile, four
 //                consecutive tiles of one (row, head) per block; the tiles of the other side, which all four contract with, are copied into LDS
 //                once per block, a tile ahead of the arithmetic.  dq: S^T = K Q^T and dP^T = V dctx^T (lane = query, so that
 //                logsumexp and delta are lane-local), dS^T, dq^T += K^T dS^T; dkv: S = Q K^T and dP = dctx V^T (lane = key), P and
@@ -633,7 +633,9 @@ __global__ __launch_bounds__(256, FULL ? 3 : 1) void k_bwd_dkv(Args a) {
 // the key rows of the wavefront it comes from.  The wavefronts work on different query tiles, so every one of
 // them has exactly one such contraction per step.
 // What bounds it: the instructions that the wavefronts of a SIMD can issue (about 130 per tile for the statistics, 190 in the second phase),
-// at four wavefronts per SIMD, hence at most 128 registers; then the bytes.  Two tiles per wavefront and two wavefronts per SIMD need fewer
+// at four wavefronts per SIMD, hence at most 128 registers (d = 16 with a bias and d = 32 without keep 28 and 12 bytes a lane in scratch memory); then the bytes.
+// From nine wavefronts on a block is alone on its compute unit: 2.25 wavefronts per SIMD at 288 positions (128 rows x 8 heads x 32 with a bias 160 us the
+// call, the three kernels 222; 320 181 / 247, 384 231 / 310, 448 274 / 382).  Two tiles per wavefront and two wavefronts per SIMD need fewer
 // LDS reads, but took 96 us at 128 rows x 8 heads x 256 x 32 with a bias; now 77, the three kernels 117 (46 + 32 + 40).  Without its tile
 // loops it takes 39 us there for the 168 MB that it moves.
 // Rows are 64 bytes whatever the head dim, the 16-byte piece p of row n at p ^ (n / 4) % 4: operand reads of rows and transposing reads alike
@@ -1132,6 +1134,26 @@ static int dbias_chunks(const ff_core_desc& d) {
     return chunks < 1 ? 1 : chunks;
 }
 
+// Whether k_bwd_rows takes the call, with a block per (row, head) and a wavefront per 32 positions, or the three kernels with their blocks of four
+// tiles.  One block holds up to kRowsTiles tiles, and from nine on it is alone on its compute unit.  Up to there it is the better one at every size
+// (4 to 1120 (row, head)s of 64 to 256 positions: 0.55 to 0.98 of the three kernels' time).  Two exceptions above:
+//  - so few (row, head)s that most units have none: four wavefronts share a SIMD while others idle.  With ever longer sequences ever more
+//    of them are too few: 4 (row, head)s, d = 32 without a bias, of 320 positions 22.2 us against 21.7, 384 26.5 / 24.4, 416 33.4 / 25.9, 512 41.3 / 29.9;
+//    64 of 384 27.5 / 28.1, 416 35.0 / 30.7, 512 42.9 / 34.8; 96 of 512 44.7 / 44.0; with a bias 4 of 512 61 / 51, 64 72 / 64, 96 74 / 74.
+//  - more than there are units by so few that the second round is nearly empty, without a bias: 264 of 512 positions at d = 8 take 75.5 us against 68.0, at
+//    d = 16 77.4 / 71.3, 320 76.5 / 69.8 and 77.8 / 74.7, of 384 48.0 / 45.4 and 49.4 / 48.6; the three kernels' time steps up where their
+//    blocks begin another round (336 of 512 at d = 8 76.7 / 79.4).  At d = 32 264 of 512 92.1 / 89.8, 296 92.6 / 92.7, of 384 58.9 / 59.6.  With a
+//    bias the three kernels read its tiles three times: 264 of 512 at d = 16 121 / 118, else never.
+static bool rows_in_lds(const ff_core_desc& d, int nt, bool bias) {
+    const int64_t rh = (int64_t)d.rows * d.heads, cu = compute_units();
+    if (nt > bwd::kRowsTiles) return false;
+    if (nt < 9) return true;
+    if (8 * rh <= cu * ((nt - 9) / 2)) return false;
+    if (bias || rh <= cu) return true;
+    const int fours = (nt + 3) / 4;
+    return d.head_dim == 32 ? nt < 13 || 8 * rh > 9 * cu : rh * fours > (fours + 1) * cu;
+}
+
 size_t core_backward_workspace(const ff_core_desc& d) {
     const size_t Lp = bwd::round_up(d.length, 32), rh = (size_t)d.rows * d.heads;
     const int chunks = dbias_chunks(d);
@@ -1185,7 +1207,7 @@ ff_status core_backward_run(const ff_core_desc& d, const void* q, const void* k,
         else if (d.head_dim == 16) FF_BWD_D(KERNEL, GRID, 16);                                           \
         else FF_BWD_D(KERNEL, GRID, 32);                                                                 \
     } while (0)
-    const bool in_lds = nt <= kRowsTiles;                   // (longer sequences: the three kernels that pass the other side through LDS)
+    const bool in_lds = rows_in_lds(d, nt, bias != nullptr);
     if (bias || (!mask && !in_lds)) {
         Timed t(KK_BWD_STATS, st);
         const size_t tasks = bias ? (size_t)d.heads * nt * nt + (size_t)d.rows * ((nt + 1) / 2) : 1;

@@ -90,6 +90,43 @@ def test_lengths_around_the_limits_of_a_block(rows, heads, length, d, bias, mask
     check_all(case, run(case), oracle(case), spec.name)
 
 
+@pytest.mark.parametrize("d", [8, 16, 32])
+@pytest.mark.parametrize("bias", [True, False])
+@pytest.mark.parametrize("rows,heads,length,mask", [(2, 2, 416, "random:0.8"), (3, 1, 430, "tail:17"), (1, 2, 544, "none"), (1, 1, 530, "random:0.7")])
+def test_kernels_that_pass_tiles(rows, heads, length, mask, bias, d):
+    """Few (row, head)s of long sequences, and sequences longer than a block holds: whole tiles and a ragged last one, at every head dim."""
+    spec = I.CoreSpec(f"t_core_tiles_{rows}_{heads}_{length}_{d}_{int(bias)}_{mask}", rows, heads, length, d, bias, mask)
+    case = I.make_core_case(spec)
+    check_all(case, run(case), oracle(case), spec.name)
+
+
+@pytest.mark.parametrize("rows,heads,length,d,bias,mask", [
+    (26, 4, 512, 32, True, "random:0.9"), (25, 4, 470, 16, False, "tail:21"), (33, 4, 449, 8, True, "none"), (86, 4, 290, 16, False, "random:0.9")])
+def test_blocks_that_hold_a_row(rows, heads, length, d, bias, mask):
+    """As many (row, head)s as one block each takes, of lengths that leave a block alone on its compute unit."""
+    spec = I.CoreSpec(f"t_core_rows_{rows}_{heads}_{length}_{d}_{int(bias)}_{mask}", rows, heads, length, d, bias, mask)
+    case = I.make_core_case(spec)
+    check_all(case, run(case), oracle(case), spec.name)
+
+
+@pytest.mark.parametrize("rows,heads,length,bias,d,whole", [
+    (1, 4, 320, True, 32, True), (1, 4, 384, False, 32, False), (16, 4, 384, False, 32, True), (16, 4, 416, True, 16, False), (16, 4, 512, False, 8, False),
+    (32, 4, 512, False, 32, True), (33, 8, 512, False, 8, False), (33, 8, 512, True, 8, True), (33, 8, 384, False, 32, True), (37, 8, 512, False, 32, True),
+    (40, 8, 512, False, 8, False), (42, 8, 512, False, 8, True), (42, 8, 384, False, 16, False), (43, 8, 384, False, 16, True),
+    (2, 4, 128, True, 32, True), (64, 8, 520, True, 32, False)])
+def test_which_kernels_take_a_call(rows, heads, length, bias, d, whole):
+    """A block per (row, head) leaves an MI355X of 256 compute units idle where there are few of them, and needs a second round where there
+    are just more than units: there the kernels that pass tiles are the faster ones."""
+    q = torch.zeros((rows, heads, length, d), dtype=torch.bfloat16, device=DEV)
+    b = torch.zeros((heads, length, length), device=DEV) if bias else None
+    P.ff_profile_enable(True)
+    P.ff_attention_core_backward(P.CoreDesc(P.FF_BF16, rows, heads, length, d), q, q, q, q, b, None, q)
+    kinds = set(P.ff_profile_collect())
+    P.ff_profile_enable(False)
+    assert ("k_bwd_rows" in kinds) == whole, kinds
+    assert ("k_bwd_dq" in kinds) != whole, kinds
+
+
 def test_fully_masked_rows_have_zero_gradients():
     spec = I.CoreSpec("t_core_dead", 4, 2, 50, 32, True, "random:0.8")
     case = I.make_core_case(spec)
