@@ -292,8 +292,8 @@ size_t ff_static_scratch_bytes(void);
 /* Name of the kernel family the SHAPE allows: "mfma_bf16" (bfloat16 matrix-core path) or
  * "generic" (float32 path).  NULL if desc is invalid.  A call takes the matrix-core family only
  * if, in addition, x, z, out and every weight pointer are 16-byte aligned and the chunk has
- * fewer than 2^22 units of 64 queries of one head of eight batch rows (of four without a bias below
- * head dim 32); ff_attention_last_path tells what a call really took. */
+ * fewer than 2^22 units of 64 queries of one head of eight batch rows (of four without a bias);
+ * ff_attention_last_path tells what a call really took. */
 const char* ff_attention_path(const ff_attn_desc* desc);
 
 /* Kernel family that the last attention call on this thread launched ("mfma_bf16" or

@@ -1299,11 +1299,20 @@ static ff_status launch_gemm(const GemmArgs& a, hipStream_t st) {
     return launch_gemm_inst<16, PROJ, RES>(a, tiles_m, st);
 }
 
+// Units of 64 queries of one head of eight batch rows (of four without a bias, where a wavefront takes two rows, and in small chunks): a unit has at
+// most 512 threads of k_attn_rows' grid (attn_rows_launch: blocks of two wavefronts and two rows up to two tiles, else of four wavefronts
+// and four rows, two without a bias) and 512 padded tokens of one head, so below 2^22 units both are less than 2^31, and the kernels count both in an int.
+constexpr int chunk_unit_rows(bool small, bool bias) { return small || !bias ? 4 : 8; }
+constexpr bool unit_holds_512_threads(bool bias) {
+    for (int nt = 1; nt <= 16384 / 32; ++nt) {
+        const int waves = nt <= 2 ? 2 : 4, rows = nt <= 2 || !bias ? 2 : 4, rb = chunk_unit_rows(false, bias);
+        if ((nt + waves - 1) / waves * ((rb + rows - 1) / rows) * waves * 64 > 512 * ((nt + 1) / 2)) return false;
+    }
+    return true;
+}
+static_assert(unit_holds_512_threads(true) && unit_holds_512_threads(false), "the limit of mfma_chunk_ok covers the grid of k_attn_rows");
 bool mfma_chunk_ok(const Problem& p, int chunk) {
-    // units of 64 queries of one head of eight batch rows (four without a bias below head dim 32): below 2^22 of them the padded
-    // tokens of the chunk (rows x Lp) and the threads of k_attn_rows' grid (blocks of 64 to 128 queries of one head of two or
-    // four rows: at most four blocks of 128 threads or two of 256 per unit) are less than 2^31, and the kernels count both in an int
-    const int rb = chunk < 8 || (!p.has_bias && p.d < 32) ? 4 : 8;
+    const int rb = chunk_unit_rows(chunk < 8, p.has_bias);
     return (int64_t)(round_up(p.L, 64) / 64) * p.H * ((chunk + rb - 1) / rb) < (1 << 22);
 }
 
