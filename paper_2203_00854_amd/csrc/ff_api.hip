@@ -22,7 +22,7 @@ static const char* kKindNames[KK_COUNT] = {"k_prep", "pair bias pass", "k_gemm<P
                                            "probe: copy", "k_tm_prep", "k_tm_proj", "k_tm_mul", "k_tm_out",
                                            "k_gca_kv", "k_gca_softmax", "k_gca_out",
                                            "k_bwd_stats", "k_bwd_dq", "k_bwd_dkv", "k_bwd_dbias", "probe: vector loop",
-                                           "k_proj_attn", "k_bwd_rows"};
+                                           "k_proj_attn", "k_bwd_rows", "k_bwd_prepare", "k_bwd_dbias_reduce"};
 
 static hipEvent_t prof_event() {
     if (!g_prof_pool.empty()) {

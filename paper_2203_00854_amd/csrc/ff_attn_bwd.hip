@@ -1209,7 +1209,7 @@ ff_status core_backward_run(const ff_core_desc& d, const void* q, const void* k,
     } while (0)
     const bool in_lds = rows_in_lds(d, nt, bias != nullptr);
     if (bias || (!mask && !in_lds)) {
-        Timed t(KK_BWD_STATS, st);
+        Timed t(KK_BWD_PREPARE, st);
         const size_t tasks = bias ? (size_t)d.heads * nt * nt + (size_t)d.rows * ((nt + 1) / 2) : 1;
         hipLaunchKernelGGL(k_bwd_prepare, dim3((unsigned)((tasks + 3) / 4)), dim3(256), 0, st, a);
     }
@@ -1256,7 +1256,7 @@ ff_status core_backward_run(const ff_core_desc& d, const void* q, const void* k,
             if (attr != hipSuccess) return fail(FF_EHIP, "k_bwd_dbias: dynamic LDS limit: %s", hipGetErrorString(attr));
         }
         if (a.row_chunks > 1) {
-            Timed t(KK_BWD_DBIAS, st);
+            Timed t(KK_BWD_DBIAS_REDUCE, st);
             hipLaunchKernelGGL(k_bwd_dbias_reduce, dim3((unsigned)((size_t)d.heads * nt * nt)), dim3(256), 0, st, a);
         }
     }

@@ -127,6 +127,19 @@ def test_which_kernels_take_a_call(rows, heads, length, bias, d, whole):
     assert ("k_bwd_dq" in kinds) != whole, kinds
 
 
+@pytest.mark.parametrize("rows,length,expected", [
+    (128, 64, {"k_bwd_prepare": 1, "k_bwd_rows": 1, "k_bwd_dbias": 1, "k_bwd_dbias_reduce": 1}),
+    (1, 513, {"k_bwd_prepare": 1, "k_bwd_stats": 1, "k_bwd_dq": 1, "k_bwd_dkv": 1, "k_bwd_dbias": 1})])
+def test_launch_timer_kinds(rows, length, expected):
+    """Every kernel has a kind of its own: the rate of one that contracts must not be taken over launches that do not."""
+    q = torch.zeros((rows, 2, length, 16), dtype=torch.bfloat16, device=DEV)
+    P.ff_profile_enable(True)
+    P.ff_attention_core_backward(P.CoreDesc(P.FF_BF16, rows, 2, length, 16), q, q, q, q, torch.zeros((2, length, length), device=DEV), None, q)
+    kinds = {k: n for k, (_, n) in P.ff_profile_collect().items()}
+    P.ff_profile_enable(False)
+    assert kinds == expected
+
+
 def test_fully_masked_rows_have_zero_gradients():
     spec = I.CoreSpec("t_core_dead", 4, 2, 50, 32, True, "random:0.8")
     case = I.make_core_case(spec)
