@@ -140,6 +140,21 @@ def test_launch_timer_kinds(rows, length, expected):
     assert kinds == expected
 
 
+@pytest.mark.parametrize("rows,heads,length,d", [(4, 2, 100, 8), (3, 2, 255, 32), (26, 4, 500, 16), (2, 2, 420, 32), (1, 1, 515, 8)])
+def test_masked_keys_with_a_far_larger_bias(rows, heads, length, d):
+    """The bias of the keys that are attended to lies 300 below that of the masked ones: weights of masked keys that a kernel forms and
+    drops are infinite (2^433), and times a zero or negative dP - delta NaN or -infinity."""
+    case = I.make_core_case(I.CoreSpec(f"t_core_shift_{rows}_{heads}_{length}_{d}", rows, heads, length, d, True, "tail:37"))
+    live = length - 37
+    case.tensors["bias"][:, :, :live] -= np.float32(300.0)
+    got = run(case)
+    check_all(case, got, oracle(case), case.spec.name)
+    for name, g in zip(NAMES, got):
+        masked = g[..., live:] if name == "dbias" else g[:, :, live:]
+        if name in ("dk", "dv", "dbias"):
+            assert not masked.any(), name
+
+
 def test_fully_masked_rows_have_zero_gradients():
     spec = I.CoreSpec("t_core_dead", 4, 2, 50, 32, True, "random:0.8")
     case = I.make_core_case(spec)
