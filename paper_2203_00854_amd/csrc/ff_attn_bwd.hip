@@ -281,42 +281,31 @@ __device__ __forceinline__ void staged_cols(Frag (&f)[2], const unsigned char* r
     }
 }
 
-// Tile loop of the two kernels whose wavefronts keep a query tile and walk over the key tiles.  Memory is two
-// tiles ahead of the arithmetic: while tile t is worked on, tile t + 1 waits in registers (it was requested during
-// tile t - 1 and goes into the free LDS stage at the end of tile t) and tile t + 2 is being requested; one tile
-// ahead the block stalled on every tile for most of a memory latency.  Two named register sets (even tiles, odd
+// Tile loop of the two kernels whose wavefronts keep a query tile and walk over the key tiles.  Memory is one
+// tile ahead of the arithmetic: while tile t is worked on, tile t + 1 is being requested, and it goes into the free LDS stage at
+// the end of tile t.  Two named register sets (even tiles, odd
 // tiles), hence a loop body written for a literal parity P and used twice: tile tt + P, stage P, sets [P].
 //   rs[P]: staged pieces of the thread; brow[P]: the lane's bias rows; mk[P]: the lane's key-mask entry.
-// tiles between a request to memory and its use (1 or 2)
-constexpr int kAhead = 1;
 #define FF_BWD_Q_PROLOGUE                                                                                        \
     uint4 rs[2][2];                                                                                              \
     float4 brow[2][4];                                                                                           \
     float mk[2] = {1.f, 1.f};                                                                                    \
     const int i0a = active ? i0 : 0;                                                                             \
     const float* mrow = a.mrow + (size_t)r * a.mstride;                                                          \
-    {                                                                                                            \
-        const int n1 = 32 < a.L ? 32 : 0;         /* (a single tile: fetched twice, the second copy unused) */   \
-        plan.fetch(0, a.L, rs[0][0], rs[0][1]);                                         \
-        if (kAhead == 2) plan.fetch(n1, a.L, rs[1][0], rs[1][1]);                       \
-        if (BIAS) {                                                                                              \
-            bias_tile_fetch(brow[0], a.biasA, h, nt, i0a >> 5, 0, lane);                                         \
-            if (kAhead == 2) bias_tile_fetch(brow[1], a.biasA, h, nt, i0a >> 5, n1 >> 5, lane);                  \
-        }                                                                                                        \
-        if (FULL || col < a.L) mk[0] = mrow[col];                                                                \
-        if (kAhead == 2 && (FULL || n1 + col < a.L)) mk[1] = mrow[n1 + col];                                     \
-    }                                                                                                            \
-    plan.store(s_stage, 0, a.L, rs[0][0], rs[0][1]);                                    \
+    plan.fetch(0, a.L, rs[0][0], rs[0][1]);                                                                      \
+    if (BIAS) bias_tile_fetch(brow[0], a.biasA, h, nt, i0a >> 5, 0, lane);                                       \
+    if (FULL || col < a.L) mk[0] = mrow[col];                                                                    \
+    plan.store(s_stage, 0, a.L, rs[0][0], rs[0][1]);                                                             \
     __syncthreads();
 // (bt and kx: what the accumulator of the logits starts from, see bias_tile_fetch.  Every load of the loop is issued on
-// every path - the last two tiles ask for themselves again - because a load under a condition makes the compiler
+// every path - the last tile asks for itself again - because a load under a condition makes the compiler
 // wait, at every later wait, also for the loads just issued.)
 #define FF_BWD_Q_HEAD(P)                                                                                         \
     const int j0 = 32 * (tt + (P));                                                                              \
     const unsigned char* stage = s_stage + (P) * kStBytes;                                                       \
-    constexpr int PF = kAhead == 2 ? (P) : 1 - (P);       /* the register set that receives what is requested now */ \
-    const int jn = j0 + 32 * kAhead < a.L ? j0 + 32 * kAhead : j0;                                               \
-    plan.fetch(jn, a.L, rs[PF][0], rs[PF][1]);                                         \
+    constexpr int PF = 1 - (P);                           /* the register set that receives what is requested now */ \
+    const int jn = j0 + 32 < a.L ? j0 + 32 : j0;                                                                 \
+    plan.fetch(jn, a.L, rs[PF][0], rs[PF][1]);                                                                   \
     const Frag kx = key_side((FULL || j0 + col < a.L) && mk[P] != 0.f, hf);                                      \
     f32x16 bt;                                                                                                   \
     if (BIAS) rows_to_acc(bt, brow[P]);                                                                          \
@@ -539,15 +528,8 @@ __global__ __launch_bounds__(256, FULL ? 3 : 1) void k_bwd_dkv(Args a) {
     uint4 rs[2][2];
     StagePlan<D, FULL> plan;
     plan.init(src, tid);
-    {
-        const int n1 = 32 < a.L ? 32 : 0;
-        plan.fetch(0, a.L, rs[0][0], rs[0][1]);
-        if (kAhead == 2) plan.fetch(n1, a.L, rs[1][0], rs[1][1]);
-        if (BIAS) {
-            bias_tile_fetch(brow[0], a.biasK, h, nt, 0, jta, lane);
-            if (kAhead == 2) bias_tile_fetch(brow[1], a.biasK, h, nt, n1 >> 5, jta, lane);
-        }
-    }
+    plan.fetch(0, a.L, rs[0][0], rs[0][1]);
+    if (BIAS) bias_tile_fetch(brow[0], a.biasK, h, nt, 0, jta, lane);
     plan.store(s_stage, 0, a.L, rs[0][0], rs[0][1]);
     __syncthreads();
 
@@ -556,9 +538,9 @@ __global__ __launch_bounds__(256, FULL ? 3 : 1) void k_bwd_dkv(Args a) {
     {                                                                                                            \
         const int i0 = 32 * (tt + (P));                                                                          \
         const unsigned char* stage = s_stage + (P) * kStBytes;                                                   \
-        constexpr int PF = kAhead == 2 ? (P) : 1 - (P);                                                          \
-        const int in = i0 + 32 * kAhead < a.L ? i0 + 32 * kAhead : i0;    /* (the last tiles ask for themselves again) */ \
-        plan.fetch(in, a.L, rs[PF][0], rs[PF][1]);                                     \
+        constexpr int PF = 1 - (P);                                                                              \
+        const int in = i0 + 32 < a.L ? i0 + 32 : i0;              /* (the last tile asks for itself again) */    \
+        plan.fetch(in, a.L, rs[PF][0], rs[PF][1]);                                                               \
         f32x16 s;                                                                                                \
         if (BIAS) {                                                                                              \
             rows_to_acc(s, brow[P]);                                                                             \
