@@ -243,7 +243,7 @@ ff_status ff_global_column_attention(const ff_global_desc* desc, const ff_global
  *   dS = P * (dP - rowsum(P * dP));  dq[i] = scale sum_j dS[i,j] k[j];  dk[j] = scale sum_i dS[i,j] q[i];
  *   dbias[h,i,j] = sum_r dS[r,h,i,j].
  * The score matrix is recomputed tile by tile, never stored (Section 3.2).  A query without unmasked keys has
- * P = 0 and all of its gradients are zero.  q, k, v, g, dout and the four gradients are bfloat16
+ * P = 0 and all of its gradients are zero; what k and v hold for a masked key, NaN included, reaches no gradient.  q, k, v, g, dout and the four gradients are bfloat16
  * [rows, heads, length, head_dim]; bias and dbias float32 [heads, length, length] (both NULL for a module without
  * bias); mask float32 [rows, length] of 0/1 or NULL.  P, dS and dctx are rounded to bfloat16 as matrix-core
  * operands; logsumexp, delta and all accumulations are float32; dbias is summed over the rows in a fixed order. */

@@ -281,6 +281,21 @@ __device__ __forceinline__ void staged_cols(Frag (&f)[2], const unsigned char* r
     }
 }
 
+// Rows of masked keys in a stage become zeros: their weights are zero, but zero times a NaN is not.  Every wavefront does so for itself before it
+// reads (its LDS operations complete in order, and the others write the same zeros), and only in tiles that hold masked keys, which it knows
+// before the barrier in front of the tile.  (Dropped on their way into the stage, every tile waited for its mask entries: 2 to 5 % of a call
+// of few (row, head)s.)
+template <int D>
+__device__ __forceinline__ void zero_masked(unsigned char* stage, bool ok, int col, int hf) {
+    if (ok) return;
+#pragma unroll
+    for (int pc = 0; pc < D / 8; pc += 2)
+        if (pc + hf < D / 8) {
+            *reinterpret_cast<uint4*>(stage + kStRowsX + col * kStPitch + (pc + hf) * 16) = make_uint4(0, 0, 0, 0);
+            *reinterpret_cast<uint4*>(stage + kStRowsY + col * kStPitch + (pc + hf) * 16) = make_uint4(0, 0, 0, 0);
+        }
+}
+
 // Tile loop of the two kernels whose wavefronts keep a query tile and walk over the key tiles.  Memory is one
 // tile ahead of the arithmetic: while tile t is worked on, tile t + 1 is being requested, and it goes into the free LDS stage at
 // the end of tile t.  Two named register sets (even tiles, odd
@@ -296,17 +311,20 @@ __device__ __forceinline__ void staged_cols(Frag (&f)[2], const unsigned char* r
     if (BIAS) bias_tile_fetch(brow[0], a.biasA, h, nt, i0a >> 5, 0, lane);                                       \
     if (FULL || col < a.L) mk[0] = mrow[col];                                                                    \
     plan.store(s_stage, 0, a.L, rs[0][0], rs[0][1]);                                                             \
+    bool masked = !__all((FULL || col < a.L) && mk[0] != 0.f);           /* the tile in the stage holds masked keys */ \
     __syncthreads();
 // (bt and kx: what the accumulator of the logits starts from, see bias_tile_fetch.  Every load of the loop is issued on
 // every path - the last tile asks for itself again - because a load under a condition makes the compiler
 // wait, at every later wait, also for the loads just issued.)
 #define FF_BWD_Q_HEAD(P)                                                                                         \
     const int j0 = 32 * (tt + (P));                                                                              \
-    const unsigned char* stage = s_stage + (P) * kStBytes;                                                       \
+    unsigned char* stage = s_stage + (P) * kStBytes;                                                             \
     constexpr int PF = 1 - (P);                           /* the register set that receives what is requested now */ \
     const int jn = j0 + 32 < a.L ? j0 + 32 : j0;                                                                 \
     plan.fetch(jn, a.L, rs[PF][0], rs[PF][1]);                                                                   \
-    const Frag kx = key_side((FULL || j0 + col < a.L) && mk[P] != 0.f, hf);                                      \
+    const bool key_ok = (FULL || j0 + col < a.L) && mk[P] != 0.f;                                                \
+    const Frag kx = key_side(key_ok, hf);                                                                        \
+    if (masked) zero_masked<D>(stage, key_ok, col, hf);                                                          \
     f32x16 bt;                                                                                                   \
     if (BIAS) rows_to_acc(bt, brow[P]);                                                                          \
     else bt = zero16();                                                                                          \
@@ -314,7 +332,8 @@ __device__ __forceinline__ void staged_cols(Frag (&f)[2], const unsigned char* r
     if (FULL || jn + col < a.L) mk[PF] = mrow[jn + col];
 #define FF_BWD_Q_TAIL(P)                                                                                         \
     if (j0 + 32 < a.L)                                                                                           \
-        plan.store(s_stage + (1 - (P)) * kStBytes, j0 + 32, a.L, rs[1 - (P)][0], rs[1 - (P)][1]); \
+        plan.store(s_stage + (1 - (P)) * kStBytes, j0 + 32, a.L, rs[1 - (P)][0], rs[1 - (P)][1]);                \
+    masked = !__all((FULL || j0 + 32 + col < a.L) && mk[1 - (P)] != 0.f);                                        \
     __syncthreads();
 
 // ====================================================================================
@@ -519,6 +538,9 @@ __global__ __launch_bounds__(256, FULL ? 3 : 1) void k_bwd_dkv(Args a) {
     load_rows<D, FULL>(kf, a.k + base, active ? j0 : 0, a.L, col, hf);
     load_rows<D, FULL>(vf, a.v + base, active ? j0 : 0, a.L, col, hf);
     const bool key_ok = active && (FULL || j < a.L) && a.mrow[(size_t)r * a.mstride + ((FULL || j < a.L) ? j : 0)] != 0.f;
+    if (!key_ok)                              // (zeros, as everywhere: the content of a masked key reaches nothing)
+#pragma unroll
+        for (int s = 0; s < KS; ++s) kf[s].u = vf[s].u = make_uint4(0, 0, 0, 0);
     // What the accumulator of the logits starts from (see bias_tile_fetch), here with lane = key and register v =
     // query i0 + 8(v/4) + 4hf + v%4: the bias tile times sqrt(d), and -inf in every register if the lane's key is
     // masked or beyond L.  Two sets of bias tiles (even and odd query tiles), requested ahead like the staged tiles.
@@ -1044,6 +1066,14 @@ __global__ __launch_bounds__(1024, 4) void k_bwd_dbias(Args a) {
         stage();
         if (active) {
             const Frag kx = key_side((lv >> col) & 1u, hf);
+            if (lv != 0xffffffffu) {                           // (wave-uniform: masked keys are zeros here too)
+                const bool ok = (lv >> col) & 1u;
+#pragma unroll
+                for (int c = 0; c < KS; ++c) {
+                    kf[c].u = only_if(ok, kf[c].u);
+                    vf[c].u = only_if(ok, vf[c].u);
+                }
+            }
             f32x16 s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kx.v, one.v, bt, 0, 0, 0), dp = zero16();
 #pragma unroll
             for (int c = 0; c < KS; ++c) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[c].v, qf[c].v, s, 0, 0, 0);

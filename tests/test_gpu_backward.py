@@ -155,6 +155,28 @@ def test_masked_keys_with_a_far_larger_bias(rows, heads, length, d):
             assert not masked.any(), name
 
 
+@pytest.mark.parametrize("d", [8, 16, 32])
+@pytest.mark.parametrize("bias", [True, False])
+@pytest.mark.parametrize("rows,heads,length", [(5, 2, 71, ), (16, 8, 128), (2, 2, 416), (1, 2, 545), (1, 1, 576)])
+def test_content_of_masked_keys_reaches_nothing(rows, heads, length, bias, d):
+    """NaN and infinities in k and v of masked keys give the very gradients that zeros there give, in both paths."""
+    case = I.make_core_case(I.CoreSpec(f"t_core_poison_{rows}_{heads}_{length}_{d}_{int(bias)}", rows, heads, length, d, bias, "random:0.8"))
+    desc, t, mask = P.core_to_device(case, DEV)
+    dead = (mask == 0)[:, None, :].expand(rows, heads, length)
+    got = []
+    for value in (0.0, float("nan"), float("inf")):
+        k, v = t["k"].clone(), t["v"].clone()
+        k[dead] = value
+        v[dead] = -value
+        got.append(P.ff_attention_core_backward(desc, t["q"], k, v, t["g"], t.get("bias"), mask, t["do"]))
+    torch.cuda.synchronize()
+    for name, a, b, c in zip(NAMES, *got):
+        if a is None:
+            continue
+        assert torch.isfinite(a).all(), name
+        assert torch.equal(a, b) and torch.equal(a, c), name
+
+
 def test_fully_masked_rows_have_zero_gradients():
     spec = I.CoreSpec("t_core_dead", 4, 2, 50, 32, True, "random:0.8")
     case = I.make_core_case(spec)
