@@ -101,8 +101,11 @@ static MfmaWs split_ws(const Problem& p, int chunk, const Workspace& ws) {
     MfmaWs m;
     m.q = (bf16_t*)ws.qkvg;
     m.k = m.q + n;
-    m.vt = m.k + n;        // (the order of the feature tiles: k_gemm steps from one tensor to the next)
-    m.g = m.vt + n;
+    // The gate between k and v^T, not behind them in the order of the feature tiles: k_attn_rows streams k and v^T at the same time, and with
+    // the two next to each other it draws more power for the same cycles and bytes, so a card at its power limit runs it at a lower
+    // clock (1024 x 384 tokens, 64 channels, head dim 8, called over and over on such a card: 436 us next to each other, 431 apart).
+    m.g = m.k + n;
+    m.vt = m.g + n;
     m.o = (bf16_t*)ws.o;
     char* pr = (char*)ws.prep;
     const size_t rows_main = 4 * (size_t)p.Hd + 32;
@@ -422,7 +425,7 @@ struct GemmArgs {
     int dsh;               // log2(D), D in {8, 16, 32}
     int odd_step, even_step; // OUT: elements from an even contraction step of 16 channels to the odd one behind it, and from that to the next even one
     int nt_main;           // PROJ: 32-feature tiles of q|k|v|gate; tile nt_main is the pair-bias tile
-    bf16_t* q;               // PROJ outputs: q, then k, v^T and gate, each `tensor` elements behind the one before
+    bf16_t* q;               // PROJ outputs: q, then k, gate and v^T, each `tensor` elements behind the one before
     int64_t tensor;
     float* bias;             // PROJ pair-bias output, [H][Lq][Lp] elements in the tiles of bias_index
     bf16_t* out;             // OUT output, token (r,l) at (r*sr + l*sl)*N
@@ -467,12 +470,15 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_fit(KC, PROJ) / 4) void k
     // Work-groups go to the 8 XCDs round-robin and each XCD has its own L2: an XCD takes a contiguous range of the order (token block,
     // share), so that the shares of the same tokens run on one XCD at the same time and every XCD has its eighth of the blocks.  (With
     // the blocks along the tokens rounded up to a multiple of 8 instead, 8 x 48 tokens were two of eight: everything ran on two XCDs
-    // behind three empty blocks for each that had work.)
+    // behind three empty blocks for each that had work.)  Projections without shares have no tokens to share and take the blocks as they
+    // come, so that what the chip writes at one time lies together: eight ranges far apart leave k_attn_rows, which reads them next, 3 % slower at
+    // 700 x 250 tokens of 64 channels (the call 164.0 -> 157.7 us on a card with power to spare, 172 -> 161 at its limit; 1024 x 384 405 -> 409
+    // and 436 -> 423 with the order of the tensors above; within 1 % elsewhere).  The output projection keeps the ranges: so do the kernels that write its tokens.
     // (all arguments are on their way before the first one is waited for: a small call waits for little else than its chain of loads)
     asm volatile("" : : "s"(a.src), "s"(a.sr), "s"(a.sl), "s"(a.r0), "s"(a.rows), "s"(a.L), "s"(a.Lp), "s"(a.K), "s"(a.w), "s"(a.aug), "s"(a.bvec),
                  "s"(a.Hd), "s"(a.H), "s"(a.D), "s"(a.dsh), "s"(a.odd_step), "s"(a.even_step));
     const int item = (int)(blockIdx.x & 7) * a.per_xcd + (int)(blockIdx.x >> 3);
-    const int block = a.split > 1 ? (int)__umulhi((unsigned)item, a.split_inv) : item, share = item - block * a.split;
+    const int block = a.split > 1 ? (int)__umulhi((unsigned)item, a.split_inv) : (PROJ ? (int)blockIdx.x : item), share = a.split > 1 ? item - block * a.split : 0;
     const int ft_begin = share * a.tiles_per_split;
     const int ft_end = ft_begin + a.tiles_per_split < a.ft_count ? ft_begin + a.tiles_per_split : a.ft_count;
     const int n_ft = ft_end - ft_begin;
@@ -592,7 +598,7 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_fit(KC, PROJ) / 4) void k
     const int per_kind = a.nt_main >> 2, tile_step = (32 >> a.dsh) * LpD;
     const int kind0 = PROJ ? (ft_begin >= per_kind) + (ft_begin >= 2 * per_kind) + (ft_begin >= 3 * per_kind) + (ft_begin >= a.nt_main) : (int)TK_OUT;
     const int kind_left0 = (kind0 + 1) * per_kind - ft_begin;
-    const int64_t to0 = kind0 * a.tensor + (per_kind - kind_left0) * tile_step;
+    const int64_t to0 = (kind0 ^ (kind0 >> 1)) * a.tensor + (per_kind - kind_left0) * tile_step;
 
     // ---- residual (RES): the matrix core adds it.  Two more contraction steps multiply a
     // selection matrix (feature f of the tile picks slot f, then f - 16) with the residual
@@ -770,7 +776,7 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_fit(KC, PROJ) / 4) void k
                     asm volatile("");                         // (a branch: seldom taken)
                     ++kind;
                     kind_left = per_kind;
-                    to += a.tensor - a.H * LpD;
+                    to += (kind == TK_V ? 2 : (kind == TK_GATE ? -1 : 1)) * a.tensor - a.H * LpD;      // (q, k, gate, v^T)
                 }
             } else {
                 to += 32;
