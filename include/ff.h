@@ -256,7 +256,7 @@ typedef struct {
 } ff_core_desc;
 
 /* Bytes of device workspace (logsumexp and delta per query, dctx, two tiled copies of the bias, partial sums of dbias
- * over groups of rows: little more than the size of q plus a few times that of the bias, never a score-sized tensor);
+ * over groups of rows: 1.1 to 1.5 times the size of q (head_dim 32 to 8) plus a few times that of the bias, never a score-sized tensor);
  * 0 if desc is invalid or unsupported. */
 size_t ff_attention_core_backward_workspace_bytes(const ff_core_desc* desc);
 

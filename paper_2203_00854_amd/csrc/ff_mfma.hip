@@ -400,7 +400,7 @@ __global__ __launch_bounds__(512) void k_prep_bias(PrepBiasArgs a) {
 // tile before it begins the next one: the matrix instructions of one hide behind the epilogues of the other three of its SIMD.  (A kernel of
 // eight wavefronts with 186 to 250 registers that alternated the matrix instructions of a tile with the epilogue of the one before: whole calls of
 // triangle attention at 333 117 us, now 104; 60 x 300 row attention 75, now 60; 300 x 48 columns 52, now 46.)  The projections of 64 x 2048
-// tokens of 128 channels take 34 us, 0.22 of the matrix rate, with 88 vector and 64 scalar instructions per tile (counters).
+// tokens of 128 channels take 34 to 36 us, 0.21 of the matrix rate, with 88 vector and 69 scalar instructions per tile (counters).
 // No instance may spill: a kernel that uses scratch memory starts 2.5 us later (8 x 48 row attention, projections 11.7 -> 9.2 us).
 //
 // LDS image of a tile: 32 rows of P = 2 KC 16-byte pieces, piece p of row r at slot
