@@ -4,29 +4,26 @@
 // product with V, output linear), Section 2.3 (axes, pair bias) and Section 5.2 (softmax with the mask and bias
 // addends fused in; gate = bias + sigmoid + product).
 //
-// All contractions run on the float32 matrix instruction v_mfma_f32_32x32x2_f32: the same float32 products and sums
-// as the vector unit's multiply-add at twice its rate, and the operands are read once per 32 x 32 tile instead of
-// once per few outputs.  Operand layouts (wave64): A (32 x 2): lane l holds row l%32, column l/32; B (2 x 32): lane l
-// holds column l%32, row l/32; C/D (32 x 32): lane l holds column l%32, register v holds row 8*(v/4) + 4*(l/32) + v%4.
-// Which contraction index a lane's half stands for is free as long as A and B agree, so a lane reads four
-// consecutive elements k0 + 4*half .. + 3 at once and feeds four instructions with them.
+// All contractions run on the bfloat16 matrix instruction v_mfma_f32_32x32x16_bf16, a float32 operand as the exact sum of three bfloat16 values
+// (see split4), a bfloat16 one as it is.  Operand layouts (wave64): A (32 x 16): lane l holds row l%32, columns 8*(l/32) .. + 7; B (16 x 32): lane l
+// holds column l%32, rows 8*(l/32) .. + 7; C/D (32 x 32): lane l holds column l%32, register v holds row 8*(v/4) + 4*(l/32) + v%4.
 // Measured (row attention, 64 x 155 tokens of 256 channels, 8 heads of 32, 8.1 GFLOP): 1.40 ms with vector
-// multiply-adds, a wavefront per query and per pair, 0.116 ms so (projections 59 us, attention 30, output
-// projection 20, rows 9; the matrix cores alone need 53); 8 x 32 tokens of 32 channels: 33.8 -> 17.7 us, all launches.
+// multiply-adds, a wavefront per query and per pair, 0.116 ms on v_mfma_f32_32x32x2_f32 (whose matrix cores alone need 53 us), 0.081 ms so (projections
+// 36 us, attention 21, output projection 14, rows 9); relative error against float64 4.0e-7 -> 2.4e-7.  128 x 150 tokens 227 -> 151 us, 256 x 256 tokens of
+// 256 channels 658 -> 491, of 32 channels 117 -> 87.
 //
 // Workspace layout of this family, per chunk of `rows` batch rows, token t = rl*L + l:
 //   stats [tokens][2]   float32 mean, 1/std of LayerNorm
 //   qkvg  [tokens][4*Hd] T : q (times log2(e)/sqrt(d)), k, v, sigmoid gate
-//   o     [tokens][Hd]   T : gate * context
+//   o     [tokens][Hd]   T : gate * context; until the attention writes it, the planes of the projection weights (weight_planes)
 //   bias  [H][L][Lb]     float32, times log2(e); rows padded to a multiple of four (16-byte reads)
+#include "ff_attn_rows.h"
 #include "ff_common.h"
 
 #include <type_traits>
 
 namespace ff {
 namespace gen {
-
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 static inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 static inline int bias_pitch(int L) { return (L + 3) & ~3; }
@@ -65,6 +62,13 @@ struct Piece<bf16_t, true> {
                                         __uint_as_float(v.y & 0xffff0000u)));
     }
 };
+// (rows of whole pieces only: neither clamped nor cleared)
+template <typename T>
+struct WholePiece {
+    Piece<T, true> p;
+    __device__ __forceinline__ void fetch(const T* row, int k, int) { p.v = *reinterpret_cast<const decltype(p.v)*>(row + k); }
+    __device__ __forceinline__ float4 value(int, int) const { return p.value(0, 1); }
+};
 template <typename T, bool VEC>
 __device__ __forceinline__ float4 load4(const T* row, int k, int n) {
     Piece<T, VEC> p;
@@ -90,6 +94,42 @@ __device__ __forceinline__ void store4(T* row, int k, int n, const float4& v) {
 }
 
 // ---------------------------------------------------------------------------------------
+// Float32 contractions on the bfloat16 matrix instruction.  A float32 value is the exact sum of three bfloat16 values (8 + 8 + 8 significant bits,
+// each the rounding of what the ones before it left): x = x0 + x1 + x2, |x1| <= 2^-9 |x|, |x2| <= 2^-18 |x|.  Of the nine products of two such
+// sums the six with i + j <= 2 are formed; what is left out is below 2^-25 of the product, a quarter of a float32 rounding of
+// it.  x0 y0 and the five corrections have sums of their own, so a chain rounds once per 16 terms of the contraction (v_mfma_f32_32x32x2_f32: once per two).
+// Six instructions of 32 cycles for 16 terms against eight of 64.  A bfloat16 operand is one plane and needs no others.  (An infinity among the operands gives NaN where
+// the float32 product would be infinite.)
+template <int NP>
+struct Planes {
+    uint2 p[NP];       // four elements in each
+};
+template <int NP>
+__device__ __forceinline__ Planes<NP> split4(const float4& v) {
+    Planes<NP> s;
+    float4 r = v;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        s.p[i] = make_uint2(pack2(r.x, r.y), pack2(r.z, r.w));
+        asm("" : "+v"(s.p[i].x));
+        asm("" : "+v"(s.p[i].y));      // (else the low halves are rounded once more by themselves)
+        if (i + 1 < NP)
+            r = make_float4(r.x - lo_f32(s.p[i].x), r.y - hi_f32(s.p[i].x), r.z - lo_f32(s.p[i].y), r.w - hi_f32(s.p[i].y));
+    }
+    return s;
+}
+// hi += x0 y0 and lo += the corrections, 16 terms of the contraction (lo of a single product stays as it is)
+template <int NA, int NB>
+__device__ __forceinline__ void mfma_split(const Frag (&x)[NA], const Frag (&y)[NB], f32x16& hi, f32x16& lo) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+            if (i + j > 0 && i + j <= 2) lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[i].v, y[j].v, lo, 0, 0, 0);
+    hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0].v, y[0].v, hi, 0, 0, 0);
+}
+
+// ---------------------------------------------------------------------------------------
 // LayerNorm rows: pair bias and token statistics in one launch.  Eight lanes per row, lane j of them with the
 // elements 4j + 32i .. + 3: a row of 32 elements is one line, and a sum over a row three exchanges instead of the six
 // of a wavefront per row (which spent most of its time on them: H + 2 sums per pair).  Rows of up to 256 elements
@@ -109,6 +149,9 @@ struct RowsArgs {
     int c, r0, tokens;
     float* stats;
     float eps;
+    const void* w[4];          // w_q, w_k, w_v, w_g [Hd][c], to be split into planes (see WeightPlanes)
+    int Hd, token_blocks;
+    unsigned char* planes;
 };
 
 __device__ __forceinline__ float sum8(float v) {
@@ -193,6 +236,22 @@ __device__ __forceinline__ void token_row(const RowsArgs& a, int t, int j8) {
     if (in && j8 == 0) *reinterpret_cast<float2*>(a.stats + 2 * (size_t)t) = make_float2(mean, rstd);
 }
 
+// The merged projection weights in the planes of their bfloat16 sums, laid out as the GEMM's LDS image wants them: [chunk of 32 elements][plane][row,
+// N rounded up to 128][64 bytes, 16-byte pieces placed as in the GEMM].  Rows beyond N repeat the first one.
+__host__ __device__ inline int plane_rows(int n) { return (n + 127) & ~127; }
+__device__ __forceinline__ int piece_place(int row, int pc) { return ((((pc >> 1) ^ (row >> 2)) & 3) << 4) + ((pc & 1) << 3); }
+__device__ __forceinline__ void split_weights(const RowsArgs& a, int id) {
+    const int np = plane_rows(4 * a.Hd), per = a.c >> 2;
+    const int row = id / per, p = id - row * per;
+    if (row >= np) return;
+    const int n = row < 4 * a.Hd ? row : 0, seg = n / a.Hd;
+    const float* w = (const float*)(seg == 0 ? a.w[0] : (seg == 1 ? a.w[1] : (seg == 2 ? a.w[2] : a.w[3])));
+    const Planes<3> sp = split4<3>(load4<float, true>(w + (size_t)(n - seg * a.Hd) * a.c, 4 * p, a.c));
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+        *reinterpret_cast<uint2*>(a.planes + ((size_t)((p >> 3) * 3 + j) * np + row) * 64 + piece_place(row, p & 7)) = sp.p[j];
+}
+
 template <typename T, bool VEC>
 __global__ __launch_bounds__(256) void k_rows_generic(RowsArgs a) {
     const int j8 = threadIdx.x & 7, r32 = threadIdx.x >> 3;
@@ -205,6 +264,12 @@ __global__ __launch_bounds__(256) void k_rows_generic(RowsArgs a) {
         else pair_row<T, VEC, 0>(a, pair, j8);
         return;
     }
+    if constexpr (sizeof(T) == 4) {
+        if ((int)blockIdx.x >= a.pair_blocks + a.token_blocks) {
+            split_weights(a, ((int)blockIdx.x - a.pair_blocks - a.token_blocks) * 256 + threadIdx.x);
+            return;
+        }
+    }
     const int t = ((int)blockIdx.x - a.pair_blocks) * 32 + r32;
     if (a.c <= 32) token_row<T, VEC, 1>(a, t, j8);
     else if (a.c <= 64) token_row<T, VEC, 2>(a, t, j8);
@@ -214,14 +279,14 @@ __global__ __launch_bounds__(256) void k_rows_generic(RowsArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------
-// GEMM, 32 WM tokens x 64 features per block of four wavefronts, contraction in chunks of 32 through double-buffered
-// LDS (the next chunk travels to registers meanwhile).  WM = 4: a wavefront takes 32 tokens x 64 features; WM = 2:
-// 32 x 32, twice the blocks, for launches that would otherwise leave compute units idle.
+// GEMM, 64 tokens x 64 WN features per block of four wavefronts, contraction in chunks of 32 through double-buffered LDS, the operands split into
+// their planes on the way there; a wavefront takes 32 tokens x 32 WN features.
 //   PROJ = true : A = LayerNorm(x) on the fly (stats, gamma, beta), B rows from w_q|w_k|w_v|w_g,
 //                 epilogue: q scaled, gate = sigmoid(acc + b_g); C -> qkvg[t][4Hd]
 //   PROJ = false: A = o[t][Hd], B = w_o, epilogue + b_o, C -> out at the token's address.
-// Bound by the matrix cores: 64 cycles per instruction of 4096 flop (153 TFLOP/s for a large float32 product on this
-// chip), against one 16-byte LDS read per operand and four instructions.
+// What bounds it (64 x 155 tokens of 256 channels, projections, times of the kernel with a part taken out): the matrix instructions 12 us of 36, splitting
+// the tokens 10, the weights' planes 6, the stores and the rest of a block's beginning and end 10: the waves of a SIMD hide little of one behind another.
+// With the weights split by every block too 44 us; with one buffer and four blocks per compute unit 38; the split woven between the matrix instructions 42.
 struct GenericGemmArgs {
     const void* a;         // x (PROJ) or o
     int64_t sr, sl;        // token strides of x / out
@@ -231,31 +296,33 @@ struct GenericGemmArgs {
     const void *ln_g, *ln_b;
     const void* w[4];      // PROJ: w_q, w_k, w_v, w_g ([Hd][K] each); else w[0] = w_o [N][K]
     const void* bvec;      // PROJ: b_g [Hd]; else b_o [N]
+    const unsigned char* planes;   // the weights already split (split_weights), or NULL
     int Hd;
     float qscale;
     void* cdst;            // qkvg or out
     const void* res;       // !PROJ: residual added to the output (laid out like out, may be out itself) or NULL
 };
 
-template <typename T, bool PROJ, bool VEC, int WM>
-__global__ __launch_bounds__(256) void k_gemm_generic(GenericGemmArgs g) {
-    constexpr int BM = 32 * WM, NT = WM == 4 ? 2 : 1;          // tokens per block; 32-feature tiles per wavefront
-    // rows of 32 floats, 16-byte piece p of row r in place p ^ (r & 7): conflict-free reads with lane = row
-    __shared__ __attribute__((aligned(16))) float As[2][BM * 32];
-    __shared__ __attribute__((aligned(16))) float Bs[2][64 * 32];
+template <typename T, bool PROJ, int VEC, int WN, bool BP>      // BP: weights from g.planes.  VEC: 0 rows of any length, 1 of whole pieces (Piece), 2 of whole chunks
+__global__ __launch_bounds__(256, WN == 1 ? 3 : 2) void k_gemm_generic(GenericGemmArgs g) {
+    constexpr int BM = 64, BN = 64 * WN;
+    constexpr int NA = PROJ || sizeof(T) == 4 ? 3 : 1, NB = sizeof(T) == 4 ? 3 : 1;      // planes of the operands
+    using Load = std::conditional_t<VEC == 2, WholePiece<T>, Piece<T, VEC != 0>>;
+    // rows of 32 elements in each plane, 16-byte piece p of row r in place p ^ (r / 4 % 4): conflict-free reads with lane = row
+    __shared__ __attribute__((aligned(16))) unsigned char As[2][NA][BM * 64];
+    __shared__ __attribute__((aligned(16))) unsigned char Bs[2][NB][BN * 64];
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, hf = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int t0 = blockIdx.x * BM, n0 = blockIdx.y * 64;
-    // a thread moves the piece tid % 8 of the rows tid / 8 + 32 i of a chunk
+    const int t0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
+    // a thread moves the piece tid % 8 of the rows tid / 8 + 32 i of a chunk.  (Rows beyond the last token or feature hold the first one: they
+    // reach no output but their own, which is not stored)
     const int pc = tid & 7, prow = tid >> 3;
-    const T *ap[WM], *bp[2];
-    float mean[WM], rstd[WM];
-    bool aok[WM], bok[2];
+    const T *ap[2], *bp[BP ? 1 : 2 * WN];
+    float mean[2], rstd[2];
 #pragma unroll
-    for (int i = 0; i < WM; ++i) {
+    for (int i = 0; i < 2; ++i) {
         const int t = t0 + prow + 32 * i;
-        aok[i] = t < g.tokens;
-        const int tc = aok[i] ? t : 0;
+        const int tc = t < g.tokens ? t : 0;
         if constexpr (PROJ) {
             const int rl = tc / g.L, l = tc - rl * g.L;
             ap[i] = (const T*)g.a + ((int64_t)(g.r0 + rl) * g.sr + (int64_t)l * g.sl) * g.K;
@@ -267,10 +334,9 @@ __global__ __launch_bounds__(256) void k_gemm_generic(GenericGemmArgs g) {
         }
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < (BP ? 0 : 2 * WN); ++i) {
         const int n = n0 + prow + 32 * i;
-        bok[i] = n < g.N;
-        const int nc = bok[i] ? n : 0;
+        const int nc = n < g.N ? n : 0;
         if constexpr (PROJ) {
             const int seg = nc / g.Hd;
             const void* w = seg == 0 ? g.w[0] : (seg == 1 ? g.w[1] : (seg == 2 ? g.w[2] : g.w[3]));
@@ -279,82 +345,133 @@ __global__ __launch_bounds__(256) void k_gemm_generic(GenericGemmArgs g) {
             bp[i] = (const T*)g.w[0] + (size_t)nc * g.K;
         }
     }
-    Piece<T, VEC> ra[WM], rb[2], gm, bt;
-    auto fetch = [&](int k0) {
+    struct Chunk {
+        Load a[2], b[BP ? 1 : 2 * WN], gm, bt;
+    };
+    const unsigned bs_lds = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)&Bs[0][0][0]);
+    auto fetch = [&](Chunk& c, int k0) __attribute__((always_inline)) {
         const int k = k0 + 4 * pc;
 #pragma unroll
-        for (int i = 0; i < WM; ++i) ra[i].fetch(ap[i], k, g.K);
+        for (int i = 0; i < 2; ++i) c.a[i].fetch(ap[i], k, g.K);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) rb[i].fetch(bp[i], k, g.K);
+        for (int i = 0; i < (BP ? 0 : 2 * WN); ++i) c.b[i].fetch(bp[i], k, g.K);
         if constexpr (PROJ) {
-            gm.fetch((const T*)g.ln_g, k, g.K);
-            bt.fetch((const T*)g.ln_b, k, g.K);
+            c.gm.fetch((const T*)g.ln_g, k, g.K);
+            c.bt.fetch((const T*)g.ln_b, k, g.K);
         }
     };
-    auto stash = [&](int buf, int k0) {
+    // BP: the planes of a chunk, 3 WN KiB per wavefront (a block's rows of a plane are one piece of memory)
+    const int np = plane_rows(g.N);
+    const unsigned char* planes = BP ? g.planes + (size_t)n0 * 64 : nullptr;
+    uint32_t plane_lane[BP ? 3 * WN : 1];
+    if constexpr (BP) {
+#pragma unroll
+        for (int i = 0; i < 3 * WN; ++i) {
+            const int c = 4 * i + wave, j = c / (4 * WN);
+            plane_lane[i] = (uint32_t)(j * np * 64 + (c - j * 4 * WN) * 1024) + 16u * lane;
+        }
+    }
+    auto fetch_planes = [&](int buf) __attribute__((always_inline)) {
+        if constexpr (BP) {
+#pragma unroll
+            for (int i = 0; i < 3 * WN; ++i) load16_to_lds(planes, plane_lane[i], bs_lds + (unsigned)(buf * NB * BN * 64 + (4 * i + wave) * 1024));
+            planes += (size_t)3 * np * 64;
+        }
+    };
+    auto stash = [&](const Chunk& c, int buf, int k0) __attribute__((always_inline)) {
         const int k = k0 + 4 * pc;
         float4 gv, bv;
         if constexpr (PROJ) {
-            gv = gm.value(k, g.K);
-            bv = bt.value(k, g.K);
-        }
-#pragma unroll
-        for (int i = 0; i < WM; ++i) {
-            const int row = prow + 32 * i;
-            float4 v = ra[i].value(k, g.K);
-            if constexpr (PROJ)       // (beyond K gamma and beta are zero, and so is the result)
-                v = make_float4((v.x - mean[i]) * rstd[i] * gv.x + bv.x, (v.y - mean[i]) * rstd[i] * gv.y + bv.y,
-                                (v.z - mean[i]) * rstd[i] * gv.z + bv.z, (v.w - mean[i]) * rstd[i] * gv.w + bv.w);
-            *reinterpret_cast<float4*>(&As[buf][row * 32 + ((pc ^ (row & 7)) << 2)]) = keep4(aok[i], v);
+            gv = c.gm.value(k, g.K);
+            bv = c.bt.value(k, g.K);
         }
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int row = prow + 32 * i;
-            *reinterpret_cast<float4*>(&Bs[buf][row * 32 + ((pc ^ (row & 7)) << 2)]) = keep4(bok[i], rb[i].value(k, g.K));
+            float4 v = c.a[i].value(k, g.K);
+            if constexpr (PROJ)       // (beyond K gamma and beta are zero, and so is the result)
+                v = make_float4((v.x - mean[i]) * rstd[i] * gv.x + bv.x, (v.y - mean[i]) * rstd[i] * gv.y + bv.y,
+                                (v.z - mean[i]) * rstd[i] * gv.z + bv.z, (v.w - mean[i]) * rstd[i] * gv.w + bv.w);
+            const Planes<NA> sp = split4<NA>(v);
+#pragma unroll
+            for (int j = 0; j < NA; ++j) *reinterpret_cast<uint2*>(&As[buf][j][row * 64 + piece_place(row, pc)]) = sp.p[j];
+        }
+#pragma unroll
+        for (int i = 0; i < (BP ? 0 : 2 * WN); ++i) {
+            const int row = prow + 32 * i;
+            const Planes<NB> sp = split4<NB>(c.b[i].value(k, g.K));
+#pragma unroll
+            for (int j = 0; j < NB; ++j) *reinterpret_cast<uint2*>(&Bs[buf][j][row * 64 + piece_place(row, pc)]) = sp.p[j];
         }
     };
-    // two sums per output, of the even and of the odd ones of every four contraction steps, added at the end: half as many roundings
-    // in a row, none of which costs the matrix core anything
-    f32x16 acc[NT], odd[NT];
+    f32x16 acc[WN], low[WN];
 #pragma unroll
-    for (int n = 0; n < NT; ++n)
+    for (int n = 0; n < WN; ++n)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[n][v] = odd[n][v] = 0.f;
-    const int wt = WM == 4 ? wave : wave >> 1, wn = WM == 4 ? 0 : (wave & 1);
-    fetch(0);
-    stash(0, 0);
-    __syncthreads();
-    int buf = 0;
-    for (int k0 = 0; k0 < g.K; k0 += 32, buf ^= 1) {
-        const bool more = k0 + 32 < g.K;
-        if (more) fetch(k0 + 32);
-        const float* ar = &As[buf][(32 * wt + col) * 32];
-        const float* br = &Bs[buf][(32 * wn + col) * 32];
+        for (int v = 0; v < 16; ++v) acc[n][v] = low[n][v] = 0.f;
+    const int wt = wave >> 1, wn = WN * (wave & 1);
+    // A chunk's operands are requested two chunks ahead (a chunk's matrix instructions are over before memory answers), its planes, from L2, one; while
+    // a chunk is contracted the next one is split and stored.
+    const int last = (g.K - 1) & ~31;
+    auto round = [&](Chunk& c1, Chunk& c2, int buf, int k0, auto ahead_c) __attribute__((always_inline)) {       // c1: chunk k0 + 32, c2: the one behind it, as far as there are any
+        constexpr int ahead = decltype(ahead_c)::value;
+        if constexpr (ahead > 0) fetch_planes(buf ^ 1);
+        if constexpr (ahead > 1) fetch(c2, k0 + 64 < last ? k0 + 64 : last);              // (past the end: a harmless repeat, so that no load is under a condition)
+        __builtin_amdgcn_sched_barrier(0);
+        Frag av[2][NA], bv[2][WN][NB];
+        const int sw = (col >> 2) & 3;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int at = ((2 * i + hf) ^ (col & 7)) << 2;            // (rows 32 apart: the same places)
-            const float4 av = *reinterpret_cast<const float4*>(ar + at);
-            float4 bv[NT];
+        for (int i = 0; i < 2; ++i) {
+            const int at = col * 64 + (((2 * i + hf) ^ sw) & 3) * 16;            // (rows 32 apart: the same places)
 #pragma unroll
-            for (int n = 0; n < NT; ++n) bv[n] = *reinterpret_cast<const float4*>(br + 32 * 32 * n + at);
+            for (int j = 0; j < NA; ++j) av[i][j].u = *reinterpret_cast<const uint4*>(&As[buf][j][32 * wt * 64 + at]);
 #pragma unroll
-            for (int n = 0; n < NT; ++n) acc[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x, bv[n].x, acc[n], 0, 0, 0);
+            for (int n = 0; n < WN; ++n) {
 #pragma unroll
-            for (int n = 0; n < NT; ++n) odd[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.y, bv[n].y, odd[n], 0, 0, 0);
-#pragma unroll
-            for (int n = 0; n < NT; ++n) acc[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.z, bv[n].z, acc[n], 0, 0, 0);
-#pragma unroll
-            for (int n = 0; n < NT; ++n) odd[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.w, bv[n].w, odd[n], 0, 0, 0);
+                for (int j = 0; j < NB; ++j) bv[i][n][j].u = *reinterpret_cast<const uint4*>(&Bs[buf][j][32 * (wn + n) * 64 + at]);
+                mfma_split<NA, NB>(av[i], bv[i][n], acc[n], low[n]);
+            }
         }
-        if (more) {
-            stash(buf ^ 1, k0 + 32);              // (read last in the round before, and that round's barrier has passed)
+        if constexpr (ahead > 0) {
+            stash(c1, buf ^ 1, k0 + 32);              // (read last in the round before, and that round's barrier has passed)
+
+#pragma unroll
+            for (int i = 0; i < 2 * WN * (NA > 1 ? (NB > 1 ? 6 : 3) : 1); ++i) {
+
+
+
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (BP) __builtin_amdgcn_s_waitcnt(ahead > 1 ? (PROJ ? 0x0F74 : 0x0F72) : kWaitVmcnt0);      // vmcnt: all but c2's four (two) loads
             __syncthreads();
         }
+    };
+    constexpr std::integral_constant<int, 2> two{};
+    constexpr std::integral_constant<int, 1> one{};
+    constexpr std::integral_constant<int, 0> none{};
+    Chunk cur, nxt;
+    fetch_planes(0);
+    fetch(cur, 0);
+    fetch(nxt, last < 32 ? last : 32);
+    __builtin_amdgcn_sched_barrier(0);
+    stash(cur, 0, 0);
+    if constexpr (BP) __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    __syncthreads();
+    int k0 = 0;
+    for (; k0 + 64 < g.K; k0 += 64) {
+        round(nxt, cur, 0, k0, two);
+        round(cur, nxt, 1, k0 + 32, two);
+    }
+    if (k0 + 32 < g.K) {
+        round(nxt, cur, 0, k0, one);
+        round(cur, nxt, 1, k0 + 32, none);
+    } else {
+        round(nxt, cur, 0, k0, none);
     }
 #pragma unroll
-    for (int n = 0; n < NT; ++n)
+    for (int n = 0; n < WN; ++n)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[n][v] += odd[n][v];
+        for (int v = 0; v < 16; ++v) acc[n][v] += low[n][v];
     // lane = feature, register v = token 8 (v / 4) + 4 hf + v % 4 of the wavefront's 32: 128-byte runs per token.  FULL: all
     // of its tokens exist (the checks are branches around every store otherwise)
     const int tw = t0 + 32 * wt;
@@ -376,25 +493,29 @@ __global__ __launch_bounds__(256) void k_gemm_generic(GenericGemmArgs g) {
             return ((int64_t)(g.r0 + r) * g.sr + (int64_t)l * g.sl) * g.N;
         };
 #pragma unroll
-        for (int n = 0; n < NT; ++n) {
+        for (int n = 0; n < WN; ++n) {
             const int f = n0 + 32 * (wn + n) + col;
             if (f >= g.N) continue;
             if constexpr (PROJ) {
                 const int seg = f / g.Hd;
-                const float bias = seg == 3 ? to_f32<T>(((const T*)g.bvec)[f - 3 * g.Hd]) : 0.f;
-                T* dst = (T*)g.cdst + (size_t)tw * g.N + f;
                 if (seg == 3) {
+                    const float bias = to_f32<T>(((const T*)g.bvec)[f - 3 * g.Hd]);
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) acc[n][v] = 1.f / (1.f + __expf(-(acc[n][v] + bias)));
+                    for (int v = 0; v < 16; ++v)
+                        acc[n][v] = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-kLog2e * (acc[n][v] + bias)));
                 } else {
                     const float scale = seg == 0 ? g.qscale : 1.f;
 #pragma unroll
                     for (int v = 0; v < 16; ++v) acc[n][v] *= scale;
                 }
+                // (a uniform address that moves on by a token and an offset per lane: nothing for the vector unit to add)
+                char* dst = (char*)g.cdst + (size_t)tw * g.N * sizeof(T);
+                const uint32_t lane_at = (uint32_t)(f + 4 * hf * g.N) * sizeof(T);
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    const int x = 8 * (v >> 2) + 4 * hf + (v & 3);
-                    if (FULL || tw + x < g.tokens) dst[(size_t)x * g.N] = from_f32<T>(acc[n][v]);
+                    const int x = 8 * (v >> 2) + (v & 3);
+                    if (FULL || tw + x + 4 * hf < g.tokens) *reinterpret_cast<T*>(dst + lane_at) = from_f32<T>(acc[n][v]);
+                    dst += (size_t)((v & 3) == 3 ? 5 : 1) * g.N * sizeof(T);
                 }
             } else {
                 const float bias = to_f32<T>(((const T*)g.bvec)[f]);
@@ -422,13 +543,14 @@ __global__ __launch_bounds__(256) void k_gemm_generic(GenericGemmArgs g) {
 
 // ---------------------------------------------------------------------------------------
 // Attention: a wavefront per 32 queries of one (batch row, head), up to eight of them in a block, which shares the keys
-// and values of that (row, head) through LDS, `keys` of them at a time (all of them for lengths up to 256 at d = 32:
+// and values of that (row, head) through LDS, `keys` of them at a time (all of them for lengths up to 160 at d = 32:
 // then every load of the block is in flight together and two barriers are all it needs).  S^T = K Q^T puts a query
-// in a lane: maximum and sum are lane-local but for one exchange between the halves, and register v of the
-// exponentiated tile is the B operand of instruction v of O^T = V^T P^T as it stands (its two halves hold the keys
-// 8 (v / 4) + v % 4 and that + 4).  The bias is added to the finished products (as the accumulator's starting value it was rounded
-// with every one of them), the key mask (0 or -inf) selects.  Online softmax; a query without any unmasked key gets
-// zero context.  Output o = gate * context.
+// in a lane: maximum and sum are lane-local but for one exchange between the halves, and registers 8 c .. 8 c + 7 of the
+// exponentiated tile, split into planes, are the B operand of step c of O^T = V^T P^T as they stand (the keys 16 c + 8 i + 4 hf + e). The bias is added to the finished products (as the
+// accumulator's starting value it was rounded with every one of them), the key mask (0 or -inf) selects, in tiles that hold a masked key.  Online softmax; a query without
+// any unmasked key gets zero context.  Output o = gate * context.
+// Bound by the vector unit (exponentials, the planes of P: 250 instructions per 32 x 32 tile against 24 matrix instructions of 32 cycles).  Up to 32 channels it is held
+// to 128 registers: with 155 a second block of five wavefronts did not fit a compute unit (64 x 155 tokens: 31 us instead of 25, both under the profiler).
 struct GenericAttnArgs {
     const void* qkvg;
     const float* bias;       // [H][L][Lb] or NULL
@@ -438,16 +560,25 @@ struct GenericAttnArgs {
     void* o;
 };
 
+// LDS per key: the planes of k (a row of channels per key, padded to an odd number of 16-byte pieces), of v^T and the mask term; per channel of v^T a
+// pad of 16 bytes, which makes the pitch of its rows an odd number of pieces.
+template <typename T>
+constexpr int attn_planes() { return sizeof(T) == 4 ? 3 : 1; }
 template <int DG>
-constexpr size_t attn_key_bytes() { return (size_t)(8 * DG + 4 + 8 * DG + 1) * 4; }      // k (padded), v, mask term
+constexpr int attn_k_pitch() { return DG == 1 ? 16 : 16 * DG + 16; }
+template <typename T, int DG>
+constexpr size_t attn_smem_bytes(int keys) {
+    return (size_t)keys * (attn_planes<T>() * (attn_k_pitch<DG>() + 16 * DG) + 4) + attn_planes<T>() * 8 * DG * 16;
+}
 
 template <typename T, bool VEC, int DG>      // DG: head dimension in groups of 8 channels (rounded up)
-__global__ __launch_bounds__(512) void k_attn_generic(GenericAttnArgs a) {
-    constexpr int DP = 8 * DG, KP = DP + 4, NE = (DP + 31) / 32;
-    extern __shared__ __attribute__((aligned(16))) float smem[];
-    float* s_k = smem;                               // [keys][KP]
-    float* s_v = s_k + (size_t)a.keys * KP;          // [keys][DP]
-    float* s_m = s_v + (size_t)a.keys * DP;          // [keys] 0 or -inf
+__global__ __launch_bounds__(512, DG <= 4 ? 4 : 2) void k_attn_generic(GenericAttnArgs a) {
+    constexpr int DP = 8 * DG, NP = attn_planes<T>(), KP = attn_k_pitch<DG>(), NE = (DP + 31) / 32, NS = (DP + 15) / 16;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int VP = 2 * a.keys + 16;                                   // bytes of a row of v^T
+    unsigned char* s_k = smem;                                        // [NP][keys][KP]
+    unsigned char* s_v = s_k + (size_t)NP * a.keys * KP;              // [NP][DP][VP]
+    float* s_m = reinterpret_cast<float*>(s_v + (size_t)NP * DP * VP);   // [keys] 0 or -inf
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, hf = lane >> 5, nthreads = blockDim.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rl = blockIdx.x / a.H, h = blockIdx.x - rl * a.H;
@@ -457,9 +588,19 @@ __global__ __launch_bounds__(512) void k_attn_generic(GenericAttnArgs a) {
     const int Hd = a.H * a.d, N4 = 4 * Hd;
     const T* base = (const T*)a.qkvg + (size_t)rl * a.L * N4 + (size_t)h * a.d;
 
-    float4 qf[DG];                                   // channels 8 i + 4 hf .. + 3 of the lane's query
+    Frag qf[NS][NP];                                 // channels 16 s + 8 hf .. + 7 of the lane's query
 #pragma unroll
-    for (int i = 0; i < DG; ++i) qf[i] = load4<T, VEC>(base + (size_t)qc * N4, 8 * i + 4 * hf, a.d);
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int e = 16 * s + 8 * hf + 4 * i;
+            const Planes<NP> sp = split4<NP>(load4<T, VEC>(base + (size_t)qc * N4, e, a.d));
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                qf[s][j].w[2 * i] = sp.p[j].x;
+                qf[s][j].w[2 * i + 1] = sp.p[j].y;
+            }
+        }
     const float* brow = a.bias ? a.bias + ((size_t)h * a.L + qc) * a.Lb : nullptr;
     const float* mask_row = a.mask ? a.mask + (int64_t)(a.r0 + rl) * a.sr : nullptr;
     f32x16 acc[NE];
@@ -467,95 +608,154 @@ __global__ __launch_bounds__(512) void k_attn_generic(GenericAttnArgs a) {
     for (int n = 0; n < NE; ++n)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[n][v] = 0.f;
-    float m = -INFINITY, sum = 0.f;
+    float m = -INFINITY, sum = 0.f;                  // m: reference of the exponentials
 
     for (int c0 = 0; c0 < a.L; c0 += a.keys) {
         const int nk = a.L - c0 < a.keys ? a.L - c0 : a.keys, nkp = (nk + 31) & ~31;
         if (c0) __syncthreads();                     // every wavefront is done with the keys before
-        constexpr int PR = DP / 4;                   // pieces of a row
-        for (int id = tid; id < nkp * PR; id += nthreads) {
-            const int k = id / PR, e = 4 * (id - k * PR);
-            float4 kv = make_float4(0.f, 0.f, 0.f, 0.f), vv = kv;
-            if (k < nk) {
-                const T* row = base + (size_t)(c0 + k) * N4;
-                const float mk = mask_row ? mask_row[(int64_t)(c0 + k) * a.sl] : 1.f;
-                kv = load4<T, VEC>(row + Hd, e, a.d);
-                vv = load4<T, VEC>(row + 2 * Hd, e, a.d);
-                vv = keep4(mk != 0.f, vv);           // (what a masked token holds may be anything, and 0 x NaN is NaN)
-            }
-            *reinterpret_cast<float4*>(s_k + k * KP + e) = kv;
-            *reinterpret_cast<float4*>(s_v + k * DP + e) = vv;
-        }
         for (int k = tid; k < nkp; k += nthreads) {
             bool ok = k < nk;
             if (ok && mask_row) ok = mask_row[(int64_t)(c0 + k) * a.sl] != 0.f;
             s_m[k] = ok ? 0.f : -INFINITY;
         }
+        // k: pieces of four channels of a key.  v^T: four neighbouring keys of a channel, lanes along the channels; the keys 16 c + 8 i + 4 hf + e of a
+        // row lie in the places 16 c + 8 hf + 4 i + e, so that those of a half-wave of P^T, see below, are one piece.  As many of both, and U
+        // of each are on their way together (a wavefront per 32 keys: all that the block needs, up to 32 channels).
+        constexpr int PR = DP / 4, U = DG < 4 ? DG : 4;
+        const T *kb = base + (size_t)c0 * N4 + Hd, *vb = kb + Hd;
+        for (int b0 = 0; b0 < nkp * PR; b0 += U * nthreads) {
+            Piece<T, VEC> kp[U];
+            T vv[U][4];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int id = b0 + u * nthreads + tid, k = id / PR, k4 = 4 * (id / DP), e = id % DP;
+                kp[u].fetch(kb + (size_t)(k < nk ? k : nk - 1) * N4, 4 * (id % PR), a.d);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) vv[u][i] = vb[(size_t)(k4 + i < nk ? k4 + i : nk - 1) * N4 + (e < a.d ? e : a.d - 1)];
+            }
+            if (b0 == 0) __syncthreads();         // the mask terms are there
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int id = b0 + u * nthreads + tid, k = id / PR, k4 = 4 * (id / DP), e = id % DP;
+                if (id >= nkp * PR) break;
+                const Planes<NP> ks = split4<NP>(keep4(k < nk, kp[u].value(4 * (id % PR), a.d)));
+                const float4 m4 = *reinterpret_cast<const float4*>(s_m + k4);
+                // (what a masked token holds may be anything, and 0 x NaN is NaN)
+                const bool in = e < a.d;
+                const Planes<NP> vs = split4<NP>(make_float4(in && m4.x == 0.f ? to_f32<T>(vv[u][0]) : 0.f, in && m4.y == 0.f ? to_f32<T>(vv[u][1]) : 0.f,
+                                                             in && m4.z == 0.f ? to_f32<T>(vv[u][2]) : 0.f, in && m4.w == 0.f ? to_f32<T>(vv[u][3]) : 0.f));
+                const int at = (k4 & ~15) + 2 * (k4 & 4) + ((k4 & 8) >> 1);
+#pragma unroll
+                for (int j = 0; j < NP; ++j) {
+                    *reinterpret_cast<uint2*>(s_k + (j * a.keys + k) * KP + 8 * (id % PR)) = ks.p[j];
+                    *reinterpret_cast<uint2*>(s_v + (j * DP + e) * VP + 2 * at) = vs.p[j];
+                }
+            }
+        }
         __syncthreads();
         if (!active) continue;
         for (int kt = 0; kt < nkp; kt += 32) {
             // lane = query, register 4 g + e = key kt + 8 g + 4 hf + e
-            f32x16 s;
+            f32x16 s, lo;
             float4 bias[4];
 #pragma unroll
+            for (int g = 0; g < 4; ++g) bias[g] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (brow) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {        // (beyond the row: any of it, those keys are masked)
+                    const int k = c0 + kt + 8 * g + 4 * hf;
+                    bias[g] = *reinterpret_cast<const float4*>(brow + (k < a.Lb ? k : a.Lb - 4));
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) s[v] = lo[v] = 0.f;
+#pragma unroll
+            for (int i = 0; i < NS; ++i) {
+                Frag kf[NP];
+#pragma unroll
+                for (int j = 0; j < NP; ++j) {
+                    kf[j].u = *reinterpret_cast<const uint4*>(s_k + (j * a.keys + kt + col) * KP + (DG == 1 ? 0 : 32 * i + 16 * hf));
+                    if (DG == 1 && hf) kf[j].u = make_uint4(0, 0, 0, 0);
+                }
+                mfma_split<NP, NP>(kf, qf[i], s, lo);
+            }
+#pragma unroll
             for (int g = 0; g < 4; ++g) {
-                const int k = kt + 8 * g + 4 * hf;
-                bias[g] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (brow && c0 + k < a.Lb) bias[g] = *reinterpret_cast<const float4*>(brow + c0 + k);
-                s[4 * g] = s[4 * g + 1] = s[4 * g + 2] = s[4 * g + 3] = 0.f;
+                s[4 * g] += lo[4 * g] + bias[g].x;
+                s[4 * g + 1] += lo[4 * g + 1] + bias[g].y;
+                s[4 * g + 2] += lo[4 * g + 2] + bias[g].z;
+                s[4 * g + 3] += lo[4 * g + 3] + bias[g].w;
             }
-            const float* kr = s_k + (kt + col) * KP + 4 * hf;
+            if (__ballot(s_m[kt + col] != 0.f)) {                // (tiles with masked keys only)
 #pragma unroll
-            for (int i = 0; i < DG; ++i) {
-                const float4 kf = *reinterpret_cast<const float4*>(kr + 8 * i);
-                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.x, qf[i].x, s, 0, 0, 0);
-                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.y, qf[i].y, s, 0, 0, 0);
-                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.z, qf[i].z, s, 0, 0, 0);
-                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.w, qf[i].w, s, 0, 0, 0);
+                for (int g = 0; g < 4; ++g) {
+                    const float4 m4 = *reinterpret_cast<const float4*>(s_m + kt + 8 * g + 4 * hf);
+                    // (a select, not a sum: what a masked key or the padded end of a bias row holds may be anything)
+                    s[4 * g] = m4.x == 0.f ? s[4 * g] : m4.x;
+                    s[4 * g + 1] = m4.y == 0.f ? s[4 * g + 1] : m4.y;
+                    s[4 * g + 2] = m4.z == 0.f ? s[4 * g + 2] : m4.z;
+                    s[4 * g + 3] = m4.w == 0.f ? s[4 * g + 3] : m4.w;
+                }
             }
-            float tmax = -INFINITY;
+            float tmax = s[0];
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const float4 m4 = *reinterpret_cast<const float4*>(s_m + kt + 8 * g + 4 * hf);
-                // (a select, not a sum: what the padded end of a bias row holds may be anything)
-                s[4 * g] = m4.x == 0.f ? s[4 * g] + bias[g].x : m4.x;
-                s[4 * g + 1] = m4.y == 0.f ? s[4 * g + 1] + bias[g].y : m4.y;
-                s[4 * g + 2] = m4.z == 0.f ? s[4 * g + 2] + bias[g].z : m4.z;
-                s[4 * g + 3] = m4.w == 0.f ? s[4 * g + 3] + bias[g].w : m4.w;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) tmax = fmaxf(tmax, s[4 * g + e]);
-            }
-            tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-            const float m_new = fmaxf(m, tmax), ref = m_new == -INFINITY ? 0.f : m_new;
-            const float alpha = exp2f(m - ref);
-            m = m_new;
-            float part = 0.f;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                s[v] = exp2f(s[v] - ref);
-                part += s[v];
-            }
-            sum = sum * alpha + part;
-            f32x16 pv[NE];                           // the tile's own sums, so that 32 keys and the tiles round, not all keys in a row
-#pragma unroll
-            for (int n = 0; n < NE; ++n)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) pv[n][v] = 0.f;
-            // lane = channel 32 n + col (channels beyond DP read the row's neighbours and are dropped), half: keys + 4
-            const float* vr = s_v + (kt + 4 * hf) * DP + (DP < 32 ? (col < DP ? col : 0) : col);
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
+            for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, s[v]);
+            tmax = fmaxf(tmax, other_half(tmax));
+            // the reference follows the maximum only where a score exceeds it by more than 8: weights stay below 2^8, and most tiles rescale nothing
+            if (__ballot(tmax > m + 8.f)) {
+                const float m_new = fmaxf(m, tmax);
+                const float alpha = __builtin_amdgcn_exp2f(m - (m_new == -INFINITY ? 0.f : m_new));
+                m = m_new;
+                sum *= alpha;
 #pragma unroll
                 for (int n = 0; n < NE; ++n)
-                    pv[n] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[(8 * (v >> 2) + (v & 3)) * DP + 32 * n], s[v], pv[n], 0, 0, 0);
 #pragma unroll
-            for (int n = 0; n < NE; ++n)
+                    for (int v = 0; v < 16; ++v) acc[n][v] *= alpha;
+            }
+            const float ref = m == -INFINITY ? 0.f : m;
+            float part = 0.f;
+            Frag pf[2][3];                           // step c of P^T: registers 8 c .. 8 c + 7, keys kt + 16 c + 8 i + 4 hf + e
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[n][v] = fmaf(acc[n][v], alpha, pv[n][v]);
+            for (int g = 0; g < 4; ++g) {
+                float4 p;
+                p.x = __builtin_amdgcn_exp2f(s[4 * g] - ref);
+                p.y = __builtin_amdgcn_exp2f(s[4 * g + 1] - ref);
+                p.z = __builtin_amdgcn_exp2f(s[4 * g + 2] - ref);
+                p.w = __builtin_amdgcn_exp2f(s[4 * g + 3] - ref);
+                part += p.x;
+                part += p.y;
+                part += p.z;
+                part += p.w;
+                const Planes<3> sp = split4<3>(p);
+#pragma unroll
+                for (int j = 0; j < 3; ++j) {
+                    pf[g >> 1][j].w[2 * (g & 1)] = sp.p[j].x;
+                    pf[g >> 1][j].w[2 * (g & 1) + 1] = sp.p[j].y;
+                }
+            }
+            sum += part;
+            // the tile's own sums, so that a few products and the tiles round, not all keys in a row.  lane = query, register v = channel
+            // 32 n + 8 (v / 4) + 4 hf + v % 4; channels beyond DP read a row again and are dropped
+#pragma unroll
+            for (int n = 0; n < NE; ++n) {
+                f32x16 pv, lv;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) pv[v] = lv[v] = 0.f;
+                const unsigned char* vr = s_v + (DP < 32 ? (col < DP ? col : 0) : 32 * n + col) * VP + 2 * kt + 16 * hf;
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    Frag vf[NP];
+#pragma unroll
+                    for (int j = 0; j < NP; ++j) vf[j].u = *reinterpret_cast<const uint4*>(vr + j * DP * VP + 32 * c);
+                    mfma_split<NP, 3>(vf, pf[c], pv, lv);
+                }
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[n][v] += pv[v] + lv[v];
+            }
         }
     }
     if (!active || qi >= a.L) return;
-    sum += __shfl_xor(sum, 32, 64);
+    sum += other_half(sum);
     const float inv = sum > 0.f ? 1.f / sum : 0.f;
     T* op = (T*)a.o + ((size_t)rl * a.L + qi) * Hd + (size_t)h * a.d;
     const T* gp = base + (size_t)qi * N4 + 3 * Hd;
@@ -574,7 +774,22 @@ __global__ __launch_bounds__(512) void k_attn_generic(GenericAttnArgs a) {
 // ---------------------------------------------------------------------------------------
 static bool aligned_to(const void* p, size_t n) { return ((uintptr_t)p & (n - 1)) == 0; }
 
-// token statistics of `rows` batch rows from r0 on, and the pair bias if `pairs`
+// Whether the merged projection's loads are whole 16-byte (bfloat16: 8-byte) pieces.
+template <typename T>
+static bool proj_vec(const Problem& p, const ff_attn_weights& w, const void* x) {
+    const size_t al = 4 * sizeof(T);
+    return p.c % 4 == 0 && aligned_to(x, al) && aligned_to(w.ln_g, al) && aligned_to(w.ln_b, al) && aligned_to(w.w_q, al) &&
+           aligned_to(w.w_k, al) && aligned_to(w.w_v, al) && aligned_to(w.w_g, al);
+}
+// The place of the split projection weights, or NULL: the context's, which nobody needs before the attention, if a chunk has tokens enough for
+// it to hold them (then the weights are also split often enough to be worth a pass of their own: each 64 tokens do it again otherwise).
+template <typename T>
+static unsigned char* weight_planes(const Problem& p, const ff_attn_weights& w, const void* x, const Workspace& ws) {
+    if (sizeof(T) != 4 || p.c % 32 != 0 || !proj_vec<T>(p, w, x)) return nullptr;
+    return (size_t)6 * plane_rows(4 * p.Hd) * p.c <= (size_t)ws.chunk * p.L * p.Hd * 4 ? (unsigned char*)ws.o : nullptr;
+}
+
+// token statistics of `rows` batch rows from r0 on, the pair bias if `pairs`, and the weights' planes
 template <typename T>
 static ff_status rows_t(const Problem& p, const ff_attn_weights& w, const void* x, const void* z, const Workspace& ws, int r0,
                         int rows, bool pairs, hipStream_t st) {
@@ -593,36 +808,49 @@ static ff_status rows_t(const Problem& p, const ff_attn_weights& w, const void* 
         vec = vec && a.cp % 4 == 0 && aligned_to(a.src, 4 * sizeof(T)) && aligned_to(a.g, 4 * sizeof(T)) && aligned_to(a.b, 4 * sizeof(T)) &&
               aligned_to(a.wb, 4 * sizeof(T));
     }
-    const dim3 grid((unsigned)(a.pair_blocks + (a.tokens + 31) / 32));
+    a.token_blocks = (a.tokens + 31) / 32;
+    a.planes = weight_planes<T>(p, w, x, ws);
+    int split_blocks = 0;
+    if (a.planes) {
+        a.w[0] = w.w_q; a.w[1] = w.w_k; a.w[2] = w.w_v; a.w[3] = w.w_g; a.Hd = p.Hd;
+        split_blocks = (plane_rows(4 * p.Hd) * (p.c / 4) + 255) / 256;
+    }
+    const dim3 grid((unsigned)(a.pair_blocks + a.token_blocks + split_blocks));
     if (vec) hipLaunchKernelGGL((k_rows_generic<T, true>), grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL((k_rows_generic<T, false>), grid, dim3(256), 0, st, a);
     return check_launch("rows (generic)");
 }
 
+template <typename T, bool PROJ, int VEC, bool BP>
+static void launch_gemm_vec(const GenericGemmArgs& g, hipStream_t st) {
+    // 128 features per block (the tokens are split half as often) where that gives at least four blocks per compute unit: with it from two blocks on
+    // 128 x 40 tokens of 256 channels 54 us instead of 51, 200 x 200 tokens of 64 channels 83 instead of 78; from eight on 64 x 155 tokens 90 instead of 86;
+    // never, 256 x 256 tokens 530 instead of 497.
+    const unsigned nx = (unsigned)((g.tokens + 63) / 64);
+    const unsigned wide = (unsigned)((g.N + 127) / 128);
+    if ((int64_t)nx * wide >= 4 * compute_units())
+        hipLaunchKernelGGL((k_gemm_generic<T, PROJ, VEC, 2, BP>), dim3(nx, wide), dim3(256), 0, st, g);
+    else
+        hipLaunchKernelGGL((k_gemm_generic<T, PROJ, VEC, 1, BP>), dim3(nx, (unsigned)((g.N + 63) / 64)), dim3(256), 0, st, g);
+}
 template <typename T, bool PROJ>
 static void launch_gemm(const GenericGemmArgs& g, bool vec, hipStream_t st) {
-    const unsigned ny = (unsigned)((g.N + 63) / 64);
-    // 128 tokens per block where that gives at least four blocks per compute unit, else 64.  (64 x 155 tokens, 256
-    // channels: projections 59 us with 128 tokens, 64 with 64; output projection, with a quarter of the blocks, 20 us with 64)
-    const bool big = (int64_t)((g.tokens + 127) / 128) * ny >= 4 * compute_units();
-#define FF_GEN_GEMM(VECV)                                                                                                         \
-    do {                                                                                                                          \
-        if (big) hipLaunchKernelGGL((k_gemm_generic<T, PROJ, VECV, 4>), dim3((g.tokens + 127) / 128, ny), dim3(256), 0, st, g);    \
-        else hipLaunchKernelGGL((k_gemm_generic<T, PROJ, VECV, 2>), dim3((g.tokens + 63) / 64, ny), dim3(256), 0, st, g);          \
-    } while (0)
-    if (vec) FF_GEN_GEMM(true);
-    else FF_GEN_GEMM(false);
-#undef FF_GEN_GEMM
+    if constexpr (PROJ && sizeof(T) == 4) {
+        if (g.planes) return launch_gemm_vec<T, PROJ, 2, true>(g, st);
+    }
+    if (vec && g.K % 32 == 0) launch_gemm_vec<T, PROJ, 2, false>(g, st);
+    else if (vec) launch_gemm_vec<T, PROJ, 1, false>(g, st);
+    else launch_gemm_vec<T, PROJ, 0, false>(g, st);
 }
 
 template <typename T, bool VEC, int DG>
 static ff_status launch_attn(GenericAttnArgs a, hipStream_t st) {
     // as many keys at a time as 72 KiB hold (two blocks per compute unit), a multiple of 32
     const int lp = (a.L + 31) & ~31;
-    int keys = (int)(72 * 1024 / attn_key_bytes<DG>()) & ~31;
-    if (keys > lp) keys = lp;
+    int keys = 32;
+    while (keys < lp && attn_smem_bytes<T, DG>(keys + 32) <= 72 * 1024) keys += 32;
     a.keys = keys;
-    const size_t smem = attn_key_bytes<DG>() * keys;
+    const size_t smem = attn_smem_bytes<T, DG>(keys);
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_generic<T, VEC, DG>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 72 * 1024);
     if (attr != hipSuccess) return fail(FF_EHIP, "k_attn_generic: dynamic LDS limit: %s", hipGetErrorString(attr));
@@ -643,8 +871,8 @@ static ff_status chunk_t(const Problem& p, const ff_attn_weights& w, const void*
     g.w[0] = w.w_q; g.w[1] = w.w_k; g.w[2] = w.w_v; g.w[3] = w.w_g; g.bvec = w.b_g; g.Hd = p.Hd;
     g.qscale = kLog2e / sqrtf((float)p.d);
     g.cdst = ws.qkvg;
-    launch_gemm<T, true>(g, p.c % 4 == 0 && aligned_to(x, al) && aligned_to(w.ln_g, al) && aligned_to(w.ln_b, al) && aligned_to(w.w_q, al) &&
-                                aligned_to(w.w_k, al) && aligned_to(w.w_v, al) && aligned_to(w.w_g, al), st);
+    g.planes = weight_planes<T>(p, w, x, ws);
+    launch_gemm<T, true>(g, proj_vec<T>(p, w, x), st);
 
     GenericAttnArgs a{};
     a.qkvg = ws.qkvg; a.bias = ws.bias; a.mask = mask; a.sr = p.sr; a.sl = p.sl; a.r0 = r0; a.rows = rows; a.L = p.L;

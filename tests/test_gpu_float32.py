@@ -92,3 +92,32 @@ def test_rounding_of_the_float32_sums(mode, n_a, n_b, c, c_z, heads, d, limit):
     rl = rel_l2(got, O.gated_attention(mode, xf, zf, mf, wf, heads, spec.ln_eps))
     print(f"{spec.name}: rel_l2={rl:.3e}", flush=True)
     assert rl <= limit
+
+
+@pytest.mark.parametrize("mode,n_a,n_b,c,heads,d,chunk", [
+    (ROW, 12, 33, 64, 2, 32, 0), (ROW, 11, 33, 64, 2, 32, 0),        # 64 channels: weights split ahead from 384 tokens on (396 and 363 here)
+    (ROW, 24, 45, 32, 3, 16, 5), (COL, 37, 40, 96, 1, 40, 13), (TS, 200, 200, 160, 2, 64, 0), (TE, 90, 90, 32, 5, 8, 90), (ROW, 640, 129, 32, 4, 8, 0)])
+def test_weights_split_ahead_and_chunks(mode, n_a, n_b, c, heads, d, chunk):
+    """The projection weights are split once per chunk where the chunk has tokens enough, else by every block: both sides of that line,
+    feature counts around the 64 and 128 of a block, and the unchunked call bit for bit with a chunked one that splits per block."""
+    case = I.make_case(small_spec(mode, n_a, n_b, c, heads, d, c_z=16, dtype="f32", mask="none"))
+    desc, w, x, z, m = P.to_device(case, "cuda:0")
+    got = P.ff_gated_attention(desc, w, x, z, m)
+    assert P.ff_attention_last_path() == "generic"
+    for rows in {1, chunk} - {0}:
+        assert torch.equal(P.ff_attention_chunked(desc, w, x, z, m, chunk_rows=rows), got)
+    if n_a * n_b <= 20000:
+        xf, zf, mf, wf = f64_inputs(case)
+        ref = O.gated_attention(mode, xf, zf, mf, wf, heads, case.spec.ln_eps)
+        assert rel_l2(got.cpu().numpy().astype(np.float64), ref) <= 5e-7      # (above the largest limit of the sums' rounding, see below)
+
+
+def test_large_and_small_magnitudes():
+    """Scales far from one pass through the splitting as they do through float32: LayerNorm takes the scale of x away, that of w_v and w_o remains."""
+    case = I.make_case(small_spec(ROW, 9, 40, 64, 2, 32, c_z=16, dtype="f32", mask="none"))
+    desc, w, x, z, m = P.to_device(case, "cuda:0")
+    w = dict(w, b_o=torch.zeros_like(w["b_o"]))
+    base = P.ff_gated_attention(desc, w, x, z, m).clone()
+    for s in (2.0 ** 60, 2.0 ** -60):
+        big = P.ff_gated_attention(desc, dict(w, w_v=w["w_v"] * s, w_o=w["w_o"] * 2.0 ** -20), x, z, m)
+        assert torch.equal(big, base * (s * 2.0 ** -20))
