@@ -45,7 +45,7 @@ __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
 }  // namespace
 
 // wavefronts per SIMD the registers of an instantiation are held to.  Without a bias and below head dim 32 two rows are held to 128
-// registers (five spilled, none inside the step loops): four wavefronts per SIMD, where the exponentials of a wavefront hide
+// registers: four wavefronts per SIMD, where the exponentials of a wavefront hide
 // another's waits (1024-sequence column attention at d = 8, the whole call: 438 us; three wavefronts 456; four rows and
 // three wavefronts 499, two 469).  Blocks of two wavefronts: three per SIMD fit without spills (64 x 384 columns at d = 8:
 // 8.1 us, with four 10.4).
@@ -166,11 +166,10 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, NW, HAS_BIAS)) void k_a
     // ---- bias tiles of the wavefront's queries, one after the other
     const float* bias_q = HAS_BIAS ? a.bias + ((size_t)h * (a.Lq >> 5) + qtc) * (a.Lp >> 5) * 1024 : nullptr;
     const uint32_t b_lane = (uint32_t)lane * 16;
-    auto load_bias = [&](int kt, f32x16& b) __attribute__((always_inline)) {
+    auto load_bias = [&](int kt, f32x16& b, uint32_t off) __attribute__((always_inline)) {
         if constexpr (HAS_BIAS) {
             if (kt > nt - 1) kt = nt - 1;
             const char* bp = reinterpret_cast<const char*>(bias_q + (size_t)kt * 1024);
-            uint32_t off = b_lane;
             asm volatile("" : "+v"(off));
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
@@ -183,8 +182,8 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, NW, HAS_BIAS)) void k_a
         }
     };
     f32x16 bias_a, bias_b;
-    load_bias(0, bias_a);
-    load_bias(1, bias_b);
+    load_bias(0, bias_a, b_lane);
+    load_bias(1, bias_b, b_lane);
 
     // ---- which keys are attended to, one bit per key
     for (int i0 = wave; i0 < NR * n_pairs; i0 += 8 * NW) {
@@ -321,7 +320,7 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, NW, HAS_BIAS)) void k_a
             const f32x16& bt = j == LAST ? bn : bc;
             tile(plain_c, j == LAST ? live_n[0] : live_c[j == LAST ? 0 : j + 1], s_acc[j & 1], s_acc[(j + 1) & 1], bt, kf[(j + 1) & 1],
                  kf[j & 1], vf[(j + 1) & 1], vf[j & 1], qn, kl_off, v0 + v_at(j), v1 + v_at(j), op, l_run[j == 0 ? LAST : j - 1]);
-            if (j == LAST) load_bias(kt + 2, bc);
+            if (j == LAST) load_bias(kt + 2, bc, b_lane);
         }
         if constexpr (!PLAIN) {
 #pragma unroll
@@ -364,12 +363,17 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, NW, HAS_BIAS)) void k_a
     }
 
     // ---- normalise, gate, store.  Lane = query, register v = element 8*(v/4) + 4*hf + v%4
-    const int qi = 32 * qt + col;
+    // (the lane's indices anew: those from the beginning of the kernel would be held in registers through the steps, of which there are none left: without
+    // this three to five went to scratch memory, and a kernel that uses it starts later.  1024 x 384 columns at d = 8 411 us the call instead of 407, 2000 x 300 1055
+    // instead of 1048, 60 x 300 row attention 59.7 instead of 57.8)
+    const int ln = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), ecol = ln & 31, ehf = ln >> 5;
+    const uint32_t eq_lane = (uint32_t)(ecol * D + (D > 8 ? 8 * ehf : 0)) * 2;
+    const int qi = 32 * qt + ecol;
     auto load_gate = [&](int r, uint2 (&gr)[D / 8]) __attribute__((always_inline)) {
         const bf16_t* gp = a.g + ((size_t)r * a.H + h) * head_elems + (size_t)qt * (32 * D);
 #pragma unroll
         for (int g = 0; g < D / 8; ++g)
-            gr[g] = *reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(gp + 8 * g) + (uint32_t)(col * D + 4 * hf) * 2);
+            gr[g] = *reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(gp + 8 * g) + (uint32_t)(ecol * D + 4 * ehf) * 2);
     };
     auto finish = [&](const f32x16& o, float l_tot, int r, const uint2 (&gate)[D / 8]) __attribute__((always_inline)) {
         const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
@@ -385,8 +389,8 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, NW, HAS_BIAS)) void k_a
         merge_halves(pk[1], pk[3]);
         merge_halves(pk[4], pk[6]);      // lower: e 16..23, upper: e 24..31
         merge_halves(pk[5], pk[7]);
-        if (qi < a.L && (D > 8 || hf == 0)) {
-            char* op = reinterpret_cast<char*>(a.o + off) + q_lane;
+        if (qi < a.L && (D > 8 || ehf == 0)) {
+            char* op = reinterpret_cast<char*>(a.o + off) + eq_lane;
             *reinterpret_cast<uint4*>(op) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
             if (D == 32) *reinterpret_cast<uint4*>(op + 32) = make_uint4(pk[4], pk[5], pk[6], pk[7]);
         }
@@ -395,7 +399,7 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, NW, HAS_BIAS)) void k_a
     auto denominator = [&](const f32x16& o, float l) __attribute__((always_inline)) {
         if constexpr (!ONES) return l + other_half(l);
         const float x = o[ONES ? D / 2 : 0], y = other_half(x);      // (row D: register D / 2 of the lower half-wave)
-        return hf == 0 ? x : y;
+        return ehf == 0 ? x : y;
     };
     // rows that do not stand (softmax_stands) are done again below
     int again = 0;
@@ -418,8 +422,8 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, NW, HAS_BIAS)) void k_a
         Frag qs[KS];
 #pragma unroll
         for (int i = 0; i < KS; ++i) {
-            qs[i].u = ldg16(a.q + off + (size_t)qt * (32 * D) + 16 * i, q_lane);
-            if (D == 8 && hf != 0) qs[i].u = make_uint4(0, 0, 0, 0);
+            qs[i].u = ldg16(a.q + off + (size_t)qt * (32 * D) + 16 * i, eq_lane);
+            if (D == 8 && ehf != 0) qs[i].u = make_uint4(0, 0, 0, 0);
         }
         f32x16 o;
 #pragma unroll
@@ -429,9 +433,10 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, NW, HAS_BIAS)) void k_a
             const uint32_t live = __builtin_amdgcn_readfirstlane(s_live[kt * NR + j]);
             if (live == 0) continue;
             f32x16 s;
-            load_bias(kt, s);
+            load_bias(kt, s, (uint32_t)ln * 16);
             Frag vs[2];
-            const uint32_t kv = (uint32_t)(kperm * D + (D > 8 ? 8 * hf : 0)) * 2, ve = (uint32_t)((v_row ? col : 0) * 32 + 8 * hf) * 2;
+            const int ekperm = 16 * (ecol >> 4) + 8 * ((ecol >> 2) & 1) + 4 * ((ecol >> 3) & 1) + (ecol & 3);
+            const uint32_t kv = (uint32_t)(ekperm * D + (D > 8 ? 8 * ehf : 0)) * 2, ve = (uint32_t)((ecol < D ? ecol : 0) * 32 + 8 * ehf) * 2;
 #pragma unroll
             for (int c = 0; c < 2; ++c) vs[c].u = ldg16(a.vt + off + (size_t)kt * (32 * D) + 16 * c, ve);      // (rows D .. 31 of the context: unused)
 #pragma unroll
@@ -440,7 +445,7 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, NW, HAS_BIAS)) void k_a
                 k.u = ldg16(a.k + off + (size_t)kt * (32 * D) + 16 * i, kv);
                 s = mfma(k.v, qs[i].v, s);
             }
-            general_tile(s, vs, live, hf, o, m, l);
+            general_tile(s, vs, live, ehf, o, m, l);
         }
         uint2 gr[D / 8];
         load_gate(r, gr);
