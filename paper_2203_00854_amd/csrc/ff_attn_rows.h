@@ -59,11 +59,18 @@ __device__ __forceinline__ void merge_halves(uint32_t& a, uint32_t& b) {
 
 constexpr int kWaitVmcnt0 = 0x0F70;      // s_waitcnt vmcnt(0), the other counters untouched
 
-// Sum of the lane's own four bf16 values (w0, w1), added to every element of acc: a 4 x 4 x 4 matrix instruction (sixteen
-// independent blocks of four lanes) against ones.
-__device__ __forceinline__ f32x4 add_four(uint32_t w0, uint32_t w1, f32x4 acc) {
-    const i16x4 ones = __builtin_bit_cast(i16x4, make_uint2(0x3f803f80u, 0x3f803f80u));
-    return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_bit_cast(i16x4, make_uint2(w0, w1)), acc, 0, 0, 0);
+// Sums over a piece of P^T as the 32 x 32 x 16 instructions hold it (lane = query, the lower half-wave the keys 0 .. 7, the upper 8 .. 15), added to acc: element 0 of
+// the result is the sum over both halves for the lane's query.  One 16 x 16 x 32 matrix instruction: it reads the same registers as sixteen columns
+// of 32 rows, in which query q % 16 has its keys in the rows 0 .. 7 and 16 .. 23, query 16 + q % 16 in the others; the rows of `sel` select one or the other, so that
+// each group of four result rows belongs to the sixteen lanes that hold it.
+__device__ __forceinline__ bf16x8 sum_select(int lane) {
+    const uint32_t w = (((lane & 15) >> 2) ^ (lane >> 4)) & 1 ? 0u : 0x3f803f80u;
+    Frag f;
+    f.u = make_uint4(w, w, w, w);
+    return f.v;
+}
+__device__ __forceinline__ f32x4 add_piece(bf16x8 sel, bf16x8 piece, f32x4 acc) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel, piece, acc, 0, 0, 0);
 }
 // -inf for the keys of a tile of S^T whose bit in live is not set: one more contraction step, the key side 0 or -inf against a
 // one.  kperm: key of the lane's row of S^T, hf: half-wave

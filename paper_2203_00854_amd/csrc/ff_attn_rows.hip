@@ -9,7 +9,7 @@
 // in LDS, filled by loads that write LDS directly, three steps ahead, with one barrier per step.
 //
 // The vector unit and the matrix cores bound it together: per tile 16 exponentials (8 cycles each) and 8 packs (4)
-// against four 32 x 32 x 16 matrix instructions (32 each) and four 4 x 4 x 4 ones for the denominator, so nothing else is
+// against four 32 x 32 x 16 matrix instructions (32 each) and two 16 x 16 x 32 ones for the denominator, so nothing else is
 // left in the loop:
 //  - no reference is subtracted from the scores.  float32 and bfloat16 keep their relative precision over the whole
 //    exponent range, so exp2(s) / sum exp2(s) needs none while the sums stay in range; a row of a
@@ -17,9 +17,9 @@
 //    pipelined: with the logsumexp of one head's queries beyond [-41, 66] (a pair bias offset by 97) 333 x 333 triangle attention takes
 //    190 us instead of 120, 1024 x 1024 in chunks 2910 instead of 1420 (its operands requested a tile ahead: 2720, but the
 //    ordinary 333 call then takes 4 % more).
-//  - the denominator is summed from the rounded weights by 4 x 4 x 4 matrix instructions: eight v_dot2 per tile do not overlap
-//    with matrix instructions (bare loops of the tile's mix, two wavefronts per SIMD: 123 ns with dots, 104 so, 93
-//    without any denominator).
+//  - the denominator is summed from the rounded weights by two 16 x 16 x 32 matrix instructions (add_piece): eight v_dot2 per tile do not overlap
+//    with matrix instructions (bare loops of the tile's mix, two wavefronts per SIMD: 123 ns with dots, 104 with four 4 x 4 x 4
+//    matrix instructions, 93 without any denominator); with those four instead of the two 2048 x 2048 in chunks takes 8040 us, 7968 so.
 //    Below head dim 32 the context's matrix instructions have rows to spare: a row of ones in v^T sums the denominator.
 //  - masked keys cost one more matrix instruction, in steps that hold any; steps before the first masked key skip the test.
 //  - matrix instructions of the next and the previous tile alternate with the exponentials of this one.
@@ -165,7 +165,9 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, NW, HAS_BIAS)) void k_a
     }
     // ---- bias tiles of the wavefront's queries, one after the other
     const float* bias_q = HAS_BIAS ? a.bias + ((size_t)h * (a.Lq >> 5) + qtc) * (a.Lp >> 5) * 1024 : nullptr;
-    const uint32_t b_lane = (uint32_t)lane * 16;
+    // (the lane of a query beyond L takes the last real one's: nobody has written its own, and the denominators multiply its weights by zero)
+    const int last_q = a.L - 1 - 32 * qtc;
+    const uint32_t b_lane = (uint32_t)((col < last_q ? col : last_q) + 32 * hf) * 16;
     auto load_bias = [&](int kt, f32x16& b, uint32_t off) __attribute__((always_inline)) {
         if constexpr (HAS_BIAS) {
             if (kt > nt - 1) kt = nt - 1;
@@ -250,6 +252,7 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, NW, HAS_BIAS)) void k_a
         for (int v = 0; v < 16; ++v) o_acc[j][v] = 0.f;
     }
     Frag kf[2][KS], vf[2][2], pf[2];
+    const bf16x8 sel = sum_select(lane);
 #pragma unroll
     for (int c = 0; c < 2; ++c) pf[c].u = vf[1][c].u = make_uint4(0, 0, 0, 0);
     // One tile (row j of the step) of the software pipeline: the exponentials of tile t run while the matrix core forms
@@ -267,7 +270,7 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, NW, HAS_BIAS)) void k_a
             if (g == 4) op = mfma(vp[0].v, pf[0].v, op);
             if (g == 6) op = mfma(vp[1].v, pf[1].v, op);
             if (!decltype(plain_c)::value && g == 4 && live != 0xffffffffu) sn = mask_step(live, kperm, hf, sn);
-            if (!ONES && (g & 1)) lt = add_four(pf[g >> 2].w[(g >> 1) % 2 * 2], pf[g >> 2].w[(g >> 1) % 2 * 2 + 1], lt);
+            if (!ONES && (g & 3) == 3) lt = add_piece(sel, pf[g >> 2].v, lt);
             if (g == 0) {
                 kl[0].u = lds16(kl_off + rd_k);
                 if (KS > 1) kl[KS - 1].u = lds16(kl_off + (rd_k ^ 32u));
@@ -358,7 +361,7 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, NW, HAS_BIAS)) void k_a
     if constexpr (!ONES) {
         f32x4 lt = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int c = 0; c < 4; ++c) lt = add_four(pf[c >> 1].w[2 * (c & 1)], pf[c >> 1].w[2 * (c & 1) + 1], lt);
+        for (int c = 0; c < 2; ++c) lt = add_piece(sel, pf[c].v, lt);
         l_run[NR - 1] += lt[0];
     }
 
@@ -397,7 +400,7 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, NW, HAS_BIAS)) void k_a
     };
     // the denominator of the lane's query: both halves' partial sums, or row D of the context
     auto denominator = [&](const f32x16& o, float l) __attribute__((always_inline)) {
-        if constexpr (!ONES) return l + other_half(l);
+        if constexpr (!ONES) return l;
         const float x = o[ONES ? D / 2 : 0], y = other_half(x);      // (row D: register D / 2 of the lower half-wave)
         return ehf == 0 ? x : y;
     };

@@ -1092,7 +1092,9 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
             }
             // (tiled bias, see bias_index: the tiles of the wavefront's 32 queries follow each other)
             const float* bh = HAS_BIAS ? a.bias + ((size_t)h * (a.Lq >> 5) + wave) * nt * 1024 : nullptr;
-            const uint32_t b_lane = (uint32_t)lane_a * 16;
+            // (the lane of a query beyond L takes the last real one's: nobody has written its own, and the denominators multiply its weights by zero)
+            const int last_q = a.L - 1 - 32 * wave;
+            const uint32_t b_lane = (uint32_t)((col_a < last_q ? col_a : last_q) + 32 * hf_a) * 16;
             auto load_bias = [&](int kt, f32x16& bt) __attribute__((always_inline)) {
                 if constexpr (HAS_BIAS) {
                     if (kt > nk - 1) kt = nk - 1;             // (past the end: a harmless repeat)
@@ -1123,6 +1125,7 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
                 vf[1].u = *reinterpret_cast<const uint4*>(vr + 32);
             };
             Frag kf[2][2], vf[2][2], pf[2];
+            const bf16x8 sel = sum_select(lane_a);
 #pragma unroll
             for (int c = 0; c < 2; ++c) pf[c].u = vf[1][c].u = make_uint4(0, 0, 0, 0);
             // The pipeline of k_attn_rows over the tiles (kt, row 0), (kt, row 1), ...: the exponentials of a tile run while the
@@ -1139,7 +1142,7 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
                     if (g == 4) op = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vp[0].v, pf[0].v, op, 0, 0, 0);
                     if (g == 6) op = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vp[1].v, pf[1].v, op, 0, 0, 0);
                     if (g == 4 && live_n != 0xffffffffu) sn = mask_step(live_n, kperm_a, hf_a, sn);
-                    if (g & 1) lt = add_four(pf[g >> 2].w[(g >> 1) % 2 * 2], pf[g >> 2].w[(g >> 1) % 2 * 2 + 1], lt);
+                    if ((g & 3) == 3) lt = add_piece(sel, pf[g >> 2].v, lt);
                     if (g == 0) loads();
                     float n0 = 0.f, n1 = 0.f;
                     if (g < 7) {
@@ -1192,15 +1195,14 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
                     o_acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[1][c].v, pf[c].v, o_acc[1], 0, 0, 0);
-                    lt = add_four(pf[c].w[0], pf[c].w[1], lt);
-                    lt = add_four(pf[c].w[2], pf[c].w[3], lt);
+                    lt = add_piece(sel, pf[c].v, lt);
                 }
                 l_run[1] += lt[0];
             }
             // rows that do not stand are done again with a running maximum
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                if (!__any(!softmax_stands<16>(o_acc[j], l_run[j] + other_half(l_run[j])) && l_tok < a.L)) continue;
+                if (!__any(!softmax_stands<16>(o_acc[j], l_run[j]) && l_tok < a.L)) continue;
                 float m = -INFINITY;
                 l_run[j] = 0.f;
 #pragma unroll
@@ -1216,12 +1218,13 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
                     s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0][1].v, qf[j][1].v, s, 0, 0, 0);
                     general_tile(s, vf[0], live, hf_a, o_acc[j], m, l_run[j]);
                 }
+                l_run[j] += other_half(l_run[j]);
             }
 
             // ---- normalise, gate, store: o_acc[j]: lane = query, register v = e = 8*(v/4) + 4*hf + v%4
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const float l_tot = l_run[j] + other_half(l_run[j]);
+                const float l_tot = l_run[j];
                 const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
                 uint32_t pk[8];
 #pragma unroll
