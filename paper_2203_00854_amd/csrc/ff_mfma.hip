@@ -882,6 +882,13 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, slots = gridDim.x >> 3;
     const int n_local = xcd < n_rp ? ((n_rp - xcd + 7) >> 3) * a.H : 0;
     int h_loaded = -1;
+    // the lane's index formed anew, where an address made of it would otherwise be held through the whole item: at 256 channels it was held in scratch memory, and
+    // fetched from there behind every load in flight
+    auto fresh_lane = []() __attribute__((always_inline)) {
+        int l = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        asm volatile("" : "+v"(l));
+        return l;
+    };
     const int l_tok = 32 * wave + col;
     const bool tok_in = active && l_tok < a.L;
     const bool has_mask = a.mask != nullptr;
@@ -892,7 +899,7 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
         // ---- raw tokens (row 0 issued first; row 1 follows line by line as the registers fall free),
         // the mask entries.  Eight lanes fetch one 128-byte line of a token (a load with lane =
         // token, the operand layout, touches 64 lines for 1 KiB and the cache looks up one line per
-        // cycle: 5 us per item instead of 1.2); raw[m][hh][i] holds line m of the tokens 16hh + 8i +
+        // cycle: 5 us per item instead of 1.2; no load is under a condition, each a branch of its own); raw[m][hh][i] holds line m of the tokens 16hh + 8i +
         // lane/8 of the wavefront's tile, piece lane%8.  Issued before the barrier: the loads are on
         // their way while the block waits for its last wavefront.
         constexpr int NG = KC / 4;              // 128-byte lines per token
@@ -915,9 +922,7 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     const int l = 32 * wave + 16 * hh + 8 * i + (lane >> 3);
-                    const bool in = active && l < a.L;
-                    raw[m][hh][i] = make_uint4(0, 0, 0, 0);
-                    if (in) raw[m][hh][i] = ldg16(a.x + (row_tok + (int64_t)l * a.sl) * K + (lane & 7) * 8 + 64 * m);
+                    raw[m][hh][i] = ldg16(a.x + (row_tok + (int64_t)(l < a.L ? l : a.L - 1) * a.sl) * K + (lane & 7) * 8 + 64 * m);
                 }
         };
 #pragma unroll
@@ -929,23 +934,24 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
         if (h != h_loaded) {
             // (128 rows of 2 KC pieces, KC / 2 pieces per thread, up to four loads in flight)
             constexpr int WB = KC / 2 < 4 ? KC / 2 : 4;          // loads in flight per thread
+            const int t = 64 * wave + fresh_lane();
 #pragma unroll
             for (int n0 = 0; n0 < KC / 2; n0 += WB) {
                 uint4 wv[WB];
 #pragma unroll
                 for (int n = 0; n < WB; ++n) {
-                    const int p = tid + (n0 + n) * kFuWaves * 64;
+                    const int p = t + (n0 + n) * kFuWaves * 64;
                     const int row = p / (2 * KC), pp = p - row * (2 * KC);
                     wv[n] = ldg16(a.wp + ((size_t)((row >> 5) * a.Hd + h * 32 + (row & 31)) * K + pp * 8));
                 }
 #pragma unroll
                 for (int n = 0; n < WB; ++n) {
-                    const int p = tid + (n0 + n) * kFuWaves * 64;
+                    const int p = t + (n0 + n) * kFuWaves * 64;
                     const int row = p / (2 * KC), pp = p - row * (2 * KC);
                     *reinterpret_cast<uint4*>(s_w + row * WP + pp * 16) = wv[n];
                 }
             }
-            if (tid < 128) s_aug[tid] = a.aug[(tid >> 5) * a.Hd + h * 32 + (tid & 31)];
+            if (t < 128) s_aug[t] = a.aug[(t >> 5) * a.Hd + h * 32 + (t & 31)];
             h_loaded = h;
             __syncthreads();
         }
@@ -985,6 +991,12 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
                         __builtin_amdgcn_wave_barrier();
                     }
                     if (j == 0) fetch_line(1, m);         // (the line's registers are free again)
+                    if (32 * wave + 32 > a.L) {           // (wave-uniform; tokens beyond L hold the last one: they must not bring its infinities or NaN to the keys)
+                        const uint32_t keep = l_tok < a.L ? 0xffffffffu : 0u;
+#pragma unroll
+                        for (int sp = 0; sp < 4; ++sp)
+                            xg[sp].u = make_uint4(xg[sp].u.x & keep, xg[sp].u.y & keep, xg[sp].u.z & keep, xg[sp].u.w & keep);
+                    }
                     // LayerNorm statistics as in token_stats, one line at a time
 #pragma unroll
                     for (int sp = 0; sp < 4; ++sp)
@@ -1019,7 +1031,7 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
                 xaug.u = make_uint4(0, 0, 0, 0);
                 if (hf == 0) {
                     xaug.u = make_uint4(pack2(m_hi, m_hi), pack2(m_lo, r_hi), pack2(r_hi, r_lo), 0u);
-                    s_stat[(wave * 2 + j) * 32 + col] = rstd;
+                    s_stat[(wave * 2 + j) * 32 + (fresh_lane() & 31)] = rstd;
                 }
                 const bool key_valid = tok_in && mval[j] != 0.f;
                 const uint64_t live = __ballot(key_valid);           // (the two half-waves hold the same 32 tokens)
@@ -1235,8 +1247,9 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
                 merge_halves(pk[4], pk[6]);      // lower: e 16..23, upper: e 24..31
                 merge_halves(pk[5], pk[7]);
                 bf16_t* op = a.o + ((size_t)(rlv[j] * a.H + h) * a.Lp + 32 * wave) * 32;        // (uniform)
-                const uint32_t o_lane = (uint32_t)(col * 32 + 8 * hf) * 2;
-                if (row_ok[j] && l_tok < a.L) {
+                const int ln = fresh_lane();
+                const uint32_t o_lane = (uint32_t)((ln & 31) * 32 + 8 * (ln >> 5)) * 2;
+                if (row_ok[j] && 32 * wave + (ln & 31) < a.L) {
                     stg16(op, o_lane, make_uint4(pk[0], pk[1], pk[2], pk[3]));
                     stg16(op + 16, o_lane, make_uint4(pk[4], pk[5], pk[6], pk[7]));
                 }
