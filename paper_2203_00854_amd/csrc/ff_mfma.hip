@@ -960,20 +960,25 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
         Frag qf[2][2];          // (set and used by wavefronts with tokens only)
         uint32_t gpk[2][8];
         if (active) {
+            // ---- both rows' tokens as operands, with their statistics
+            Frag xa[2][KC], xaug[2];
+            float rstd[2];
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 // The lines pass through the wavefront's staging area (16 tokens x 128 bytes, the eight
                 // pieces of a token rotated by its index: conflict-free) and come back in the operand
                 // layout, lane = token, pieces 2s' + hf of line m = contraction steps 4m + s'.  The
                 // area is private to the wavefront, whose LDS operations complete in order.
-                f32x16 aq, ak, av, ag;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) aq[v] = ak[v] = av[v] = ag[v] = 0.f;
-                const unsigned char* wrow = s_w + col * WP + hf * 16;
                 float sum = 0.f, sq = 0.f;
 #pragma unroll
                 for (int m = 0; m < NG; ++m) {
-                    Frag xg[4];
+                    Frag* xg = &xa[j][4 * m];
+                    // (defined anew, with whatever the registers hold: each half of the lanes is loaded under a condition below, and the compiler would keep
+                    // the last item's operands through the attention for the other half)
+#pragma unroll
+                    for (int sp = 0; sp < 4; ++sp)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) asm volatile("" : "=v"(xg[sp].w[i]));
 #pragma unroll
                     for (int hh = 0; hh < 2; ++hh) {
 #pragma unroll
@@ -1005,78 +1010,92 @@ __global__ __launch_bounds__(kFuWaves * 64) void k_proj_attn(FusedArgs a) {
                             sum = add_pair(xg[sp].w[i], sum);
                             sq = add_pair_sq(xg[sp].w[i], sq);
                         }
-#pragma unroll
-                    for (int sp = 0; sp < 4; ++sp) {
-                        const int st = 4 * m + sp;
-                        Frag wq, wk, wv, wg;
-                        wq.u = *reinterpret_cast<const uint4*>(wrow + 0 * 32 * WP + 32 * st);
-                        wk.u = *reinterpret_cast<const uint4*>(wrow + 1 * 32 * WP + 32 * st);
-                        wv.u = *reinterpret_cast<const uint4*>(wrow + 2 * 32 * WP + 32 * st);
-                        wg.u = *reinterpret_cast<const uint4*>(wrow + 3 * 32 * WP + 32 * st);
-                        aq = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wq.v, xg[sp].v, aq, 0, 0, 0);
-                        ak = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wk.v, xg[sp].v, ak, 0, 0, 0);
-                        av = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xg[sp].v, wv.v, av, 0, 0, 0);
-                        ag = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wg.v, xg[sp].v, ag, 0, 0, 0);
-                    }
                 }
                 sum += other_half(sum);
                 sq += other_half(sq);
                 const float mu = sum * (1.f / (float)K);
                 const float var = fmaxf(sq * (1.f / (float)K) - mu * mu, 0.f) + a.eps;
-                const float rstd = tok_in ? rsqrtf(var) : 0.f;
-                const float mneg = tok_in ? -mu : 0.f, r = var * rstd;
+                rstd[j] = tok_in ? rsqrtf(var) : 0.f;
+                const float mneg = tok_in ? -mu : 0.f, r = var * rstd[j];
                 const float m_hi = bf16_round(mneg), m_lo = bf16_round(mneg - m_hi);
                 const float r_hi = bf16_round(r), r_lo = bf16_round(r - r_hi);
-                Frag xaug;
-                xaug.u = make_uint4(0, 0, 0, 0);
+                xaug[j].u = make_uint4(0, 0, 0, 0);
                 if (hf == 0) {
-                    xaug.u = make_uint4(pack2(m_hi, m_hi), pack2(m_lo, r_hi), pack2(r_hi, r_lo), 0u);
-                    s_stat[(wave * 2 + j) * 32 + (fresh_lane() & 31)] = rstd;
+                    xaug[j].u = make_uint4(pack2(m_hi, m_hi), pack2(m_lo, r_hi), pack2(r_hi, r_lo), 0u);
+                    s_stat[(wave * 2 + j) * 32 + (fresh_lane() & 31)] = rstd[j];
                 }
                 const bool key_valid = tok_in && mval[j] != 0.f;
                 const uint64_t live = __ballot(key_valid);           // (the two half-waves hold the same 32 tokens)
                 if (lane == 0) s_live[j * 8 + wave] = (int)(uint32_t)live;
-                {
-                    Frag wq, wk, wv, wg;
-                    wq.u = s_aug[col];
-                    wk.u = s_aug[32 + col];
-                    wv.u = s_aug[64 + col];
-                    wg.u = s_aug[96 + col];
-                    aq = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wq.v, xaug.v, aq, 0, 0, 0);
-                    ak = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wk.v, xaug.v, ak, 0, 0, 0);
-                    av = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xaug.v, wv.v, av, 0, 0, 0);
-                    ag = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wg.v, xaug.v, ag, 0, 0, 0);
+            }
+            // ---- the head's four feature tiles one after the other, every weight operand read from LDS once for the tokens of both rows
+            f32x16 acc[2];
+            auto contract = [&](int T, bool tokens_first) __attribute__((always_inline)) {
+                // (opaque and fenced: else the operands of all steps are in registers at once, and others in scratch memory)
+                unsigned rd = (unsigned)(T * 32 * WP + col * WP + hf * 16);
+                asm volatile("" : "+v"(rd));
+                constexpr int AHEAD = 3;
+                Frag wf[AHEAD];
+#pragma unroll
+                for (int st = 0; st < AHEAD; ++st) wf[st].u = *reinterpret_cast<const uint4*>(s_w + (rd + 32u * st));
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.f;
+#pragma unroll
+                for (int st = 0; st <= KC; ++st) {
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const Frag& x = st < KC ? xa[j][st < KC ? st : 0] : xaug[j];
+                        acc[j] = tokens_first ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.v, wf[st % AHEAD].v, acc[j], 0, 0, 0)
+                                              : __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[st % AHEAD].v, x.v, acc[j], 0, 0, 0);
+                    }
+                    if (st + AHEAD < KC) wf[st % AHEAD].u = *reinterpret_cast<const uint4*>(s_w + (rd + 32u * (st + AHEAD)));
+                    else if (st + AHEAD == KC) wf[st % AHEAD].u = s_aug[32 * T + col];
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                // q: B operand of S^T, step s = registers 8s .. 8s+7; k: the same pieces into the token's LDS row
+            };
+            // k: one 16-byte piece per step and half-wave into the token's LDS row
+            contract(1, false);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
                 unsigned char* krow = s_k + (j * 256 + l_tok) * kFuKPitch;
 #pragma unroll
                 for (int s = 0; s < 2; ++s) {
                     uint32_t kw[4];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        qf[j][s].w[i] = pack2(aq[8 * s + 2 * i] * rstd, aq[8 * s + 2 * i + 1] * rstd);
-                        kw[i] = pack2(ak[8 * s + 2 * i] * rstd, ak[8 * s + 2 * i + 1] * rstd);
-                    }
+                    for (int i = 0; i < 4; ++i) kw[i] = pack2(acc[j][8 * s + 2 * i] * rstd[j], acc[j][8 * s + 2 * i + 1] * rstd[j]);
                     *reinterpret_cast<uint4*>(krow + (2 * s + hf) * 16) = make_uint4(kw[0], kw[1], kw[2], kw[3]);
                 }
-                // gate: the layout of O^T
+            }
+            // v: lane = feature col, register v = token 8*(v/4) + 4*hf + v%4 of the wavefront's tile
+            // (1/std of those tokens comes back from LDS: written above by this wavefront, whose LDS
+            // operations complete in order)
+            contract(2, true);
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const float g0 = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-(ag[2 * i] * rstd) * kLog2e));
-                    const float g1 = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-(ag[2 * i + 1] * rstd) * kLog2e));
-                    gpk[j][i] = pack2(g0, g1);
-                }
-                // v: lane = feature col, register v = token 8*(v/4) + 4*hf + v%4 of the wavefront's tile
-                // (1/std of those tokens comes back from LDS: written above by this wavefront, whose LDS
-                // operations complete in order)
-                __builtin_amdgcn_wave_barrier();
+            for (int j = 0; j < 2; ++j) {
                 unsigned char* vrow = s_vt + (j * 32 + col) * kFuVPitch + (32 * wave + 4 * hf) * 2;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const float4 rs = *reinterpret_cast<const float4*>(s_stat + (wave * 2 + j) * 32 + 8 * g + 4 * hf);
-                    *reinterpret_cast<uint2*>(vrow + 16 * g) =
-                        make_uint2(pack2(av[4 * g] * rs.x, av[4 * g + 1] * rs.y), pack2(av[4 * g + 2] * rs.z, av[4 * g + 3] * rs.w));
+                    *reinterpret_cast<uint2*>(vrow + 16 * g) = make_uint2(pack2(acc[j][4 * g] * rs.x, acc[j][4 * g + 1] * rs.y),
+                                                                          pack2(acc[j][4 * g + 2] * rs.z, acc[j][4 * g + 3] * rs.w));
                 }
+            }
+            // q: B operand of S^T, step s = registers 8s .. 8s+7, the order of k's pieces
+            contract(0, false);
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) qf[j][i >> 2].w[i & 3] = pack2(acc[j][2 * i] * rstd[j], acc[j][2 * i + 1] * rstd[j]);
+            // gate: the layout of O^T
+            contract(3, false);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const float nr = -kLog2e * rstd[j];
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    gpk[j][i] = pack2(__builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(acc[j][2 * i] * nr)),
+                                      __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(acc[j][2 * i + 1] * nr)));
             }
         }
         __syncthreads();
