@@ -180,7 +180,7 @@ static ff_status run(const ff_attn_desc* desc, const ff_attn_weights* w, const v
             st = mfma_chunk(p, *w, x, mask, residual ? x : nullptr, out, ws, r0, rows, stream);
         } else {
             Timed t(KK_GENERIC, stream);
-            st = generic_chunk(p, *w, x, mask, residual ? x : nullptr, out, ws, r0, rows, stream);
+            st = generic_chunk(p, *w, x, z, mask, residual ? x : nullptr, out, ws, r0, rows, stream);
         }
         if (st != FF_OK) return st;
     }

@@ -101,11 +101,11 @@ ff_status check_launch(const char* what);
 // generic float32 path (ff_generic.hip); T selected by p.dtype
 size_t generic_workspace(const Problem& p, int chunk, Workspace* ws, void* base);
 // once per call, before the chunks: the pair-bias tensor (and, for the matrix-core family, the
-// prepared weights; for the generic one the token statistics of the first chunk)
+// prepared weights; for the generic one the token statistics of the first chunk, both by the chunk itself where it is small)
 ff_status generic_prepare(const Problem& p, const ff_attn_weights& w, const void* x, const void* z,
                           const Workspace& ws, hipStream_t stream);
 // res: NULL, or a tensor laid out like out that is added to the module's output (may be out itself)
-ff_status generic_chunk(const Problem& p, const ff_attn_weights& w, const void* x, const float* mask,
+ff_status generic_chunk(const Problem& p, const ff_attn_weights& w, const void* x, const void* z, const float* mask,
                         const void* res, void* out, const Workspace& ws, int r0, int rows, hipStream_t stream);
 
 // bf16 matrix-core path (ff_mfma_*.hip)

@@ -253,15 +253,21 @@ __device__ __forceinline__ void split_weights(const RowsArgs& a, int id) {
 }
 
 template <typename T, bool VEC>
+__device__ __forceinline__ void pair_rows(const RowsArgs& a, int block) {
+    const int j8 = threadIdx.x & 7;
+    const int64_t pair = (int64_t)block * 32 + (threadIdx.x >> 3);
+    if (a.cp <= 32) pair_row<T, VEC, 1>(a, pair, j8);
+    else if (a.cp <= 64) pair_row<T, VEC, 2>(a, pair, j8);
+    else if (a.cp <= 128) pair_row<T, VEC, 4>(a, pair, j8);
+    else if (a.cp <= 256) pair_row<T, VEC, 8>(a, pair, j8);
+    else pair_row<T, VEC, 0>(a, pair, j8);
+}
+
+template <typename T, bool VEC>
 __global__ __launch_bounds__(256) void k_rows_generic(RowsArgs a) {
     const int j8 = threadIdx.x & 7, r32 = threadIdx.x >> 3;
     if ((int)blockIdx.x < a.pair_blocks) {
-        const int64_t pair = (int64_t)blockIdx.x * 32 + r32;
-        if (a.cp <= 32) pair_row<T, VEC, 1>(a, pair, j8);
-        else if (a.cp <= 64) pair_row<T, VEC, 2>(a, pair, j8);
-        else if (a.cp <= 128) pair_row<T, VEC, 4>(a, pair, j8);
-        else if (a.cp <= 256) pair_row<T, VEC, 8>(a, pair, j8);
-        else pair_row<T, VEC, 0>(a, pair, j8);
+        pair_rows<T, VEC>(a, blockIdx.x);
         return;
     }
     if constexpr (sizeof(T) == 4) {
@@ -301,10 +307,12 @@ struct GenericGemmArgs {
     float qscale;
     void* cdst;            // qkvg or out
     const void* res;       // !PROJ: residual added to the output (laid out like out, may be out itself) or NULL
+    float eps;             // OWN: of the LayerNorm
 };
 
-template <typename T, bool PROJ, int VEC, int WN, bool BP>      // BP: weights from g.planes.  VEC: 0 rows of any length, 1 of whole pieces (Piece), 2 of whole chunks
-__global__ __launch_bounds__(256, WN == 1 ? 3 : 2) void k_gemm_generic(GenericGemmArgs g) {
+// BP: weights from g.planes.  VEC: 0 rows of any length, 1 of whole pieces (Piece), 2 of whole chunks.  OWN: the block forms the statistics of its tokens itself
+template <typename T, bool PROJ, int VEC, int WN, bool BP, bool OWN>
+__device__ __forceinline__ void gemm_block(const GenericGemmArgs& g, int bx, int by) {
     constexpr int BM = 64, BN = 64 * WN;
     constexpr int NA = PROJ || sizeof(T) == 4 ? 3 : 1, NB = sizeof(T) == 4 ? 3 : 1;      // planes of the operands
     using Load = std::conditional_t<VEC == 2, WholePiece<T>, Piece<T, VEC != 0>>;
@@ -313,7 +321,7 @@ __global__ __launch_bounds__(256, WN == 1 ? 3 : 2) void k_gemm_generic(GenericGe
     __shared__ __attribute__((aligned(16))) unsigned char Bs[2][NB][BN * 64];
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, hf = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int t0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
+    const int t0 = bx * BM, n0 = by * BN;
     // a thread moves the piece tid % 8 of the rows tid / 8 + 32 i of a chunk.  (Rows beyond the last token or feature hold the first one: they
     // reach no output but their own, which is not stored)
     const int pc = tid & 7, prow = tid >> 3;
@@ -326,9 +334,19 @@ __global__ __launch_bounds__(256, WN == 1 ? 3 : 2) void k_gemm_generic(GenericGe
         if constexpr (PROJ) {
             const int rl = tc / g.L, l = tc - rl * g.L;
             ap[i] = (const T*)g.a + ((int64_t)(g.r0 + rl) * g.sr + (int64_t)l * g.sl) * g.K;
-            const float2 st = *reinterpret_cast<const float2*>(g.stats + 2 * (size_t)tc);
-            mean[i] = st.x;
-            rstd[i] = st.y;
+            if constexpr (OWN) {         // (the eight lanes of a row, as in token_row)
+                constexpr bool V = VEC != 0;
+                float4 r1[1], r2[2], r4[4], r8[8];
+                if (g.K <= 32) row_stats<T, V, 1>(ap[i], g.K, pc, g.eps, mean[i], rstd[i], r1);
+                else if (g.K <= 64) row_stats<T, V, 2>(ap[i], g.K, pc, g.eps, mean[i], rstd[i], r2);
+                else if (g.K <= 128) row_stats<T, V, 4>(ap[i], g.K, pc, g.eps, mean[i], rstd[i], r4);
+                else if (g.K <= 256) row_stats<T, V, 8>(ap[i], g.K, pc, g.eps, mean[i], rstd[i], r8);
+                else row_stats<T, V, 0>(ap[i], g.K, pc, g.eps, mean[i], rstd[i], r1);
+            } else {
+                const float2 st = *reinterpret_cast<const float2*>(g.stats + 2 * (size_t)tc);
+                mean[i] = st.x;
+                rstd[i] = st.y;
+            }
         } else {
             ap[i] = (const T*)g.a + (size_t)tc * g.K;
         }
@@ -539,6 +557,23 @@ __global__ __launch_bounds__(256, WN == 1 ? 3 : 2) void k_gemm_generic(GenericGe
     };
     if (tw + 32 <= g.tokens) emit(std::integral_constant<bool, true>{});
     else emit(std::integral_constant<bool, false>{});
+}
+
+template <typename T, bool PROJ, int VEC, int WN, bool BP>
+__global__ __launch_bounds__(256, WN == 1 ? 3 : 2) void k_gemm_generic(GenericGemmArgs g) {
+    gemm_block<T, PROJ, VEC, WN, BP, false>(g, blockIdx.x, blockIdx.y);
+}
+// The projections of a small call and, in the blocks behind theirs, the pair bias, on which they do not depend (one_launch).
+template <typename T, int VEC>
+__global__ __launch_bounds__(256, 3) void k_proj_rows_generic(GenericGemmArgs g, RowsArgs a, int nx, int gemm_blocks, int pair_vec) {
+    if ((int)blockIdx.x < gemm_blocks) {
+        const int by = (int)blockIdx.x / nx;
+        gemm_block<T, true, VEC, 1, false, true>(g, (int)blockIdx.x - by * nx, by);
+    } else if (pair_vec) {
+        pair_rows<T, true>(a, (int)blockIdx.x - gemm_blocks);
+    } else {
+        pair_rows<T, false>(a, (int)blockIdx.x - gemm_blocks);
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -789,25 +824,44 @@ static unsigned char* weight_planes(const Problem& p, const ff_attn_weights& w, 
     return (size_t)6 * plane_rows(4 * p.Hd) * p.c <= (size_t)ws.chunk * p.L * p.Hd * 4 ? (unsigned char*)ws.o : nullptr;
 }
 
+// Whether the projections form the token statistics themselves and the pair bias rides in their launch: where a chunk's projections are at most four
+// blocks per compute unit and the pairs at most forty (their blocks hold the projections' LDS and registers).  The rows' launch and its latency are a fifth of a small call: 8 x 32
+// row attention of 32 channels 18.0 -> 15.6 us, 46 x 46 triangle attention of 256 channels 40.7 -> 35.4 (40.3 with a limit of one block), 8 x 200 row attention 52.7 -> 46.8 (with at most four blocks of pairs 52.6),
+// 4 x 256 of 32 channels 31.9 -> 29.9, 30 x 100 43.2 -> 40.6.  With eight blocks 53 x 100 60.8 -> 64, with sixteen 64 x 155 90 -> 107: every block of 64 features reads all of its tokens twice.
+static bool one_launch(const Problem& p, const Workspace& ws) {
+    const int64_t tokens = (int64_t)ws.chunk * p.L;
+    return (tokens + 63) / 64 * ((4 * p.Hd + 63) / 64) <= 4 * compute_units() &&
+           (!p.has_bias || (int64_t)p.L * p.L <= 40 * 32 * compute_units());
+}
+
+// the pair bias in `a`; returns whether its loads are whole pieces
+template <typename T>
+static bool pair_args(const Problem& p, const ff_attn_weights& w, const void* x, const void* z, RowsArgs& a) {
+    if (p.mode == FF_MSA_ROW) {
+        a.src = z; a.sq = p.L; a.sk = 1; a.cp = p.c_z; a.g = w.lnz_g; a.b = w.lnz_b;
+    } else {
+        a.src = x; a.sq = p.sr; a.sk = p.sl; a.cp = p.c; a.g = w.ln_g; a.b = w.ln_b;
+    }
+    a.wb = w.w_b;
+    a.pair_blocks = (int)(((int64_t)p.L * p.L + 31) / 32);
+    return a.cp % 4 == 0 && aligned_to(a.src, 4 * sizeof(T)) && aligned_to(a.g, 4 * sizeof(T)) && aligned_to(a.b, 4 * sizeof(T)) &&
+           aligned_to(a.wb, 4 * sizeof(T));
+}
+static RowsArgs rows_args(const Problem& p, const void* x, const Workspace& ws, int r0, int rows) {
+    RowsArgs a{};
+    a.H = p.H; a.L = p.L; a.Lb = bias_pitch(p.L); a.bias = ws.bias; a.eps = p.eps;
+    a.x = x; a.sr = p.sr; a.sl = p.sl; a.c = p.c; a.r0 = r0; a.tokens = rows * p.L; a.stats = ws.stats;
+    return a;
+}
+
 // token statistics of `rows` batch rows from r0 on, the pair bias if `pairs`, and the weights' planes
 template <typename T>
 static ff_status rows_t(const Problem& p, const ff_attn_weights& w, const void* x, const void* z, const Workspace& ws, int r0,
                         int rows, bool pairs, hipStream_t st) {
-    RowsArgs a{};
-    a.H = p.H; a.L = p.L; a.Lb = bias_pitch(p.L); a.bias = ws.bias; a.eps = p.eps;
-    a.x = x; a.sr = p.sr; a.sl = p.sl; a.c = p.c; a.r0 = r0; a.tokens = rows * p.L; a.stats = ws.stats;
+    if (one_launch(p, ws)) return FF_OK;
+    RowsArgs a = rows_args(p, x, ws, r0, rows);
     bool vec = p.c % 4 == 0 && aligned_to(x, 4 * sizeof(T));
-    if (pairs) {
-        if (p.mode == FF_MSA_ROW) {
-            a.src = z; a.sq = p.L; a.sk = 1; a.cp = p.c_z; a.g = w.lnz_g; a.b = w.lnz_b;
-        } else {
-            a.src = x; a.sq = p.sr; a.sk = p.sl; a.cp = p.c; a.g = w.ln_g; a.b = w.ln_b;
-        }
-        a.wb = w.w_b;
-        a.pair_blocks = (int)(((int64_t)p.L * p.L + 31) / 32);
-        vec = vec && a.cp % 4 == 0 && aligned_to(a.src, 4 * sizeof(T)) && aligned_to(a.g, 4 * sizeof(T)) && aligned_to(a.b, 4 * sizeof(T)) &&
-              aligned_to(a.wb, 4 * sizeof(T));
-    }
+    if (pairs) vec = pair_args<T>(p, w, x, z, a) && vec;
     a.token_blocks = (a.tokens + 31) / 32;
     a.planes = weight_planes<T>(p, w, x, ws);
     int split_blocks = 0;
@@ -861,7 +915,7 @@ static ff_status launch_attn(GenericAttnArgs a, hipStream_t st) {
 }
 
 template <typename T>
-static ff_status chunk_t(const Problem& p, const ff_attn_weights& w, const void* x, const float* mask, const void* res,
+static ff_status chunk_t(const Problem& p, const ff_attn_weights& w, const void* x, const void* z, const float* mask, const void* res,
                          void* out, const Workspace& ws, int r0, int rows, hipStream_t st) {
     const int tokens = rows * p.L;
     const size_t al = 4 * sizeof(T);
@@ -871,8 +925,19 @@ static ff_status chunk_t(const Problem& p, const ff_attn_weights& w, const void*
     g.w[0] = w.w_q; g.w[1] = w.w_k; g.w[2] = w.w_v; g.w[3] = w.w_g; g.bvec = w.b_g; g.Hd = p.Hd;
     g.qscale = kLog2e / sqrtf((float)p.d);
     g.cdst = ws.qkvg;
-    g.planes = weight_planes<T>(p, w, x, ws);
-    launch_gemm<T, true>(g, proj_vec<T>(p, w, x), st);
+    if (one_launch(p, ws)) {
+        g.eps = p.eps;
+        RowsArgs a = rows_args(p, x, ws, r0, rows);
+        const int pair_vec = r0 == 0 && p.has_bias && pair_args<T>(p, w, x, z, a);
+        const int nx = (tokens + 63) / 64, blocks = nx * ((g.N + 63) / 64);
+        const dim3 grid((unsigned)(blocks + a.pair_blocks));
+        if (!proj_vec<T>(p, w, x)) hipLaunchKernelGGL((k_proj_rows_generic<T, 0>), grid, dim3(256), 0, st, g, a, nx, blocks, pair_vec);
+        else if (g.K % 32 != 0) hipLaunchKernelGGL((k_proj_rows_generic<T, 1>), grid, dim3(256), 0, st, g, a, nx, blocks, pair_vec);
+        else hipLaunchKernelGGL((k_proj_rows_generic<T, 2>), grid, dim3(256), 0, st, g, a, nx, blocks, pair_vec);
+    } else {
+        g.planes = weight_planes<T>(p, w, x, ws);
+        launch_gemm<T, true>(g, proj_vec<T>(p, w, x), st);
+    }
 
     GenericAttnArgs a{};
     a.qkvg = ws.qkvg; a.bias = ws.bias; a.mask = mask; a.sr = p.sr; a.sl = p.sl; a.r0 = r0; a.rows = rows; a.L = p.L;
@@ -930,15 +995,15 @@ ff_status generic_prepare(const Problem& p, const ff_attn_weights& w, const void
                              : gen::rows_t<bf16_t>(p, w, x, z, ws, 0, rows, p.has_bias, stream);
 }
 
-ff_status generic_chunk(const Problem& p, const ff_attn_weights& w, const void* x, const float* mask,
+ff_status generic_chunk(const Problem& p, const ff_attn_weights& w, const void* x, const void* z, const float* mask,
                         const void* res, void* out, const Workspace& ws, int r0, int rows, hipStream_t stream) {
     if (r0 > 0) {
         const ff_status st = p.dtype == FF_F32 ? gen::rows_t<float>(p, w, x, nullptr, ws, r0, rows, false, stream)
                                                : gen::rows_t<bf16_t>(p, w, x, nullptr, ws, r0, rows, false, stream);
         if (st != FF_OK) return st;
     }
-    return p.dtype == FF_F32 ? gen::chunk_t<float>(p, w, x, mask, res, out, ws, r0, rows, stream)
-                             : gen::chunk_t<bf16_t>(p, w, x, mask, res, out, ws, r0, rows, stream);
+    return p.dtype == FF_F32 ? gen::chunk_t<float>(p, w, x, z, mask, res, out, ws, r0, rows, stream)
+                             : gen::chunk_t<bf16_t>(p, w, x, z, mask, res, out, ws, r0, rows, stream);
 }
 
 }  // namespace ff

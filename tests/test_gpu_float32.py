@@ -96,10 +96,12 @@ def test_rounding_of_the_float32_sums(mode, n_a, n_b, c, c_z, heads, d, limit):
 
 @pytest.mark.parametrize("mode,n_a,n_b,c,heads,d,chunk", [
     (ROW, 12, 33, 64, 2, 32, 0), (ROW, 11, 33, 64, 2, 32, 0),        # 64 channels: weights split ahead from 384 tokens on (396 and 363 here)
-    (ROW, 24, 45, 32, 3, 16, 5), (COL, 37, 40, 96, 1, 40, 13), (TS, 200, 200, 160, 2, 64, 0), (TE, 90, 90, 32, 5, 8, 90), (ROW, 640, 129, 32, 4, 8, 0)])
+    (ROW, 24, 45, 32, 3, 16, 5), (COL, 37, 40, 96, 1, 40, 13), (TS, 200, 200, 160, 2, 64, 0), (TE, 90, 90, 32, 5, 8, 90), (ROW, 640, 129, 32, 4, 8, 0),
+    (ROW, 3, 572, 30, 2, 8, 2), (ROW, 3, 573, 32, 2, 12, 2), (ROW, 50, 70, 300, 1, 8, 0)])      # 572: the longest whose pair bias rides in the projections' launch
 def test_weights_split_ahead_and_chunks(mode, n_a, n_b, c, heads, d, chunk):
     """The projection weights are split once per chunk where the chunk has tokens enough, else by every block: both sides of that line,
-    feature counts around the 64 and 128 of a block, and the unchunked call bit for bit with a chunked one that splits per block."""
+    feature counts around the 64 and 128 of a block, and the unchunked call bit for bit with a chunked one that splits per block and forms
+    the token statistics there."""
     case = I.make_case(small_spec(mode, n_a, n_b, c, heads, d, c_z=16, dtype="f32", mask="none"))
     desc, w, x, z, m = P.to_device(case, "cuda:0")
     got = P.ff_gated_attention(desc, w, x, z, m)
