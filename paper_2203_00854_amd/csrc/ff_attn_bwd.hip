@@ -55,7 +55,6 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
 }
 __device__ __forceinline__ float lo_f32(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float hi_f32(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
-__device__ __forceinline__ float other_half(float v) { return __shfl_xor(v, 32, 64); }
 
 static inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 static inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
@@ -383,7 +382,7 @@ __global__ __launch_bounds__(256) void k_bwd_stats(Args a) {
                than kSlack - after a query's first tiles almost never, and then the tile pays neither for the    \
                exchange between the halves nor for the rescaling; weights stay below 2^kSlack */                 \
             if (__builtin_amdgcn_ballot_w64(tmax > m + kSlack) != 0) {                                           \
-                const float m_new = fmaxf(m, fmaxf(tmax, other_half(tmax)));                                     \
+                const float m_new = fmaxf(m, half_max(tmax));                                     \
                 const float alpha = __builtin_amdgcn_exp2f(m - m_new);                                           \
                 _Pragma("unroll") for (int v = 0; v < 16; ++v) ctx[v] *= alpha;                                  \
                 l *= alpha;                                                                                      \
@@ -407,7 +406,7 @@ __global__ __launch_bounds__(256) void k_bwd_stats(Args a) {
     }
 #undef FF_BWD_STATS_TILE
     if (!active) return;             // (no barrier after this point)
-    const float l_tot = l + other_half(l);
+    const float l_tot = half_sum(l);
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
     // a query without unmasked keys: logsumexp = +inf makes every recomputed weight exp2(s - inf) = 0
     const float lse = l_tot > 0.f ? m + __builtin_amdgcn_logf(l_tot) : INFINITY;
@@ -437,7 +436,7 @@ __global__ __launch_bounds__(256) void k_bwd_stats(Args a) {
             }
         }
     }
-    dl += other_half(dl);
+    dl = half_sum(dl);
     if (hf == 0) {       // (Lp slots per (row, head): queries beyond L get a defined value too)
         a.lse[(size_t)rh * 2 * a.Lp + i] = i < a.L ? lse : INFINITY;
         a.delta[(size_t)rh * 2 * a.Lp + i] = dl;
@@ -796,7 +795,7 @@ __global__ __launch_bounds__(64 * kRowsTiles, 4) void k_bwd_rows(Args a) {
             for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, s[v]);
             tmax *= a.qscale2;
             if (__builtin_amdgcn_ballot_w64(tmax > m + kSlack) != 0) {
-                const float m_new = fmaxf(m, fmaxf(tmax, other_half(tmax)));
+                const float m_new = fmaxf(m, half_max(tmax));
                 const float alpha = __builtin_amdgcn_exp2f(m - m_new);
 #pragma unroll
                 for (int v = 0; v < 16; ++v) ctx[v] *= alpha;
@@ -822,7 +821,7 @@ __global__ __launch_bounds__(64 * kRowsTiles, 4) void k_bwd_rows(Args a) {
             dcv[g] = *reinterpret_cast<const uint2*>(s_d + n * 64 + ((g ^ piece_swizzle(n)) << 4) + 8 * hf);
         }
         // (all lanes take part in what follows: the two lanes of a query exchange halves; only queries below L are stored)
-        const float l_tot = l + other_half(l), inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+        const float l_tot = half_sum(l), inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
         // a query without unmasked keys: logsumexp = +inf makes every recomputed weight exp2(s - inf) = 0
         lse = l_tot > 0.f && n < a.L ? m + __builtin_amdgcn_logf(l_tot) : INFINITY;
         float dl = 0.f;          // delta uses the very dctx values the other contractions read
@@ -838,7 +837,7 @@ __global__ __launch_bounds__(64 * kRowsTiles, 4) void k_bwd_rows(Args a) {
                 ctx[4 * g + e] = d_o[e] * c;
             }
         }
-        delta = dl + other_half(dl);
+        delta = half_sum(dl);
         pack_position<D>(wg, ctx, 1.f);
         if (n < a.L) store_position<D>(a.dg + base + (size_t)n * D, wg, hf);
         if (BIAS && hf == 0) {

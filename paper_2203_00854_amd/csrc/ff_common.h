@@ -43,11 +43,36 @@ __device__ __forceinline__ void load16_to_lds(const void* base, uint32_t lane_by
                  : "memory", "m0");
 }
 
-// ---- wave64 reductions --------------------------------------------------------------
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+// ---- reductions over lanes --------------------------------------------------------------
+// Exchanges inside a row of sixteen lanes are DPP operands of the addition, between the rows and halves one swap: a few cycles each, where
+// an exchange through the LDS crossbar (__shfl_xor) is a round trip of about a hundred, twelve of them one after the other in a folded weight row.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppRor8 = 0x128;      // lane l reads l ^ 1, l ^ 2, l ^ 7, l ^ 8
+// over eight neighbouring lanes (the mirror of eight lanes whose fours agree is their exchange)
+__device__ __forceinline__ float sum8(float v) {
+    v += dpp<kDppXor1>(v);
+    v += dpp<kDppXor2>(v);
+    v += dpp<kDppHalfMirror>(v);
     return v;
+}
+// over the lane and the one 32 away
+__device__ __forceinline__ float half_sum(float v) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float half_max(float v) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float wave_sum(float v) {
+    v = sum8(v);
+    v += dpp<kDppRor8>(v);
+    // (of a value and itself the swaps give the lower rows or half in one result, the upper ones in the other)
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return half_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll

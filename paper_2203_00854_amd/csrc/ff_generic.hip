@@ -154,13 +154,6 @@ struct RowsArgs {
     unsigned char* planes;
 };
 
-__device__ __forceinline__ float sum8(float v) {
-    v += __shfl_xor(v, 1, 64);
-    v += __shfl_xor(v, 2, 64);
-    v += __shfl_xor(v, 4, 64);
-    return v;
-}
-
 template <typename T, bool VEC, int NJ>
 __device__ __forceinline__ void row_stats(const T* row, int c, int j8, float eps, float& mean, float& rstd, float4 (&reg)[NJ > 0 ? NJ : 1]) {
     float s = 0.f, q = 0.f;

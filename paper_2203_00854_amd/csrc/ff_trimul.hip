@@ -78,8 +78,8 @@ __device__ __forceinline__ void token_stats(const Frag (&xa)[KC], int K, float e
             sum = __builtin_amdgcn_fdot2_f32_bf16(w, ones, sum, false);
             sq = __builtin_amdgcn_fdot2_f32_bf16(w, w, sq, false);
         }
-    sum += __shfl_xor(sum, 32, 64);
-    sq += __shfl_xor(sq, 32, 64);
+    sum = half_sum(sum);
+    sq = half_sum(sq);
     const float rk = 1.f / (float)K;
     mean = sum * rk;
     const float ve = fmaxf(sq * rk - mean * mean, 0.f) + eps;
