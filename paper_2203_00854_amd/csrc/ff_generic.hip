@@ -98,8 +98,9 @@ __device__ __forceinline__ void store4(T* row, int k, int n, const float4& v) {
 // each the rounding of what the ones before it left): x = x0 + x1 + x2, |x1| <= 2^-9 |x|, |x2| <= 2^-18 |x|.  Of the nine products of two such
 // sums the six with i + j <= 2 are formed; what is left out is below 2^-25 of the product, a quarter of a float32 rounding of
 // it.  x0 y0 and the five corrections have sums of their own, so a chain rounds once per 16 terms of the contraction (v_mfma_f32_32x32x2_f32: once per two).
-// Six instructions of 32 cycles for 16 terms against eight of 64.  A bfloat16 operand is one plane and needs no others.  (An infinity among the operands gives NaN where
-// the float32 product would be infinite.)
+// Six instructions of 32 cycles for 16 terms against eight of 64.  A bfloat16 operand is one plane and needs no others.
+// An operand that is infinite or rounds to infinity (from 3.39e38 on) has NaN in its lower planes: results that are not finite are formed again by the float32
+// instruction (float32_tile, float32_queries).
 template <int NP>
 struct Planes {
     uint2 p[NP];       // four elements in each
@@ -303,6 +304,71 @@ struct GenericGemmArgs {
     float eps;             // OWN: of the LayerNorm
 };
 
+// A tile of 32 tokens x 32 features (lane = feature f0 + lane % 32) whose split sums are not all finite: those elements again, their products formed by the
+// float32 instruction (a lane reads four consecutive elements k0 + 4 half .. + 3 of its row of either operand and feeds four instructions
+// with them), two sums per output as everywhere.  The finite ones stay, so that an element's bits do not depend on its neighbours'.  Rows that hold a NaN, or
+// LayerNorm rows with anything that is not finite, are NaN by right: what masked tokens hold does not come here.
+template <typename T, bool PROJ, bool V>
+__device__ __forceinline__ void float32_tile(const GenericGemmArgs& g, int tw, int f0, const float2* own_stats, f32x16& acc) {
+    const int lane = threadIdx.x & 63, col = lane & 31, hf = lane >> 5;
+    const int t = tw + col < g.tokens ? tw + col : g.tokens - 1;
+    const T* row;
+    if constexpr (PROJ) {
+        const int rl = t / g.L, l = t - rl * g.L;
+        row = (const T*)g.a + ((int64_t)(g.r0 + rl) * g.sr + (int64_t)l * g.sl) * g.K;
+    } else {
+        row = (const T*)g.a + (size_t)t * g.K;
+    }
+    bool dead = false;
+    for (int k = 4 * hf; k < g.K; k += 8) {
+        const float4 v = load4<T, V>(row, k, g.K);
+        if constexpr (PROJ) dead = dead || !(fabsf(v.x) < INFINITY && fabsf(v.y) < INFINITY && fabsf(v.z) < INFINITY && fabsf(v.w) < INFINITY);
+        else dead = dead || v.x != v.x || v.y != v.y || v.z != v.z || v.w != v.w;
+    }
+    const uint64_t b = __ballot(dead);
+    const uint32_t skip = (uint32_t)b | (uint32_t)(b >> 32);
+    uint32_t redo = 0;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int x = 8 * (v >> 2) + 4 * hf + (v & 3);
+        if (!(fabsf(acc[v]) < INFINITY) && tw + x < g.tokens && !((skip >> x) & 1)) redo |= 1u << v;
+    }
+    const int f = f0 + col < g.N ? f0 + col : g.N - 1;
+    if (f0 + col >= g.N) redo = 0;
+    if (!__ballot(redo != 0)) return;
+    const T* wrow;
+    float2 st = make_float2(0.f, 0.f);
+    if constexpr (PROJ) {
+        const int seg = f / g.Hd;
+        const void* w = seg == 0 ? g.w[0] : (seg == 1 ? g.w[1] : (seg == 2 ? g.w[2] : g.w[3]));
+        wrow = (const T*)w + (size_t)(f - seg * g.Hd) * g.K;
+        st = own_stats ? own_stats[t - tw] : *reinterpret_cast<const float2*>(g.stats + 2 * (size_t)t);
+    } else {
+        wrow = (const T*)g.w[0] + (size_t)f * g.K;
+    }
+    f32x16 even, odd;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) even[v] = odd[v] = 0.f;
+#pragma unroll 1
+    for (int k0 = 0; k0 < g.K; k0 += 8) {
+        const int k = k0 + 4 * hf;
+        float4 a = load4<T, V>(row, k, g.K);
+        const float4 w = load4<T, V>(wrow, k, g.K);
+        if constexpr (PROJ) {
+            const float4 gv = load4<T, V>((const T*)g.ln_g, k, g.K), bv = load4<T, V>((const T*)g.ln_b, k, g.K);
+            a = make_float4((a.x - st.x) * st.y * gv.x + bv.x, (a.y - st.x) * st.y * gv.y + bv.y, (a.z - st.x) * st.y * gv.z + bv.z,
+                            (a.w - st.x) * st.y * gv.w + bv.w);
+        }
+        even = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, w.x, even, 0, 0, 0);
+        odd = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, w.y, odd, 0, 0, 0);
+        even = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, w.z, even, 0, 0, 0);
+        odd = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, w.w, odd, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+        if ((redo >> v) & 1) acc[v] = even[v] + odd[v];
+}
+
 // BP: weights from g.planes.  VEC: 0 rows of any length, 1 of whole pieces (Piece), 2 of whole chunks.  OWN: the block forms the statistics of its tokens itself
 template <typename T, bool PROJ, int VEC, int WN, bool BP, bool OWN>
 __device__ __forceinline__ void gemm_block(const GenericGemmArgs& g, int bx, int by) {
@@ -312,6 +378,7 @@ __device__ __forceinline__ void gemm_block(const GenericGemmArgs& g, int bx, int
     // rows of 32 elements in each plane, 16-byte piece p of row r in place p ^ (r / 4 % 4): conflict-free reads with lane = row
     __shared__ __attribute__((aligned(16))) unsigned char As[2][NA][BM * 64];
     __shared__ __attribute__((aligned(16))) unsigned char Bs[2][NB][BN * 64];
+    __shared__ float2 s_stat[OWN ? BM : 1];
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, hf = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int t0 = bx * BM, n0 = by * BN;
@@ -335,6 +402,7 @@ __device__ __forceinline__ void gemm_block(const GenericGemmArgs& g, int bx, int
                 else if (g.K <= 128) row_stats<T, V, 4>(ap[i], g.K, pc, g.eps, mean[i], rstd[i], r4);
                 else if (g.K <= 256) row_stats<T, V, 8>(ap[i], g.K, pc, g.eps, mean[i], rstd[i], r8);
                 else row_stats<T, V, 0>(ap[i], g.K, pc, g.eps, mean[i], rstd[i], r1);
+                if (pc == 0) s_stat[prow + 32 * i] = make_float2(mean[i], rstd[i]);
             } else {
                 const float2 st = *reinterpret_cast<const float2*>(g.stats + 2 * (size_t)tc);
                 mean[i] = st.x;
@@ -487,6 +555,18 @@ __device__ __forceinline__ void gemm_block(const GenericGemmArgs& g, int bx, int
     // of its tokens exist (the checks are branches around every store otherwise)
     const int tw = t0 + 32 * wt;
     if (tw >= g.tokens) return;                                  // (no barrier after this point)
+    // An operand that is infinite, or rounds to infinity, leaves NaN in its planes' products, and sums near the top of the range may overflow in a part: any
+    // result that is not finite is formed again (float32_tile)
+    float zero = 0.f;                   // (stays so while everything is finite)
+#pragma unroll
+    for (int n = 0; n < WN; ++n)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) zero = fmaf(acc[n][v], 0.f, zero);
+    if (__builtin_expect(__ballot(zero != 0.f) != 0, 0)) {
+#pragma unroll
+        for (int n = 0; n < WN; ++n)
+            float32_tile<T, PROJ, VEC != 0>(g, tw, n0 + 32 * (wn + n), OWN ? s_stat + 32 * wt : nullptr, acc[n]);
+    }
     auto emit = [&](auto full_c) __attribute__((always_inline)) {
         constexpr bool FULL = decltype(full_c)::value;
         // element offset of token tw + x in out: one division per wavefront where a row of tokens is at least a tile long
@@ -553,12 +633,12 @@ __device__ __forceinline__ void gemm_block(const GenericGemmArgs& g, int bx, int
 }
 
 template <typename T, bool PROJ, int VEC, int WN, bool BP>
-__global__ __launch_bounds__(256, WN == 1 ? 3 : 2) void k_gemm_generic(GenericGemmArgs g) {
+__global__ __launch_bounds__(256, WN == 1 ? (sizeof(T) == 2 ? 4 : 3) : 2) void k_gemm_generic(GenericGemmArgs g) {
     gemm_block<T, PROJ, VEC, WN, BP, false>(g, blockIdx.x, blockIdx.y);
 }
 // The projections of a small call and, in the blocks behind theirs, the pair bias, on which they do not depend (one_launch).
 template <typename T, int VEC>
-__global__ __launch_bounds__(256, 3) void k_proj_rows_generic(GenericGemmArgs g, RowsArgs a, int nx, int gemm_blocks, int pair_vec) {
+__global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 3) void k_proj_rows_generic(GenericGemmArgs g, RowsArgs a, int nx, int gemm_blocks, int pair_vec) {
     if ((int)blockIdx.x < gemm_blocks) {
         const int by = (int)blockIdx.x / nx;
         gemm_block<T, true, VEC, 1, false, true>(g, (int)blockIdx.x - by * nx, by);
@@ -578,7 +658,8 @@ __global__ __launch_bounds__(256, 3) void k_proj_rows_generic(GenericGemmArgs g,
 // accumulator's starting value it was rounded with every one of them), the key mask (0 or -inf) selects, in tiles that hold a masked key.  Online softmax; a query without
 // any unmasked key gets zero context.  Output o = gate * context.
 // Bound by the vector unit (exponentials, the planes of P: 250 instructions per 32 x 32 tile against 24 matrix instructions of 32 cycles).  Up to 32 channels it is held
-// to 128 registers: with 155 a second block of five wavefronts did not fit a compute unit (64 x 155 tokens: 31 us instead of 25, both under the profiler).
+// to 128 registers: with 155 a second block of five wavefronts did not fit a compute unit (64 x 155 tokens: 31 us instead of 25, both under the profiler); with bfloat16
+// storage, whose operands are one plane, to 96: with 112 the same call at 16 heads of 8 channels, all launches, 65.6 us instead of 56.8.
 struct GenericAttnArgs {
     const void* qkvg;
     const float* bias;       // [H][L][Lb] or NULL
@@ -599,8 +680,91 @@ constexpr size_t attn_smem_bytes(int keys) {
     return (size_t)keys * (attn_planes<T>() * (attn_k_pitch<DG>() + 16 * DG) + 4) + attn_planes<T>() * 8 * DG * 16;
 }
 
+// the lane's index formed anew: what comes behind the loops holds no registers through them
+__device__ __forceinline__ int fresh_lane() {
+    int l = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    asm volatile("" : "+v"(l));
+    return l;
+}
+// The context and (partial, per half-wave) sum of the wavefront's queries with `again`, all products on the float32 instruction: the operands come from the
+// projected tensors, a lane's key, query or channel row.  Register v of the exponentiated tile is the B operand of instruction v of O^T = V^T P^T
+// (its halves hold the keys 8 (v / 4) + v % 4 and that + 4).  Per 32 channels anew, for the registers; there are few such queries.
+template <typename T, bool VEC, int DG>
+__device__ __forceinline__ void float32_queries(const GenericAttnArgs& a, const T* base, const float* bias, const float* mask_row, int q0, bool again,
+                                                f32x16 (&acc)[(8 * DG + 31) / 32], float& sum) {
+    constexpr int NE = (8 * DG + 31) / 32;
+    const int lane = fresh_lane(), col = lane & 31, hf = lane >> 5, Hd = a.H * a.d, N4 = 4 * Hd;
+    const int qc = q0 + col < a.L ? q0 + col : a.L - 1;
+    const T *qrow = base + (size_t)qc * N4, *kb = base + Hd, *vb = kb + Hd;
+    const float* brow = bias ? bias + (size_t)qc * a.Lb : nullptr;
+    float l = 0.f;
+#pragma unroll
+    for (int n = 0; n < NE; ++n) {
+        if (32 * n >= a.d) break;
+        const int ch = 32 * n + col < a.d ? 32 * n + col : a.d - 1;
+        f32x16 c;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) c[v] = 0.f;
+        float m = -INFINITY;
+        l = 0.f;
+#pragma unroll 1
+        for (int kt = 0; kt < a.L; kt += 32) {
+            const T* krow = kb + (size_t)(kt + col < a.L ? kt + col : a.L - 1) * N4;
+            f32x16 s;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) s[v] = 0.f;
+#pragma unroll 1
+            for (int e0 = 0; e0 < a.d; e0 += 8) {
+                const float4 kf = load4<T, VEC>(krow, e0 + 4 * hf, a.d), qf = load4<T, VEC>(qrow, e0 + 4 * hf, a.d);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.x, qf.x, s, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.y, qf.y, s, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.z, qf.z, s, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.w, qf.w, s, 0, 0, 0);
+            }
+            uint32_t live = 0;
+            int k0 = kt + 4 * hf;
+            asm volatile("" : "+v"(k0));           // (opaque: the addresses of all keys are formed here, none is held through the loop)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int k = k0 + 8 * (v >> 2) + (v & 3);
+                const bool ok = k < a.L && (!mask_row || mask_row[(int64_t)k * a.sl] != 0.f);
+                live |= ok ? 1u << v : 0u;
+                s[v] = ok ? s[v] + (brow ? brow[k] : 0.f) : -INFINITY;
+            }
+            float tmax = s[0];
+#pragma unroll
+            for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, s[v]);
+            const float m_new = fmaxf(m, fmaxf(tmax, other_half(tmax))), ref = m_new == -INFINITY ? 0.f : m_new;
+            const float alpha = exp2f(m - ref);
+            m = m_new;
+            float part = 0.f;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                s[v] = exp2f(s[v] - ref);
+                part += s[v];
+            }
+            l = l * alpha + part;
+            f32x16 pv;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) pv[v] = 0.f;
+            asm volatile("" : "+v"(k0));
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int k = k0 + 8 * (v >> 2) + (v & 3);
+                const float x = (live >> v) & 1 ? to_f32<T>(vb[(size_t)k * N4 + ch]) : 0.f;
+                pv = __builtin_amdgcn_mfma_f32_32x32x2f32(x, s[v], pv, 0, 0, 0);
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) c[v] = fmaf(c[v], alpha, pv[v]);
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[n][v] = again ? c[v] : acc[n][v];
+    }
+    sum = again ? l : sum;
+}
+
 template <typename T, bool VEC, int DG>      // DG: head dimension in groups of 8 channels (rounded up)
-__global__ __launch_bounds__(512, DG <= 4 ? 4 : 2) void k_attn_generic(GenericAttnArgs a) {
+__global__ __launch_bounds__(512, DG <= 4 ? (sizeof(T) == 2 ? 5 : 4) : 2) void k_attn_generic(GenericAttnArgs a) {
     constexpr int DP = 8 * DG, NP = attn_planes<T>(), KP = attn_k_pitch<DG>(), NE = (DP + 31) / 32, NS = (DP + 15) / 16;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int VP = 2 * a.keys + 16;                                   // bytes of a row of v^T
@@ -782,7 +946,28 @@ __global__ __launch_bounds__(512, DG <= 4 ? 4 : 2) void k_attn_generic(GenericAt
             }
         }
     }
-    if (!active || qi >= a.L) return;
+    if (!active) return;
+    // Contexts that are not finite, as in the projections (an infinite value against the lower planes of a weight, a product of huge and tiny factors, a
+    // score of -infinity): the query again with float32 products, from the projected tensors, its own maximum in every tile.  The queries' results
+    // are their own; a query that holds a NaN is left as it is.
+    float zero = sum * 0.f;             // (stays so while everything is finite)
+#pragma unroll
+    for (int n = 0; n < NE; ++n)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) zero = fmaf(acc[n][v], 0.f, zero);
+    const uint64_t b = __ballot(zero != 0.f);
+    if (__builtin_expect(b != 0, 0)) {
+        bool nan = false;
+        const int ln = fresh_lane(), qn = q0 + (ln & 31) < a.L ? q0 + (ln & 31) : a.L - 1;
+        for (int e = 4 * (ln >> 5); e < a.d; e += 8) {
+            const float4 v = load4<T, VEC>(base + (size_t)qn * N4, e, a.d);
+            nan = nan || v.x != v.x || v.y != v.y || v.z != v.z || v.w != v.w;
+        }
+        const uint64_t nb = __ballot(nan);
+        const uint32_t again = ((uint32_t)b | (uint32_t)(b >> 32)) & ~((uint32_t)nb | (uint32_t)(nb >> 32));
+        if (again) float32_queries<T, VEC, DG>(a, base, a.bias ? a.bias + (size_t)h * a.L * a.Lb : nullptr, mask_row, q0, (again >> (ln & 31)) & 1, acc, sum);
+    }
+    if (qi >= a.L) return;
     sum += other_half(sum);
     const float inv = sum > 0.f ? 1.f / sum : 0.f;
     T* op = (T*)a.o + ((size_t)rl * a.L + qi) * Hd + (size_t)h * a.d;

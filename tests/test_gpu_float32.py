@@ -123,3 +123,106 @@ def test_large_and_small_magnitudes():
     for s in (2.0 ** 60, 2.0 ** -60):
         big = P.ff_gated_attention(desc, dict(w, w_v=w["w_v"] * s, w_o=w["w_o"] * 2.0 ** -20), x, z, m)
         assert torch.equal(big, base * (s * 2.0 ** -20))
+
+
+def same_values(got, ref, tol):
+    """got against a float64 reference that holds infinities and NaN: those in the same places, the rest within tol of the largest."""
+    with np.errstate(invalid="ignore"):
+        assert np.array_equal(np.isnan(got), np.isnan(ref))
+        assert np.array_equal(np.isinf(got), np.isinf(ref))
+        assert np.array_equal(np.sign(got[np.isinf(ref)]), np.sign(ref[np.isinf(ref)]))
+    fin = np.isfinite(ref)
+    if fin.any():
+        assert max_abs(got[fin], ref[fin]) <= tol * max(1.0, np.abs(ref[fin]).max())
+
+
+# one launch for statistics and projections; 64 and 128 features per block; split ahead and per block; head dims of every kernel;
+# the last tile of tokens, features, keys and channels partly filled
+INF_SHAPES = [(ROW, 3, 45, 64, 2, 8, 0), (COL, 70, 5, 36, 3, 12, 2), (ROW, 90, 130, 96, 3, 32, 0), (TS, 100, 100, 260, 4, 24, 0), (TE, 66, 66, 33, 1, 64, 0),
+              (ROW, 4, 601, 64, 3, 16, 1), (ROW, 5, 170, 40, 2, 128, 2)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("where", ["w_g", "w_v", "w_o"])
+@pytest.mark.parametrize("mode,n_a,n_b,c,heads,d,chunk", INF_SHAPES)
+def test_infinite_weights(dtype, where, mode, n_a, n_b, c, heads, d, chunk):
+    """An infinity in a weight does what it does to float32 products and sums: a gate of exactly 0 or 1, an infinite value channel, infinite
+    outputs of the sign of their product, NaN only where an infinity meets a zero or its opposite.  (Channel 0 is positive in every normalised token, so
+    that an infinite weight there gives one sign.)"""
+    case = I.make_case(small_spec(mode, n_a, n_b, c, heads, d, c_z=16, dtype=dtype, mask="none"))
+    hd = heads * d
+    w = {k: v.copy() for k, v in case.widened_weights().items()}
+    w["ln_b"][0] = 24.0
+    if where == "w_g":
+        w["w_g"][0, 0], w["w_g"][hd - 1, 0] = -np.inf, np.inf
+    elif where == "w_v":
+        w["w_v"][hd // 2, 0] = np.inf
+    else:
+        w["w_v"][hd - 1, 0] = 1.0               # (its context is far from zero: the sign of the infinity is certain)
+        w["w_o"][c - 1, hd - 1] = -np.inf
+    case.weights = {k: I.to_storage(v.astype(np.float32), dtype) for k, v in w.items()}
+    desc, dw, x, z, m = P.to_device(case, "cuda:0")
+    if P.ff_attention_path(desc) != "generic":
+        x = torch.cat([x.new_zeros(4), x.flatten()])[4:].view_as(x)
+    got = P.ff_gated_attention(desc, dw, x, z, m)
+    assert P.ff_attention_last_path() == "generic"
+    if chunk:
+        assert torch.equal(P.ff_attention_chunked(desc, dw, x, z, m, chunk_rows=chunk).nan_to_num(5.0), got.nan_to_num(5.0))
+    xf, zf, mf, wf = f64_inputs(case)
+    with np.errstate(all="ignore"):
+        ref = O.gated_attention(mode, xf, zf, mf, wf, heads, case.spec.ln_eps)
+    same_values(got.float().cpu().numpy().astype(np.float64), ref, 1e-4 if dtype == "f32" else 2e-2)
+
+
+@pytest.mark.parametrize("where", ["w_v", "w_o", "score", "masked"])
+@pytest.mark.parametrize("mode,n_a,n_b,c,heads,d,chunk", INF_SHAPES)
+def test_top_of_the_float32_range(where, mode, n_a, n_b, c, heads, d, chunk):
+    """Finite values up to the largest float32: weights, products of huge and tiny factors, a key whose score is -infinity in float32 (weight
+    exactly 0), and infinities and the like in masked tokens next to them."""
+    case = I.make_case(small_spec(mode, n_a, n_b, c, heads, d, c_z=16, dtype="f32", mask="none"))
+    hd, top = heads * d, np.finfo(np.float32).max
+    w = {k: v.copy() for k, v in case.weights.items()}
+    x = case.x.copy()
+    w["b_o"][:] = 0
+    if where == "w_o":
+        w["w_v"] *= np.float32(2.0 ** -70)
+        w["w_o"][:] = np.sign(w["w_o"]) * top * np.linspace(0.99, 1.0, c, dtype=np.float32)[:, None]
+    elif where == "score":
+        # token 1 of every batch row has nothing but channel 0, zero elsewhere: its key overflows to infinity, its product with every
+        # query, negative there, to -infinity (-700 or less in float64)
+        x[:, :, 0] = 0
+        tok = x[:, 1] if mode in (ROW, TS) else x[1]
+        tok[:] = 0
+        tok[:, 0] = 1000.0
+        w["ln_g"][:], w["ln_b"][:] = 1, 0
+        w["ln_b"][1] = -8.0
+        w["w_k"][::d] = 0
+        w["w_k"][::d, 0] = top / np.sqrt(c - 1.0) * 1.01
+        w["w_q"][::d] = 0
+        w["w_q"][::d, 1] = 2.0 ** -118
+    else:
+        w["ln_g"] *= np.float32(2.0 ** -80)
+        w["ln_b"] *= np.float32(2.0 ** -80)
+        for k in ("w_q", "w_k", "w_g") + (("w_b",) if mode in (TS, TE) else ()):
+            w[k] *= np.float32(2.0 ** 80)
+        w["w_v"][:] = np.sign(w["w_v"]) * top * np.linspace(0.99, 1.0, hd, dtype=np.float32)[:, None]
+        w["w_o"] *= np.float32(2.0 ** -48)
+    case.weights, case.x = w, x
+    bad = x
+    if where == "masked":
+        bad = poison_masked_tokens(case, np.random.default_rng(3).random((n_a, n_b)) < 0.7)
+        if mode in (TS, TE):           # (a masked token is an entry of the pair bias of all rows: finite there)
+            bad = case.x
+    xf, zf, mf, wf = f64_inputs(case)
+    case.x = bad
+    desc, dw, dx, z, m = P.to_device(case, "cuda:0")
+    got = P.ff_gated_attention(desc, dw, dx, z, m)
+    if chunk:
+        assert torch.equal(P.ff_attention_chunked(desc, dw, dx, z, m, chunk_rows=chunk).nan_to_num(5.0), got.nan_to_num(5.0))
+    got = got.cpu().numpy().astype(np.float64)
+    ref = O.gated_attention(mode, xf, zf, mf, wf, heads, case.spec.ln_eps)
+    if where == "masked":
+        got, ref = got[mf != 0], ref[mf != 0]
+    assert np.isfinite(got).all()
+    # (scores of up to a hundred carry errors of 100 x 2^-23 where they are that large)
+    assert rel_l2(got, ref) <= (3e-5 if where == "score" else 2e-6)
