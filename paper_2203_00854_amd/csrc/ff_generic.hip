@@ -592,8 +592,7 @@ __device__ __forceinline__ void gemm_block(const GenericGemmArgs& g, int bx, int
                 if (seg == 3) {
                     const float bias = to_f32<T>(((const T*)g.bvec)[f - 3 * g.Hd]);
 #pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        acc[n][v] = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-kLog2e * (acc[n][v] + bias)));
+                    for (int v = 0; v < 16; ++v) acc[n][v] = 1.f / (1.f + __expf(-(acc[n][v] + bias)));
                 } else {
                     const float scale = seg == 0 ? g.qscale : 1.f;
 #pragma unroll

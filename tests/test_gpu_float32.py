@@ -226,3 +226,23 @@ def test_top_of_the_float32_range(where, mode, n_a, n_b, c, heads, d, chunk):
     assert np.isfinite(got).all()
     # (scores of up to a hundred carry errors of 100 x 2^-23 where they are that large)
     assert rel_l2(got, ref) <= (3e-5 if where == "score" else 2e-6)
+
+
+def test_gate_is_divided_exactly():
+    """sigmoid(t) = 1 / (1 + exp(-t)) for t in [0, 8]: with the division rounded correctly its relative error is 3.80e-8 (root mean square of 20480
+    values, good to 0.3 %), with the reciprocal instruction in its place 3.89e-8.  (One token, value 1 in every channel, the output
+    projection the identity.)"""
+    n = 512
+    case = I.make_case(small_spec(COL, 1, 1, n, 16, 32, dtype="f32", mask="none"))
+    for v in case.weights.values():
+        v[...] = 0
+    case.weights["ln_b"][:], case.weights["w_v"][:, 0], case.weights["w_o"][:] = 1, 1, np.eye(n)
+    desc, w, x, z, m = P.to_device(case, "cuda:0")
+    rng, sq = np.random.default_rng(0), []
+    for _ in range(40):
+        t = rng.uniform(0, 8, n).astype(np.float32)
+        got = P.ff_gated_attention(desc, dict(w, b_g=torch.from_numpy(t).cuda()), x, z, m).cpu().numpy()[0, 0].astype(np.float64)
+        sq.append((got * (1 + np.exp(-t.astype(np.float64))) - 1) ** 2)
+    rms = float(np.sqrt(np.mean(sq)))
+    print(f"relative error of a gate: {rms:.3e}", flush=True)
+    assert rms <= 3.87e-8
