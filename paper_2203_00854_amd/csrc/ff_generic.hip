@@ -99,8 +99,11 @@ __device__ __forceinline__ void store4(T* row, int k, int n, const float4& v) {
 // sums the six with i + j <= 2 are formed; what is left out is below 2^-25 of the product, a quarter of a float32 rounding of
 // it.  x0 y0 and the five corrections have sums of their own, so a chain rounds once per 16 terms of the contraction (v_mfma_f32_32x32x2_f32: once per two).
 // Six instructions of 32 cycles for 16 terms against eight of 64.  A bfloat16 operand is one plane and needs no others.
-// An operand that is infinite or rounds to infinity (from 3.39e38 on) has NaN in its lower planes: results that are not finite are formed again by the float32
+// The operands are taken times 2^24, exactly, so that the third plane of the smallest float32 lies inside the range of bfloat16 too (unscaled, operands below
+// 2^-109 lose their last bits: relative error 3e-4 at 2^-120 instead of 2e-7).  An infinite one, or one that overflows so, has NaN in its lower planes: results that are not finite are formed again by the float32
 // instruction (float32_tile, float32_queries).
+constexpr float kUp = 0x1p24f, kDown = 0x1p-24f;
+__device__ __forceinline__ float4 times4(const float4& v, float f) { return make_float4(v.x * f, v.y * f, v.z * f, v.w * f); }
 template <int NP>
 struct Planes {
     uint2 p[NP];       // four elements in each
@@ -240,7 +243,7 @@ __device__ __forceinline__ void split_weights(const RowsArgs& a, int id) {
     if (row >= np) return;
     const int n = row < 4 * a.Hd ? row : 0, seg = n / a.Hd;
     const float* w = (const float*)(seg == 0 ? a.w[0] : (seg == 1 ? a.w[1] : (seg == 2 ? a.w[2] : a.w[3])));
-    const Planes<3> sp = split4<3>(load4<float, true>(w + (size_t)(n - seg * a.Hd) * a.c, 4 * p, a.c));
+    const Planes<3> sp = split4<3>(times4(load4<float, true>(w + (size_t)(n - seg * a.Hd) * a.c, 4 * p, a.c), kUp));
 #pragma unroll
     for (int j = 0; j < 3; ++j)
         *reinterpret_cast<uint2*>(a.planes + ((size_t)((p >> 3) * 3 + j) * np + row) * 64 + piece_place(row, p & 7)) = sp.p[j];
@@ -374,6 +377,7 @@ template <typename T, bool PROJ, int VEC, int WN, bool BP, bool OWN>
 __device__ __forceinline__ void gemm_block(const GenericGemmArgs& g, int bx, int by) {
     constexpr int BM = 64, BN = 64 * WN;
     constexpr int NA = PROJ || sizeof(T) == 4 ? 3 : 1, NB = sizeof(T) == 4 ? 3 : 1;      // planes of the operands
+    constexpr float down = (NA == 3 ? kDown : 1.f) * (NB == 3 ? kDown : 1.f);
     using Load = std::conditional_t<VEC == 2, WholePiece<T>, Piece<T, VEC != 0>>;
     // rows of 32 elements in each plane, 16-byte piece p of row r in place p ^ (r / 4 % 4): conflict-free reads with lane = row
     __shared__ __attribute__((aligned(16))) unsigned char As[2][NA][BM * 64];
@@ -408,6 +412,7 @@ __device__ __forceinline__ void gemm_block(const GenericGemmArgs& g, int bx, int
                 mean[i] = st.x;
                 rstd[i] = st.y;
             }
+            rstd[i] *= kUp;
         } else {
             ap[i] = (const T*)g.a + (size_t)tc * g.K;
         }
@@ -462,12 +467,13 @@ __device__ __forceinline__ void gemm_block(const GenericGemmArgs& g, int bx, int
         float4 gv, bv;
         if constexpr (PROJ) {
             gv = c.gm.value(k, g.K);
-            bv = c.bt.value(k, g.K);
+            bv = times4(c.bt.value(k, g.K), kUp);
         }
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int row = prow + 32 * i;
             float4 v = c.a[i].value(k, g.K);
+            if constexpr (!PROJ && NA == 3) v = times4(v, kUp);
             if constexpr (PROJ)       // (beyond K gamma and beta are zero, and so is the result)
                 v = make_float4((v.x - mean[i]) * rstd[i] * gv.x + bv.x, (v.y - mean[i]) * rstd[i] * gv.y + bv.y,
                                 (v.z - mean[i]) * rstd[i] * gv.z + bv.z, (v.w - mean[i]) * rstd[i] * gv.w + bv.w);
@@ -478,7 +484,8 @@ __device__ __forceinline__ void gemm_block(const GenericGemmArgs& g, int bx, int
 #pragma unroll
         for (int i = 0; i < (BP ? 0 : 2 * WN); ++i) {
             const int row = prow + 32 * i;
-            const Planes<NB> sp = split4<NB>(c.b[i].value(k, g.K));
+            const float4 v = c.b[i].value(k, g.K);
+            const Planes<NB> sp = split4<NB>(NB == 3 ? times4(v, kUp) : v);
 #pragma unroll
             for (int j = 0; j < NB; ++j) *reinterpret_cast<uint2*>(&Bs[buf][j][row * 64 + piece_place(row, pc)]) = sp.p[j];
         }
@@ -550,7 +557,7 @@ __device__ __forceinline__ void gemm_block(const GenericGemmArgs& g, int bx, int
 #pragma unroll
     for (int n = 0; n < WN; ++n)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[n][v] += low[n][v];
+        for (int v = 0; v < 16; ++v) acc[n][v] = (acc[n][v] + low[n][v]) * down;
     // lane = feature, register v = token 8 (v / 4) + 4 hf + v % 4 of the wavefront's 32: 128-byte runs per token.  FULL: all
     // of its tokens exist (the checks are branches around every store otherwise)
     const int tw = t0 + 32 * wt;
@@ -785,7 +792,8 @@ __global__ __launch_bounds__(512, DG <= 4 ? (sizeof(T) == 2 ? 5 : 4) : 2) void k
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int e = 16 * s + 8 * hf + 4 * i;
-            const Planes<NP> sp = split4<NP>(load4<T, VEC>(base + (size_t)qc * N4, e, a.d));
+            const float4 q = load4<T, VEC>(base + (size_t)qc * N4, e, a.d);
+            const Planes<NP> sp = split4<NP>(NP == 3 ? times4(q, kUp) : q);
 #pragma unroll
             for (int j = 0; j < NP; ++j) {
                 qf[s][j].w[2 * i] = sp.p[j].x;
@@ -829,12 +837,14 @@ __global__ __launch_bounds__(512, DG <= 4 ? (sizeof(T) == 2 ? 5 : 4) : 2) void k
             for (int u = 0; u < U; ++u) {
                 const int id = b0 + u * nthreads + tid, k = id / PR, k4 = 4 * (id / DP), e = id % DP;
                 if (id >= nkp * PR) break;
-                const Planes<NP> ks = split4<NP>(keep4(k < nk, kp[u].value(4 * (id % PR), a.d)));
+                const float4 kv = keep4(k < nk, kp[u].value(4 * (id % PR), a.d));
+                const Planes<NP> ks = split4<NP>(NP == 3 ? times4(kv, kUp) : kv);
                 const float4 m4 = *reinterpret_cast<const float4*>(s_m + k4);
                 // (what a masked token holds may be anything, and 0 x NaN is NaN)
                 const bool in = e < a.d;
-                const Planes<NP> vs = split4<NP>(make_float4(in && m4.x == 0.f ? to_f32<T>(vv[u][0]) : 0.f, in && m4.y == 0.f ? to_f32<T>(vv[u][1]) : 0.f,
-                                                             in && m4.z == 0.f ? to_f32<T>(vv[u][2]) : 0.f, in && m4.w == 0.f ? to_f32<T>(vv[u][3]) : 0.f));
+                const float4 v4 = make_float4(in && m4.x == 0.f ? to_f32<T>(vv[u][0]) : 0.f, in && m4.y == 0.f ? to_f32<T>(vv[u][1]) : 0.f,
+                                              in && m4.z == 0.f ? to_f32<T>(vv[u][2]) : 0.f, in && m4.w == 0.f ? to_f32<T>(vv[u][3]) : 0.f);
+                const Planes<NP> vs = split4<NP>(NP == 3 ? times4(v4, kUp) : v4);
                 const int at = (k4 & ~15) + 2 * (k4 & 4) + ((k4 & 8) >> 1);
 #pragma unroll
                 for (int j = 0; j < NP; ++j) {
@@ -872,10 +882,11 @@ __global__ __launch_bounds__(512, DG <= 4 ? (sizeof(T) == 2 ? 5 : 4) : 2) void k
             }
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                s[4 * g] += lo[4 * g] + bias[g].x;
-                s[4 * g + 1] += lo[4 * g + 1] + bias[g].y;
-                s[4 * g + 2] += lo[4 * g + 2] + bias[g].z;
-                s[4 * g + 3] += lo[4 * g + 3] + bias[g].w;
+                constexpr float down = NP == 3 ? kDown * kDown : 1.f;
+                s[4 * g] = fmaf(s[4 * g] + lo[4 * g], down, bias[g].x);
+                s[4 * g + 1] = fmaf(s[4 * g + 1] + lo[4 * g + 1], down, bias[g].y);
+                s[4 * g + 2] = fmaf(s[4 * g + 2] + lo[4 * g + 2], down, bias[g].z);
+                s[4 * g + 3] = fmaf(s[4 * g + 3] + lo[4 * g + 3], down, bias[g].w);
             }
             if (__ballot(s_m[kt + col] != 0.f)) {                // (tiles with masked keys only)
 #pragma unroll
@@ -946,6 +957,12 @@ __global__ __launch_bounds__(512, DG <= 4 ? (sizeof(T) == 2 ? 5 : 4) : 2) void k
         }
     }
     if (!active) return;
+    if constexpr (NP == 3) {
+#pragma unroll
+        for (int n = 0; n < NE; ++n)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[n][v] *= kDown;
+    }
     // Contexts that are not finite, as in the projections (an infinite value against the lower planes of a weight, a product of huge and tiny factors, a
     // score of -infinity): the query again with float32 products, from the projected tensors, its own maximum in every tile.  The queries' results
     // are their own; a query that holds a NaN is left as it is.

@@ -246,3 +246,31 @@ def test_gate_is_divided_exactly():
     rms = float(np.sqrt(np.mean(sq)))
     print(f"relative error of a gate: {rms:.3e}", flush=True)
     assert rms <= 3.87e-8
+
+
+@pytest.mark.parametrize("where", ["values", "tokens", "scores"])
+@pytest.mark.parametrize("mode,n_a,n_b,c,heads,d,chunk", INF_SHAPES)
+def test_bottom_of_the_float32_range(where, mode, n_a, n_b, c, heads, d, chunk):
+    """Operands around 2^-120 against others around 2^120 lose no bits: the result is as accurate as without the factors (float32 products
+    have 2.4e-7 to 2.9e-7 with and without; planes without the bits below 2^-133 have 4e-5 to 4e-4)."""
+    case = I.make_case(small_spec(mode, n_a, n_b, c, heads, d, c_z=16, dtype="f32", mask="none"))
+    w, f = case.weights, np.float32(2.0 ** 118)
+    if where == "values":
+        w["w_v"] /= f
+        w["w_o"] *= f
+    elif where == "tokens":
+        for k in ("ln_g", "ln_b"):
+            w[k] /= f
+        for k in ("w_q", "w_k", "w_v", "w_g") + (("w_b",) if mode in (TS, TE) else ()):
+            w[k] *= f
+    else:
+        w["w_q"] /= f
+        w["w_k"] *= f
+    desc, dw, x, z, m = P.to_device(case, "cuda:0")
+    got = P.ff_gated_attention(desc, dw, x, z, m)
+    if chunk:
+        assert torch.equal(P.ff_attention_chunked(desc, dw, x, z, m, chunk_rows=chunk), got)
+    xf, zf, mf, wf = f64_inputs(case)
+    rl = rel_l2(got.cpu().numpy().astype(np.float64), O.gated_attention(mode, xf, zf, mf, wf, heads, case.spec.ln_eps))
+    print(f"{case.spec.name} {where}: rel_l2={rl:.3e}", flush=True)
+    assert rl <= 5e-7
