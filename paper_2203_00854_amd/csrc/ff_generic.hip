@@ -665,7 +665,9 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 3) void k_proj_rows_gener
 // any unmasked key gets zero context.  Output o = gate * context.
 // Bound by the vector unit (exponentials, the planes of P: 250 instructions per 32 x 32 tile against 24 matrix instructions of 32 cycles).  Up to 32 channels it is held
 // to 128 registers: with 155 a second block of five wavefronts did not fit a compute unit (64 x 155 tokens: 31 us instead of 25, both under the profiler); with bfloat16
-// storage, whose operands are one plane, to 96: with 112 the same call at 16 heads of 8 channels, all launches, 65.6 us instead of 56.8.
+// storage, whose operands are one plane, to 96: with 112 the same call at 16 heads of 8 channels, all launches, 65.6 us instead of 57.4.
+// Weights below 2^-126 of the largest are zeros here and those below 2^-109 lose bits; whether any counts is decided once per query behind the loops (the smallest score
+// and the context tell): exponentials with a way of their own for tiles that hold any take 0.6 % more of a call, over 240 shapes, than the smallest score.
 struct GenericAttnArgs {
     const void* qkvg;
     const float* bias;       // [H][L][Lb] or NULL
@@ -769,8 +771,41 @@ __device__ __forceinline__ void float32_queries(const GenericAttnArgs& a, const 
     sum = again ? l : sum;
 }
 
+// Whether weights below 2^-109 may count in the lane's context: a channel of it is below 2^-80 times the largest of that channel's values.
+template <typename T, bool VEC, int DG>
+__device__ __forceinline__ bool small_weights_count(const GenericAttnArgs& a, const T* base, const float* mask_row, const f32x16 (&acc)[(8 * DG + 31) / 32], float sum) {
+    constexpr int NG = DG < 4 ? DG : 4;              // pieces of a lane per 32 channels
+    const int lane = fresh_lane(), col = lane & 31, hf = lane >> 5, Hd = a.H * a.d;
+    bool low = false;
+#pragma unroll
+    for (int n = 0; n < (8 * DG + 31) / 32; ++n) {
+        float top[4 * NG];
+#pragma unroll
+        for (int i = 0; i < 4 * NG; ++i) top[i] = 0.f;
+#pragma unroll 1
+        for (int k = col; k < a.L; k += 32) {
+            if (mask_row && mask_row[(int64_t)k * a.sl] == 0.f) continue;
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                const float4 v = load4<T, VEC>(base + (size_t)k * 4 * Hd + 2 * Hd, 32 * n + 8 * g + 4 * hf, a.d);
+                top[4 * g] = fmaxf(top[4 * g], fabsf(v.x));
+                top[4 * g + 1] = fmaxf(top[4 * g + 1], fabsf(v.y));
+                top[4 * g + 2] = fmaxf(top[4 * g + 2], fabsf(v.z));
+                top[4 * g + 3] = fmaxf(top[4 * g + 3], fabsf(v.w));
+            }
+        }
+#pragma unroll 1
+        for (int o = 16; o > 0; o >>= 1)
+#pragma unroll
+            for (int i = 0; i < 4 * NG; ++i) top[i] = fmaxf(top[i], __shfl_xor(top[i], o, 64));
+#pragma unroll
+        for (int i = 0; i < 4 * NG; ++i) low = low || fabsf(acc[n][i]) < top[i] * 0x1p-80f;
+    }
+    return low && half_sum(sum) > 0.f;
+}
+
 template <typename T, bool VEC, int DG>      // DG: head dimension in groups of 8 channels (rounded up)
-__global__ __launch_bounds__(512, DG <= 4 ? (sizeof(T) == 2 ? 5 : 4) : 2) void k_attn_generic(GenericAttnArgs a) {
+__global__ __launch_bounds__(512, DG <= 4 ? (sizeof(T) == 2 && (VEC || DG < 4) ? 5 : 4) : 2) void k_attn_generic(GenericAttnArgs a) {
     constexpr int DP = 8 * DG, NP = attn_planes<T>(), KP = attn_k_pitch<DG>(), NE = (DP + 31) / 32, NS = (DP + 15) / 16;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int VP = 2 * a.keys + 16;                                   // bytes of a row of v^T
@@ -808,6 +843,7 @@ __global__ __launch_bounds__(512, DG <= 4 ? (sizeof(T) == 2 ? 5 : 4) : 2) void k
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[n][v] = 0.f;
     float m = -INFINITY, sum = 0.f;                  // m: reference of the exponentials
+    float smin = INFINITY;                           // smallest score, those of masked keys among them
 
     for (int c0 = 0; c0 < a.L; c0 += a.keys) {
         const int nk = a.L - c0 < a.keys ? a.L - c0 : a.keys, nkp = (nk + 31) & ~31;
@@ -888,6 +924,8 @@ __global__ __launch_bounds__(512, DG <= 4 ? (sizeof(T) == 2 ? 5 : 4) : 2) void k
                 s[4 * g + 2] = fmaf(s[4 * g + 2] + lo[4 * g + 2], down, bias[g].z);
                 s[4 * g + 3] = fmaf(s[4 * g + 3] + lo[4 * g + 3], down, bias[g].w);
             }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) smin = fminf(smin, s[v]);
             if (__ballot(s_m[kt + col] != 0.f)) {                // (tiles with masked keys only)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
@@ -906,7 +944,7 @@ __global__ __launch_bounds__(512, DG <= 4 ? (sizeof(T) == 2 ? 5 : 4) : 2) void k
             // the reference follows the maximum only where a score exceeds it by more than 8: weights stay below 2^8, and most tiles rescale nothing
             if (__ballot(tmax > m + 8.f)) {
                 const float m_new = fmaxf(m, tmax);
-                const float alpha = __builtin_amdgcn_exp2f(m - (m_new == -INFINITY ? 0.f : m_new));
+                const float alpha = exp2f(m - (m_new == -INFINITY ? 0.f : m_new));
                 m = m_new;
                 sum *= alpha;
 #pragma unroll
@@ -964,14 +1002,17 @@ __global__ __launch_bounds__(512, DG <= 4 ? (sizeof(T) == 2 ? 5 : 4) : 2) void k
             for (int v = 0; v < 16; ++v) acc[n][v] *= kDown;
     }
     // Contexts that are not finite, as in the projections (an infinite value against the lower planes of a weight, a product of huge and tiny factors, a
-    // score of -infinity): the query again with float32 products, from the projected tensors, its own maximum in every tile.  The queries' results
-    // are their own; a query that holds a NaN is left as it is.
+    // score of -infinity), and those that may owe something to a weight of which the exponential's instruction makes zero (below 2^-126) or whose last
+    // plane loses bits (below 2^-109): the query again with float32 products and the library's exponential, from the projected tensors, its own
+    // maximum in every tile.  The queries' results are their own; a query that holds a NaN is left as it is.
     float zero = sum * 0.f;             // (stays so while everything is finite)
 #pragma unroll
     for (int n = 0; n < NE; ++n)
 #pragma unroll
         for (int v = 0; v < 16; ++v) zero = fmaf(acc[n][v], 0.f, zero);
-    const uint64_t b = __ballot(zero != 0.f);
+    bool odd = zero != 0.f;
+    if (__builtin_expect(__ballot(smin < m - 100.f) != 0, 0)) odd = odd || small_weights_count<T, VEC, DG>(a, base, mask_row, acc, sum);
+    const uint64_t b = __ballot(odd);
     if (__builtin_expect(b != 0, 0)) {
         bool nan = false;
         const int ln = fresh_lane(), qn = q0 + (ln & 31) < a.L ? q0 + (ln & 31) : a.L - 1;

@@ -274,3 +274,34 @@ def test_bottom_of_the_float32_range(where, mode, n_a, n_b, c, heads, d, chunk):
     rl = rel_l2(got.cpu().numpy().astype(np.float64), O.gated_attention(mode, xf, zf, mf, wf, heads, case.spec.ln_eps))
     print(f"{case.spec.name} {where}: rel_l2={rl:.3e}", flush=True)
     assert rl <= 5e-7
+
+
+@pytest.mark.parametrize("exponent", [-90, -112, -120, -127, -131])
+@pytest.mark.parametrize("n_a,n_b,c,heads,d", [(3, 45, 64, 2, 8), (40, 200, 96, 3, 32), (2, 70, 36, 1, 128)])
+def test_small_softmax_weights(n_a, n_b, c, heads, d, exponent):
+    """One key with a weight of 2^exponent of the others' and a value so large that both count alike in the context: weights below the normal range
+    of float32, and ones whose lower planes are below that of bfloat16.  (The score's own rounding is |exponent| 2^-24, a weight of 2^-131 has 18 bits.)"""
+    case = I.make_case(small_spec(ROW, n_a, n_b, c, heads, d, c_z=16, dtype="f32", mask="none"))
+    half, w = c // 2, case.weights
+    rng = np.random.default_rng(1)
+    x = np.zeros_like(case.x)
+    x[:, :, 2:half] = rng.integers(1, 9, (n_a, n_b, half - 2)) / 8
+    x[:, :, half:] = -x[:, :, :half]                # means are exactly zero
+    x[:, 1] = 0
+    x[:, 1, 0], x[:, 1, half] = 1, -1               # the only token with channel 0
+    case.x = x
+    w["ln_g"][:], w["ln_b"][:] = 1, 0
+    w["ln_b"][1] = 8                                # channel 1 is 8 in every token
+    w["b_o"][:] = w["w_b"][:] = w["w_q"][:] = w["w_k"][:] = 0
+    w["w_q"][::d, 1] = 1
+    w["w_k"][::d, 0] = exponent * np.log(2.0) * np.sqrt(d) / 8 / np.sqrt(half)
+    w["w_v"][:, :2] = 0
+    w["w_v"] *= np.float32(2.0 ** -34)
+    w["w_v"][:, 0] = 2.0 ** (-34 - exponent)
+    w["w_o"] *= np.float32(2.0 ** 34)
+    desc, dw, dx, z, m = P.to_device(case, "cuda:0")
+    got = P.ff_gated_attention(desc, dw, dx, z, m).cpu().numpy().astype(np.float64)
+    xf, zf, mf, wf = f64_inputs(case)
+    rl = rel_l2(got, O.gated_attention(ROW, xf, zf, mf, wf, heads, case.spec.ln_eps))
+    print(f"weight 2^{exponent}: rel_l2={rl:.3e}", flush=True)
+    assert rl <= 2e-5
