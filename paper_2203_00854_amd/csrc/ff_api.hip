@@ -170,7 +170,6 @@ static ff_status run(const ff_attn_desc* desc, const ff_attn_weights* w, const v
     if (fast) {
         st = mfma_prepare(p, *w, x, z, ws, stream);
     } else {
-        Timed t(KK_GENERIC, stream);
         st = generic_prepare(p, *w, x, z, ws, stream);
     }
     if (st != FF_OK) return st;

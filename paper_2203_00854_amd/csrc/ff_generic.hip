@@ -1225,6 +1225,8 @@ size_t generic_workspace(const Problem& p, int chunk, Workspace* ws, void* base)
 
 // before the chunks: the pair bias and, in the same launch, the token statistics of the first chunk
 ff_status generic_prepare(const Problem& p, const ff_attn_weights& w, const void* x, const void* z, const Workspace& ws, hipStream_t stream) {
+    if (gen::one_launch(p, ws)) return FF_OK;
+    Timed t(KK_GENERIC, stream);
     const int rows = ws.chunk < p.R ? ws.chunk : p.R;
     return p.dtype == FF_F32 ? gen::rows_t<float>(p, w, x, z, ws, 0, rows, p.has_bias, stream)
                              : gen::rows_t<bf16_t>(p, w, x, z, ws, 0, rows, p.has_bias, stream);

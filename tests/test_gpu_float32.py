@@ -305,3 +305,26 @@ def test_small_softmax_weights(n_a, n_b, c, heads, d, exponent):
     rl = rel_l2(got, O.gated_attention(ROW, xf, zf, mf, wf, heads, case.spec.ln_eps))
     print(f"weight 2^{exponent}: rel_l2={rl:.3e}", flush=True)
     assert rl <= 2e-5
+
+
+def intervals(desc, w, x, z, m, chunk=0):
+    """How often the launch timer saw the family in one call."""
+    P.ff_profile_enable(True)
+    if chunk:
+        P.ff_attention_chunked(desc, w, x, z, m, chunk_rows=chunk)
+    else:
+        P.ff_gated_attention(desc, w, x, z, m)
+    torch.cuda.synchronize()
+    n = P.ff_profile_collect()["generic family"][1]
+    P.ff_profile_enable(False)
+    return n
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("mode,n_a,n_b,c,heads,d,chunk,n", [(ROW, 8, 32, 36, 4, 8, 0, 1), (ROW, 8, 32, 36, 4, 8, 3, 3), (COL, 20, 9, 40, 1, 24, 4, 3),
+                                                            (TS, 300, 300, 96, 3, 40, 0, 2), (ROW, 3, 573, 36, 2, 12, 2, 3)])
+def test_launch_timer_counts_what_was_launched(dtype, mode, n_a, n_b, c, heads, d, chunk, n):
+    """An interval per chunk, and one ahead of them only where something is launched there: small calls form the token statistics and the pair
+    bias in the projections' launch."""
+    case = I.make_case(small_spec(mode, n_a, n_b, c, heads, d, c_z=16, dtype=dtype))
+    assert intervals(*P.to_device(case, "cuda:0"), chunk=chunk) == n
