@@ -104,6 +104,13 @@ __device__ __forceinline__ void store4(T* row, int k, int n, const float4& v) {
 // instruction (float32_tile, float32_queries).
 constexpr float kUp = 0x1p24f, kDown = 0x1p-24f;
 __device__ __forceinline__ float4 times4(const float4& v, float f) { return make_float4(v.x * f, v.y * f, v.z * f, v.w * f); }
+// The same of a piece whose loads are under conditions (VEC false): opaque, or the compiler moves the product to the load, where it waits for it (rows of no
+// whole pieces took 16 % longer)
+template <bool VEC>
+__device__ __forceinline__ float4 times4_piece(float4 v, float f) {
+    if constexpr (!VEC) asm("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+    return times4(v, f);
+}
 template <int NP>
 struct Planes {
     uint2 p[NP];       // four elements in each
@@ -467,13 +474,13 @@ __device__ __forceinline__ void gemm_block(const GenericGemmArgs& g, int bx, int
         float4 gv, bv;
         if constexpr (PROJ) {
             gv = c.gm.value(k, g.K);
-            bv = times4(c.bt.value(k, g.K), kUp);
+            bv = times4_piece<VEC != 0>(c.bt.value(k, g.K), kUp);
         }
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int row = prow + 32 * i;
             float4 v = c.a[i].value(k, g.K);
-            if constexpr (!PROJ && NA == 3) v = times4(v, kUp);
+            if constexpr (!PROJ && NA == 3) v = times4_piece<VEC != 0>(v, kUp);
             if constexpr (PROJ)       // (beyond K gamma and beta are zero, and so is the result)
                 v = make_float4((v.x - mean[i]) * rstd[i] * gv.x + bv.x, (v.y - mean[i]) * rstd[i] * gv.y + bv.y,
                                 (v.z - mean[i]) * rstd[i] * gv.z + bv.z, (v.w - mean[i]) * rstd[i] * gv.w + bv.w);
@@ -485,7 +492,7 @@ __device__ __forceinline__ void gemm_block(const GenericGemmArgs& g, int bx, int
         for (int i = 0; i < (BP ? 0 : 2 * WN); ++i) {
             const int row = prow + 32 * i;
             const float4 v = c.b[i].value(k, g.K);
-            const Planes<NB> sp = split4<NB>(NB == 3 ? times4(v, kUp) : v);
+            const Planes<NB> sp = split4<NB>(NB == 3 ? times4_piece<VEC != 0>(v, kUp) : v);
 #pragma unroll
             for (int j = 0; j < NB; ++j) *reinterpret_cast<uint2*>(&Bs[buf][j][row * 64 + piece_place(row, pc)]) = sp.p[j];
         }
@@ -873,8 +880,9 @@ __global__ __launch_bounds__(512, DG <= 4 ? (sizeof(T) == 2 && (VEC || DG < 4) ?
             for (int u = 0; u < U; ++u) {
                 const int id = b0 + u * nthreads + tid, k = id / PR, k4 = 4 * (id / DP), e = id % DP;
                 if (id >= nkp * PR) break;
-                const float4 kv = keep4(k < nk, kp[u].value(4 * (id % PR), a.d));
-                const Planes<NP> ks = split4<NP>(NP == 3 ? times4(kv, kUp) : kv);
+                float4 kv = kp[u].value(4 * (id % PR), a.d);
+                if constexpr (NP == 3) kv = times4_piece<VEC>(kv, kUp);
+                const Planes<NP> ks = split4<NP>(keep4(k < nk, kv));
                 const float4 m4 = *reinterpret_cast<const float4*>(s_m + k4);
                 // (what a masked token holds may be anything, and 0 x NaN is NaN)
                 const bool in = e < a.d;
