@@ -1071,10 +1071,21 @@ static unsigned char* weight_planes(const Problem& p, const ff_attn_weights& w, 
 // blocks per compute unit and the pairs at most forty (their blocks hold the projections' LDS and registers).  The rows' launch and its latency are a fifth of a small call: 8 x 32
 // row attention of 32 channels 18.0 -> 15.6 us, 46 x 46 triangle attention of 256 channels 40.7 -> 35.4 (40.3 with a limit of one block), 8 x 200 row attention 52.7 -> 46.8 (with at most four blocks of pairs 52.6),
 // 4 x 256 of 32 channels 31.9 -> 29.9, 30 x 100 43.2 -> 40.6.  With eight blocks 53 x 100 60.8 -> 64, with sixteen 64 x 155 90 -> 107: every block of 64 features reads all of its tokens twice.
+// Rows of more than 256 channels do not stay in registers, so a block reads its tokens twice more for their statistics: 114 x 56 column attention of 1600 channels 124
+// us instead of 102, 64 x 155 row attention of 512 channels 105 instead of 84.  There the pair bias decides, a serial pass over H + 2 rows per pair, in triangle
+// attention: with two heads or more and few blocks of few tokens it hides behind the projections (31 x 31 of 1511 channels, 15 heads, 398 us instead of 490, 78 x 78 of
+// 320 channels, 4 heads, 49 instead of 56, 100 x 100 of 640 channels, 4 heads of 8, 80 instead of 90; 115 x 115 of it, above the line of tokens times blocks, 113
+// instead of 102, and 128 x 128 of 1152 channels, 2 heads of 16, 156 instead of 130; 23 x 23 of 1408 channels, 2 heads, 64 instead of 70, 100 x 100 of 1600 channels,
+// one head of 32, 163 instead of 142).  With bfloat16 storage, half the bytes, every call with a bias (4 x 20 of 512 channels 29 us instead of 32), but rows of no
+// whole pieces only in triangle attention of up to three blocks per compute unit (60 x 60 of 515 channels, 4 heads, 123 instead of 163; 70 x 70 of 1531 channels, 12
+// heads, 1182 instead of 1023).
 static bool one_launch(const Problem& p, const Workspace& ws) {
-    const int64_t tokens = (int64_t)ws.chunk * p.L;
-    return (tokens + 63) / 64 * ((4 * p.Hd + 63) / 64) <= 4 * compute_units() &&
-           (!p.has_bias || (int64_t)p.L * p.L <= 40 * 32 * compute_units());
+    const int64_t cu = compute_units(), tokens = (int64_t)ws.chunk * p.L, features = (4 * p.Hd + 63) / 64, blocks = (tokens + 63) / 64 * features;
+    if (blocks > 4 * cu || (p.has_bias && (int64_t)p.L * p.L > 40 * 32 * cu)) return false;
+    if (p.c <= 256) return true;
+    const bool triangle = p.mode == FF_TRI_START || p.mode == FF_TRI_END;
+    if (p.dtype == FF_BF16) return p.has_bias && (p.c % 4 == 0 || (triangle && blocks <= 3 * cu));
+    return triangle && p.H >= 2 && 2 * blocks <= (p.H > 2 ? 5 : 2) * cu && tokens * blocks <= 64 * cu * cu;
 }
 
 // the pair bias in `a`; returns whether its loads are whole pieces

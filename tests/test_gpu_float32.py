@@ -328,3 +328,24 @@ def test_launch_timer_counts_what_was_launched(dtype, mode, n_a, n_b, c, heads, 
     bias in the projections' launch."""
     case = I.make_case(small_spec(mode, n_a, n_b, c, heads, d, c_z=16, dtype=dtype))
     assert intervals(*P.to_device(case, "cuda:0"), chunk=chunk) == n
+
+
+@pytest.mark.parametrize("dtype,mode,n_a,n_b,c,heads,d,n", [
+    ("f32", COL, 40, 9, 256, 2, 8, 1), ("f32", COL, 40, 9, 260, 2, 8, 2), ("bf16", COL, 40, 9, 260, 2, 8, 2), ("f32", ROW, 7, 40, 260, 2, 8, 2),
+    ("bf16", ROW, 7, 40, 260, 2, 8, 1), ("bf16", ROW, 7, 40, 261, 2, 8, 2), ("bf16", TS, 20, 20, 261, 2, 8, 1), ("f32", TE, 30, 30, 260, 3, 8, 1),
+    ("f32", TS, 90, 90, 261, 4, 8, 1), ("f32", TS, 90, 90, 260, 4, 24, 2), ("f32", TS, 41, 41, 260, 9, 40, 1),
+    ("f32", TS, 48, 48, 260, 9, 40, 2), ("f32", TE, 30, 30, 260, 2, 8, 1), ("f32", TE, 38, 38, 260, 2, 96, 2),
+    ("f32", TE, 30, 30, 260, 1, 8, 2), ("f32", TE, 104, 104, 260, 4, 8, 1), ("f32", TE, 109, 109, 260, 4, 8, 2), ("bf16", TS, 66, 66, 261, 8, 20, 1),
+    ("bf16", TS, 70, 70, 261, 8, 20, 2)])
+def test_long_rows_have_a_launch_for_their_statistics(dtype, mode, n_a, n_b, c, heads, d, n):
+    """Rows of more than 256 channels, which every block of 64 features would read two more times: a launch of their own, but where the pair
+    bias is worth hiding behind the projections.  Both ways against float64."""
+    case = I.make_case(small_spec(mode, n_a, n_b, c, heads, d, c_z=16, dtype=dtype))
+    desc, w, x, z, m = P.to_device(case, "cuda:0")
+    if P.ff_attention_path(desc) != "generic":
+        x = torch.cat([x.new_zeros(4), x.flatten()])[4:].view_as(x)
+    assert intervals(desc, w, x, z, m) == n
+    got = P.ff_gated_attention(desc, w, x, z, m).float().cpu().numpy().astype(np.float64)
+    xf, zf, mf, wf = f64_inputs(case)
+    rl = rel_l2(got, O.gated_attention(mode, xf, zf, mf, wf, heads, case.spec.ln_eps))
+    assert rl <= (5e-7 if dtype == "f32" else 1e-2)
