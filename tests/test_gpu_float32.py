@@ -94,24 +94,82 @@ def test_rounding_of_the_float32_sums(mode, n_a, n_b, c, c_z, heads, d, limit):
     assert rl <= limit
 
 
-@pytest.mark.parametrize("mode,n_a,n_b,c,heads,d,chunk", [
-    (ROW, 12, 33, 64, 2, 32, 0), (ROW, 11, 33, 64, 2, 32, 0),        # 64 channels: weights split ahead from 384 tokens on (396 and 363 here)
-    (ROW, 24, 45, 32, 3, 16, 5), (COL, 37, 40, 96, 1, 40, 13), (TS, 200, 200, 160, 2, 64, 0), (TE, 90, 90, 32, 5, 8, 90), (ROW, 640, 129, 32, 4, 8, 0),
-    (ROW, 3, 572, 30, 2, 8, 2), (ROW, 3, 573, 32, 2, 12, 2), (ROW, 50, 70, 300, 1, 8, 0)])      # 572: the longest whose pair bias rides in the projections' launch
-def test_weights_split_ahead_and_chunks(mode, n_a, n_b, c, heads, d, chunk):
-    """The projection weights are split once per chunk where the chunk has tokens enough, else by every block: both sides of that line,
-    feature counts around the 64 and 128 of a block, and the unchunked call bit for bit with a chunked one that splits per block and forms
-    the token statistics there."""
+@pytest.mark.parametrize("mode,n_a,n_b,c,c_z,heads,d,limit", [
+    (ROW, 8, 32, 32, 16, 4, 8, 1.81e-7), (ROW, 16, 200, 64, 32, 4, 16, 1.91e-7), (ROW, 40, 155, 256, 128, 8, 32, 2.53e-7), (TE, 96, 96, 256, 0, 8, 32, 2.60e-7),
+    (TS, 120, 120, 32, 0, 4, 8, 1.90e-7), (COL, 70, 20, 128, 0, 4, 32, 1.90e-7), (ROW, 4, 601, 64, 32, 4, 16, 1.76e-7), (TS, 60, 60, 36, 0, 3, 20, 2.16e-7),
+    (COL, 150, 9, 300, 0, 2, 64, 2.02e-7), (ROW, 6, 90, 30, 16, 2, 128, 2.13e-7), (TE, 40, 40, 512, 0, 8, 32, 3.15e-7), (ROW, 2, 1030, 32, 16, 4, 8, 1.75e-7),
+    (COL, 33, 300, 261, 0, 3, 40, 2.39e-7), (ROW, 100, 130, 128, 64, 8, 16, 2.30e-7)])
+def test_rounding_of_the_split_sums(mode, n_a, n_b, c, c_z, heads, d, limit):
+    """Relative error against float64 of the sums of bfloat16 planes.  limit: 1.08 times the measured one, for another order of the sums; the float32
+    matrix instruction in two sums per output has 2.15, 2.33, 3.82, 3.90, 2.22, 3.02, 2.15, 2.61, 3.39, 3.34, 5.06, 1.89, 3.91 and 3.16e-7 on these
+    inputs, so that a loss of any of the six products of planes or a return to that instruction's error shows."""
+    spec = small_spec(mode, n_a, n_b, c, heads, d, c_z=c_z, dtype="f32")
+    case = I.make_case(spec)
+    desc, w, x, z, m = P.to_device(case, "cuda:0")
+    got = P.ff_gated_attention(desc, w, x, z, m).cpu().numpy().astype(np.float64)
+    assert P.ff_attention_last_path() == "generic"
+    xf, zf, mf, wf = f64_inputs(case)
+    rl = rel_l2(got, O.gated_attention(mode, xf, zf, mf, wf, heads, spec.ln_eps))
+    print(f"{spec.name}: rel_l2={rl:.3e}", flush=True)
+    assert rl <= limit
+
+
+def intervals(desc, w, x, z, m, chunk=0):
+    """How often the launch timer saw the family in one call."""
+    P.ff_profile_enable(True)
+    if chunk:
+        P.ff_attention_chunked(desc, w, x, z, m, chunk_rows=chunk)
+    else:
+        P.ff_gated_attention(desc, w, x, z, m)
+    torch.cuda.synchronize()
+    n = P.ff_profile_collect()["generic family"][1]
+    P.ff_profile_enable(False)
+    return n
+
+
+# The form of the projections: statistics and weights in the blocks themselves (one), weights split ahead (planes) or per block (blocks)
+ONE, PLANES, BLOCKS = "one", "planes", "blocks"
+
+
+def projections(mode, n_a, n_b, c, heads, d, chunk):
+    """The form that an unchunked call (chunk = 0) or chunks of so many batch rows take, of aligned float32 tensors and 256 compute units."""
+    rows, length = (n_a, n_b) if mode in (ROW, TS) else (n_b, n_a)
+    tokens, feat = min(chunk or rows, rows) * length, 4 * heads * d
+    blocks, tri = -(-tokens // 64) * -(-feat // 64), mode in (TS, TE)
+    if blocks <= 1024 and (mode == COL or length ** 2 <= 40 * 32 * 256):
+        if c <= 256 or (tri and heads >= 2 and 2 * blocks <= (5 if heads > 2 else 2) * 256 and tokens * blocks <= 64 * 256 ** 2):
+            return ONE
+    return PLANES if c % 32 == 0 and 6 * (-(-feat // 128) * 128) * c <= tokens * heads * d * 4 else BLOCKS
+
+
+@pytest.mark.parametrize("mode,n_a,n_b,c,heads,d,chunk,forms", [      # forms: unchunked, chunks of `chunk`, chunks of one row
+    (ROW, 12, 33, 64, 2, 32, 0, (ONE, ONE, ONE)), (ROW, 11, 33, 64, 2, 32, 0, (ONE, ONE, ONE)),
+    (ROW, 24, 45, 32, 3, 16, 5, (ONE, ONE, ONE)), (COL, 37, 40, 96, 1, 40, 13, (ONE, ONE, ONE)),
+    (TS, 200, 200, 160, 2, 64, 0, (PLANES, PLANES, ONE)), (TE, 90, 90, 32, 5, 8, 90, (ONE, ONE, ONE)), (ROW, 640, 129, 32, 4, 8, 0, (PLANES, PLANES, ONE)),
+    (ROW, 3, 572, 30, 2, 8, 2, (ONE, ONE, ONE)), (ROW, 3, 573, 32, 2, 12, 2, (PLANES, PLANES, PLANES)), (ROW, 50, 70, 300, 1, 8, 0, (BLOCKS, BLOCKS, BLOCKS)),
+    (ROW, 3, 600, 128, 4, 32, 2, (PLANES, PLANES, BLOCKS)),              # 128 channels: 768 tokens hold the planes
+    (COL, 10, 84, 288, 2, 16, 2, (BLOCKS, BLOCKS, BLOCKS)), (COL, 10, 200, 288, 2, 16, 173, (PLANES, PLANES, BLOCKS)),      # 1728 tokens
+    (COL, 60, 100, 1024, 16, 32, 11, (BLOCKS, BLOCKS, BLOCKS)),          # blocks of 128 features, weights split by each
+    (ROW, 640, 129, 36, 4, 8, 64, (BLOCKS, ONE, ONE)), (ROW, 640, 129, 33, 4, 8, 64, (BLOCKS, ONE, ONE)),                   # rows of whole pieces, and not
+    (COL, 33, 30, 260, 3, 8, 4, (BLOCKS, BLOCKS, BLOCKS)), (COL, 33, 30, 261, 3, 8, 4, (BLOCKS, BLOCKS, BLOCKS)), (TS, 104, 104, 288, 4, 8, 40, (ONE, ONE, ONE))])
+def test_weights_split_ahead_and_chunks(mode, n_a, n_b, c, heads, d, chunk, forms):
+    """Statistics in the projections' launch or ahead of it, weights split once per chunk where the chunk has tokens enough or else by every block, blocks
+    of 64 and 128 features: every form against float64, and all of them bit for bit the same."""
+    assert forms == tuple(projections(mode, n_a, n_b, c, heads, d, k) for k in (0, chunk, 1))
     case = I.make_case(small_spec(mode, n_a, n_b, c, heads, d, c_z=16, dtype="f32", mask="none"))
     desc, w, x, z, m = P.to_device(case, "cuda:0")
     got = P.ff_gated_attention(desc, w, x, z, m)
     assert P.ff_attention_last_path() == "generic"
+    assert (intervals(desc, w, x, z, m) == 1) == (forms[0] == ONE)
     for rows in {1, chunk} - {0}:
         assert torch.equal(P.ff_attention_chunked(desc, w, x, z, m, chunk_rows=rows), got)
+    # an address that is no multiple of sixteen takes the form of rows of no whole pieces, which splits per block
+    odd = torch.cat([x.new_zeros(1), x.flatten()])[1:].view_as(x)
+    assert torch.equal(P.ff_gated_attention(desc, w, odd, z, m), got)
     if n_a * n_b <= 20000:
         xf, zf, mf, wf = f64_inputs(case)
         ref = O.gated_attention(mode, xf, zf, mf, wf, heads, case.spec.ln_eps)
-        assert rel_l2(got.cpu().numpy().astype(np.float64), ref) <= 5e-7      # (above the largest limit of the sums' rounding, see below)
+        assert rel_l2(got.cpu().numpy().astype(np.float64), ref) <= 5e-7      # (above the largest limit of the sums' rounding)
 
 
 def test_large_and_small_magnitudes():
@@ -305,19 +363,6 @@ def test_small_softmax_weights(n_a, n_b, c, heads, d, exponent):
     rl = rel_l2(got, O.gated_attention(ROW, xf, zf, mf, wf, heads, case.spec.ln_eps))
     print(f"weight 2^{exponent}: rel_l2={rl:.3e}", flush=True)
     assert rl <= 2e-5
-
-
-def intervals(desc, w, x, z, m, chunk=0):
-    """How often the launch timer saw the family in one call."""
-    P.ff_profile_enable(True)
-    if chunk:
-        P.ff_attention_chunked(desc, w, x, z, m, chunk_rows=chunk)
-    else:
-        P.ff_gated_attention(desc, w, x, z, m)
-    torch.cuda.synchronize()
-    n = P.ff_profile_collect()["generic family"][1]
-    P.ff_profile_enable(False)
-    return n
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
