@@ -316,8 +316,8 @@ struct GenericGemmArgs {
 
 // A tile of 32 tokens x 32 features (lane = feature f0 + lane % 32) whose split sums are not all finite: those elements again, their products formed by the
 // float32 instruction (a lane reads four consecutive elements k0 + 4 half .. + 3 of its row of either operand and feeds four instructions
-// with them), two sums per output as everywhere.  The finite ones stay, so that an element's bits do not depend on its neighbours'.  Rows that hold a NaN, or
-// LayerNorm rows with anything that is not finite, are NaN by right: what masked tokens hold does not come here.
+// with them), two sums per output as everywhere.  The finite ones stay, so that an element's bits do not depend on its neighbours'.  Rows whose statistics are
+// NaN, and those of the context that begin with a NaN, are NaN by right: what masked tokens hold (their own queries' contexts are NaN throughout) is not worked on.
 template <typename T, bool PROJ, bool V>
 __device__ __forceinline__ void float32_tile(const GenericGemmArgs& g, int tw, int f0, const float2* own_stats, f32x16& acc) {
     const int lane = threadIdx.x & 63, col = lane & 31, hf = lane >> 5;
@@ -329,14 +329,10 @@ __device__ __forceinline__ void float32_tile(const GenericGemmArgs& g, int tw, i
     } else {
         row = (const T*)g.a + (size_t)t * g.K;
     }
-    bool dead = false;
-    for (int k = 4 * hf; k < g.K; k += 8) {
-        const float4 v = load4<T, V>(row, k, g.K);
-        if constexpr (PROJ) dead = dead || !(fabsf(v.x) < INFINITY && fabsf(v.y) < INFINITY && fabsf(v.z) < INFINITY && fabsf(v.w) < INFINITY);
-        else dead = dead || v.x != v.x || v.y != v.y || v.z != v.z || v.w != v.w;
-    }
-    const uint64_t b = __ballot(dead);
-    const uint32_t skip = (uint32_t)b | (uint32_t)(b >> 32);
+    float2 st = make_float2(0.f, 0.f);
+    if constexpr (PROJ) st = own_stats ? own_stats[t - tw] : *reinterpret_cast<const float2*>(g.stats + 2 * (size_t)t);
+    const float first = PROJ ? st.y : to_f32<T>(row[0]);
+    const uint32_t skip = (uint32_t)__ballot(first != first);            // (the two half-waves hold the same tokens)
     uint32_t redo = 0;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
@@ -347,12 +343,10 @@ __device__ __forceinline__ void float32_tile(const GenericGemmArgs& g, int tw, i
     if (f0 + col >= g.N) redo = 0;
     if (!__ballot(redo != 0)) return;
     const T* wrow;
-    float2 st = make_float2(0.f, 0.f);
     if constexpr (PROJ) {
         const int seg = f / g.Hd;
         const void* w = seg == 0 ? g.w[0] : (seg == 1 ? g.w[1] : (seg == 2 ? g.w[2] : g.w[3]));
         wrow = (const T*)w + (size_t)(f - seg * g.Hd) * g.K;
-        st = own_stats ? own_stats[t - tw] : *reinterpret_cast<const float2*>(g.stats + 2 * (size_t)t);
     } else {
         wrow = (const T*)g.w[0] + (size_t)f * g.K;
     }
@@ -1012,7 +1006,8 @@ __global__ __launch_bounds__(512, DG <= 4 ? (sizeof(T) == 2 && (VEC || DG < 4) ?
     // Contexts that are not finite, as in the projections (an infinite value against the lower planes of a weight, a product of huge and tiny factors, a
     // score of -infinity), and those that may owe something to a weight of which the exponential's instruction makes zero (below 2^-126) or whose last
     // plane loses bits (below 2^-109): the query again with float32 products and the library's exponential, from the projected tensors, its own
-    // maximum in every tile.  The queries' results are their own; a query that holds a NaN is left as it is.
+    // maximum in every tile.  The queries' results are their own; one that begins with a NaN, as all of a
+    // token with anything that is not finite do, is left as it is.
     float zero = sum * 0.f;             // (stays so while everything is finite)
 #pragma unroll
     for (int n = 0; n < NE; ++n)
@@ -1022,14 +1017,9 @@ __global__ __launch_bounds__(512, DG <= 4 ? (sizeof(T) == 2 && (VEC || DG < 4) ?
     if (__builtin_expect(__ballot(smin < m - 100.f) != 0, 0)) odd = odd || small_weights_count<T, VEC, DG>(a, base, mask_row, acc, sum);
     const uint64_t b = __ballot(odd);
     if (__builtin_expect(b != 0, 0)) {
-        bool nan = false;
         const int ln = fresh_lane(), qn = q0 + (ln & 31) < a.L ? q0 + (ln & 31) : a.L - 1;
-        for (int e = 4 * (ln >> 5); e < a.d; e += 8) {
-            const float4 v = load4<T, VEC>(base + (size_t)qn * N4, e, a.d);
-            nan = nan || v.x != v.x || v.y != v.y || v.z != v.z || v.w != v.w;
-        }
-        const uint64_t nb = __ballot(nan);
-        const uint32_t again = ((uint32_t)b | (uint32_t)(b >> 32)) & ~((uint32_t)nb | (uint32_t)(nb >> 32));
+        const float first = to_f32<T>(base[(size_t)qn * N4]);
+        const uint32_t again = ((uint32_t)b | (uint32_t)(b >> 32)) & ~(uint32_t)__ballot(first != first);
         if (again) float32_queries<T, VEC, DG>(a, base, a.bias ? a.bias + (size_t)h * a.L * a.Lb : nullptr, mask_row, q0, (again >> (ln & 31)) & 1, acc, sum);
     }
     if (qi >= a.L) return;
