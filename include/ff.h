@@ -28,7 +28,13 @@
  *     output when an argument is rejected.  ff_last_error() gives a message (thread-local).
  *   - Arithmetic: LayerNorm statistics, softmax maxima and sums and all accumulations are
  *     float32.  In FF_BF16 the projected q/k/v/gate, the softmax weights and the gated
- *     context are rounded to bfloat16 as matrix-core operands; FF_F32 uses no bfloat16.
+ *     context are rounded to bfloat16 as matrix-core operands.  In FF_F32 nothing is rounded to
+ *     fewer bits than float32: a factor of a contraction is taken as the exact sum of three
+ *     bfloat16 values, and of the nine products of two such sums the six largest are added up
+ *     (what is left out is at most 2^-24 of the product, like one float32 rounding; results are
+ *     closer to float64 than those of float32 multiply-adds on every shape measured).  Results
+ *     that are not finite so - infinite factors, factors from 2^104 on - are formed again by
+ *     float32 products and are what those give.
  */
 #ifndef FF_H
 #define FF_H

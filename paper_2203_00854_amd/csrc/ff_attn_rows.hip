@@ -19,7 +19,7 @@
 //    ordinary 333 call then takes 4 % more).
 //  - the denominator is summed from the rounded weights by two 16 x 16 x 32 matrix instructions (add_piece): eight v_dot2 per tile do not overlap
 //    with matrix instructions (bare loops of the tile's mix, two wavefronts per SIMD: 123 ns with dots, 104 with four 4 x 4 x 4
-//    matrix instructions, 93 without any denominator); with those four instead of the two 2048 x 2048 in chunks takes 8040 us, 7968 so.
+//    matrix instructions, 93 without any denominator); with those four instead of the two 2048 x 2048 in chunks takes 8291 us, 8200 so.
 //    Below head dim 32 the context's matrix instructions have rows to spare: a row of ones in v^T sums the denominator.
 //  - masked keys cost one more matrix instruction, in steps that hold any; steps before the first masked key skip the test.
 //  - matrix instructions of the next and the previous tile alternate with the exponentials of this one.
@@ -367,8 +367,8 @@ __global__ __launch_bounds__(NW * 64, attn_rows_waves(D, NW, HAS_BIAS)) void k_a
 
     // ---- normalise, gate, store.  Lane = query, register v = element 8*(v/4) + 4*hf + v%4
     // (the lane's indices anew: those from the beginning of the kernel would be held in registers through the steps, of which there are none left: without
-    // this three to five went to scratch memory, and a kernel that uses it starts later.  1024 x 384 columns at d = 8 411 us the call instead of 407, 2000 x 300 1055
-    // instead of 1048, 60 x 300 row attention 59.7 instead of 57.8)
+    // this three to five went to scratch memory, and a kernel that uses it starts later.  1024 x 384 columns at d = 8 430 us the call instead of 426, 60 x 300
+    // row attention 61.3 instead of 59.9)
     const int ln = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), ecol = ln & 31, ehf = ln >> 5;
     const uint32_t eq_lane = (uint32_t)(ecol * D + (D > 8 ? 8 * ehf : 0)) * 2;
     const int qi = 32 * qt + ecol;

@@ -74,11 +74,6 @@ __device__ __forceinline__ float wave_sum(float v) {
     const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return half_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
 
 // ---- the problem as the kernels see it ------------------------------------------------
 // Every mode is "R independent batch rows, each a sequence of L tokens".  Token (r, l)

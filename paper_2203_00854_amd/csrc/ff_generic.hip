@@ -1,5 +1,5 @@
-// Generic kernel family: every step of the gated attention in float32, for any shape and for both storage types.  It
-// is the float32 path (no bfloat16 anywhere when T = float) and the fallback for bfloat16 shapes the bfloat16
+// Generic kernel family: every step of the gated attention with float32 accuracy, for any shape and for both storage types.  It
+// is the float32 path (nothing is held in fewer bits when T = float) and the fallback for bfloat16 shapes the bfloat16
 // matrix-core family does not take.  Steps follow FastFold Section 2.1 (projections, scaled dot product, softmax,
 // product with V, output linear), Section 2.3 (axes, pair bias) and Section 5.2 (softmax with the mask and bias
 // addends fused in; gate = bias + sigmoid + product).
@@ -8,9 +8,10 @@
 // (see split4), a bfloat16 one as it is.  Operand layouts (wave64): A (32 x 16): lane l holds row l%32, columns 8*(l/32) .. + 7; B (16 x 32): lane l
 // holds column l%32, rows 8*(l/32) .. + 7; C/D (32 x 32): lane l holds column l%32, register v holds row 8*(v/4) + 4*(l/32) + v%4.
 // Measured (row attention, 64 x 155 tokens of 256 channels, 8 heads of 32, 8.1 GFLOP): 1.40 ms with vector
-// multiply-adds, a wavefront per query and per pair, 0.116 ms on v_mfma_f32_32x32x2_f32 (whose matrix cores alone need 53 us), 0.081 ms so (projections
-// 36 us, attention 21, output projection 14, rows 9); relative error against float64 4.0e-7 -> 2.4e-7.  128 x 150 tokens 227 -> 151 us, 256 x 256 tokens of
-// 256 channels 658 -> 491, of 32 channels 117 -> 87.
+// multiply-adds, a wavefront per query and per pair, 0.116 ms on v_mfma_f32_32x32x2_f32 (whose matrix cores alone need 53 us), 0.090 ms so (kernels under the
+// profiler: projections 42 to 47 us, attention 25 to 28, output projection 17 to 19, rows 9 to 10); relative error against float64 3.9e-7 -> 2.3e-7, and below the float32
+// instruction's, 0.55 to 0.9 of it, in each of 670 other shapes of 4 to 3000 channels and head dims 4 to 128.  Where the planes do not reach, the float32 instruction takes over
+// (float32_tile, float32_queries).
 //
 // Workspace layout of this family, per chunk of `rows` batch rows, token t = rl*L + l:
 //   stats [tokens][2]   float32 mean, 1/std of LayerNorm
@@ -95,12 +96,12 @@ __device__ __forceinline__ void store4(T* row, int k, int n, const float4& v) {
 
 // ---------------------------------------------------------------------------------------
 // Float32 contractions on the bfloat16 matrix instruction.  A float32 value is the exact sum of three bfloat16 values (8 + 8 + 8 significant bits,
-// each the rounding of what the ones before it left): x = x0 + x1 + x2, |x1| <= 2^-9 |x|, |x2| <= 2^-18 |x|.  Of the nine products of two such
-// sums the six with i + j <= 2 are formed; what is left out is below 2^-25 of the product, a quarter of a float32 rounding of
-// it.  x0 y0 and the five corrections have sums of their own, so a chain rounds once per 16 terms of the contraction (v_mfma_f32_32x32x2_f32: once per two).
+// each the rounding of what the ones before it left): x = x0 + x1 + x2, |x1| <= 2^-8 |x|, |x2| <= 2^-17 |x|.  Of the nine products of two such
+// sums the six with i + j <= 2 are formed; what is left out is at most 2^-24 (1 + 2^-10) of the product, as much as one float32 rounding of it (x = y = 0x1.00ff8p0: 2^-24.0),
+// and 2^-27.4 in the root mean square of normal values, of either sign.  x0 y0 and the five corrections have sums of their own, so a chain rounds once per 16 terms of the contraction (v_mfma_f32_32x32x2_f32: once per two).
 // Six instructions of 32 cycles for 16 terms against eight of 64.  A bfloat16 operand is one plane and needs no others.
 // The operands are taken times 2^24, exactly, so that the third plane of the smallest float32 lies inside the range of bfloat16 too (unscaled, operands below
-// 2^-109 lose their last bits: relative error 3e-4 at 2^-120 instead of 2e-7).  An infinite one, or one that overflows so, has NaN in its lower planes: results that are not finite are formed again by the float32
+// 2^-109 lose their last bits: relative error 3e-4 at 2^-120 instead of 2e-7).  An infinite one, or one that overflows so (from 2^104 on), has NaN in its lower planes: results that are not finite are formed again by the float32
 // instruction (float32_tile, float32_queries).
 constexpr float kUp = 0x1p24f, kDown = 0x1p-24f;
 __device__ __forceinline__ float4 times4(const float4& v, float f) { return make_float4(v.x * f, v.y * f, v.z * f, v.w * f); }
@@ -160,7 +161,7 @@ struct RowsArgs {
     int c, r0, tokens;
     float* stats;
     float eps;
-    const void* w[4];          // w_q, w_k, w_v, w_g [Hd][c], to be split into planes (see WeightPlanes)
+    const void* w[4];          // w_q, w_k, w_v, w_g [Hd][c], to be split into planes (see weight_planes)
     int Hd, token_blocks;
     unsigned char* planes;
 };
@@ -294,9 +295,9 @@ __global__ __launch_bounds__(256) void k_rows_generic(RowsArgs a) {
 //   PROJ = true : A = LayerNorm(x) on the fly (stats, gamma, beta), B rows from w_q|w_k|w_v|w_g,
 //                 epilogue: q scaled, gate = sigmoid(acc + b_g); C -> qkvg[t][4Hd]
 //   PROJ = false: A = o[t][Hd], B = w_o, epilogue + b_o, C -> out at the token's address.
-// What bounds it (64 x 155 tokens of 256 channels, projections, times of the kernel with a part taken out): the matrix instructions 12 us of 36, splitting
-// the tokens 10, the weights' planes 6, the stores and the rest of a block's beginning and end 10: the waves of a SIMD hide little of one behind another.
-// With the weights split by every block too 44 us; with one buffer and four blocks per compute unit 38; the split woven between the matrix instructions 42.
+// What bounds it (64 x 155 tokens of 256 channels, projections, under the profiler, what a part of the kernel adds to the others): the matrix instructions 12.5 us of 43,
+// splitting the tokens 10, the weights' planes 6, loads, stores and a block's beginning and end 15: the waves of a SIMD hide little of one behind another.
+// With one buffer and four blocks per compute unit the call takes 84 to 87 us instead of 81 to 84, with the split woven between the matrix instructions 92 (one box).
 struct GenericGemmArgs {
     const void* a;         // x (PROJ) or o
     int64_t sr, sl;        // token strides of x / out
@@ -529,13 +530,6 @@ __device__ __forceinline__ void gemm_block(const GenericGemmArgs& g, int bx, int
         }
         if constexpr (ahead > 0) {
             stash(c1, buf ^ 1, k0 + 32);              // (read last in the round before, and that round's barrier has passed)
-
-#pragma unroll
-            for (int i = 0; i < 2 * WN * (NA > 1 ? (NB > 1 ? 6 : 3) : 1); ++i) {
-
-
-
-            }
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (BP) __builtin_amdgcn_s_waitcnt(ahead > 1 ? (PROJ ? 0x0F74 : 0x0F72) : kWaitVmcnt0);      // vmcnt: all but c2's four (two) loads
             __syncthreads();
@@ -683,7 +677,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 2 ? 4 : 3) void k_proj_rows_gener
 // exponentiated tile, split into planes, are the B operand of step c of O^T = V^T P^T as they stand (the keys 16 c + 8 i + 4 hf + e). The bias is added to the finished products (as the
 // accumulator's starting value it was rounded with every one of them), the key mask (0 or -inf) selects, in tiles that hold a masked key.  Online softmax; a query without
 // any unmasked key gets zero context.  Output o = gate * context.
-// Bound by the vector unit (exponentials, the planes of P: 250 instructions per 32 x 32 tile against 24 matrix instructions of 32 cycles).  Up to 32 channels it is held
+// Bound by the vector unit (exponentials, the planes of P: 260 instructions per 32 x 32 tile against 24 matrix instructions of 32 cycles).  Up to 32 channels it is held
 // to 128 registers: with 155 a second block of five wavefronts did not fit a compute unit (64 x 155 tokens: 31 us instead of 25, both under the profiler); with bfloat16
 // storage, whose operands are one plane, to 96: with 112 the same call at 16 heads of 8 channels, all launches, 65.6 us instead of 57.4.
 // Weights below 2^-126 of the largest are zeros here and those below 2^-109 lose bits; whether any counts is decided once per query behind the loops (the smallest score

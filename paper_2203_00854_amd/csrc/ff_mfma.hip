@@ -29,8 +29,8 @@
 // fetched, so nothing moves between the two contractions.
 //
 // Workspace layout of this family (Lp = Lq = L rounded up to 32, token p = rl*Lp + l):
-//   bias [H][Lq][Lp] float32 (times log2 e) in 32 x 32 tiles (bias_index); rows of pad queries are never written, and
-//   only the lanes of those queries, which store nothing, see them
+//   bias [H][Lq][Lp] float32 (times log2 e) in 32 x 32 tiles (bias_index); rows of pad queries are never written nor read: their
+//   lanes take the last real query's (a NaN there would reach the denominators of others, see add_piece)
 //   q, k, g, o [rows][H][Lp][D] bf16;  vt [rows][H][Lp/32][D][32] bf16
 //   prepared weights [(4*Hd + 32)][c] (+ [32][c_z] in row mode) bf16, their sums and offsets
 // Pad tokens (l in [L, Lp)) hold finite values everywhere; they are masked as keys.
@@ -849,9 +849,9 @@ __global__ __launch_bounds__(gemm_waves(KC) * 64, gemm_fit(KC, PROJ) / 4) void k
 // The attention phase is the pipeline of k_attn_rows over two rows: no reference in the softmax, masked keys cost a matrix
 // instruction only in tiles that hold any, matrix instructions of the next and the previous tile between the exponentials.
 //
-// Measured on the training crop of the row-wise attention (128 x 256 tokens, 8 heads): 43.4 us (46.3 with a reference and dot
-// products in the softmax) against 34 + 31 us for k_gemm<PROJ> and an attention kernel; triangle attention at 256: 34.9 (36.7).
-// In the projections every matrix instruction waits for a fresh weight operand from LDS; of the two wavefronts of a SIMD
+// Measured on the training crop of the row-wise attention (128 x 256 tokens, 8 heads): 41 to 43 us under the profiler, where k_gemm<PROJ> and an attention kernel took
+// 34 + 31; triangle attention at 256: 34 to 36.  In the projections a weight operand is read from LDS once for the tokens of both rows, three steps ahead (one
+// read per instruction, waited for: 62.7 us the call instead of 62.3, no more than the runs of one side differ); of the two wavefronts of a SIMD
 // the older one is served first and finishes each phase about a quarter earlier, and the block waits for the younger one
 // at both barriers.
 
