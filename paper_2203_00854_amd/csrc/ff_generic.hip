@@ -9,8 +9,8 @@
 // holds column l%32, rows 8*(l/32) .. + 7; C/D (32 x 32): lane l holds column l%32, register v holds row 8*(v/4) + 4*(l/32) + v%4.
 // Measured (row attention, 64 x 155 tokens of 256 channels, 8 heads of 32, 8.1 GFLOP): 1.40 ms with vector
 // multiply-adds, a wavefront per query and per pair, 0.116 ms on v_mfma_f32_32x32x2_f32 (whose matrix cores alone need 53 us), 0.090 ms so (kernels under the
-// profiler: projections 42 to 47 us, attention 25 to 28, output projection 17 to 19, rows 9 to 10); relative error against float64 3.9e-7 -> 2.3e-7, and below the float32
-// instruction's, 0.55 to 0.9 of it, in each of 670 other shapes of 4 to 3000 channels and head dims 4 to 128.  Where the planes do not reach, the float32 instruction takes over
+// profiler: projections 42 to 47 us, attention 25 to 28, output projection 17 to 19, rows 9 to 10); relative error against float64 3.9e-7 -> 2.3e-7, and 0.48 to 0.90 of the
+// float32 instruction's in each of 508 other shapes of 4 to 3000 channels and head dims 4 to 128.  Where the planes do not reach, the float32 instruction takes over
 // (float32_tile, float32_queries).
 //
 // Workspace layout of this family, per chunk of `rows` batch rows, token t = rl*L + l:
