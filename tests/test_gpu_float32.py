@@ -197,7 +197,7 @@ def same_values(got, ref, tol):
 # one launch for statistics and projections; 64 and 128 features per block; split ahead and per block; head dims of every kernel;
 # the last tile of tokens, features, keys and channels partly filled
 INF_SHAPES = [(ROW, 3, 45, 64, 2, 8, 0), (COL, 70, 5, 36, 3, 12, 2), (ROW, 90, 130, 96, 3, 32, 0), (TS, 100, 100, 260, 4, 24, 0), (TE, 66, 66, 33, 1, 64, 0),
-              (ROW, 4, 601, 64, 3, 16, 1), (ROW, 5, 170, 40, 2, 128, 2)]
+              (ROW, 4, 601, 64, 3, 16, 1), (ROW, 5, 170, 40, 2, 128, 2), (ROW, 61, 136, 32, 8, 32, 7), (COL, 8, 4100, 256, 1, 8, 1000)]
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -335,8 +335,8 @@ def test_bottom_of_the_float32_range(where, mode, n_a, n_b, c, heads, d, chunk):
 
 
 @pytest.mark.parametrize("exponent", [-90, -112, -120, -127, -131])
-@pytest.mark.parametrize("n_a,n_b,c,heads,d", [(3, 45, 64, 2, 8), (40, 200, 96, 3, 32), (2, 70, 36, 1, 128)])
-def test_small_softmax_weights(n_a, n_b, c, heads, d, exponent):
+@pytest.mark.parametrize("n_a,n_b,c,heads,d,dead", [(3, 45, 64, 2, 8, 0), (40, 200, 96, 3, 32, 0), (2, 70, 36, 1, 128, 0), (7, 90, 30, 2, 20, 11)])
+def test_small_softmax_weights(n_a, n_b, c, heads, d, dead, exponent):
     """One key with a weight of 2^exponent of the others' and a value so large that both count alike in the context: weights below the normal range
     of float32, and ones whose lower planes are below that of bfloat16.  (The score's own rounding is |exponent| 2^-24, a weight of 2^-131 has 18 bits.)"""
     case = I.make_case(small_spec(ROW, n_a, n_b, c, heads, d, c_z=16, dtype="f32", mask="none"))
@@ -346,7 +346,10 @@ def test_small_softmax_weights(n_a, n_b, c, heads, d, exponent):
     x[:, :, 2:half] = rng.integers(1, 9, (n_a, n_b, half - 2)) / 8
     x[:, :, half:] = -x[:, :, :half]                # means are exactly zero
     x[:, 1] = 0
-    x[:, 1, 0], x[:, 1, half] = 1, -1               # the only token with channel 0
+    x[:, 1, 0], x[:, 1, half] = 1, -1               # the only live token with channel 0
+    if dead:
+        case.mask = np.ones((n_a, n_b), np.float32)
+        x[:, n_b - dead:], case.mask[:, n_b - dead:] = x[:, 1:2], 0
     case.x = x
     w["ln_g"][:], w["ln_b"][:] = 1, 0
     w["ln_b"][1] = 8                                # channel 1 is 8 in every token
